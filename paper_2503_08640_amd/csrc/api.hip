@@ -493,6 +493,7 @@ void fill_lists(AttnParams& p, const dbsa_layout* L) {
   p.n_split = L->n_split;
   p.n_queries = L->n_queries;
   p.block_m = L->block_m;
+  p.largest_tile = L->largest_tile;
   p.block_n = L->block_n;
 }
 
@@ -531,7 +532,7 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
                                         std::max(p.k_self.stride_tok, p.v_self.stride_tok));
     // of the matrix kernels only the pipelined one re-positions: other shapes take the plain kernel then
     if (rope_table && !(d == 128 && max_stride < (int64_t{1} << 24))) {
-      e = launch_prefill_plain(p, d, /*bf16_storage=*/true, static_cast<hipStream_t>(stream));
+      e = launch_prefill_plain(p, d, /*bf16_storage=*/true, L->compute_units, static_cast<hipStream_t>(stream));
       return e == hipSuccess ? DBSA_OK : DBSA_ERR_HIP;
     }
     if (!mfma_tile_sizes_ok(L)) return DBSA_ERR_UNSUPPORTED;
@@ -572,7 +573,7 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
             ? launch_prefill_pipelined(p, static_cast<hipStream_t>(stream))
             : launch_prefill_mfma(p, d, static_cast<hipStream_t>(stream));
   } else {
-    e = launch_prefill_plain(p, d, /*bf16_storage=*/false, static_cast<hipStream_t>(stream));
+    e = launch_prefill_plain(p, d, /*bf16_storage=*/false, L->compute_units, static_cast<hipStream_t>(stream));
   }
   return e == hipSuccess ? DBSA_OK : DBSA_ERR_HIP;
 }
@@ -1003,13 +1004,13 @@ int decode_common(const dbsa_layout* L, dbsa_tensor q_step, dbsa_tensor k_selfca
       e = launch_decode_group(p, s);
     } else if (rope_table) {
       // of the matrix kernels only the group-major one re-positions
-      e = launch_decode_plain(p, head_dim, /*bf16_storage=*/true, s);
+      e = launch_decode_plain(p, head_dim, /*bf16_storage=*/true, L->compute_units, s);
     } else {
       e = launch_decode_mfma(p, head_dim, s);
       if (e == hipSuccess) e = launch_decode_merge(p, head_dim, /*out_bf16=*/true, s);
     }
   } else {
-    e = launch_decode_plain(p, head_dim, /*bf16_storage=*/false, s);
+    e = launch_decode_plain(p, head_dim, /*bf16_storage=*/false, L->compute_units, s);
   }
   return e == hipSuccess ? DBSA_OK : DBSA_ERR_HIP;
 }

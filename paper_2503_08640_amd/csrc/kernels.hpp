@@ -55,6 +55,7 @@ struct AttnParams {
   int32_t n_rows;             // prefill: rows of q / o
   // shapes
   int32_t n_q_heads, n_kv_heads, block_m, block_n;
+  int32_t largest_tile;       // prefill: most rows any Q tile has
   int32_t heads_per_block;    // query heads handled by one workgroup (divides Hq/Hkv)
   // persistent prefill-shaped launch (null: one workgroup per Q tile): workgroup w serves head block
   // w % n_head_blocks and records sched_ptr[c] .. sched_ptr[c+1]-1, c = w / n_head_blocks, of
@@ -109,6 +110,6 @@ hipError_t launch_rope_apply(const TensorView& x, const TensorView& out, int n_t
                              bool bf16, const int32_t* positions, int first_id, const float* table, int n_pos,
                              hipStream_t stream);
 
-// plain fp32-arithmetic kernels for fp32 or bf16 storage (attn_plain.hip)
-hipError_t launch_prefill_plain(const AttnParams& p, int head_dim, bool bf16_storage, hipStream_t stream);
-hipError_t launch_decode_plain(const AttnParams& p, int head_dim, bool bf16_storage, hipStream_t stream);
+// fp32-arithmetic kernel for fp32 or bf16 storage (attn_plain.hip); compute_units: of the device the layout was built for
+hipError_t launch_prefill_plain(const AttnParams& p, int head_dim, bool bf16_storage, int compute_units, hipStream_t stream);
+hipError_t launch_decode_plain(const AttnParams& p, int head_dim, bool bf16_storage, int compute_units, hipStream_t stream);

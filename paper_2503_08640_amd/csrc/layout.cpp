@@ -502,6 +502,7 @@ int dbsa_build_host_lists(const dbsa_pool_desc* pool, const dbsa_select_desc* se
   L->shortest_list = INT64_MAX;
   for (int64_t t = 0; t < L->n_qtiles(); ++t) {
     L->shortest_list = std::min(L->shortest_list, L->list_ptr[t + 1] - L->list_ptr[t]);
+    L->largest_tile = std::max(L->largest_tile, L->qtile_tab[4 * t + 1]);
     if (!L->list_shift.empty())
       for (int64_t e = L->list_ptr[t]; e < L->list_ptr[t + 1]; ++e)
         L->max_rotation_id = std::max<int64_t>(L->max_rotation_id,

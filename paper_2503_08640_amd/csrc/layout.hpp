@@ -115,6 +115,7 @@ struct dbsa_layout {
   // figures the attention calls need on every launch, taken once at build time
   int32_t gm_max_queries = 1;       // most queries any schedule item serves
   int64_t shortest_list = 0;        // fewest entries any Q tile lists
+  int32_t largest_tile = 0;         // most rows any Q tile has (at most block_m)
   int64_t max_rotation_id = -1;     // largest id a prefill row looks up: max(list_shift[e] + rows of the tile) - 1
   int64_t max_decode_shift = 0;     // largest gm_qshift: a decode row of self_len n looks up id shift + n - 1
   // compute units of the device the launches are sized for (set before the host lists are built;
