@@ -281,10 +281,13 @@ void dbsa_layout_destroy(dbsa_layout* layout);
 /*
  * Bytes of device workspace the query-stage calls use for this layout: one partial softmax
  * state of (head_dim + 4) floats per query head and slot.  dbsa_decode_attn needs the larger
- * of its two schedules (B * n_split slots, or slot_ptr[B] slots).  dbsa_query_attn may use up
- * to 4 slots per query token when the layout has so few Q tiles that the launch would leave
- * compute units idle; it then cuts every KV list into runs and merges their partial states
- * (without a workspace it runs every list in one pass: same result up to summation order).
+ * of its two schedules (B * n_split slots, or slot_ptr[B] slots), and at least 4 slots per query
+ * token while the layout has few Q tiles.  dbsa_query_attn uses it when the layout has so few Q
+ * tiles that whole lists would leave compute units idle or unevenly loaded; it then cuts KV lists
+ * into pieces and merges their partial states (at most two pieces more than there are compute
+ * units per head block: 69 MB on 256 compute units at head_dim 128, much less for short queries;
+ * without a workspace, or with a smaller one, it cuts less or not at all: same result up to
+ * summation order).
  * The pre-encode call needs none.  Returns 0 for a pre-encode layout.
  */
 size_t dbsa_workspace_bytes(const dbsa_layout* layout, int32_t n_q_heads, int32_t head_dim);

@@ -137,6 +137,31 @@ void release_block(const ListBlock& blk) {
   trim_pool_locked(kMaxPoolBlocks);
 }
 
+// Room for the lists of a cut schedule (ensure_cut_schedule): at most one cut per worker adds a record, and at most
+// that many Q tiles are cut.
+size_t cut_room_bytes(const dbsa_layout* L) {
+  if (!L->query_stage) return 0;
+  const size_t nt = static_cast<size_t>(L->n_qtiles()), cuts = kMaxSchedClasses;
+  return (5 * (nt + cuts) + (cuts + 1) + 4 * std::min(nt, cuts)) * sizeof(int32_t) + 4 * 256;
+}
+
+// Copies the lists of the cut schedule to their place in the staging twin of L->dev.cut_room and notes where they
+// will be on the device; returns the bytes they take.
+size_t place_cut_lists(const dbsa_layout* L, unsigned char* staging) {
+  size_t at = 0;
+  auto put = [&](const std::vector<int32_t>& v) {
+    int32_t* where = reinterpret_cast<int32_t*>(L->dev.cut_room + at);
+    if (!v.empty()) std::memcpy(staging + at, v.data(), v.size() * sizeof(int32_t));
+    at += (v.size() * sizeof(int32_t) + 255) / 256 * 256;
+    return where;
+  };
+  L->dev.cut_rec = put(L->cut_rec);
+  L->dev.cut_ptr = put(L->cut_ptr);
+  L->dev.cut_part = put(L->cut_part);
+  L->dev.cut_tab = put(L->cut_tab);
+  return at;
+}
+
 // Copy every list into ONE device block with a single asynchronous copy from pinned memory.
 hipError_t upload_lists(dbsa_layout* L, hipStream_t stream) {
   auto pad = [](size_t n) { return (n + 255) / 256 * 256; };
@@ -156,8 +181,8 @@ hipError_t upload_lists(dbsa_layout* L, hipStream_t stream) {
                o_lsh = o_gsp + pad(b_gsp), o_gir = o_lsh + pad(b_lsh), o_grp = o_gir + pad(b_gir),
                o_grw = o_grp + pad(b_grp), o_gse = o_grw + pad(b_grw), o_gqr = o_gse + pad(b_gse),
                o_dsh = o_gqr + pad(b_gqr), o_gqs = o_dsh + pad(b_dsh), o_mqr = o_gqs + pad(b_gqs), o_mqs = o_mqr + pad(b_mqr), o_msp = o_mqs + pad(b_mqs),
-               o_srec = o_msp + pad(b_msp), o_sptr = o_srec + pad(b_srec), o_mrec = o_sptr + pad(b_sptr),
-               o_mptr = o_mrec + pad(b_mrec), lists_end = o_srec, total = o_mptr + pad(b_sptr) + 256;
+               o_cut = o_msp + pad(b_msp), o_srec = o_cut + pad(cut_room_bytes(L)), o_sptr = o_srec + pad(b_srec),
+               o_mrec = o_sptr + pad(b_sptr), o_mptr = o_mrec + pad(b_mrec), total = o_mptr + pad(b_sptr) + 256;
   ListBlock blk{};
   hipError_t e = acquire_block(total, &blk);
   if (e != hipSuccess) return e;
@@ -183,12 +208,15 @@ hipError_t upload_lists(dbsa_layout* L, hipStream_t stream) {
   put(o_mqr, L->mx_qrefs.data(), b_mqr);
   put(o_mqs, L->mx_qshift.data(), b_mqs);
   put(o_msp, L->mx_slot_ptr.data(), b_msp);
+  L->dev.cut_room = static_cast<unsigned char*>(blk.dev) + o_cut;
+  size_t lists_end = o_cut;
+  if (L->cut_worth) lists_end += place_cut_lists(L, h + o_cut);
   // the staging twin stays with the block, so nothing has to wait for the copy here; calls on
   // other streams are ordered behind it through the event
   hipEvent_t uploaded = nullptr;
   e = hipEventCreateWithFlags(&uploaded, hipEventDisableTiming);
   if (e == hipSuccess) {
-    // (the room behind lists_end is filled by the first calls that use a schedule)
+    // (the room behind lists_end is filled by the first calls that use another schedule)
     e = hipMemcpyAsync(blk.dev, blk.pinned, lists_end, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipEventRecord(uploaded, stream);
     if (e != hipSuccess) {
@@ -229,6 +257,10 @@ hipError_t upload_lists(dbsa_layout* L, hipStream_t stream) {
   L->dev.sched_ptr = reinterpret_cast<int32_t*>(b + o_sptr);
   L->dev.mx_sched_rec = reinterpret_cast<int32_t*>(b + o_mrec);
   L->dev.mx_sched_ptr = reinterpret_cast<int32_t*>(b + o_mptr);
+  if (L->cut_worth) {  // the upload's own event orders other streams behind these lists
+    L->dev.cut_stream = stream;
+    L->cut_on_device = true;
+  }
   return hipSuccess;
 }
 
@@ -268,6 +300,7 @@ void free_device_lists(dbsa_layout* L) {
     if (d.uploaded) (void)hipEventDestroy(static_cast<hipEvent_t>(d.uploaded));
     if (d.sched_uploaded) (void)hipEventDestroy(static_cast<hipEvent_t>(d.sched_uploaded));
     if (d.mx_uploaded) (void)hipEventDestroy(static_cast<hipEvent_t>(d.mx_uploaded));
+    if (d.cut_uploaded) (void)hipEventDestroy(static_cast<hipEvent_t>(d.cut_uploaded));
     release_block(blk);
     if (current != d.device) (void)hipSetDevice(current);
   }
@@ -385,6 +418,58 @@ bool ensure_matrix_schedule(const dbsa_layout* L, int32_t n_classes, bool planne
   });
 }
 
+// The schedule of a query prefill with lists cut to measure for n_classes workers per head block, on the device and
+// ordered before `stream`'s next work.  Like ensure_slot's schedules a layout keeps ONE: false if it holds one for
+// another number of workers, if the launch gains nothing from it, or if it would have to be copied under capture.
+bool ensure_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd, hipStream_t stream) {
+  if (n_classes < 1 || n_classes > kMaxSchedClasses || !L->dev.cut_room) return false;
+  std::lock_guard<std::mutex> lock(L->sched_mutex);
+  if (L->cut_classes != 0 && L->cut_classes != n_classes) {
+    if (!L->cut_guessed) return false;
+    // the schedule that came with the lists is for another model and nothing has read it: a new one takes its place
+    // (its copy is ordered behind the lists', and overwrites whatever that one picks up of it)
+    L->cut_classes = 0;
+    L->cut_on_device = L->cut_worth = false;
+  }
+  if (!L->cut_on_device) {
+    if (L->cut_classes != 0 && !L->cut_worth) return false;
+    // (under capture nothing can be copied; the call then takes its other launch form)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return false;
+    }
+    if (L->cut_classes == 0) {
+      try {
+        dbsa_cut_schedule(L, n_classes, crowd);
+      } catch (...) {
+        L->cut_classes = 0;
+        return false;
+      }
+    }
+    L->cut_guessed = false;
+    if (!L->cut_worth) return false;
+    const size_t first = static_cast<size_t>(L->dev.cut_room - static_cast<unsigned char*>(L->dev.base));
+    unsigned char* const staging = static_cast<unsigned char*>(L->dev.staging) + first;
+    const size_t bytes = place_cut_lists(L, staging);
+    hipEvent_t done = nullptr;
+    if (hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess) return false;
+    if (hipMemcpyAsync(L->dev.cut_room, staging, bytes, hipMemcpyHostToDevice, stream) != hipSuccess ||
+        hipEventRecord(done, stream) != hipSuccess) {
+      (void)hipStreamSynchronize(stream);
+      (void)hipEventDestroy(done);
+      return false;
+    }
+    L->dev.cut_uploaded = done;
+    L->dev.cut_stream = stream;
+    L->cut_on_device = true;
+  } else if (stream != L->dev.cut_stream && L->dev.cut_uploaded) {
+    if (hipStreamWaitEvent(stream, static_cast<hipEvent_t>(L->dev.cut_uploaded), 0) != hipSuccess) return false;
+  }
+  L->cut_guessed = false;
+  return true;
+}
+
 bool tensor_ok(const dbsa_tensor& t, int dtype) {
   const int64_t align_elems = dtype == DBSA_BF16 ? 8 : 4;
   return t.ptr != nullptr && (reinterpret_cast<uintptr_t>(t.ptr) % 16 == 0) && t.stride_tok > 0 &&
@@ -414,13 +499,12 @@ int pick_heads_per_block(int r, int block_m) {
   return best;
 }
 
-// split query prefill: most runs per list, fewest tiles per run
-constexpr int64_t kMaxQuerySplit = 4;
-constexpr int64_t kMinRun = 16;
-// The kernel that re-positions (attn_prefill.hip) starts a row's running maximum from the first
+// attn_prefill.hip starts a row's running maximum from the first
 // tile of its run, so that tile must hold a key the row sees.  Only the tiles on a Q tile's own
 // diagonal hide keys from some of its rows, they are the last block_m / 64 entries of a list and
 // every row sees the first of them: a run of more entries than that never starts behind it.
+// Q tiles per worker up to which a query prefill may cut its lists to measure (with more, whole Q tiles balance)
+constexpr int64_t kCutTiles = 8;
 static_assert(kMinRun > 256 / 64, "a run of a split list must reach back beyond the diagonal tiles of a Q tile");
 // workgroups the device the layout was built for holds at two per compute unit
 int64_t workgroup_slots(const dbsa_layout* L) { return 2 * static_cast<int64_t>(L->compute_units); }
@@ -431,6 +515,64 @@ size_t decode_workspace_need(const dbsa_layout* L, int32_t n_q_heads, int32_t he
                                         std::max<size_t>(L->gm_slot_ptr.empty() ? 0 : static_cast<size_t>(L->gm_slot_ptr.back()),
                                                    L->mx_slot_ptr.empty() ? 0 : static_cast<size_t>(L->mx_slot_ptr.back())));
   return slots * n_q_heads * (head_dim + kPartialPad) * sizeof(float);
+}
+
+// Workgroups of a prefill-shaped launch that the chip holds at once: eight-wave-sized ones (112 KiB of LDS) sit alone
+// on a compute unit, smaller ones in pairs.
+int64_t prefill_places(const dbsa_layout* L, int row_blocks) { return workgroup_slots(L) / (row_blocks == 8 ? 2 : 1); }
+
+// what a list entry costs with all workers busy over what it costs with few (dbsa_cut_schedule)
+double cut_crowding(int row_blocks) { return row_blocks == 4 ? 1.5 : 1.0; }
+
+// Runs per list of a launch of `wgs` workgroups (one run each) on `places`: the number that makes rounds * length
+// shortest.  A run costs kPieceCost entries to start and finish; every further run of a row is one more partial state,
+// 2 * 528 bytes for each of rows * heads / places states per place at the 20 KB a place gets in the time of a tile.
+int64_t query_runs(const dbsa_layout* L, int64_t wgs, int64_t places, int64_t states) {
+  if (wgs <= 0 || wgs >= places) return 1;
+  const int64_t most = std::min(std::min(kMaxQuerySplit, L->shortest_list / kMinRun), 2 * places / wgs);
+  const double entries = static_cast<double>(L->n_ent()) / static_cast<double>(std::max<int64_t>(1, L->n_qtiles()));
+  const double merge = static_cast<double>(states) * 1056.0 / static_cast<double>(places) / 20000.0;
+  int64_t best = 1;
+  double least = entries + kPieceCost;
+  for (int64_t s = 2; s <= most; ++s) {
+    const double rounds = static_cast<double>((wgs * s + places - 1) / places);
+    const double cost = rounds * (entries / static_cast<double>(s) + kPieceCost) + 2.0 + merge * static_cast<double>(s);
+    if (cost < least) {
+      least = cost;
+      best = s;
+    }
+  }
+  return best;
+}
+
+// Most partial states (rows of head_dim + 4 floats) a query prefill of n_q_heads can use, over the numbers of heads a
+// workgroup may take (the number of KV heads is not known here): workers - 1 cuts make at most one piece more each
+// than there are cut Q tiles, split lists have query_runs() runs.
+size_t query_prefill_states(const dbsa_layout* L, int32_t n_q_heads) {
+  size_t most = 0;
+  for (int hpb = 1; hpb <= 8; hpb *= 2) {
+    const int row_blocks = hpb * (L->block_m / 32);
+    if (n_q_heads % hpb != 0 || row_blocks < 1 || row_blocks > 8) continue;
+    const int64_t head_blocks = n_q_heads / hpb, places = prefill_places(L, row_blocks), states = int64_t{1} * L->n_query_tokens * n_q_heads;
+    if (row_blocks >= 4) {
+      const int64_t classes = std::min<int64_t>(places / head_blocks, kMaxSchedClasses);
+      const int64_t cuts = std::max<int64_t>(0, dbsa_cut_workers(L, classes) - 1);
+      const int64_t pieces = std::min(2 * cuts, cuts + L->n_qtiles());
+      if (L->n_qtiles() < kCutTiles * classes) most = std::max(most, static_cast<size_t>(pieces * L->largest_tile * n_q_heads));
+    }
+    const int64_t runs = query_runs(L, L->n_qtiles() * head_blocks, places, states);
+    if (runs > 1) most = std::max(most, static_cast<size_t>(runs * states));
+  }
+  return most;
+}
+
+// The workspace a decode call asks for: its own partial states, and never less than kStatesPerToken per query token
+// while the query prefill of the layout may split (one workspace serves both calls).
+constexpr int64_t kStatesPerToken = 4;
+size_t decode_workspace_bytes(const dbsa_layout* L, int32_t n_q_heads, int32_t head_dim) {
+  const size_t row = static_cast<size_t>(n_q_heads) * (head_dim + kPartialPad) * sizeof(float);
+  const size_t tokens = L->n_qtiles() < workgroup_slots(L) ? static_cast<size_t>(L->n_query_tokens) * kStatesPerToken : 0;
+  return std::max(decode_workspace_need(L, n_q_heads, head_dim), tokens * row);
 }
 
 bool mfma_tile_sizes_ok(const dbsa_layout* L) {
@@ -537,41 +679,46 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
     }
     if (!mfma_tile_sizes_ok(L)) return DBSA_ERR_UNSUPPORTED;
     p.heads_per_block = pick_heads_per_block(hq / hkv, L->block_m);
-    // A query prefill with fewer workgroups than the chip holds (two per compute unit) cuts every
-    // list into runs of at least kMinRun tiles, up to kMaxQuerySplit of them, if the caller gave the workspace.
     p.n_rows = L->n_query_tokens;
     p.q_split = 1;
-    if (want_query_stage && d == 128 && workspace && reinterpret_cast<uintptr_t>(workspace) % 16 == 0) {
-      const int64_t wgs = L->n_qtiles() * (hq / p.heads_per_block);
-      // eight-wave workgroups (112 KiB of LDS) sit alone on a compute unit, smaller ones in pairs
-      const int64_t slots = workgroup_slots(L) / (p.heads_per_block * (L->block_m / 32) == 8 ? 2 : 1);
-      int64_t split = wgs > 0 ? std::min<int64_t>(kMaxQuerySplit, (slots + wgs - 1) / wgs) : 1;
-      split = std::min(split, L->shortest_list / kMinRun);
-      const size_t need = static_cast<size_t>(L->n_query_tokens) * hq * static_cast<size_t>(std::max<int64_t>(split, 1)) *
-                          (d + kPartialPad) * sizeof(float);
-      if (wgs < slots && split > 1 && workspace_bytes >= need) {
-        p.q_split = static_cast<int32_t>(split);
+    const bool pipelined = d == 128 && max_stride < (int64_t{1} << 24);
+    const int row_blocks = p.heads_per_block * (L->block_m / 32);
+    const int64_t head_blocks = hq / p.heads_per_block, places = prefill_places(L, row_blocks);
+    const size_t state_bytes = (d + kPartialPad) * sizeof(float);
+    const size_t room = workspace && reinterpret_cast<uintptr_t>(workspace) % 16 == 0 ? workspace_bytes / state_bytes : 0;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    // The kernel for four or eight row blocks runs persistently: as many workgroups as the chip holds (one of four
+    // waves or two of two per compute unit), each walking a balanced share of the Q tiles of its head block.  With
+    // several Q tiles per worker whole tiles balance; a query prefill with fewer (down to one question of 64 tokens,
+    // which is one Q tile) cuts the lists to measure if the caller gave a workspace for the pieces' partial states.
+    if (pipelined && (row_blocks == 4 || row_blocks == 8)) {
+      const int32_t classes = static_cast<int32_t>(std::min<int64_t>(places / head_blocks, kMaxSchedClasses));
+      p.n_head_blocks = static_cast<int32_t>(head_blocks);
+      p.sched_classes = classes;
+      if (want_query_stage && L->n_qtiles() < kCutTiles * classes && room > 0 &&
+          ensure_cut_schedule(L, classes, cut_crowding(row_blocks), s) &&
+          static_cast<size_t>(L->cut_rows) * hq <= room) {
+        p.sched_rec = L->dev.cut_rec;
+        p.sched_ptr = L->dev.cut_ptr;
+        p.sched_part = L->dev.cut_part;
+        p.cut_tab = L->dev.cut_tab;
+        p.n_cut_tiles = static_cast<int32_t>(L->cut_tab.size() / 4);
+        p.partial = static_cast<float*>(workspace);
+      } else if (classes >= 1 && places / head_blocks <= kMaxSchedClasses && L->n_qtiles() >= 2 * classes && ensure_schedule(L, classes, s)) {
+        p.sched_rec = L->dev.sched_rec;
+        p.sched_ptr = L->dev.sched_ptr;
+      }
+    }
+    // Otherwise a query prefill with fewer workgroups than the chip holds cuts every list into the same number of runs.
+    if (want_query_stage && d == 128 && !p.sched_rec) {
+      const int64_t states = static_cast<int64_t>(L->n_query_tokens) * hq;
+      const int64_t runs = std::min<int64_t>(query_runs(L, L->n_qtiles() * head_blocks, places, states), room / std::max<int64_t>(states, 1));
+      if (runs > 1) {
+        p.q_split = static_cast<int32_t>(runs);
         p.partial = static_cast<float*>(workspace);
       }
     }
-    // Launches with several Q tiles per workgroup place run persistently: as many workgroups as the
-    // chip holds (one of four waves or two of two per compute unit), each walking a balanced share
-    // of the Q tiles of its head block.
-    const int row_blocks = p.heads_per_block * (L->block_m / 32);
-    if (d == 128 && max_stride < (int64_t{1} << 24) && p.q_split == 1 && (row_blocks == 4 || row_blocks == 8)) {
-      const int64_t head_blocks = hq / p.heads_per_block;
-      const int64_t places = static_cast<int64_t>(L->compute_units) * (row_blocks == 8 ? 1 : 2);
-      const int64_t classes = places / head_blocks;
-      if (classes >= 1 && L->n_qtiles() >= 2 * classes && ensure_schedule(L, static_cast<int32_t>(classes), static_cast<hipStream_t>(stream))) {
-        p.sched_rec = L->dev.sched_rec;
-        p.sched_ptr = L->dev.sched_ptr;
-        p.sched_classes = static_cast<int32_t>(classes);
-        p.n_head_blocks = static_cast<int32_t>(head_blocks);
-      }
-    }
-    e = (d == 128 && max_stride < (int64_t{1} << 24))
-            ? launch_prefill_pipelined(p, static_cast<hipStream_t>(stream))
-            : launch_prefill_mfma(p, d, static_cast<hipStream_t>(stream));
+    e = pipelined ? launch_prefill_pipelined(p, s) : launch_prefill_mfma(p, d, s);
   } else {
     e = launch_prefill_plain(p, d, /*bf16_storage=*/false, L->compute_units, static_cast<hipStream_t>(stream));
   }
@@ -620,6 +767,20 @@ int build_layout(const dbsa_pool_desc* pool, const dbsa_select_desc* sel, int32_
     return rc;
   }
   if (!(flags & DBSA_LAYOUT_HOST_ONLY)) {
+    // The schedule of the query prefill for 8 KV heads and workgroups of four query heads travels with the lists; for
+    // other models the first call makes its own (host work and a copy of some 20 us).
+    if (L->query_stage && (block_m == 32 || block_m == 64)) {
+      const int32_t classes = static_cast<int32_t>(std::min<int64_t>(prefill_places(L, block_m / 8) / 8, kMaxSchedClasses));
+      try {
+        if (classes >= 1 && L->n_qtiles() < kCutTiles * classes) {
+          dbsa_cut_schedule(L, classes, cut_crowding(block_m / 8));
+          L->cut_guessed = true;
+        }
+      } catch (...) {
+        delete L;
+        return DBSA_ERR_INVALID_ARG;
+      }
+    }
     const hipError_t e = upload_lists(L, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) {
       delete L;
@@ -750,13 +911,8 @@ void dbsa_layout_destroy(dbsa_layout* L) {
 
 size_t dbsa_workspace_bytes(const dbsa_layout* L, int32_t n_q_heads, int32_t head_dim) {
   if (!L || !L->query_stage || n_q_heads <= 0 || head_dim <= 0) return 0;
-  size_t slots = std::max<size_t>(static_cast<size_t>(L->n_queries) * L->n_split,
-                                  std::max<size_t>(L->gm_slot_ptr.empty() ? 0 : static_cast<size_t>(L->gm_slot_ptr.back()),
-                                                   L->mx_slot_ptr.empty() ? 0 : static_cast<size_t>(L->mx_slot_ptr.back())));
-  // a split query prefill keeps up to kMaxQuerySplit partial states per row; it is only used when
-  // the launch has fewer workgroups than the chip holds, which bounds the number of Q tiles
-  if (L->n_qtiles() < workgroup_slots(L)) slots = std::max<size_t>(slots, static_cast<size_t>(L->n_query_tokens) * kMaxQuerySplit);
-  return slots * n_q_heads * (head_dim + kPartialPad) * sizeof(float);
+  return std::max(decode_workspace_bytes(L, n_q_heads, head_dim),
+                  query_prefill_states(L, n_q_heads) * (head_dim + kPartialPad) * sizeof(float));
 }
 
 int dbsa_preencode_attn(const dbsa_layout* layout, dbsa_tensor q, dbsa_tensor k, dbsa_tensor v, dbsa_tensor o,
@@ -818,7 +974,7 @@ int decode_kv8_common(const dbsa_layout* L, dbsa_tensor q_step, dbsa_tensor k_se
                                       std::max(k_selfcache.stride_tok, v_selfcache.stride_tok));
   if (head_dim != 128 || L->block_n != 64 || r > 32 || 32 % r != 0 || max_stride >= (int64_t{1} << 24))
     return DBSA_ERR_UNSUPPORTED;
-  const size_t need = dbsa_workspace_bytes(L, n_q_heads, head_dim);
+  const size_t need = decode_workspace_bytes(L, n_q_heads, head_dim);
   if (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)
     return DBSA_ERR_WORKSPACE;
   if (rope_table && !decode_ids_in_table(L, stride_query, k_selfcache.stride_tok, rope_n_pos)) return DBSA_ERR_INVALID_ARG;
@@ -956,7 +1112,7 @@ int decode_common(const dbsa_layout* L, dbsa_tensor q_step, dbsa_tensor k_selfca
   if (dtype == DBSA_BF16) {
     if (L->block_n != 64 || r > 32) return DBSA_ERR_UNSUPPORTED;
     // need_bytes: what the caller has checked the step to write (the fixed-buffer entry point)
-    const size_t need = need_bytes ? need_bytes : dbsa_workspace_bytes(L, n_q_heads, head_dim);
+    const size_t need = need_bytes ? need_bytes : decode_workspace_bytes(L, n_q_heads, head_dim);
     if (!workspace || workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)
       return DBSA_ERR_WORKSPACE;
     p.partial = static_cast<float*>(workspace);

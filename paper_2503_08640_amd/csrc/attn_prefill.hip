@@ -507,6 +507,72 @@ __global__ __launch_bounds__(32 * kMergePairs) void prefill_merge_kernel(AttnPar
   if (p.lse && d == 0) p.lse[static_cast<int64_t>(head) * p.lse_stride + row] = (m_star + __log2f(l)) * 0.69314718055994531f;
 }
 
+// Merge for lists cut to measure (AttnParams::cut_tab): blockIdx.y = cut Q tile, 32 threads per (row, head), four
+// channels each.  Bound by latency while a Q tile has a few pieces (everything is requested at once then: 16 questions
+// in two or three pieces each 16 -> 10 us) and by the partial states' way through the cache when it has as many as the
+// schedule has workers (one question alone on the chip; the threads then fetch the statistics side by side and the
+// states stream eight at a time: 64 rows x 32 heads x 32 pieces, 35 MB, 7.5 us).
+__global__ __launch_bounds__(32 * kMergePairs) void prefill_cut_merge_kernel(AttnParams p) {
+  const const_words tab = (const_words)(reinterpret_cast<uintptr_t>(p.cut_tab)) + 4 * blockIdx.y;
+  const int q_start = tab[0], q_len = tab[1], part0 = tab[2], pieces = tab[3];
+  const int pair = static_cast<int>(blockIdx.x) * kMergePairs + threadIdx.x / 32;
+  if (pair >= q_len * p.n_q_heads) return;  // (all 32 threads of a pair)
+  const int row = pair / p.n_q_heads, head = pair % p.n_q_heads, lane = threadIdx.x % 32;
+  constexpr int kRow = kD + kPartialPad;
+  const int64_t stride = static_cast<int64_t>(q_len) * p.n_q_heads * kRow;  // from piece to piece
+  const float* part = p.partial + (static_cast<int64_t>(part0 + row) * p.n_q_heads + head) * kRow;
+  float m_star = -1.0e30f, l = 0.f;
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int kFew = 4;
+  if (pieces <= kFew) {
+    floatx2 ml[kFew];
+    floatx4 state[kFew];
+#pragma unroll
+    for (int z = 0; z < kFew; ++z) {
+      const float* at = part + min(z, pieces - 1) * stride;
+      ml[z] = *reinterpret_cast<const floatx2*>(at + kD);
+      state[z] = *reinterpret_cast<const floatx4*>(at + 4 * lane);
+    }
+#pragma unroll
+    for (int z = 0; z < kFew; ++z) m_star = fmaxf(m_star, ml[z][0]);
+#pragma unroll
+    for (int z = 0; z < kFew; ++z) {
+      if (z >= pieces) break;
+      const float w = __builtin_amdgcn_exp2f(ml[z][0] - m_star);
+      l = fmaf(w, ml[z][1], l);
+      acc += state[z] * w;
+    }
+  } else {
+    for (int z0 = 0; z0 < pieces; z0 += 32) m_star = fmaxf(m_star, part[min(z0 + lane, pieces - 1) * stride + kD]);
+#pragma unroll
+    for (int s = 16; s > 0; s >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, s, 32));
+    for (int z0 = 0; z0 < pieces; z0 += 32) {
+      const int n = min(32, pieces - z0);
+      const float* mine = part + (z0 + min(lane, n - 1)) * stride + kD;
+      const float w_mine = lane < n ? __builtin_amdgcn_exp2f(mine[0] - m_star) : 0.f;
+      l = fmaf(w_mine, mine[1], l);
+      const float* state = part + z0 * stride + 4 * lane;
+      for (int z1 = 0; z1 < n; z1 += 8)  // (pieces past the last repeat it with weight zero)
+#pragma unroll
+        for (int z = z1; z < z1 + 8; ++z)
+          acc += *reinterpret_cast<const floatx4*>(state + min(z, n - 1) * stride) * __shfl(w_mine, z, 32);
+    }
+#pragma unroll
+    for (int s = 16; s > 0; s >>= 1) l += __shfl_xor(l, s, 32);
+  }
+  const float inv = 1.f / l;
+  union {
+    bf16x4 v;
+    bf16x2 p2[2];
+  } w;
+  w.p2[0] = __builtin_convertvector(floatx2{acc[0] * inv, acc[1] * inv}, bf16x2);
+  w.p2[1] = __builtin_convertvector(floatx2{acc[2] * inv, acc[3] * inv}, bf16x2);
+  __bf16* o = static_cast<__bf16*>(const_cast<void*>(p.o.ptr));
+  const int tok = q_start + row;
+  *reinterpret_cast<bf16x4*>(o + static_cast<int64_t>(tok) * p.o.stride_tok + static_cast<int64_t>(head) * p.o.stride_head + 4 * lane) = w.v;
+  if (p.lse && lane == 0) p.lse[static_cast<int64_t>(head) * p.lse_stride + tok] = (m_star + __log2f(l)) * 0.69314718055994531f;
+}
+
 template <int NW, int SL, bool SELF, bool ROPE = false>
 hipError_t launch_cfg(const AttnParams& p, hipStream_t stream) {
   constexpr int lds_bytes = (3 + 2 * SL) * kTileBytes;
@@ -546,6 +612,12 @@ hipError_t launch_prefill_pipelined(const AttnParams& p, hipStream_t stream) {
   // the call carries a schedule, else one workgroup per Q tile and run)
   if (row_blocks == 4 || row_blocks == 8) {
     hipError_t e = launch_prefill64(p, stream);
+    if (e == hipSuccess && p.sched_part) {
+      if (p.n_cut_tiles == 0) return e;
+      const int pairs = p.largest_tile * p.n_q_heads;
+      prefill_cut_merge_kernel<<<dim3((pairs + kMergePairs - 1) / kMergePairs, p.n_cut_tiles), dim3(32 * kMergePairs), 0, stream>>>(p);
+      return hipGetLastError();
+    }
     const int n_split = p.q_split > 1 ? p.q_split : 1;
     if (e != hipSuccess || n_split == 1) return e;
     const int64_t pairs = static_cast<int64_t>(p.n_rows) * p.n_q_heads;

@@ -113,6 +113,9 @@ struct StepCfg {
 // the last tiles of a Q tile are being multiplied, the first tiles of the next one are already on
 // their way into the LDS ring, so that a Q tile costs no load latency beyond its own rows of Q.
 //
+// A persistent query prefill may come with lists cut to measure (AttnParams::sched_part): a record is then a
+// run of a Q tile's list, and the pieces of a Q tile leave partial softmax states that a merge pass combines.
+//
 // GATHER (with PERSIST): the rows of a "Q tile" are not consecutive tokens but the references
 // gather_refs[q_start .. q_start + q_len), pairs (row of q, slot): row i of the tile is q row
 // refs[i][0], and instead of a normalised output the kernel leaves the row's partial softmax state
@@ -135,6 +138,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   // the query prefill rotates a Q tile per list entry (the ids ride with the entries); gathered rows are
   // rotated once per record, each at its own id
   constexpr bool kEntryIds = ROPE && !GATHER;
+  constexpr bool kPieces = PERSIST && SELF;  // records may be pieces of a Q tile's list
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   constexpr int kBlocksPerWave = 16 / NW;  // 1-KiB load blocks of one operand per wave
   constexpr int KS = 2 + SL, VS = 1 + SL;  // LDS stages of K and of V
@@ -151,6 +155,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   const int hb = PERSIST ? static_cast<int>(blockIdx.x) % p.n_head_blocks : static_cast<int>(blockIdx.x);
   int rec_k = 0, rec_end = 1;            // PERSIST: index of the current record in sched_rec, end of the class
   int q_start, q_len, e0, n_tiles;
+  int part_row = -1;  // kPieces: first partial row of the record, -1 = it leaves finished rows
   if constexpr (PERSIST) {
     const int cls = static_cast<int>(blockIdx.x) / p.n_head_blocks;
     rec_k = __builtin_amdgcn_readfirstlane(p.sched_ptr[cls]);
@@ -160,6 +165,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     q_len = __builtin_amdgcn_readfirstlane(p.sched_rec[4 * rec_k + 1]);
     e0 = __builtin_amdgcn_readfirstlane(p.sched_rec[4 * rec_k + 2]);
     n_tiles = __builtin_amdgcn_readfirstlane(p.sched_rec[4 * rec_k + 3]);
+    if constexpr (kPieces)
+      if (p.sched_part) part_row = __builtin_amdgcn_readfirstlane(p.sched_part[rec_k]);
   } else {
     const int tile = __builtin_amdgcn_readfirstlane(p.order[blockIdx.y]);
     q_start = __builtin_amdgcn_readfirstlane(p.qtile_tab[tile * 4 + 0]);
@@ -732,13 +739,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       rotate_q(kEntryIds ? rw2[0] : 0);
     else
       scale_q();
-    int nq_start = 0, nq_len = 0, nq_e0 = 0, nq_n = 0;  // PERSIST: the record after this one
+    int nq_start = 0, nq_len = 0, nq_e0 = 0, nq_n = 0, nq_part = -1;  // PERSIST: the record after this one
     if constexpr (PERSIST) {
       if (rec_k + 1 < rec_end) {
         nq_start = sched[4 * (rec_k + 1) + 0];
         nq_len = sched[4 * (rec_k + 1) + 1];
         nq_e0 = sched[4 * (rec_k + 1) + 2];
         nq_n = sched[4 * (rec_k + 1) + 3];
+        if constexpr (kPieces)
+          if (p.sched_part) nq_part = ((const_words)(reinterpret_cast<uintptr_t>(p.sched_part)))[rec_k + 1];
       }
     }
 #pragma unroll
@@ -791,7 +800,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     period_barrier();
     // the rows this Q tile writes; then the next Q tile's rows of Q are requested along the drain steps,
     // and arrive during the epilogue
-    const int o_start = q_start, o_len = q_len;
+    const int o_start = q_start, o_len = q_len, o_part = part_row;
     int o_head[2], o_tok[2], o_slot[2];
     bool o_valid[2];
 #pragma unroll
@@ -808,6 +817,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       q_len = nq_len;
       e0 = nq_e0;
       n_tiles = nq_n;
+      part_row = nq_part;
       place_rows();
     }
     {
@@ -824,7 +834,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     l_run[1] += ls[1];
 
     // ---- epilogue ----
-    if constexpr (GATHER) {
+    // (kPieces: an opaque copy of the lane index, because what the two ways out derive from it would otherwise be kept
+    // in registers all through the tile loop, where none are free)
+    int ln = lane;
+    if constexpr (kPieces) asm volatile("" : "+v"(ln));
+    const int el32 = ln % 32, ehalf = ln / 32;
+    if (GATHER || (kPieces && o_part >= 0) || (!PERSIST && gridDim.z > 1)) {
       // Partial states, 528-byte rows of fp32: like the normalised outputs below they go through LDS
       // so that a store instruction writes whole 256-byte pieces of four rows instead of 16 bytes of
       // each of 32 rows; a row block passes in two halves of 64 channels, 8 KiB of staging per wave.
@@ -836,7 +851,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
         const float l_tot = half_swap_sum(l_run[rb]);
-        float* head_base = p.partial + static_cast<int64_t>(o_head[rb]) * (kD + kPartialPad) + (lane % 16) * 4;
+        const int row_base = ((2 * wave + rb) % spb) * 32;
+        // Query prefill: the states of all pieces together stay far below 4 GiB (the workspace), so a uniform base
+        // and 32-bit offsets name a row: few registers are free here, the next Q tile's rows are arriving.
+        constexpr unsigned kStateBytes = (kD + kPartialPad) * 4;
+        const unsigned runs = PERSIST ? 1 : gridDim.z, row_bytes = static_cast<unsigned>(p.n_q_heads) * runs * kStateBytes;
+        unsigned char* const out = reinterpret_cast<unsigned char*>(p.partial) +
+                                   (static_cast<size_t>(__builtin_amdgcn_readfirstlane(o_head[rb])) * runs + (PERSIST ? 0 : blockIdx.z)) * kStateBytes;
+        const int first_row = PERSIST ? o_part : o_start;
 #pragma unroll
         for (int h2 = 0; h2 < 2; ++h2) {
 #pragma unroll
@@ -844,40 +866,28 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               const int ob = 2 * h2 + ob2;
-              *(lds_f128)(static_cast<uintptr_t>(stag + l32 * kRowBytes + (((8 * ob2 + 2 * g + half) ^ (l32 % 16)) * 16))) =
+              *(lds_f128)(static_cast<uintptr_t>(stag + el32 * kRowBytes + (((8 * ob2 + 2 * g + ehalf) ^ (el32 % 16)) * 16))) =
                   floatx4{o[rb][ob][4 * g], o[rb][ob][4 * g + 1], o[rb][ob][4 * g + 2], o[rb][ob][4 * g + 3]};
             }
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
-            const int row = 4 * i + lane / 16;
-            const floatx4 piece = *(lds_f128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((lane % 16) ^ (row % 16)) * 16)));
-            // the slot of that row is held by the lane that owns the row
-            const int slot = __builtin_amdgcn_ds_bpermute(4 * row, o_slot[rb]);
-            if (32 * rb + row < o_len)
-              *reinterpret_cast<floatx4*>(head_base + static_cast<int64_t>(slot) * p.n_q_heads * (kD + kPartialPad) + 64 * h2) = piece;
+            const int row = 4 * i + ln / 16;
+            const floatx4 piece = *(lds_f128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((ln % 16) ^ (row % 16)) * 16)));
+            // (GATHER: the slot of that row is held by the lane that owns the row)
+            const int slot = GATHER ? __builtin_amdgcn_ds_bpermute(4 * row, o_slot[rb]) : first_row + row_base + row;
+            if (row_base + row < o_len) {
+              if constexpr (GATHER)
+                *reinterpret_cast<floatx4*>(p.partial + static_cast<int64_t>(o_head[rb]) * (kD + kPartialPad) + (ln % 16) * 4 +
+                                            static_cast<int64_t>(slot) * p.n_q_heads * (kD + kPartialPad) + 64 * h2) = piece;
+              else
+                *reinterpret_cast<floatx4*>(out + (static_cast<unsigned>(slot) * row_bytes + (ln % 16) * 16u) + 256 * h2) = piece;
+            }
           }
         }
-        if (half == 0 && o_valid[rb]) {
-          float* part = p.partial + (static_cast<int64_t>(o_slot[rb]) * p.n_q_heads + o_head[rb]) * (kD + kPartialPad);
-          part[kD] = seen[rb] ? m_run[rb] : -1.0e30f;
-          part[kD + 1] = l_tot;
-        }
-      }
-    } else if (!PERSIST && gridDim.z > 1) {
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb) {
-        const float l_tot = half_swap_sum(l_run[rb]);
-        if (!o_valid[rb]) continue;
-        float* part = p.partial + ((static_cast<int64_t>(o_tok[rb]) * p.n_q_heads + o_head[rb]) * gridDim.z + blockIdx.z) *
-                                      (kD + kPartialPad);
-#pragma unroll
-        for (int ob = 0; ob < kD / 32; ++ob)
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<floatx4*>(part + 32 * ob + 8 * g + 4 * half) =
-                floatx4{o[rb][ob][4 * g], o[rb][ob][4 * g + 1], o[rb][ob][4 * g + 2], o[rb][ob][4 * g + 3]};
-        if (half == 0) {
-          // a run none of whose keys the row may see contributes nothing: the merge weighs it with 2^(m - m*)
+        if (ehalf == 0 && o_valid[rb]) {
+          float* part = GATHER ? p.partial + (static_cast<int64_t>(o_slot[rb]) * p.n_q_heads + o_head[rb]) * (kD + kPartialPad)
+                               : reinterpret_cast<float*>(out + static_cast<unsigned>(first_row + row_base + el32) * row_bytes);
+          // a record none of whose keys the row may see contributes nothing: the merge weighs it with 2^(m - m*)
           part[kD] = seen[rb] ? m_run[rb] : -1.0e30f;
           part[kD + 1] = l_tot;
         }
@@ -910,19 +920,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
             } w;
             w.p2[0] = __builtin_convertvector(floatx2{o[rb][ob][4 * g] * inv, o[rb][ob][4 * g + 1] * inv}, bf16x2);
             w.p2[1] = __builtin_convertvector(floatx2{o[rb][ob][4 * g + 2] * inv, o[rb][ob][4 * g + 3] * inv}, bf16x2);
-            *(lds_b64)(static_cast<uintptr_t>(stag + l32 * kRowBytes + (((4 * ob + g) ^ (l32 % 16)) * 16) + half * 8)) = w.v;
+            *(lds_b64)(static_cast<uintptr_t>(stag + el32 * kRowBytes + (((4 * ob + g) ^ (el32 % 16)) * 16) + ehalf * 8)) = w.v;
           }
         const int row_base = ((2 * wave + rb) % spb) * 32;
         __bf16* op = static_cast<__bf16*>(const_cast<void*>(p.o.ptr)) + static_cast<int64_t>(o_head[rb]) * p.o.stride_head +
-                     (lane % 16) * 8;
+                     (ln % 16) * 8;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const int row = 4 * i + lane / 16;
-          const intx4 piece = *(lds_b128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((lane % 16) ^ (row % 16)) * 16)));
+          const int row = 4 * i + ln / 16;
+          const intx4 piece = *(lds_b128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((ln % 16) ^ (row % 16)) * 16)));
           if (row_base + row < o_len)
             *reinterpret_cast<intx4*>(op + static_cast<int64_t>(o_start + row_base + row) * p.o.stride_tok) = piece;
         }
-        if (p.lse && half == 0 && o_valid[rb])
+        if (p.lse && ehalf == 0 && o_valid[rb])
           p.lse[static_cast<int64_t>(o_head[rb]) * p.lse_stride + o_tok[rb]] = (m_run[rb] + __log2f(l_tot)) * 0.69314718055994531f;
       }
     }

@@ -39,7 +39,8 @@ struct AttnParams {
   float* lse;                 // optional [Hq][n_rows]
   int64_t lse_stride;         // rows per head in lse
   float* partial;             // decode: [slot][Hq][D + kPartialPad]; per-query splits use slot = u*n_split + s;
-                              // split prefill: [row][Hq][q_split][D + kPartialPad]
+                              // split prefill: [row][Hq][q_split][D + kPartialPad];
+                              // prefill with cut lists: [partial row][Hq][D + kPartialPad], see sched_part
   // group-major decode launch: workgroup id -> row (id / 8) % launch_rows of gm_rows + row_offset,
   // KV head (id / 8) / launch_rows, item 8 * block + id % 8 of the row's block; blocks below
   // n_pool_blocks hold pool items, the others self items (one per query)
@@ -63,6 +64,12 @@ struct AttnParams {
   const int32_t* sched_rec;
   const int32_t* sched_ptr;
   int32_t sched_classes, n_head_blocks;
+  // query prefill whose schedule cuts lists to measure (null: every record is a whole Q tile): record k leaves
+  // the partial states of its rows in partial rows sched_part[k] .., or the finished rows if that is -1.
+  // cut_tab: [n_cut_tiles][4] = (q_start, q_len, first partial row, pieces), the pieces q_len rows apart
+  const int32_t* sched_part;
+  const int32_t* cut_tab;
+  int32_t n_cut_tiles;
   // rows gathered through references (launch_decode_matrix_items): [n_refs][2] = (row of q, partial slot)
   const int32_t* gather_refs;
   const int32_t* gather_shift;  // [n_refs]: with re-positioning, rotation id of reference i's row = gather_shift[i] + self_len - 1

@@ -544,7 +544,6 @@ int dbsa_build_host_lists(const dbsa_pool_desc* pool, const dbsa_select_desc* se
 
 void dbsa_balance_records(const std::vector<int32_t>& rec_in, int32_t n_classes, std::vector<int32_t>* class_ptr,
                           std::vector<int32_t>* rec) {
-  constexpr int64_t kTileCost = 3;  // what a record costs beyond its list, in list entries
   const int64_t nt = static_cast<int64_t>(rec_in.size() / 4);
   std::vector<int64_t> load(static_cast<size_t>(n_classes), 0);
   std::vector<std::vector<int32_t>> recs_of(static_cast<size_t>(n_classes));
@@ -585,4 +584,111 @@ void dbsa_balance_schedule(const dbsa_layout* L, int32_t n_classes, std::vector<
     in_order.push_back(static_cast<int32_t>(L->list_ptr[t + 1] - L->list_ptr[t]));
   }
   dbsa_balance_records(in_order, n_classes, class_ptr, rec);
+}
+
+int64_t dbsa_cut_workers(const dbsa_layout* L, int64_t n_classes) {
+  // (a share of fewer entries than it costs to start, finish and merge a piece is not worth a worker)
+  constexpr int64_t kMinShare = 6;
+  return std::max<int64_t>(1, std::min<int64_t>(n_classes, L->n_ent() / kMinShare));
+}
+
+void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd) {
+  const int64_t nt = L->n_qtiles();
+  auto entries = [&](int32_t t) { return L->list_ptr[t + 1] - L->list_ptr[t]; };
+  const int64_t total = L->n_ent(), workers = dbsa_cut_workers(L, n_classes);
+  // One walk for a given share.  Returns the cost of the last worker, who takes the rest, or with `emit` fills the lists.
+  int64_t longest = 0;  // cost of the busiest worker of the last walk
+  auto deal = [&](int64_t share, bool emit) {
+    if (emit) {
+      L->cut_ptr.assign(1, 0);
+      L->cut_rec.clear();
+      L->cut_part.clear();
+      L->cut_tab.clear();
+      L->cut_rows = 0;
+    }
+    int64_t w = 0, acc = 0, n_rec = 0;
+    longest = 0;
+    auto next_worker = [&]() {
+      ++w;
+      acc = 0;
+      if (emit) L->cut_ptr.push_back(static_cast<int32_t>(n_rec));
+    };
+    for (int64_t i = 0; i < nt; ++i) {
+      const int32_t t = L->order[static_cast<size_t>(i)];
+      const int32_t* tile = &L->qtile_tab[4 * static_cast<size_t>(t)];
+      const int64_t n = entries(t), first_rec = n_rec;
+      for (int64_t pos = 0; pos < n;) {
+        const int64_t room = share - acc - kPieceCost, rem = n - pos;
+        int64_t take = rem;
+        if (w + 1 < workers && rem > room) {
+          // cut here, or leave the tile to the next worker where a piece would come out too short; a worker
+          // that has nothing yet always takes something
+          take = std::min(room, rem - kMinPiece);
+          if (take < kMinPiece && acc > 0) {
+            next_worker();
+            continue;
+          }
+          if (take < kMinPiece) take = rem < 2 * kMinPiece ? rem : kMinPiece;
+        }
+        acc += kPieceCost + take;
+        longest = std::max(longest, acc);
+        ++n_rec;
+        if (emit) {
+          L->cut_rec.insert(L->cut_rec.end(), {tile[0], tile[1], static_cast<int32_t>(L->list_ptr[t] + pos), static_cast<int32_t>(take)});
+          L->cut_part.push_back(-1);
+        }
+        pos += take;
+        if (w + 1 < workers && acc + kPieceCost + kMinPiece > share) next_worker();
+      }
+      if (emit && n_rec - first_rec > 1) {
+        L->cut_tab.insert(L->cut_tab.end(), {tile[0], tile[1], static_cast<int32_t>(L->cut_rows), static_cast<int32_t>(n_rec - first_rec)});
+        for (int64_t k = first_rec; k < n_rec; ++k) {
+          L->cut_part[static_cast<size_t>(k)] = static_cast<int32_t>(L->cut_rows);
+          L->cut_rows += tile[1];
+        }
+      }
+    }
+    if (emit) {
+      while (static_cast<int64_t>(L->cut_ptr.size()) <= n_classes) L->cut_ptr.push_back(static_cast<int32_t>(n_rec));
+    }
+    return w + 1 < workers ? int64_t{0} : acc;
+  };
+  // The smallest share with which the last worker is left no more than the others.  (With `hi` it surely is: a
+  // worker stops less than kPieceCost + 2 kMinPiece short of its share, and there are at most nt + workers records.)
+  int64_t lo = total / workers, hi = (total + kPieceCost * (nt + workers)) / workers + kPieceCost + 2 * kMinPiece + 1;
+  while (lo + 1 < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    (deal(mid, false) <= mid ? hi : lo) = mid;
+  }
+  deal(hi, false);
+  // Against whole Q tiles dealt to the same workers, and against runs of one length, one per workgroup: where these
+  // come out even (16 Q tiles over 32 workers in two runs each: 412 us against 421) every worker has one record to
+  // start and finish, and workers walk in step.  The merge pass costs about as much as two entries.  `crowd` is what
+  // an entry costs with every place taken over what it costs with few: two small workgroups per compute unit fetch a
+  // K/V pair per 128 rows each and are then bound by that traffic (512 of them move 7.4 TB/s; 50 questions of 20
+  // tokens on 400 of 512 places: whole lists 771 us, all places with cut lists 803).
+  auto per_entry = [&](int64_t busy) { return std::max(1.0, crowd * std::min(1.0, static_cast<double>(busy) / static_cast<double>(n_classes))); };
+  int64_t longest_list = 0;
+  for (int64_t t = 0; t < nt; ++t) longest_list = std::max(longest_list, entries(static_cast<int32_t>(t)));
+  const double list = static_cast<double>(longest_list), cost = static_cast<double>(kPieceCost);
+  const double cut = 1.03 * static_cast<double>(longest) * per_entry(workers) + 2.0;
+  double other = 1e30;
+  if (nt >= 2 * n_classes) {
+    std::vector<int32_t> ptr, rec;
+    dbsa_balance_schedule(L, n_classes, &ptr, &rec);
+    int64_t whole = 0;
+    for (int32_t c = 0; c < n_classes; ++c) {
+      int64_t load = 0;
+      for (int32_t k = ptr[static_cast<size_t>(c)]; k < ptr[static_cast<size_t>(c) + 1]; ++k) load += rec[4 * static_cast<size_t>(k) + 3] + kTileCost;
+      whole = std::max(whole, load);
+    }
+    other = static_cast<double>(whole) * per_entry(nt);
+  } else {
+    for (int64_t runs = 1; runs <= std::max<int64_t>(1, std::min(kMaxQuerySplit, L->shortest_list / kMinRun)); ++runs)
+      other = std::min(other, static_cast<double>((nt * runs + n_classes - 1) / n_classes) *
+                                      (list / static_cast<double>(runs) * per_entry(nt * runs) + cost) + (runs > 1 ? 2.0 : 0.0));
+  }
+  L->cut_worth = cut < other;
+  if (L->cut_worth) deal(hi, true);
+  L->cut_classes = n_classes;
 }

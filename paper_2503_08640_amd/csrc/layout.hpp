@@ -36,6 +36,14 @@ struct dbsa_device_lists {
   int32_t* sched_ptr = nullptr;   // [kMaxSchedClasses + 1]
   void* sched_uploaded = nullptr; // event recorded behind the schedule's copy
   void* sched_stream = nullptr;   // stream of that copy
+  // room for ONE schedule with lists cut to measure (dbsa_layout::cut_*), filled by the first query prefill that uses one
+  unsigned char* cut_room = nullptr;
+  int32_t* cut_rec = nullptr;     // [n_records][4]
+  int32_t* cut_ptr = nullptr;     // [workers + 1]
+  int32_t* cut_part = nullptr;    // [n_records]
+  int32_t* cut_tab = nullptr;     // [n_cut_tiles][4]
+  void* cut_uploaded = nullptr;
+  void* cut_stream = nullptr;
   // decode steps that run their pool items as a contraction (dbsa_layout::mx_rec): the segments'
   // tile entries, the flat references, and room for that launch's schedule, filled by the first
   // decode call that uses it
@@ -130,6 +138,15 @@ struct dbsa_layout {
   mutable int32_t sched_classes = 0;
   mutable std::vector<int32_t> sched_ptr, sched_rec;
   mutable bool sched_on_device = false;
+  // Schedule of a query prefill whose lists are cut to measure for cut_classes workers (dbsa_cut_schedule): class c
+  // walks records cut_ptr[c] .. cut_ptr[c+1]-1 of cut_rec (words as in sched_rec, a record being a run of a Q
+  // tile's list); cut_part: first partial row of a record, -1 = the record is a whole Q tile; cut_tab: the cut Q
+  // tiles (q_start, q_len, first partial row, pieces).  cut_worth: the launch gains from it.
+  mutable int32_t cut_classes = 0;
+  mutable std::vector<int32_t> cut_ptr, cut_rec, cut_part, cut_tab;
+  mutable int64_t cut_rows = 0;
+  mutable bool cut_worth = false, cut_on_device = false;
+  mutable bool cut_guessed = false;  // made with the lists for a likely model, not used by a call yet
   // the same for the records of mx_rec (a second, independent schedule)
   mutable int32_t mx_classes = 0;
   mutable std::vector<int32_t> mx_sched_ptr, mx_sched_rec;
@@ -149,6 +166,11 @@ struct dbsa_layout {
 };
 
 constexpr int32_t kMaxSchedClasses = 512;
+// what a record of a persistent prefill costs beyond its list, in list entries (whole Q tiles; a piece also leaves
+// partial states: 64-token pieces of 4 heads run at 3.0 k cycles an entry and 14 k around the list)
+constexpr int64_t kTileCost = 3, kPieceCost = 5;
+// runs of one length a query prefill's lists may be cut into instead: most runs per list, fewest entries per run
+constexpr int64_t kMaxQuerySplit = 16, kMinRun = 8;
 // share of a wave's 64 rows that must carry a query before a decode step runs its pool items as a
 // contraction (measured on a 90k-token pool, 8 KV heads, 32-256 queries, with the runs cut to measure:
 // at 0.24-0.5 the step is 3-26 % faster than with 32-column work items, at 0.18 and below 10-20 % slower)
@@ -165,6 +187,15 @@ void dbsa_balance_schedule(const dbsa_layout* L, int32_t n_classes, std::vector<
 // number of list entries.
 void dbsa_balance_records(const std::vector<int32_t>& rec_in, int32_t n_classes, std::vector<int32_t>* class_ptr,
                           std::vector<int32_t>* rec);
+
+// Cuts the lists of the Q tiles to measure for n_classes workers: the tiles are walked in launch order and dealt to
+// the workers one after the other, each taking list entries until its cost (entries + kPieceCost per record) reaches
+// the share; what does not fit is cut there, no piece is shorter than kMinPiece entries.  The share is the smallest
+// that leaves the last worker no more than the others.  Fills cut_classes and cut_worth of L and, if it is worth it,
+// the cut_* lists.  crowd: what an entry costs with all workers busy over what it costs with few.
+constexpr int64_t kMinPiece = 5;
+int64_t dbsa_cut_workers(const dbsa_layout* L, int64_t n_classes);  // workers that get records (the first ones)
+void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd);
 
 // Pure host integer work; returns a DBSA_* code and fills `L` on success.
 // first_group < 0: every segment; >= 0 (pre-encode only): Q tiles of groups first_group.. alone

@@ -314,3 +314,50 @@ def test_persistent_query_prefill_with_hundreds_of_ragged_queries():
     ref = _oracle_query(pc, qc, queries=queries)
     rows = np.concatenate([np.arange(qc.cu_qlens[u], qc.cu_qlens[u + 1]) for u in queries])
     assert_close(to_f64(oq)[rows], ref[rows], "persistent query prefill, 700 ragged queries")
+
+
+@pytest.mark.parametrize("hq,hkv,block_m,q_len,rope", [
+    (8, 2, 64, [64], False),            # one question: one Q tile in as many pieces as there are workers
+    (8, 2, 64, [64], True),
+    (8, 2, 64, [1, 130, 64, 20, 77], True),   # pieces of several Q tiles per worker, rows of very unequal tiles
+    (16, 4, 32, [31, 5, 32], False),    # two-wave workgroups
+    (4, 4, 256, [700, 90], False),      # four-wave workgroups of one head
+])
+def test_query_prefill_with_lists_cut_to_measure(hq, hkv, block_m, q_len, rope):
+    """Few Q tiles on many compute units: lists cut into unequal pieces, whose partial states a merge pass combines.
+    A workspace too small for them leaves the lists in fewer pieces or whole; every form must match the oracle."""
+    pc = small_pool_case("cutpool", 3400 + block_m + len(q_len), hq=hq, hkv=hkv, pool_tokens=9000, groups=3, lens=(32, 200), sigma=0.5)
+    sels = [[2, 0], [0, 1, 2], [1], [], [2, 1, 0]][:len(q_len)]
+    qc = synth.make_query_case("cutq", 3401, pc, n_queries=len(q_len), q_len=q_len, selections=sels)
+    p = pc.pool
+    lay, kp, vp = _query_setup(pc, qc, block_m, 0)
+    qs, ks, vs = to_dev(qc.q), to_dev(qc.k), to_dev(qc.v)
+    if rope:
+        from oracle import rope_oracle as ro
+        f = ro.inv_freq(500000.0, 128)
+        tab = B.dbsa_rope_table(f, 2 * p.n_tokens + 1000)
+        own = torch.from_numpy(np.concatenate([np.arange(n) for n in q_len]).astype(np.int32)).cuda()
+        ref = ro.query_attn_repositioned(synth.as_f64(qc.q), synth.as_f64(qc.k), synth.as_f64(qc.v), synth.as_f64(pc.k),
+                                         synth.as_f64(pc.v), p.sink_len, p.demo_offsets, p.group_demo_offsets, qc.cu_qlens,
+                                         qc.sel_ptr, qc.sel_idx, f, pc.scale)
+        kr, ksr = B.dbsa_rope_apply(kp, tab), B.dbsa_rope_apply(ks, tab, positions=own)
+        run = lambda ws: B.dbsa_query_attn_rope(lay, qs, ksr, vs, kr, vp, tab, pc.scale, workspace=ws)
+    else:
+        ref = _oracle_query(pc, qc)
+        lses = []
+
+        def run(ws):
+            lse = torch.zeros(hq, qs.shape[0], device="cuda")
+            o = B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, lse=lse, workspace=ws)
+            lses.append(lse)
+            return o
+    need = lay.workspace_bytes(hq, 128)
+    outs = [run(False)] + [run(torch.empty(n, dtype=torch.uint8, device="cuda")) for n in (need, need // 3, 16)]
+    for o, what in zip(outs, ("whole lists", "cut lists", "a third of the workspace", "no room")):
+        assert_close(to_f64(o), ref, f"{what} bm={block_m} T={q_len}")
+    assert not torch.equal(outs[0], outs[1]), "the workspace did not switch the cut lists on"
+    assert torch.equal(outs[0], outs[3])
+    if not rope:
+        want = oracle_query_lse(pc, qc)
+        for lse in lses:
+            assert_close(to_f64(lse), want, f"lse bm={block_m}")
