@@ -517,12 +517,18 @@ size_t decode_workspace_need(const dbsa_layout* L, int32_t n_q_heads, int32_t he
   return slots * n_q_heads * (head_dim + kPartialPad) * sizeof(float);
 }
 
-// Workgroups of a prefill-shaped launch that the chip holds at once: eight-wave-sized ones (112 KiB of LDS) sit alone
-// on a compute unit, smaller ones in pairs.
-int64_t prefill_places(const dbsa_layout* L, int row_blocks) { return workgroup_slots(L) / (row_blocks == 8 ? 2 : 1); }
+// Workgroups of a prefill-shaped launch that the chip holds at once: those of eight row blocks (four waves of 64 rows)
+// sit alone on a compute unit, smaller ones in pairs, and at head_dim 64 those of two row blocks (one wave) in fours.
+int64_t prefill_places(const dbsa_layout* L, int row_blocks, int head_dim) {
+  if (row_blocks == 8) return workgroup_slots(L) / 2;
+  return workgroup_slots(L) * (head_dim == 64 && row_blocks == 2 ? 2 : 1);
+}
+// the shapes of launch_prefill64, which walks a schedule
+bool schedulable(int row_blocks, int head_dim) { return row_blocks == 4 || row_blocks == 8 || (row_blocks == 2 && head_dim == 64); }
 
 // what a list entry costs with all workers busy over what it costs with few (dbsa_cut_schedule)
-double cut_crowding(int row_blocks) { return row_blocks == 4 ? 1.5 : 1.0; }
+// (a K/V pair serves 32 rows per row block; 256 rows keep the matrix pipes busy at the rate the pairs arrive)
+double cut_crowding(int row_blocks) { return row_blocks == 8 ? 1.0 : row_blocks == 4 ? 1.5 : 3.0; }
 
 // Runs per list of a launch of `wgs` workgroups (one run each) on `places`: the number that makes rounds * length
 // shortest.  A run costs kPieceCost entries to start and finish; every further run of a row is one more partial state,
@@ -548,13 +554,13 @@ int64_t query_runs(const dbsa_layout* L, int64_t wgs, int64_t places, int64_t st
 // Most partial states (rows of head_dim + 4 floats) a query prefill of n_q_heads can use, over the numbers of heads a
 // workgroup may take (the number of KV heads is not known here): workers - 1 cuts make at most one piece more each
 // than there are cut Q tiles, split lists have query_runs() runs.
-size_t query_prefill_states(const dbsa_layout* L, int32_t n_q_heads) {
+size_t query_prefill_states(const dbsa_layout* L, int32_t n_q_heads, int32_t head_dim) {
   size_t most = 0;
   for (int hpb = 1; hpb <= 8; hpb *= 2) {
     const int row_blocks = hpb * (L->block_m / 32);
     if (n_q_heads % hpb != 0 || row_blocks < 1 || row_blocks > 8) continue;
-    const int64_t head_blocks = n_q_heads / hpb, places = prefill_places(L, row_blocks), states = int64_t{1} * L->n_query_tokens * n_q_heads;
-    if (row_blocks >= 4) {
+    const int64_t head_blocks = n_q_heads / hpb, places = prefill_places(L, row_blocks, head_dim), states = int64_t{1} * L->n_query_tokens * n_q_heads;
+    if (schedulable(row_blocks, head_dim)) {
       const int64_t classes = std::min<int64_t>(places / head_blocks, kMaxSchedClasses);
       const int64_t cuts = std::max<int64_t>(0, dbsa_cut_workers(L, classes) - 1);
       const int64_t pieces = std::min(2 * cuts, cuts + L->n_qtiles());
@@ -681,17 +687,17 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
     p.heads_per_block = pick_heads_per_block(hq / hkv, L->block_m);
     p.n_rows = L->n_query_tokens;
     p.q_split = 1;
-    const bool pipelined = d == 128 && max_stride < (int64_t{1} << 24);
     const int row_blocks = p.heads_per_block * (L->block_m / 32);
-    const int64_t head_blocks = hq / p.heads_per_block, places = prefill_places(L, row_blocks);
+    const bool pipelined = max_stride < (int64_t{1} << 24) && (d == 128 || schedulable(row_blocks, d));
+    const int64_t head_blocks = hq / p.heads_per_block, places = prefill_places(L, row_blocks, d);
     const size_t state_bytes = (d + kPartialPad) * sizeof(float);
     const size_t room = workspace && reinterpret_cast<uintptr_t>(workspace) % 16 == 0 ? workspace_bytes / state_bytes : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // The kernel for four or eight row blocks runs persistently: as many workgroups as the chip holds (one of four
+    // The kernel with 64 rows per wave runs persistently: as many workgroups as the chip holds (one of four
     // waves or two of two per compute unit), each walking a balanced share of the Q tiles of its head block.  With
     // several Q tiles per worker whole tiles balance; a query prefill with fewer (down to one question of 64 tokens,
     // which is one Q tile) cuts the lists to measure if the caller gave a workspace for the pieces' partial states.
-    if (pipelined && (row_blocks == 4 || row_blocks == 8)) {
+    if (pipelined && schedulable(row_blocks, d)) {
       const int32_t classes = static_cast<int32_t>(std::min<int64_t>(places / head_blocks, kMaxSchedClasses));
       p.n_head_blocks = static_cast<int32_t>(head_blocks);
       p.sched_classes = classes;
@@ -710,7 +716,7 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
       }
     }
     // Otherwise a query prefill with fewer workgroups than the chip holds cuts every list into the same number of runs.
-    if (want_query_stage && d == 128 && !p.sched_rec) {
+    if (want_query_stage && pipelined && !p.sched_rec) {
       const int64_t states = static_cast<int64_t>(L->n_query_tokens) * hq;
       const int64_t runs = std::min<int64_t>(query_runs(L, L->n_qtiles() * head_blocks, places, states), room / std::max<int64_t>(states, 1));
       if (runs > 1) {
@@ -718,7 +724,7 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
         p.partial = static_cast<float*>(workspace);
       }
     }
-    e = pipelined ? launch_prefill_pipelined(p, s) : launch_prefill_mfma(p, d, s);
+    e = pipelined ? launch_prefill_pipelined(p, d, s) : launch_prefill_mfma(p, d, s);
   } else {
     e = launch_prefill_plain(p, d, /*bf16_storage=*/false, L->compute_units, static_cast<hipStream_t>(stream));
   }
@@ -770,7 +776,7 @@ int build_layout(const dbsa_pool_desc* pool, const dbsa_select_desc* sel, int32_
     // The schedule of the query prefill for 8 KV heads and workgroups of four query heads travels with the lists; for
     // other models the first call makes its own (host work and a copy of some 20 us).
     if (L->query_stage && (block_m == 32 || block_m == 64)) {
-      const int32_t classes = static_cast<int32_t>(std::min<int64_t>(prefill_places(L, block_m / 8) / 8, kMaxSchedClasses));
+      const int32_t classes = static_cast<int32_t>(std::min<int64_t>(prefill_places(L, block_m / 8, 128) / 8, kMaxSchedClasses));
       try {
         if (classes >= 1 && L->n_qtiles() < kCutTiles * classes) {
           dbsa_cut_schedule(L, classes, cut_crowding(block_m / 8));
@@ -912,7 +918,7 @@ void dbsa_layout_destroy(dbsa_layout* L) {
 size_t dbsa_workspace_bytes(const dbsa_layout* L, int32_t n_q_heads, int32_t head_dim) {
   if (!L || !L->query_stage || n_q_heads <= 0 || head_dim <= 0) return 0;
   return std::max(decode_workspace_bytes(L, n_q_heads, head_dim),
-                  query_prefill_states(L, n_q_heads) * (head_dim + kPartialPad) * sizeof(float));
+                  query_prefill_states(L, n_q_heads, head_dim) * (head_dim + kPartialPad) * sizeof(float));
 }
 
 int dbsa_preencode_attn(const dbsa_layout* layout, dbsa_tensor q, dbsa_tensor k, dbsa_tensor v, dbsa_tensor o,

@@ -477,14 +477,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
   }
 }
 
-// Merge of the n_split partial states of a (row, head): 32 threads per pair, four channels each.
+// Merge of the n_split partial states of a (row, head): D / 4 threads per pair, four channels each.
 // o = sum_z 2^(m_z - m*) acc_z / sum_z 2^(m_z - m*) l_z, statistics in the log2 domain.
-constexpr int kMergePairs = 8;  // (row, head) pairs per workgroup of 256 threads
-__global__ __launch_bounds__(32 * kMergePairs) void prefill_merge_kernel(AttnParams p, int n_rows, int n_split) {
-  const int64_t pair = static_cast<int64_t>(blockIdx.x) * kMergePairs + threadIdx.x / 32;
+constexpr int kMergeThreads = 256;
+template <int kD>
+__global__ __launch_bounds__(kMergeThreads) void prefill_merge_kernel(AttnParams p, int n_rows, int n_split) {
+  constexpr int kLanes = kD / 4;
+  const int64_t pair = static_cast<int64_t>(blockIdx.x) * (kMergeThreads / kLanes) + threadIdx.x / kLanes;
   if (pair >= static_cast<int64_t>(n_rows) * p.n_q_heads) return;
   const int row = static_cast<int>(pair / p.n_q_heads), head = static_cast<int>(pair % p.n_q_heads);
-  const int d = 4 * (threadIdx.x % 32);
+  const int d = 4 * (threadIdx.x % kLanes);
   const float* part = p.partial + pair * n_split * (kD + kPartialPad);
   float m_star = -1.0e30f;
   for (int z = 0; z < n_split; ++z) m_star = fmaxf(m_star, part[z * (kD + kPartialPad) + kD]);
@@ -507,17 +509,19 @@ __global__ __launch_bounds__(32 * kMergePairs) void prefill_merge_kernel(AttnPar
   if (p.lse && d == 0) p.lse[static_cast<int64_t>(head) * p.lse_stride + row] = (m_star + __log2f(l)) * 0.69314718055994531f;
 }
 
-// Merge for lists cut to measure (AttnParams::cut_tab): blockIdx.y = cut Q tile, 32 threads per (row, head), four
-// channels each.  Bound by latency while a Q tile has a few pieces (everything is requested at once then: 16 questions
+// Merge for lists cut to measure (AttnParams::cut_tab): blockIdx.y = cut Q tile, D / 4 threads per (row, head),
+// four channels each.  Bound by latency while a Q tile has a few pieces (everything is requested at once then: 16 questions
 // in two or three pieces each 16 -> 10 us) and by the partial states' way through the cache when it has as many as the
 // schedule has workers (one question alone on the chip; the threads then fetch the statistics side by side and the
 // states stream eight at a time: 64 rows x 32 heads x 32 pieces, 35 MB, 7.5 us).
-__global__ __launch_bounds__(32 * kMergePairs) void prefill_cut_merge_kernel(AttnParams p) {
+template <int kD>
+__global__ __launch_bounds__(kMergeThreads) void prefill_cut_merge_kernel(AttnParams p) {
+  constexpr int kLanes = kD / 4;
   const const_words tab = (const_words)(reinterpret_cast<uintptr_t>(p.cut_tab)) + 4 * blockIdx.y;
   const int q_start = tab[0], q_len = tab[1], part0 = tab[2], pieces = tab[3];
-  const int pair = static_cast<int>(blockIdx.x) * kMergePairs + threadIdx.x / 32;
-  if (pair >= q_len * p.n_q_heads) return;  // (all 32 threads of a pair)
-  const int row = pair / p.n_q_heads, head = pair % p.n_q_heads, lane = threadIdx.x % 32;
+  const int pair = static_cast<int>(blockIdx.x) * (kMergeThreads / kLanes) + threadIdx.x / kLanes;
+  if (pair >= q_len * p.n_q_heads) return;  // (all threads of a pair)
+  const int row = pair / p.n_q_heads, head = pair % p.n_q_heads, lane = threadIdx.x % kLanes;
   constexpr int kRow = kD + kPartialPad;
   const int64_t stride = static_cast<int64_t>(q_len) * p.n_q_heads * kRow;  // from piece to piece
   const float* part = p.partial + (static_cast<int64_t>(part0 + row) * p.n_q_heads + head) * kRow;
@@ -543,11 +547,11 @@ __global__ __launch_bounds__(32 * kMergePairs) void prefill_cut_merge_kernel(Att
       acc += state[z] * w;
     }
   } else {
-    for (int z0 = 0; z0 < pieces; z0 += 32) m_star = fmaxf(m_star, part[min(z0 + lane, pieces - 1) * stride + kD]);
+    for (int z0 = 0; z0 < pieces; z0 += kLanes) m_star = fmaxf(m_star, part[min(z0 + lane, pieces - 1) * stride + kD]);
 #pragma unroll
-    for (int s = 16; s > 0; s >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, s, 32));
-    for (int z0 = 0; z0 < pieces; z0 += 32) {
-      const int n = min(32, pieces - z0);
+    for (int s = kLanes / 2; s > 0; s >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, s, kLanes));
+    for (int z0 = 0; z0 < pieces; z0 += kLanes) {
+      const int n = min(kLanes, pieces - z0);
       const float* mine = part + (z0 + min(lane, n - 1)) * stride + kD;
       const float w_mine = lane < n ? __builtin_amdgcn_exp2f(mine[0] - m_star) : 0.f;
       l = fmaf(w_mine, mine[1], l);
@@ -555,10 +559,10 @@ __global__ __launch_bounds__(32 * kMergePairs) void prefill_cut_merge_kernel(Att
       for (int z1 = 0; z1 < n; z1 += 8)  // (pieces past the last repeat it with weight zero)
 #pragma unroll
         for (int z = z1; z < z1 + 8; ++z)
-          acc += *reinterpret_cast<const floatx4*>(state + min(z, n - 1) * stride) * __shfl(w_mine, z, 32);
+          acc += *reinterpret_cast<const floatx4*>(state + min(z, n - 1) * stride) * __shfl(w_mine, z, kLanes);
     }
 #pragma unroll
-    for (int s = 16; s > 0; s >>= 1) l += __shfl_xor(l, s, 32);
+    for (int s = kLanes / 2; s > 0; s >>= 1) l += __shfl_xor(l, s, kLanes);
   }
   const float inv = 1.f / l;
   union {
@@ -571,6 +575,22 @@ __global__ __launch_bounds__(32 * kMergePairs) void prefill_cut_merge_kernel(Att
   const int tok = q_start + row;
   *reinterpret_cast<bf16x4*>(o + static_cast<int64_t>(tok) * p.o.stride_tok + static_cast<int64_t>(head) * p.o.stride_head + 4 * lane) = w.v;
   if (p.lse && lane == 0) p.lse[static_cast<int64_t>(head) * p.lse_stride + tok] = (m_star + __log2f(l)) * 0.69314718055994531f;
+}
+
+// the merge pass of a query prefill whose lists were cut (p.sched_part) or split (p.q_split)
+template <int kD>
+hipError_t launch_merge(const AttnParams& p, hipStream_t stream) {
+  constexpr int64_t kPairs = kMergeThreads / (kD / 4);  // (row, head) pairs per workgroup
+  if (p.sched_part) {
+    if (p.n_cut_tiles == 0) return hipSuccess;
+    const int64_t pairs = static_cast<int64_t>(p.largest_tile) * p.n_q_heads;
+    prefill_cut_merge_kernel<kD><<<dim3(static_cast<unsigned>((pairs + kPairs - 1) / kPairs), p.n_cut_tiles), dim3(kMergeThreads), 0, stream>>>(p);
+    return hipGetLastError();
+  }
+  if (p.q_split <= 1) return hipSuccess;
+  const int64_t pairs = static_cast<int64_t>(p.n_rows) * p.n_q_heads;
+  prefill_merge_kernel<kD><<<dim3(static_cast<unsigned>((pairs + kPairs - 1) / kPairs)), dim3(kMergeThreads), 0, stream>>>(p, p.n_rows, p.q_split);
+  return hipGetLastError();
 }
 
 template <int NW, int SL, bool SELF, bool ROPE = false>
@@ -586,12 +606,8 @@ hipError_t launch_cfg(const AttnParams& p, hipStream_t stream) {
   const int n_split = p.q_split > 1 ? p.q_split : 1;
   dim3 grid(p.n_q_heads / p.heads_per_block, p.n_qtiles, n_split), block(NW * 64);
   attn_prefill_kernel<NW, SL, SELF, ROPE><<<grid, block, lds_bytes, stream>>>(p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || n_split == 1) return e;
-  const int64_t pairs = static_cast<int64_t>(p.n_rows) * p.n_q_heads;
-  prefill_merge_kernel<<<dim3(static_cast<unsigned>((pairs + kMergePairs - 1) / kMergePairs)), dim3(32 * kMergePairs), 0,
-                         stream>>>(p, p.n_rows, n_split);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? launch_merge<kD>(p, stream) : e;
 }
 
 template <int NW, int SL>
@@ -605,31 +621,19 @@ hipError_t launch_stage(const AttnParams& p, hipStream_t stream) {
 // One workgroup takes heads_per_block * (block_m / 32) row blocks of 32 rows, one per wave.  Eight
 // waves fill a compute unit on their own (one workgroup per CU: 112 KiB of LDS buy two steps of
 // load slack); smaller workgroups share a CU in pairs and take 80 KiB each.
-hipError_t launch_prefill_pipelined(const AttnParams& p, hipStream_t stream) {
+hipError_t launch_prefill_pipelined(const AttnParams& p, int head_dim, hipStream_t stream) {
   if (p.n_qtiles == 0) return hipSuccess;
   const int row_blocks = p.heads_per_block * (p.block_m / 32);
-  // four or eight row blocks: the kernel with 64 rows per wave, one wave per SIMD (persistent if
-  // the call carries a schedule, else one workgroup per Q tile and run)
-  if (row_blocks == 4 || row_blocks == 8) {
-    hipError_t e = launch_prefill64(p, stream);
-    if (e == hipSuccess && p.sched_part) {
-      if (p.n_cut_tiles == 0) return e;
-      const int pairs = p.largest_tile * p.n_q_heads;
-      prefill_cut_merge_kernel<<<dim3((pairs + kMergePairs - 1) / kMergePairs, p.n_cut_tiles), dim3(32 * kMergePairs), 0, stream>>>(p);
-      return hipGetLastError();
-    }
-    const int n_split = p.q_split > 1 ? p.q_split : 1;
-    if (e != hipSuccess || n_split == 1) return e;
-    const int64_t pairs = static_cast<int64_t>(p.n_rows) * p.n_q_heads;
-    prefill_merge_kernel<<<dim3(static_cast<unsigned>((pairs + kMergePairs - 1) / kMergePairs)), dim3(32 * kMergePairs), 0,
-                           stream>>>(p, p.n_rows, n_split);
-    return hipGetLastError();
+  // four or eight row blocks (head_dim 64: or two): the kernel with 64 rows per wave, one wave per SIMD (persistent
+  // if the call carries a schedule, else one workgroup per Q tile and run)
+  if (head_dim == 64 || row_blocks == 4 || row_blocks == 8) {
+    const hipError_t e = launch_prefill64(p, head_dim, stream);
+    if (e != hipSuccess) return e;
+    return head_dim == 64 ? launch_merge<64>(p, stream) : launch_merge<128>(p, stream);
   }
   switch (row_blocks) {
     case 1: return launch_stage<1, 1>(p, stream);
     case 2: return launch_stage<2, 1>(p, stream);
-    case 4: return launch_stage<4, 1>(p, stream);
-    case 8: return launch_stage<8, 2>(p, stream);
     default: return hipErrorInvalidValue;
   }
 }

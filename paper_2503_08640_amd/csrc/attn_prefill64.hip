@@ -35,15 +35,7 @@
 namespace {
 using namespace dbsa_mfma;
 
-constexpr int kD = 128;
 constexpr int kBN = 64;                       // keys per KV tile
-constexpr int kRowBytes = kD * 2;             // 256
-constexpr int kTileBytes = kBN * kRowBytes;   // 16 KiB per K or V tile
-// Operand fragments are read from LDS kDist fragments (two matrix instructions each) before their use, into
-// slot (index in the step) % kRing of a ring; kRing divides the fragments of every step, so that the fragments
-// one step reads for the next land where that step looks for them.
-constexpr int kRing = 8;
-constexpr int kDist = 5;
 // a lane's sum of the 16 probabilities of one step above which the step is redone around the true
 // row maximum: below it every probability is under 2^10, far inside bf16 and fp32
 constexpr float kOverflowSum = 1024.f;
@@ -131,7 +123,7 @@ struct StepCfg {
 // the shift, so the fragments are rebuilt only where it changes, from the rows in memory.
 // With GATHER (decode step) a record lies inside one segment, so its rows are rotated once, at the record's
 // start, each at its own id gather_shift[reference] + self_len[query] - 1.
-template <int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false>
+template <int kD, int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_prefill64_kernel(AttnParams p) {
   static_assert(!GATHER || (PERSIST && !SELF), "gathered rows come with a schedule and pool tiles only");
   static_assert(!ROPE || (SELF != GATHER), "rows are re-positioned at the query prefill and at the decode step");
@@ -140,9 +132,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   constexpr bool kEntryIds = ROPE && !GATHER;
   constexpr bool kPieces = PERSIST && SELF;  // records may be pieces of a Q tile's list
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  constexpr int kBlocksPerWave = 16 / NW;  // 1-KiB load blocks of one operand per wave
+  constexpr int kRowBytes = kD * 2;            // 256 or 128
+  constexpr int kTileBytes = kBN * kRowBytes;  // 16 or 8 KiB per K or V tile
+  constexpr int kChunks = kD / 16, kBlocks = kD / 32;  // 16-channel chunks of a row, 32-channel blocks of the output
+  constexpr int kPieces16 = kRowBytes / 16;            // 16-byte pieces of a row
+  constexpr int kLoadRows = 1024 / kRowBytes;          // rows of a 1-KiB load block
+  // Operand fragments are read from LDS kDist fragments (two matrix instructions each) before their use, into
+  // slot (index in the step) % kRing of a ring; kRing divides the fragments of every step, so that the fragments
+  // one step reads for the next land where that step looks for them.
+  constexpr int kRing = kChunks, kDist = kD == 128 ? 5 : 3;
+  // head_dim 128: Q is multiplied by scale * log2 e before its fragments are rounded to bf16 again, scores come out in
+  // log2 units and a probability is one exponential of a matrix result.  head_dim 64: the fragments are the rows of Q
+  // as they are, scores are raw dot products and a probability costs a multiplication more (the rounding of the
+  // scaled row weighs twice as much over half the channels; the matrix pipe waits for the exponentials either way).
+  constexpr bool kRawQ = kD == 64;
+  constexpr int kBlocksPerWave = kTileBytes / 1024 / NW;  // 1-KiB load blocks of one operand per wave
   constexpr int KS = 2 + SL, VS = 1 + SL;  // LDS stages of K and of V
-  static_assert(NW == 2 || NW == 4, "wave count");
+  static_assert(kD == 128 || kD == 64, "head dimension");
+  static_assert(NW == 2 || NW == 4 || (NW == 1 && kD == 64), "wave count");
+  static_assert(!ROPE || kD == 128, "rows of 64 channels are not re-positioned here");
   static_assert(SL == 1 || SL == 2 || SL == 3, "load slack");
   const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_byte*)smem));
 
@@ -199,7 +207,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
   // ---- global -> LDS loads: this wave fills blocks wave*kBlocksPerWave .. of each operand ----
   // lane -> (row, slot) inside block b: row = 4*b + lane/16, slot = lane%16; the piece fetched
-  // into that slot is column (slot ^ swizzle(row)): K by row % 16, V by 4 * (row % 4).
+  // into that slot is column (slot ^ swizzle(row)): K by row % 16, V by 4 * (row % 4).  (Rows of 128 bytes lie in
+  // pairs on the 64 banks, 8 rows to a block: swizzles by row pair, K by (row / 2) % 8, V by 4 * ((row / 2) % 2).)
+  auto k_swizzle = [](int row) { return kD == 128 ? row % 16 : (row / 2) % 8; };
+  auto v_swizzle = [](int row) { return kD == 128 ? 4 * (row % 4) : 4 * ((row / 2) % 2); };
+  auto block_row = [&](int b) { return kLoadRows * (wave * kBlocksPerWave + b) + lane / kPieces16; };
   // The loads a step spreads over its matrix instructions come in groups of four 1-KiB blocks: the first of a
   // group sets the LDS base (m0), the others reach their block with the instruction's offset field, which moves
   // the global address along with the LDS address.  The per-lane offsets therefore carry lane_bias(j) =
@@ -209,9 +221,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   unsigned k_lane_off[kBlocksPerWave], v_lane_off[kBlocksPerWave];
 #pragma unroll
   for (int j = 0; j < kBlocksPerWave; ++j) {
-    const int row_in = 4 * (wave * kBlocksPerWave + j) + lane / 16;
-    k_lane_off[j] = static_cast<unsigned>(row_in * kp_stride + (((lane % 16) ^ (row_in % 16)) * 8)) * 2u + lane_bias(j);
-    v_lane_off[j] = static_cast<unsigned>(row_in * vp_stride + (((lane % 16) ^ (4 * (row_in % 4))) * 8)) * 2u + lane_bias(j);
+    const int row_in = block_row(j);
+    k_lane_off[j] = static_cast<unsigned>(row_in * kp_stride + (((lane % kPieces16) ^ k_swizzle(row_in)) * 8)) * 2u + lane_bias(j);
+    v_lane_off[j] = static_cast<unsigned>(row_in * vp_stride + (((lane % kPieces16) ^ v_swizzle(row_in)) * 8)) * 2u + lane_bias(j);
   }
   auto issue_k = [&](const TileRef& t, int stage) DBSA_INLINE {
     const uint64_t base = pick(t.self, kself, kpool) + static_cast<uint64_t>(static_cast<unsigned>(t.start)) *
@@ -224,9 +236,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       const int stride = pick(t.self, ks_stride, kp_stride);
 #pragma unroll
       for (int j = 0; j < kBlocksPerWave; ++j) {
-        const int row_in = 4 * (wave * kBlocksPerWave + j) + lane / 16;
+        const int row_in = block_row(j);
         const int row = min(row_in, t.len - 1);  // rows past the tail repeat the last key
-        dma16(base, static_cast<unsigned>(row * stride + (((lane % 16) ^ (row_in % 16)) * 8)) * 2u, dst + j * 1024);
+        dma16(base, static_cast<unsigned>(row * stride + (((lane % kPieces16) ^ k_swizzle(row_in)) * 8)) * 2u, dst + j * 1024);
       }
     }
   };
@@ -241,9 +253,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       const int stride = pick(t.self, vs_stride, vp_stride);
 #pragma unroll
       for (int j = 0; j < kBlocksPerWave; ++j) {
-        const int row_in = 4 * (wave * kBlocksPerWave + j) + lane / 16;
+        const int row_in = block_row(j);
         const int row = min(row_in, t.len - 1);
-        dma16(base, static_cast<unsigned>(row * stride + (((lane % 16) ^ (4 * (row_in % 4))) * 8)) * 2u,
+        dma16(base, static_cast<unsigned>(row * stride + (((lane % kPieces16) ^ v_swizzle(row_in)) * 8)) * 2u,
               dst + j * 1024);
       }
     }
@@ -251,27 +263,27 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
   // ---- per-lane LDS read addresses (absolute LDS byte addresses, stage included) ----
   // K fragment (kb, c): row kb*32 + l32, slot (2c + half) ^ (l32 % 16) = k_base ^ (32*c)
-  const int k_base = l32 * kRowBytes + ((half ^ (l32 % 16)) * 16);
+  const int k_base = l32 * kRowBytes + ((half ^ k_swizzle(l32)) * 16);
   // V transpose-read fragment (ob, keys k0..): row k0 + 4*half + j, j = (lane%16)/4; channel
   // slot 4*ob + 2*(l32/16) + (lane%4)/2, swizzled by 4*j; 8-byte half (lane%2) = v_base ^ (64*ob)
   const int v_base = (4 * half + (lane % 16) / 4) * kRowBytes +
-                     (((2 * (l32 / 16) + (lane % 4) / 2) ^ (4 * ((lane % 16) / 4))) * 16) + (lane % 2) * 8;
-  int kaddr[8], vaddr[4];  // of the K stage / V stage the fragment reads currently walk
+                     (((2 * (l32 / 16) + (lane % 4) / 2) ^ v_swizzle((lane % 16) / 4)) * 16) + (lane % 2) * 8;
+  int kaddr[kChunks], vaddr[kBlocks];  // of the K stage / V stage the fragment reads currently walk
 #pragma unroll
-  for (int c = 0; c < 8; ++c) kaddr[c] = static_cast<int>(lds0) + (k_base ^ (32 * c));
+  for (int c = 0; c < kChunks; ++c) kaddr[c] = static_cast<int>(lds0) + (k_base ^ (32 * c));
 #pragma unroll
-  for (int ob = 0; ob < 4; ++ob) vaddr[ob] = static_cast<int>(lds0) + KS * kTileBytes + (v_base ^ (64 * ob));
+  for (int ob = 0; ob < kBlocks; ++ob) vaddr[ob] = static_cast<int>(lds0) + KS * kTileBytes + (v_base ^ (64 * ob));
   int k_rd = 0, v_rd = 0;  // stage the K / V fragment addresses point into
-  // K fragment t (t = kb*8 + c); V fragment t (t = kb*8 + ch*4 + ob)
+  // K fragment t (t = kb*kChunks + c); V fragment t (t = kb*kChunks + ch*kBlocks + ob)
   auto ld_k = [&](auto T) DBSA_INLINE {
     constexpr int t = decltype(T)::value;
-    return *(reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(static_cast<uintptr_t>(kaddr[t % 8])) +
-             (t / 8) * 32 * kRowBytes / 16);
+    return *(reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(static_cast<uintptr_t>(kaddr[t % kChunks])) +
+             (t / kChunks) * 32 * kRowBytes / 16);
   };
   auto ld_v = [&](auto T) DBSA_INLINE {
     constexpr int t = decltype(T)::value;
-    const lds_byte* vp = reinterpret_cast<const lds_byte*>(static_cast<uintptr_t>(vaddr[t % 4])) +
-                         ((t / 8) * 32 + ((t / 4) % 2) * 16) * kRowBytes;
+    const lds_byte* vp = reinterpret_cast<const lds_byte*>(static_cast<uintptr_t>(vaddr[t % kBlocks])) +
+                         ((t / kChunks) * 32 + ((t / kBlocks) % 2) * 16) * kRowBytes;
     const bf16x4 lo = lds_read_tr(vp);
     const bf16x4 hi = lds_read_tr(vp + 8 * kRowBytes);
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -280,14 +292,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     const int k_next = (k_rd + 1 == KS) ? 0 : k_rd + 1;
     const int dk = (k_next - k_rd) * kTileBytes;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) kaddr[c] += dk;
+    for (int c = 0; c < kChunks; ++c) kaddr[c] += dk;
     k_rd = k_next;
   };
   auto advance_v = [&]() DBSA_INLINE {
     const int v_next = (v_rd + 1 == VS) ? 0 : v_rd + 1;
     const int dv = (v_next - v_rd) * kTileBytes;
 #pragma unroll
-    for (int ob = 0; ob < 4; ++ob) vaddr[ob] += dv;
+    for (int ob = 0; ob < kBlocks; ++ob) vaddr[ob] += dv;
     v_rd = v_next;
   };
 
@@ -356,6 +368,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
   // ---- per Q tile: rows, Q^T fragments, softmax state ----
   const float c2 = p.scale_log2e;
+  const float score_unit = kRawQ ? 1.f / c2 : 1.f;  // one log2 unit in units of the scores
+  auto log2_units = [&](float s) DBSA_INLINE { return kRawQ ? s * c2 : s; };
+  // a running maximum moves by whole log2 units, which rescales exactly; raw scores are scaled in fp32 anyway, and the
+  // exact maximum leaves the largest probability without a rounding error
+  auto whole_units = [&](float x) DBSA_INLINE { return kRawQ ? x : __builtin_ceilf(x); };
   int head[2], row_local[2], row_tok[2], q_pos[2];
   int row_slot[2] = {0, 0};  // GATHER: where the row's partial state goes
   int row_rot[2] = {0, 0};   // GATHER with ROPE: the row's rotation id
@@ -398,7 +415,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll
       for (int c = 0; c < kD / 16; ++c) q_raw[rb][c] = *reinterpret_cast<const bf16x8*>(q_next[rb] + 16 * c);
   };
-  intx4 qf[2][kD / 16];  // Q^T fragments pre-multiplied by scale*log2(e), in accumulation registers
+  intx4 qf[2][kD / 16];  // Q^T fragments (pre-multiplied by scale*log2(e) unless kRawQ), in accumulation registers
   auto scale_q = [&]() DBSA_INLINE {
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
@@ -408,10 +425,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
           bf16x8 v;
           bf16x2 p2[4];
         } sc;
+        sc.v = q_raw[rb][c];
+        if constexpr (!kRawQ) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          sc.p2[e] = __builtin_convertvector(floatx2{static_cast<float>(q_raw[rb][c][2 * e]) * c2,
-                                                     static_cast<float>(q_raw[rb][c][2 * e + 1]) * c2}, bf16x2);
+          for (int e = 0; e < 4; ++e)
+            sc.p2[e] = __builtin_convertvector(floatx2{static_cast<float>(q_raw[rb][c][2 * e]) * c2,
+                                                       static_cast<float>(q_raw[rb][c][2 * e + 1]) * c2}, bf16x2);
+        }
         qf[rb][c] = __builtin_bit_cast(intx4, sc.v);
         asm volatile("" : "+a"(qf[rb][c]));
       }
@@ -428,7 +448,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
                          static_cast<int64_t>(head[rb]) * p.q.stride_head + 8 * half;
       const int id = min(max(GATHER ? row_rot[rb] : shift + row_local[rb], 0), p.rope_n_pos - 1);
       const float* rot = p.rope_table + static_cast<int64_t>(id) * kD + 16 * half;
-      bf16x8 frag[kD / 16];
+      bf16x8 frag[8];
       load_query_fragments<true>(qp, rot, c2, frag);
 #pragma unroll
       for (int c = 0; c < kD / 16; ++c) {
@@ -442,7 +462,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   if constexpr (!ROPE) load_q();
 
   floatx16 o[2][kD / 32];
-  floatx16 neg_m[2];                     // minus the running maximum in every element: C operand of a score block's first product
+  floatx16 neg_m[2];                     // minus the running maximum (in units of the scores) in every element: C operand of a score block's first product
   float m_run[2], l_run[2];              // running max (log2 domain, meaningful once seen); this lane's share of the row sum
   bool seen[2];                          // the row has met a visible key
 
@@ -489,7 +509,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   auto step = [&](auto CFG, floatx16 (&S_w)[2], floatx16 (&S_r)[2], bf16x2 (&P_w)[2][8], bf16x2 (&P_r)[2][8],
                   const TileRef& tq) DBSA_INLINE {
     using C = decltype(CFG);
-    constexpr int nK = C::QK ? 8 : 0, nV = C::PV ? 8 : 0, nF = nK + nV, nSlots = 2 * nF;
+    constexpr int nK = C::QK ? kChunks : 0, nV = C::PV ? kChunks : 0, nF = nK + nV, nSlots = 2 * nF;
+    constexpr bool kWhole = C::QK && C::PV;  // a step of the steady state; the others are half as long
     constexpr int nRead = nF + (C::PRE_OUT ? kDist : 0);  // fragments this step reads from LDS, its own first
     static_assert(nF % kRing == 0 && kDist < kRing, "ring slots carry over from step to step");
 
@@ -503,7 +524,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         matrix_result_fence();
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
-          const float delta = __builtin_ceilf(fmaxf(row_max(S_w[rb]), 0.f));  // whole log2 units
+          const float delta = whole_units(fmaxf(log2_units(row_max(S_w[rb])), 0.f));
           const float alpha = __builtin_amdgcn_exp2f(-delta);
           m_run[rb] += delta;
           l_run[rb] *= alpha;
@@ -519,15 +540,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
           float sum = 0.f;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            const float x0 = __builtin_amdgcn_exp2f(S_w[rb][2 * e] - delta), x1 = __builtin_amdgcn_exp2f(S_w[rb][2 * e + 1] - delta);
+            const float x0 = __builtin_amdgcn_exp2f(log2_units(S_w[rb][2 * e]) - delta), x1 = __builtin_amdgcn_exp2f(log2_units(S_w[rb][2 * e + 1]) - delta);
             P_r[rb][e] = __builtin_convertvector(floatx2{x0, x1}, bf16x2);
             sum += x0 + x1;
           }
           ls[rb] = sum;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) S_r[rb][i] -= delta;
+          for (int i = 0; i < 16; ++i) S_r[rb][i] -= delta * score_unit;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) neg_m[rb][i] -= delta;
+          for (int i = 0; i < 16; ++i) neg_m[rb][i] -= delta * score_unit;
         }
         valu_result_fence();
       }
@@ -545,13 +566,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         for (int rb = 0; rb < 2; ++rb) {
           const float m_true = row_max(S_r[rb]);
           const bool first = !seen[rb] & (m_true > kNoKey);
-          const float delta = first ? __builtin_ceilf(m_true) : 0.f;
+          const float delta = first ? whole_units(log2_units(m_true)) : 0.f;
           seen[rb] = seen[rb] | first;
           m_run[rb] += delta;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) S_r[rb][i] -= delta;
+          for (int i = 0; i < 16; ++i) S_r[rb][i] -= delta * score_unit;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) neg_m[rb][i] -= delta;
+          for (int i = 0; i < 16; ++i) neg_m[rb][i] -= delta * score_unit;
         }
         all_seen = __builtin_amdgcn_ballot_w64(!seen[0] | !seen[1]) == 0;
         valu_result_fence();
@@ -563,11 +584,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     auto read_frag = [&](auto I) DBSA_INLINE {
       constexpr int i = decltype(I)::value;
       if constexpr (i < nK)
-        ring[i % kRing] = ld_k(std::integral_constant<int, C::KBQ * 8 + i>{});
+        ring[i % kRing] = ld_k(std::integral_constant<int, C::KBQ * kChunks + i>{});
       else if constexpr (i < nF)
-        ring[i % kRing] = ld_v(std::integral_constant<int, C::KBP * 8 + (i - nK)>{});
+        ring[i % kRing] = ld_v(std::integral_constant<int, C::KBP * kChunks + (i - nK)>{});
       else
-        ring[i % kRing] = ld_k(std::integral_constant<int, (C::QK ? 1 - C::KBQ : 0) * 8 + (i - nF)>{});
+        ring[i % kRing] = ld_k(std::integral_constant<int, (C::QK ? 1 - C::KBQ : 0) * kChunks + (i - nF)>{});
     };
     if constexpr (!C::PRE_IN) static_for<(kDist < nRead ? kDist : nRead)>([&](auto I) DBSA_INLINE { read_frag(I); });
 
@@ -588,7 +609,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         else
           mfma_scores_acc(S_w[rb], ring[f % kRing], qf[rb][f]);
       } else {
-        constexpr int g = f - nK, ch = g / 4, ob = g % 4;
+        constexpr int g = f - nK, ch = g / kBlocks, ob = g % kBlocks;
         union {
           bf16x8 v;
           bf16x2 p2[4];
@@ -628,10 +649,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         // 16 units (8 per row block) of two exponentials.  A full step has two slots per unit: one
         // exponential in each, and behind it one half of the previous unit's packing (a result of the
         // transcendental unit cannot be used by the very next instructions), so that every matrix
-        // instruction shadows about the same vector work.  A short step has one slot per unit.
+        // instruction shadows about the same vector work.  Shorter steps (and all of head dimension 64) take one or
+        // two whole units per slot.
         if constexpr (nSlots >= 32) {
           constexpr int u = t / 2, w = t % 2;
-          ee[u % 2][w] = __builtin_amdgcn_exp2f(S_r[u / 8][2 * (u % 8) + w]);
+          ee[u % 2][w] = __builtin_amdgcn_exp2f(log2_units(S_r[u / 8][2 * (u % 8) + w]));
           asm volatile("" : "+v"(ee[u % 2][w]));
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (u > 0) {
@@ -646,23 +668,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
             }
           }
         } else {
-          constexpr int u = t;
-          ee[u % 2][0] = __builtin_amdgcn_exp2f(S_r[u / 8][2 * (u % 8)]);
-          ee[u % 2][1] = __builtin_amdgcn_exp2f(S_r[u / 8][2 * (u % 8) + 1]);
-          asm volatile("" : "+v"(ee[u % 2][0]), "+v"(ee[u % 2][1]));
-          // the previous unit is packed behind these exponentials
-          __builtin_amdgcn_sched_barrier(0);
-          if constexpr (u > 0) pack_unit(std::integral_constant<int, u - 1>{});
+          static_for<16 / nSlots>([&](auto K) DBSA_INLINE {
+            constexpr int u = t * (16 / nSlots) + decltype(K)::value;
+            ee[u % 2][0] = __builtin_amdgcn_exp2f(log2_units(S_r[u / 8][2 * (u % 8)]));
+            ee[u % 2][1] = __builtin_amdgcn_exp2f(log2_units(S_r[u / 8][2 * (u % 8) + 1]));
+            asm volatile("" : "+v"(ee[u % 2][0]), "+v"(ee[u % 2][1]));
+            // the previous unit is packed behind these exponentials
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (u > 0) pack_unit(std::integral_constant<int, u - 1>{});
+          });
         }
       }
-      if constexpr (C::QK && C::MASK && nSlots >= 32 && t == 24) {
+      if constexpr (C::MASK && kWhole && t == 2 * nK + 8 - (kD == 64)) {
         // the new scores' last product is eight matrix instructions back
         if (__builtin_expect(tq.causal || tq.len < kBN, 0)) apply_mask(S_w, tq, C::KBQ);
       }
       __builtin_amdgcn_sched_barrier(0);
     });
     if constexpr (C::SM) pack_unit(std::integral_constant<int, 15>{});
-    if constexpr (C::QK && nSlots < 32) {
+    if constexpr (C::QK && !kWhole) {
       // a short step: the next step reads these scores right away
       matrix_result_fence();
       if constexpr (C::MASK) {
@@ -678,10 +702,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   auto lane_offsets = [&](unsigned (&off)[kBlocksPerWave], const TileRef& t, int stride, bool for_v) DBSA_INLINE {
 #pragma unroll
     for (int i = 0; i < kBlocksPerWave; ++i) {
-      const int row_in = 4 * (wave * kBlocksPerWave + i) + lane / 16;
+      const int row_in = block_row(i);
       const int row = min(row_in, t.len - 1);  // rows past the tail repeat the last key
-      const int sw = for_v ? 4 * (row_in % 4) : row_in % 16;
-      off[i] = static_cast<unsigned>(row * stride + (((lane % 16) ^ sw) * 8)) * 2u + lane_bias(i);
+      const int sw = for_v ? v_swizzle(row_in) : k_swizzle(row_in);
+      off[i] = static_cast<unsigned>(row * stride + (((lane % kPieces16) ^ sw) * 8)) * 2u + lane_bias(i);
     }
   };
   // the K tile (entry 1+SL ahead) / the V tile (entry SL-1 ahead) a period loads
@@ -839,14 +863,20 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     int ln = lane;
     if constexpr (kPieces) asm volatile("" : "+v"(ln));
     const int el32 = ln % 32, ehalf = ln / 32;
+    // 8 KiB of LDS per wave to turn its rows around in: in the stages of the last K and V tiles, and for the waves those
+    // do not hold (four waves, tiles of 8 KiB) behind the ring
+    auto staging = [&]() DBSA_INLINE {
+      const int k_last = (k_rd == 0 ? KS : k_rd) - 1, v_last = (v_rd == 0 ? VS : v_rd) - 1;
+      constexpr int kPerStage = NW == 4 ? kTileBytes / 8192 : 1;
+      const int stage = wave / kPerStage == 0 ? k_last : wave / kPerStage == 1 ? KS + v_last : KS + VS + wave / kPerStage - 2;
+      return lds0 + static_cast<unsigned>(stage * kTileBytes + (wave % kPerStage) * 8192);
+    };
     if (GATHER || (kPieces && o_part >= 0) || (!PERSIST && gridDim.z > 1)) {
-      // Partial states, 528-byte rows of fp32: like the normalised outputs below they go through LDS
+      // Partial states, rows of kD + 4 floats: like the normalised outputs below they go through LDS
       // so that a store instruction writes whole 256-byte pieces of four rows instead of 16 bytes of
       // each of 32 rows; a row block passes in two halves of 64 channels, 8 KiB of staging per wave.
       __builtin_amdgcn_s_barrier();
-      const int k_last = (k_rd == 0 ? KS : k_rd) - 1, v_last = (v_rd == 0 ? VS : v_rd) - 1;
-      const bool in_k = (NW == 4 ? wave / 2 : wave) == 0;
-      const unsigned stag = lds0 + (in_k ? k_last : KS + v_last) * kTileBytes + (NW == 4 ? (wave % 2) * 8192 : 0);
+      const unsigned stag = staging();
       typedef __attribute__((address_space(3))) floatx4* lds_f128;
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
@@ -860,19 +890,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
                                    (static_cast<size_t>(__builtin_amdgcn_readfirstlane(o_head[rb])) * runs + (PERSIST ? 0 : blockIdx.z)) * kStateBytes;
         const int first_row = PERSIST ? o_part : o_start;
 #pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2) {
+        for (int h2 = 0; h2 < kD / 64; ++h2) {
 #pragma unroll
           for (int ob2 = 0; ob2 < 2; ++ob2)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
               const int ob = 2 * h2 + ob2;
-              *(lds_f128)(static_cast<uintptr_t>(stag + el32 * kRowBytes + (((8 * ob2 + 2 * g + ehalf) ^ (el32 % 16)) * 16))) =
+              *(lds_f128)(static_cast<uintptr_t>(stag + el32 * 256 + (((8 * ob2 + 2 * g + ehalf) ^ (el32 % 16)) * 16))) =
                   floatx4{o[rb][ob][4 * g], o[rb][ob][4 * g + 1], o[rb][ob][4 * g + 2], o[rb][ob][4 * g + 3]};
             }
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             const int row = 4 * i + ln / 16;
-            const floatx4 piece = *(lds_f128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((ln % 16) ^ (row % 16)) * 16)));
+            const floatx4 piece = *(lds_f128)(static_cast<uintptr_t>(stag + row * 256 + (((ln % 16) ^ (row % 16)) * 16)));
             // (GATHER: the slot of that row is held by the lane that owns the row)
             const int slot = GATHER ? __builtin_amdgcn_ds_bpermute(4 * row, o_slot[rb]) : first_row + row_base + row;
             if (row_base + row < o_len) {
@@ -901,9 +931,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       // with r % 16, so that both the writes (one row per lane) and the reads (16 lanes per row)
       // spread over all banks.
       __builtin_amdgcn_s_barrier();
-      const int k_last = (k_rd == 0 ? KS : k_rd) - 1, v_last = (v_rd == 0 ? VS : v_rd) - 1;
-      const bool in_k = (NW == 4 ? wave / 2 : wave) == 0;
-      const unsigned stag = lds0 + (in_k ? k_last : KS + v_last) * kTileBytes + (NW == 4 ? (wave % 2) * 8192 : 0);
+      const unsigned stag = staging();
       typedef __attribute__((address_space(3))) bf16x4* lds_b64;
       typedef __attribute__((address_space(3))) intx4* lds_b128;
 #pragma unroll
@@ -920,15 +948,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
             } w;
             w.p2[0] = __builtin_convertvector(floatx2{o[rb][ob][4 * g] * inv, o[rb][ob][4 * g + 1] * inv}, bf16x2);
             w.p2[1] = __builtin_convertvector(floatx2{o[rb][ob][4 * g + 2] * inv, o[rb][ob][4 * g + 3] * inv}, bf16x2);
-            *(lds_b64)(static_cast<uintptr_t>(stag + el32 * kRowBytes + (((4 * ob + g) ^ (el32 % 16)) * 16) + ehalf * 8)) = w.v;
+            *(lds_b64)(static_cast<uintptr_t>(stag + el32 * kRowBytes + (((4 * ob + g) ^ k_swizzle(el32)) * 16) + ehalf * 8)) = w.v;
           }
         const int row_base = ((2 * wave + rb) % spb) * 32;
         __bf16* op = static_cast<__bf16*>(const_cast<void*>(p.o.ptr)) + static_cast<int64_t>(o_head[rb]) * p.o.stride_head +
-                     (ln % 16) * 8;
+                     (ln % kPieces16) * 8;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int row = 4 * i + ln / 16;
-          const intx4 piece = *(lds_b128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((ln % 16) ^ (row % 16)) * 16)));
+        for (int i = 0; i < 32 / kLoadRows; ++i) {
+          const int row = kLoadRows * i + ln / kPieces16;
+          const intx4 piece = *(lds_b128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((ln % kPieces16) ^ k_swizzle(row)) * 16)));
           if (row_base + row < o_len)
             *reinterpret_cast<intx4*>(op + static_cast<int64_t>(o_start + row_base + row) * p.o.stride_tok) = piece;
         }
@@ -940,12 +968,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   }
 }
 
-template <int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false>
+template <int kD, int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false>
 hipError_t launch_cfg64(const AttnParams& p, hipStream_t stream) {
-  constexpr int lds_bytes = (3 + 2 * SL) * kTileBytes;
+  // (four waves over tiles of 8 KiB: two more for the epilogue)
+  constexpr int lds_bytes = (3 + 2 * SL + (NW == 4 && kD == 64 ? 2 : 0)) * kBN * kD * 2;
   static std::atomic<bool> attr_set{false};  // setting it twice from two threads is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill64_kernel<NW, SL, SELF, PERSIST, GATHER, ROPE>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill64_kernel<kD, NW, SL, SELF, PERSIST, GATHER, ROPE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (e != hipSuccess) return e;
     attr_set = true;
@@ -953,34 +982,44 @@ hipError_t launch_cfg64(const AttnParams& p, hipStream_t stream) {
   const int n_split = p.q_split > 1 ? p.q_split : 1;
   const dim3 grid = PERSIST ? dim3(p.sched_classes * p.n_head_blocks)
                             : dim3(p.n_q_heads / p.heads_per_block, p.n_qtiles, n_split);
-  attn_prefill64_kernel<NW, SL, SELF, PERSIST, GATHER, ROPE><<<grid, dim3(NW * 64), lds_bytes, stream>>>(p);
+  attn_prefill64_kernel<kD, NW, SL, SELF, PERSIST, GATHER, ROPE><<<grid, dim3(NW * 64), lds_bytes, stream>>>(p);
   return hipGetLastError();
 }
 
-template <int NW, int SL>
+template <int kD, int NW, int SL>
 hipError_t launch_stage64(const AttnParams& p, hipStream_t stream) {
-  if (p.rope_table) {
-    if (!p.query_stage || !p.list_shift) return hipErrorInvalidValue;
-    return p.sched_rec ? launch_cfg64<NW, SL, true, true, false, true>(p, stream)
-                       : launch_cfg64<NW, SL, true, false, false, true>(p, stream);
+  if constexpr (kD == 128) {
+    if (p.rope_table) {
+      if (!p.query_stage || !p.list_shift) return hipErrorInvalidValue;
+      return p.sched_rec ? launch_cfg64<kD, NW, SL, true, true, false, true>(p, stream)
+                         : launch_cfg64<kD, NW, SL, true, false, false, true>(p, stream);
+    }
   }
+  if (p.rope_table) return hipErrorInvalidValue;
   if (p.sched_rec)
-    return p.query_stage ? launch_cfg64<NW, SL, true, true>(p, stream) : launch_cfg64<NW, SL, false, true>(p, stream);
-  return p.query_stage ? launch_cfg64<NW, SL, true, false>(p, stream) : launch_cfg64<NW, SL, false, false>(p, stream);
+    return p.query_stage ? launch_cfg64<kD, NW, SL, true, true>(p, stream) : launch_cfg64<kD, NW, SL, false, true>(p, stream);
+  return p.query_stage ? launch_cfg64<kD, NW, SL, true, false>(p, stream) : launch_cfg64<kD, NW, SL, false, false>(p, stream);
 }
 
 }  // namespace
 
 // Eight row blocks per workgroup: four waves alone on a compute unit (112 KiB of LDS, two tiles
-// of load slack); four row blocks: two waves, two workgroups per compute unit (80 KiB each).
+// of load slack); four row blocks: two waves, two workgroups per compute unit (80 KiB each); two row blocks (head
+// dimension 64 only, whose tiles are half as large): one wave, four workgroups per compute unit (40 KiB each).
 // With a schedule in p (sched_rec) the launch is persistent and p.q_split must be 1.  The caller
 // runs the merge pass of a split launch.
-hipError_t launch_prefill64(const AttnParams& p, hipStream_t stream) {
+hipError_t launch_prefill64(const AttnParams& p, int head_dim, hipStream_t stream) {
   if (p.n_qtiles == 0) return hipSuccess;
   const int row_blocks = p.heads_per_block * (p.block_m / 32);
+  if (head_dim == 64) switch (row_blocks) {
+      case 2: return launch_stage64<64, 1, 1>(p, stream);
+      case 4: return launch_stage64<64, 2, 1>(p, stream);
+      case 8: return launch_stage64<64, 4, 2>(p, stream);
+      default: return hipErrorInvalidValue;
+    }
   switch (row_blocks) {
-    case 4: return launch_stage64<2, 1>(p, stream);
-    case 8: return launch_stage64<4, 2>(p, stream);
+    case 4: return launch_stage64<128, 2, 1>(p, stream);
+    case 8: return launch_stage64<128, 4, 2>(p, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -994,7 +1033,7 @@ hipError_t launch_decode_matrix_items(const AttnParams& p, hipStream_t stream) {
     return hipErrorInvalidValue;
   if (p.rope_table) {
     if (!p.gather_shift || !p.self_len) return hipErrorInvalidValue;
-    return launch_cfg64<4, 2, false, true, true, true>(p, stream);
+    return launch_cfg64<128, 4, 2, false, true, true, true>(p, stream);
   }
-  return launch_cfg64<4, 2, false, true, true>(p, stream);
+  return launch_cfg64<128, 4, 2, false, true, true>(p, stream);
 }

@@ -96,11 +96,11 @@ struct AttnParams {
 
 // bf16 MFMA kernels (attn_mfma.hip)
 hipError_t launch_prefill_mfma(const AttnParams& p, int head_dim, hipStream_t stream);
-// software-pipelined variant for head_dim 128 (attn_prefill.hip)
-hipError_t launch_prefill_pipelined(const AttnParams& p, hipStream_t stream);
+// software-pipelined variants (attn_prefill.hip): head_dim 128, or 64 with more than one row block per workgroup
+hipError_t launch_prefill_pipelined(const AttnParams& p, int head_dim, hipStream_t stream);
 // the same mathematics with 64 query rows per wave, one wave per SIMD (attn_prefill64.hip); kernel
 // only: launch_prefill_pipelined runs the merge pass of a split launch
-hipError_t launch_prefill64(const AttnParams& p, hipStream_t stream);
+hipError_t launch_prefill64(const AttnParams& p, int head_dim, hipStream_t stream);
 // the same kernel over rows gathered through references, leaving partial softmax states: the pool
 // items of a decode step with many queries per group (attn_prefill64.hip)
 hipError_t launch_decode_matrix_items(const AttnParams& p, hipStream_t stream);

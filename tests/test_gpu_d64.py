@@ -1,0 +1,78 @@
+"""head_dim 64 on the pipelined kernels: workgroups of one, two and four waves, persistent and one per Q tile, whole
+lists, lists cut to measure and split, ragged tails, and scores that outgrow the running maximum."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dbsa_oracle as orc
+from paper_2503_08640_amd import binding as B
+from paper_2503_08640_amd import synth
+from gpu_util import assert_close, to_dev, to_f64
+from test_gpu_parity import _oracle_query, _query_setup, small_pool_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hq,hkv,block_m,pool,groups,sink,window", [
+    (4, 1, 64, 1100, 3, 5, 1),       # four waves of 64 rows, one workgroup per Q tile
+    (4, 2, 64, 900, 2, 64, 0),       # two waves
+    (4, 4, 64, 1100, 3, 130, 2),     # one wave
+    (4, 4, 32, 500, 2, 0, 0),        # one row block: the kernel that is not pipelined
+    (32, 8, 64, 6200, 23, 64, 0),    # the same persistently: Q tiles of many short groups in one stream
+    (16, 16, 128, 9000, 20, 4, 0),
+    (16, 16, 64, 9000, 20, 4, 0),
+])
+def test_pre_encode_at_head_dim_64(hq, hkv, block_m, pool, groups, sink, window):
+    pc = small_pool_case("d64pre", 7200 + pool + block_m, hq=hq, hkv=hkv, d=64, sink=sink, pool_tokens=pool, groups=groups,
+                         lens=(8, 120), sigma=0.5, w=window)
+    p = pc.pool
+    n = p.n_tokens
+    lay = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, window, block_m=block_m, block_n=64)
+    lse = torch.zeros((hq, n), device="cuda")
+    o = B.dbsa_preencode_attn(lay, to_dev(pc.q), to_dev(pc.k), to_dev(pc.v), pc.scale, lse=lse)
+    rows = np.arange(n) if n < 2000 else np.unique(np.concatenate([np.arange(140), np.arange(n - 140, n),
+                                                                   np.random.default_rng(1).integers(0, n, 400)]))
+    want, want_lse = orc.preencode_attn(synth.as_f64(pc.q), synth.as_f64(pc.k), synth.as_f64(pc.v), p.sink_len, p.demo_offsets,
+                                        p.group_demo_offsets, pc.scale, window, rows=rows, return_lse=True)
+    assert_close(to_f64(o)[rows], want, f"d64 pre-encode {hq}/{hkv} bm={block_m}")
+    assert_close(to_f64(lse)[:, rows], want_lse, "d64 lse")
+    # every other row: V = 1 gives 1, up to the rounding of the probabilities (2^-9) and of the output (2^-9)
+    one = B.dbsa_preencode_attn(lay, to_dev(pc.q), to_dev(pc.k), torch.ones_like(to_dev(pc.v)), pc.scale)
+    assert (one.float() - 1).abs().max().item() <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("hq,hkv,block_m,q_len", [
+    (8, 2, 64, [64]), (8, 2, 64, [1, 130, 64, 20, 77]), (8, 2, 32, [31, 5, 32]), (4, 4, 64, [150, 64, 9]), (4, 4, 256, [700, 90]),
+])
+def test_query_prefill_at_head_dim_64(hq, hkv, block_m, q_len):
+    pc = small_pool_case("d64q", 7300 + block_m + len(q_len), hq=hq, hkv=hkv, d=64, pool_tokens=9000, groups=3, lens=(32, 200),
+                         sigma=0.5)
+    sels = [[2, 0], [0, 1, 2], [1], [], [2, 1, 0]][:len(q_len)]
+    qc = synth.make_query_case("d64qq", 7301, pc, n_queries=len(q_len), q_len=q_len, selections=sels)
+    lay, kp, vp = _query_setup(pc, qc, block_m, 0)
+    qs, ks, vs = to_dev(qc.q), to_dev(qc.k), to_dev(qc.v)
+    ref = _oracle_query(pc, qc)
+    need = lay.workspace_bytes(hq, 64)
+    outs = [B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, workspace=ws)
+            for ws in (False, torch.empty(need, dtype=torch.uint8, device="cuda"), torch.empty(need // 3, dtype=torch.uint8, device="cuda"))]
+    for o, what in zip(outs, ("whole lists", "cut or split lists", "a third of the workspace")):
+        assert_close(to_f64(o), ref, f"d64 {what} bm={block_m} T={q_len}")
+    assert not torch.equal(outs[0], outs[1]), "the workspace changed nothing"
+
+
+@pytest.mark.parametrize("hq,hkv,block_m,jump", [(8, 2, 64, 300.0), (4, 4, 64, 40.0), (4, 2, 64, 300.0)])
+def test_scores_that_jump_at_head_dim_64(hq, hkv, block_m, jump):
+    """Later keys of every segment score `jump` natural-log units above the first ones, for every row."""
+    pc = small_pool_case("d64j", 7400 + hq, hq=hq, hkv=hkv, d=64, pool_tokens=2000, groups=3, lens=(32, 128))
+    p = pc.pool
+    k, q = to_dev(pc.k).float(), to_dev(pc.q).float()
+    b = p.group_token_bounds()
+    pos = np.concatenate([np.arange(p.sink_len)] + [np.arange(b[g + 1] - b[g]) for g in range(p.n_groups)])
+    lift = torch.from_numpy((pos // 97).astype(np.float32)).cuda()
+    q[..., 0] = 4.0
+    k[..., 0] = lift[:, None] * (jump / (pc.scale * 4.0))
+    q, k = q.bfloat16(), k.bfloat16()
+    lay = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, block_m=block_m, block_n=64)
+    o = B.dbsa_preencode_attn(lay, q, k, to_dev(pc.v), pc.scale)
+    assert_close(to_f64(o), orc.preencode_attn(to_f64(q), to_f64(k), synth.as_f64(pc.v), p.sink_len, p.demo_offsets,
+                                               p.group_demo_offsets, pc.scale), f"d64 jump {jump}")
