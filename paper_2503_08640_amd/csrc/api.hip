@@ -603,7 +603,7 @@ bool decode_ids_in_table(const dbsa_layout* L, int64_t stride_query, int64_t str
   return L->max_decode_shift + t_max - 1 < rope_n_pos;
 }
 
-// launch rows of the group-major decode for r query heads per KV head (32 % r == 0)
+// launch rows of the group-major decode for r columns per query (a power of two)
 void fill_decode_rows(AttnParams& p, const dbsa_layout* L, int r) {
   int k = 0;
   while ((32 >> k) > 32 / r) ++k;  // a wave takes 32 / r queries
@@ -612,7 +612,7 @@ void fill_decode_rows(AttnParams& p, const dbsa_layout* L, int r) {
   p.gm_pool_rows = L->gm_pool_rows[k];
 }
 
-// waves per decode workgroup for r query heads per KV head (32 % r == 0), see decode_common
+// waves per decode workgroup for r columns per query (a power of two), see decode_common
 int pick_decode_waves(const dbsa_layout* L, int r) {
   int k = 0;
   while ((32 >> k) > 32 / r) ++k;
@@ -1004,6 +1004,7 @@ int decode_kv8_common(const dbsa_layout* L, dbsa_tensor q_step, dbsa_tensor k_se
   p.rope_n_pos = rope_n_pos;
   p.partial = static_cast<float*>(workspace);
   p.decode_waves = pick_decode_waves(L, r);
+  p.column_heads = r;
   fill_decode_rows(p, L, r / p.decode_waves);
   if (order_behind_upload(L, static_cast<hipStream_t>(stream)) != hipSuccess) return DBSA_ERR_HIP;
   p.decode_reverse = next_walk_direction(L);  // nothing rejects the call from here on
@@ -1114,7 +1115,13 @@ int decode_common(const dbsa_layout* L, dbsa_tensor q_step, dbsa_tensor k_selfca
   const int r = n_q_heads / n_kv_heads;
   const int64_t max_stride = std::max(std::max(p.k_pool.stride_tok, p.v_pool.stride_tok),
                                       std::max(p.k_self.stride_tok, p.v_self.stride_tok));
-  const bool group_major = dtype == DBSA_BF16 && head_dim == 128 && 32 % r == 0 && max_stride < (int64_t{1} << 24);
+  // Group-major: every KV run is walked once for all the queries that selected it, r rounded up to a power of two
+  // columns per query (head ratios like 3, 5 or 7 leave some idle: the step is bound by the keys' bytes).  Re-positioning
+  // has the two shapes it had; the others take the fp32-arithmetic kernel.
+  int columns = 1;
+  while (columns < r) columns *= 2;
+  const bool group_major = dtype == DBSA_BF16 && r <= 32 && max_stride < (int64_t{1} << 24) &&
+                           (!rope_table || (head_dim == 128 && columns == r));
   if (dtype == DBSA_BF16) {
     if (L->block_n != 64 || r > 32) return DBSA_ERR_UNSUPPORTED;
     // need_bytes: what the caller has checked the step to write (the fixed-buffer entry point)
@@ -1129,17 +1136,17 @@ int decode_common(const dbsa_layout* L, dbsa_tensor q_step, dbsa_tensor k_selfca
   p.decode_reverse = next_walk_direction(L);
   if (dtype == DBSA_BF16) {
     if (group_major) {
-      // every KV run is walked once for all the queries that selected it
       // Items that serve several batches of 32 / r queries: the batches of one item run as waves
       // of ONE workgroup that share its tiles in LDS, once a key is walked often enough for that
       // to outweigh the barrier per half tile (measured over 16-256 queries at 10-100 % retrieval: 2
       // waves pay from ~1.5 walks per key on, 4 from ~2.3).
-      p.decode_waves = pick_decode_waves(L, r);
+      p.decode_waves = pick_decode_waves(L, columns);
+      p.column_heads = columns;
       // With query heads in fours per KV head and groups that serve many queries, the pool items run
       // as a contraction: 64 queries per wave, four heads of a KV head as the four waves of a
       // workgroup, one workgroup per compute unit walking a balanced share of the records
       // (kernels.hpp: launch_decode_matrix_items).  Worth it once enough of the 64 rows carry a query.
-      if (r % 4 == 0 && L->mx_row_fill >= kMatrixRowFill) {
+      if (head_dim == 128 && columns == r && r % 4 == 0 && L->mx_row_fill >= kMatrixRowFill) {
         // one workgroup per compute unit, or per record where there are fewer
         const int32_t head_blocks = n_q_heads / 4;
         const bool planned = !L->mx_plan_ptr.empty() && L->compute_units / head_blocks == L->mx_plan_workers;
@@ -1162,8 +1169,8 @@ int decode_common(const dbsa_layout* L, dbsa_tensor q_step, dbsa_tensor k_selfca
           if (own) p.gm_slot_ptr = L->dev.mx_slot_ptr;
         }
       }
-      fill_decode_rows(p, L, r / p.decode_waves);
-      e = launch_decode_group(p, s);
+      fill_decode_rows(p, L, columns / p.decode_waves);
+      e = launch_decode_group(p, head_dim, s);
     } else if (rope_table) {
       // of the matrix kernels only the group-major one re-positions
       e = launch_decode_plain(p, head_dim, /*bf16_storage=*/true, L->compute_units, s);

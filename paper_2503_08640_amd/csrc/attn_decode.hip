@@ -1,12 +1,12 @@
-// Group-major split-KV decode for bf16, head_dim 128 on gfx950 (Sec. 2.2: one new token per
+// Group-major split-KV decode for bf16, head_dim 128 or 64, on gfx950 (Sec. 2.2: one new token per
 // query attends the sink, the query's selected groups and its own cached keys).
 //
 // Queries that selected the same group read the same keys, and a decode step is bound by
 // HBM traffic, so the unit of work is not (query, split) but (run of KV tiles of one
 // segment, up to 32 queries that use it): the run is fetched ONCE and scored against all of
 // them on the matrix cores.  A workgroup is ONE wave that owns 32 score columns =
-// (32 / r) queries x the r query heads of one KV head, and walks the run once per batch of
-// 32 / r queries.  Every (item, query) pair writes one partial softmax state (m, l,
+// (32 / r) queries x the r query heads of one KV head (r rounded up to a power of two, the columns beyond a KV head's
+// last query head idle), and walks the run once per batch of as many queries.  Every (item, query) pair writes one partial softmax state (m, l,
 // unnormalised O) into its slot; a second kernel merges the slots of a query
 // (m* = max m_s, l* = sum l_s 2^(m_s - m*), o = sum O_s 2^(m_s - m*) / l*).
 //
@@ -27,14 +27,32 @@ namespace {
 
 using namespace dbsa_mfma;
 
-constexpr int kD = 128;
 constexpr int kHalf = 32;                      // keys per half tile
-constexpr int kRowBytes = kD * 2;              // 256
-constexpr int kHalfBytes = kHalf * kRowBytes;  // 8 KiB per K or V half tile
-constexpr int kSlots = 3;                      // ring slots of one K or V half tile each
-constexpr int kLdsBytes = kSlots * kHalfBytes;  // 24 KiB per wave: six waves per CU
-constexpr int kLoadsPerGroup = kHalfBytes / 1024;  // LDS-DMA instructions per K or V half tile
 constexpr float kRescaleSlack = 8.f;
+// A K or V half tile in LDS for head dimension kD: 32 rows, 16-byte pieces swizzled so that the 128-bit fragment reads
+// of K (32 rows, one piece) and the transpose reads of V (4 rows, 64 bytes) spread over all banks.  Rows of 128 bytes
+// lie on the banks in pairs, hence their swizzles go by row pair.
+template <int kD>
+struct HalfTile {
+  static constexpr int kRowBytes = kD * 2;              // 256 or 128
+  static constexpr int kBytes = kHalf * kRowBytes;      // 8 or 4 KiB
+  static constexpr int kPieces = kRowBytes / 16;        // 16-byte pieces per row
+  static constexpr int kLoadRows = 1024 / kRowBytes;    // rows a load instruction fills
+  static constexpr int kLoads = kBytes / 1024;          // LDS-DMA instructions per K or V half tile
+  static constexpr int kSlots = kD == 128 ? 3 : 6;      // ring slots of one half tile each in a single-wave workgroup
+  static constexpr int kRingBytes = kSlots * kBytes;    // 24 KiB per wave: six waves per CU
+  static __device__ DBSA_INLINE int k_swizzle(int row) { return kD == 128 ? row % 16 : (row / 2) % 8; }
+  static __device__ DBSA_INLINE int v_swizzle(int row) { return kD == 128 ? 4 * (row % 4) : 4 * ((row / 2) % 2); }
+  // a lane's K fragment c is at k_base ^ (32 * c), its transposed V fragment of channel block ob at v_base ^ (64 * ob)
+  static __device__ DBSA_INLINE int k_base(int l32, int half) { return l32 * kRowBytes + ((half ^ k_swizzle(l32)) * 16); }
+  static __device__ DBSA_INLINE int v_base(int lane, int l32, int half) {
+    return (4 * half + (lane % 16) / 4) * kRowBytes + (((2 * (l32 / 16) + (lane % 4) / 2) ^ v_swizzle((lane % 16) / 4)) * 16) +
+           (lane % 2) * 8;
+  }
+};
+// (the fp8 kernels widen to half tiles of head dimension 128)
+constexpr int kRowBytes = HalfTile<128>::kRowBytes;
+constexpr int kHalfBytes = HalfTile<128>::kBytes;
 
 // What one workgroup of the group-major step walks: a run of consecutive pool keys for up to 32
 // queries, or one query's own cache.
@@ -78,8 +96,8 @@ __device__ DBSA_INLINE bool locate_decode_item(const AttnParams& p, DecodeItem& 
   return true;
 }
 
-// A lane's score column: lanes l and l + 32 share column l % 32 = (query l32 / r of the wave's
-// batch, head l32 % r of the KV head).
+// A lane's score column: lanes l and l + 32 share column l % 32 = (query l32 / rp of the wave's
+// batch, head l32 % rp of the KV head; idle where that is r or more).
 struct DecodeColumn {
   int slot, head;
   bool valid;        // the batch has a query for this column (the others compute on a repeated reference)
@@ -87,17 +105,18 @@ struct DecodeColumn {
   const float* rot;  // ROPE: table row of the column, 16 floats (cos, sin of 8 channel pairs) per (chunk c < 4, half)
 };
 
-// pass: the wave's query batch (of 32 / r queries) inside the item; active: the wave has a batch.
+// rp: columns per query, r rounded up to a power of two.
+// pass: the wave's query batch (of 32 / rp queries) inside the item; active: the wave has a batch.
 // ROPE: the row is rotated at the id that stands for the new in-order position of the item's keys
 // (Sec. 2.2): shift of the reference + the query's own length - 1.
 // (The addresses are formed here, before the tile loads go out: they wait for the query reference
 // just loaded, and that wait must not include the tile loads.)
-template <bool ROPE>
-__device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const DecodeItem& it, int pass, bool active, int r,
+template <int kD, bool ROPE>
+__device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const DecodeItem& it, int pass, bool active, int r, int rp,
                                                   int l32, int half) {
   DecodeColumn c;
-  const int q_local = pass * (32 / r) + l32 / r;  // index into the item's query list (< 32 also without a batch)
-  c.valid = active && q_local < it.n_q;
+  const int q_local = pass * (32 / rp) + l32 / rp;  // index into the item's query list (< 32 also without a batch)
+  c.valid = active && q_local < it.n_q && l32 % rp < r;
   int u = it.self_u, rot_id = 0;
   if (it.self_item) {
     c.slot = static_cast<int>(p.gm_slot_ptr[it.self_u + 1]) - 1;
@@ -109,7 +128,7 @@ __device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const Dec
     c.slot = ref[1];
     if (ROPE) rot_id = ref[2];
   }
-  c.head = it.hk * r + l32 % r;
+  c.head = it.hk * r + min(l32 % rp, r - 1);
   c.rot = nullptr;
   if (ROPE) {
     rot_id = min(max(rot_id + p.self_len[u] - 1, 0), p.rope_n_pos - 1);
@@ -122,6 +141,24 @@ __device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const Dec
   return c;
 }
 
+// The column's Q fragments: the row as it is (the scale is applied to the scores, where it costs nothing beside the
+// subtraction of the running maximum and saves the row a second rounding).  prescale: the scale, where the row is
+// multiplied by it instead: a rotated row (ROPE) is rounded anyway, and in a step whose pool items run as a contraction
+// all partial states of a row must come from the same rounding of it (scores in the hundreds would otherwise differ by
+// whole units).
+template <int kD, bool ROPE>
+__device__ DBSA_INLINE void load_column(const DecodeColumn& c, float prescale, bf16x8 (&qf)[kD / 16]) {
+  if constexpr (ROPE) {
+    static_assert(kD == 128, "rows of 64 channels are not re-positioned here");
+    load_query_fragments<true>(c.qp, c.rot, prescale, qf);
+  } else if (kD == 128 && prescale != 1.f) {
+    if constexpr (kD == 128) load_query_fragments<false>(c.qp, nullptr, prescale, qf);
+  } else {
+#pragma unroll
+    for (int i = 0; i < kD / 16; ++i) qf[i] = *reinterpret_cast<const bf16x8*>(c.qp + 16 * i);
+  }
+}
+
 // The pieces of one half tile (32 keys) against the 32 columns of a wave.  The kernels differ in
 // where K and V come from and in what they issue between the pieces; the arithmetic is shared.
 union ProbFrag {
@@ -130,7 +167,8 @@ union ProbFrag {
 };
 
 // scores of a bf16 K half tile in LDS (swizzled as the loads of decode_group_kernel leave it):
-// two accumulator chains of four MFMAs instead of one of eight, half the latency
+// two accumulator chains instead of one, half the latency
+template <int kD>
 __device__ DBSA_INLINE floatx16 half_tile_scores(const lds_byte* ks, int k_base, const bf16x8 (&qf)[kD / 16]) {
   floatx16 s, s2;
 #pragma unroll
@@ -146,9 +184,10 @@ __device__ DBSA_INLINE floatx16 half_tile_scores(const lds_byte* ks, int k_base,
   return s;
 }
 
-// masks the keys past `len`, moves the lazily rescaled running state (o, m_run, l_run) and leaves
-// the probabilities as the B operand of the second product
-__device__ DBSA_INLINE void half_tile_softmax(floatx16& s, int len, int half, floatx16 (&o)[kD / 32], float& m_run,
+// masks the keys past `len`, moves the lazily rescaled running state (o, m_run in log2 units, l_run) and leaves
+// the probabilities as the B operand of the second product; c2 = log2 units per unit of the raw scores (positive)
+template <int kD>
+__device__ DBSA_INLINE void half_tile_softmax(floatx16& s, int len, int half, float c2, floatx16 (&o)[kD / 32], float& m_run,
                                               float& l_run, ProbFrag& pf) {
   if (len < kHalf) {
 #pragma unroll
@@ -160,7 +199,7 @@ __device__ DBSA_INLINE void half_tile_softmax(floatx16& s, int len, int half, fl
   float mx = s[0];
 #pragma unroll
   for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
-  mx = half_swap_max(mx);
+  mx = half_swap_max(mx) * c2;
   if (__builtin_amdgcn_ballot_w64(mx > m_run + kRescaleSlack) != 0) {
     const float m_new = fmaxf(m_run, mx);
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
@@ -171,22 +210,23 @@ __device__ DBSA_INLINE void half_tile_softmax(floatx16& s, int len, int half, fl
   }
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const float p0 = __builtin_amdgcn_exp2f(s[2 * i] - m_run);
-    const float p1 = __builtin_amdgcn_exp2f(s[2 * i + 1] - m_run);
+    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[2 * i], c2, -m_run));
+    const float p1 = __builtin_amdgcn_exp2f(fmaf(s[2 * i + 1], c2, -m_run));
     pf.p2[i] = __builtin_convertvector(floatx2{p0, p1}, bf16x2);
     l_run += p0 + p1;
   }
 }
 
 // o += V^T P^T for a bf16 V half tile in LDS (transposed fragments through the LDS transpose read)
+template <int kD>
 __device__ DBSA_INLINE void half_tile_weigh(const lds_byte* vs, int v_base, const ProbFrag& pf, floatx16 (&o)[kD / 32]) {
 #pragma unroll
   for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
     for (int ob = 0; ob < kD / 32; ++ob) {
-      const lds_byte* vp = vs + (v_base ^ (64 * ob)) + 16 * ch * kRowBytes;
+      const lds_byte* vp = vs + (v_base ^ (64 * ob)) + 16 * ch * HalfTile<kD>::kRowBytes;
       const bf16x4 lo = lds_read_tr(vp);
-      const bf16x4 hi = lds_read_tr(vp + 8 * kRowBytes);
+      const bf16x4 hi = lds_read_tr(vp + 8 * HalfTile<kD>::kRowBytes);
       const bf16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       o[ob] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf.v[ch], o[ob], 0, 0, 0);
     }
@@ -194,16 +234,18 @@ __device__ DBSA_INLINE void half_tile_weigh(const lds_byte* vs, int v_base, cons
 
 // One whole half tile: ks / vs are the K and V half tiles in LDS, len the valid keys, k_base /
 // v_base this lane's fragment offsets; the running state is updated in place.
+template <int kD>
 __device__ DBSA_INLINE void half_tile_attend(const lds_byte* ks, const lds_byte* vs, int len, int k_base, int v_base, int half,
-                                             const bf16x8 (&qf)[kD / 16], floatx16 (&o)[kD / 32], float& m_run,
+                                             float c2, const bf16x8 (&qf)[kD / 16], floatx16 (&o)[kD / 32], float& m_run,
                                              float& l_run) {
-  floatx16 s = half_tile_scores(ks, k_base, qf);
+  floatx16 s = half_tile_scores<kD>(ks, k_base, qf);
   ProbFrag pf;
-  half_tile_softmax(s, len, half, o, m_run, l_run, pf);
-  half_tile_weigh(vs, v_base, pf, o);
+  half_tile_softmax<kD>(s, len, half, c2, o, m_run, l_run, pf);
+  half_tile_weigh<kD>(vs, v_base, pf, o);
 }
 
 // The partial softmax state of a valid column: accumulators (times out_scale), running maximum, row sum.
+template <int kD>
 __device__ DBSA_INLINE void store_partial_state(const AttnParams& p, const DecodeColumn& c, int half, const floatx16 (&o)[kD / 32],
                                                 float m_run, float l_run, float out_scale) {
   const float l_tot = half_swap_sum(l_run);
@@ -224,18 +266,23 @@ __device__ DBSA_INLINE void store_partial_state(const AttnParams& p, const Decod
 
 // ROPE: the query row is un-rotated and is rotated here at the id that stands for the new
 // in-order position of the item's keys (Sec. 2.2), see AttnParams::gm_ref_pad.
-template <bool ROPE>
+template <int kD, bool ROPE>
 __global__ __launch_bounds__(64, 2) void decode_group_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  using T = HalfTile<kD>;
   lds_byte* lds = (lds_byte*)smem;
   const int lane = threadIdx.x, l32 = lane % 32, half = lane / 32;
-  const int r = p.n_q_heads / p.n_kv_heads;
-  const int qpw = 32 / r;  // queries per wave
+  const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
+  const int qpw = 32 / rp;  // queries per wave
   // ---- the item: a run of pool tiles for several queries, or one query's own cache ----
   DecodeItem it;
   if (!locate_decode_item(p, it)) return;
   const int hk = it.hk, pass = it.batch, n_q = it.n_q, first_key = it.first_key, n_keys = it.n_keys, self_u = it.self_u;
   const bool self_item = it.self_item;
+  // One workgroup per batch of 32 / rp queries of the item: an item that serves more queries than
+  // one wave has columns is walked by several workgroups side by side instead of by one workgroup
+  // several times, which would make it the last to finish.
+  if (pass >= (n_q + qpw - 1) / qpw) return;
   // the run is a stretch of consecutive key rows: first_key .. first_key + n_keys
   const int n_half = (n_keys + kHalf - 1) / kHalf;
   const __bf16* kbase = self_item ? static_cast<const __bf16*>(p.k_self.ptr) + self_u * p.stride_query +
@@ -255,115 +302,120 @@ __global__ __launch_bounds__(64, 2) void decode_group_kernel(AttnParams p) {
     len = min(kHalf, n_keys - pos * kHalf);
   };
 
-  // ---- loads: 8 K blocks and 8 V blocks of 1 KiB per half tile ----
-  // block b holds rows 4b .. 4b+3; lane -> row 4b + lane/16, slot lane%16 (swizzled).  For a
+  // ---- loads: T::kLoads blocks of 1 KiB for the K and for the V of a half tile ----
+  // block b holds rows kLoadRows * b ..; lane -> row + lane / kPieces, piece lane % kPieces (swizzled).  For a
   // full half tile the per-lane byte offset only depends on b % 4 (K) or not on b at all (V);
-  // the 4b rows go into the uniform base pointer.
-  unsigned k_lane_off[4];
+  // the rows of a block go into the uniform base pointer.
+  const int lane_row = lane / T::kPieces, lane_piece = lane % T::kPieces;
+  constexpr int kKOffsets = kD == 128 ? 4 : 2;  // blocks after which the K swizzle repeats
+  unsigned k_lane_off[kKOffsets];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    k_lane_off[j] = static_cast<unsigned>((lane / 16) * k_stride + (((lane % 16) ^ (4 * j + lane / 16)) * 8)) * 2u;
-  const unsigned v_lane_off =
-      static_cast<unsigned>((lane / 16) * v_stride + (((lane % 16) ^ (4 * ((lane / 16) % 4))) * 8)) * 2u;
-  // K and V of a half tile are separate load groups of kLoadsPerGroup instructions each, so that a
-  // slot can be refilled as soon as ITS product has consumed it
+  for (int j = 0; j < kKOffsets; ++j)
+    k_lane_off[j] = static_cast<unsigned>(lane_row * k_stride + ((lane_piece ^ T::k_swizzle(T::kLoadRows * j + lane_row)) * 8)) * 2u;
+  const unsigned v_lane_off = static_cast<unsigned>(lane_row * v_stride + ((lane_piece ^ T::v_swizzle(lane_row)) * 8)) * 2u;
+  // K and V of a half tile are separate load groups of kLoads instructions each, in the order K(0) V(0) K(1) V(1) ...,
+  // so that a slot can be refilled as soon as ITS product has consumed it: group g goes into slot g % kSlots
+  const int n_groups = 2 * n_half;
   auto issue_k = [&](int hh) {
     int start, len;
     half_ref(hh, start, len);
-    lds_byte* stage = lds + ((2 * hh) % kSlots) * kHalfBytes;
+    lds_byte* stage = lds + ((2 * hh) % T::kSlots) * T::kBytes;
     const __bf16* kb = kbase + static_cast<int64_t>(start) * k_stride;
     if (len == kHalf) {
 #pragma unroll
-      for (int b = 0; b < kLoadsPerGroup; ++b)
-        dma16(kb + static_cast<int64_t>(4 * b) * k_stride, k_lane_off[b % 4], stage + b * 1024);
+      for (int b = 0; b < T::kLoads; ++b)
+        dma16(kb + static_cast<int64_t>(T::kLoadRows * b) * k_stride, k_lane_off[b % kKOffsets], stage + b * 1024);
     } else {
 #pragma unroll
-      for (int b = 0; b < kLoadsPerGroup; ++b) {
-        const int row_in = 4 * b + lane / 16;
+      for (int b = 0; b < T::kLoads; ++b) {
+        const int row_in = T::kLoadRows * b + lane_row;
         const int row = min(row_in, len - 1);  // rows past the tail repeat the last key
-        dma16(kb, static_cast<unsigned>(row * k_stride + (((lane % 16) ^ (row_in % 16)) * 8)) * 2u,
-              stage + b * 1024);
+        dma16(kb, static_cast<unsigned>(row * k_stride + ((lane_piece ^ T::k_swizzle(row_in)) * 8)) * 2u, stage + b * 1024);
       }
     }
   };
   auto issue_v = [&](int hh) {
     int start, len;
     half_ref(hh, start, len);
-    lds_byte* stage = lds + ((2 * hh + 1) % kSlots) * kHalfBytes;
+    lds_byte* stage = lds + ((2 * hh + 1) % T::kSlots) * T::kBytes;
     const __bf16* vb = vbase + static_cast<int64_t>(start) * v_stride;
     if (len == kHalf) {
 #pragma unroll
-      for (int b = 0; b < kLoadsPerGroup; ++b)
-        dma16(vb + static_cast<int64_t>(4 * b) * v_stride, v_lane_off, stage + b * 1024);
+      for (int b = 0; b < T::kLoads; ++b)
+        dma16(vb + static_cast<int64_t>(T::kLoadRows * b) * v_stride, v_lane_off, stage + b * 1024);
     } else {
 #pragma unroll
-      for (int b = 0; b < kLoadsPerGroup; ++b) {
-        const int row_in = 4 * b + lane / 16;
+      for (int b = 0; b < T::kLoads; ++b) {
+        const int row_in = T::kLoadRows * b + lane_row;
         const int row = min(row_in, len - 1);
-        dma16(vb, static_cast<unsigned>(row * v_stride + (((lane % 16) ^ (4 * (row_in % 4))) * 8)) * 2u,
-              stage + b * 1024);
+        dma16(vb, static_cast<unsigned>(row * v_stride + ((lane_piece ^ T::v_swizzle(row_in)) * 8)) * 2u, stage + b * 1024);
       }
     }
   };
-  // wait until at most `groups` load groups (0..2) are still outstanding
-  auto wait_groups = [&](int groups) {
-    if (groups >= 2) wait_vmcnt<2 * kLoadsPerGroup>();
-    else if (groups == 1) wait_vmcnt<kLoadsPerGroup>();
-    else wait_vmcnt<0>();
+  // the group kSlots behind K(hh) / V(hh): K(hh) and V(hh) itself pair up with it where kSlots is even
+  constexpr int kAhead = T::kSlots / 2;
+  auto refill_k = [&](int hh) {
+    if (2 * hh + T::kSlots >= n_groups) return;
+    if constexpr (T::kSlots % 2) issue_v(hh + kAhead);
+    else issue_k(hh + kAhead);
+  };
+  auto refill_v = [&](int hh) {
+    if (2 * hh + 1 + T::kSlots >= n_groups) return;
+    if constexpr (T::kSlots % 2) issue_k(hh + kAhead + 1);
+    else issue_v(hh + kAhead);
+  };
+  // group g has landed once only the groups issued after it are outstanding
+  auto wait_group = [&](int g) {
+    if (__builtin_expect(g + T::kSlots <= n_groups, 1)) {
+      wait_vmcnt<(T::kSlots - 1) * T::kLoads>();
+      return;
+    }
+    const int after = n_groups - 1 - g;
+    static_for<T::kSlots - 1>([&](auto I) DBSA_INLINE {
+      if (after == decltype(I)::value) wait_vmcnt<decltype(I)::value * T::kLoads>();
+    });
   };
 
-  const int k_base = l32 * kRowBytes + ((half ^ (l32 % 16)) * 16);
-  const int v_base = (4 * half + (lane % 16) / 4) * kRowBytes +
-                     (((2 * (l32 / 16) + (lane % 4) / 2) ^ (4 * ((lane % 16) / 4))) * 16) + (lane % 2) * 8;
-  const float c2 = p.scale_log2e;
-  const int n_pass = (n_q + qpw - 1) / qpw;
+  const int k_base = T::k_base(l32, half), v_base = T::v_base(lane, l32, half);
+  const bool scale_rows = ROPE || p.decode_matrix;
+  const float prescale = scale_rows ? p.scale_log2e : 1.f, c2 = scale_rows ? 1.f : p.scale_log2e;
+  // ---- this lane's column: query and head ----
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp, l32, half);
 
-  // One workgroup per batch of 32 / r queries of the item: an item that serves more queries than
-  // one wave has columns is walked by several workgroups side by side instead of by one workgroup
-  // several times, which would make it the last to finish.
-  if (pass >= n_pass) return;
-  {
-    // ---- this lane's column: query and head ----
-    const DecodeColumn col = decode_column<ROPE>(p, it, pass, true, r, l32, half);
-
-    // ---- wave-private ring of three 8-KiB slots: load groups go out in the order K(0) V(0) K(1)
-    // V(1) K(2) ..., group g into slot g % 3, and group g+3 as soon as the product that reads group
-    // g is issued: two slots are in flight while the third is being computed on.  The first
-    // groups are requested before the query row, so that both latencies run together. ----
-    issue_k(0);
-    issue_v(0);
-    if (1 < n_half) issue_k(1);
-    bf16x8 qf[kD / 16];
-    load_query_fragments<ROPE>(col.qp, col.rot, c2, qf);
-    floatx16 o[kD / 32];
+  // ---- wave-private ring: group g + kSlots goes out as soon as the product that reads group g is issued.  The first
+  // groups are requested before the query row, so that both latencies run together. ----
 #pragma unroll
-    for (int ob = 0; ob < kD / 32; ++ob)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) o[ob][i] = 0.f;
-    float m_run = -1.0e30f, l_run = 0.f;
-
-    for (int hh = 0; hh < n_half; ++hh) {
-      // K(hh) has landed once only the groups issued after it are outstanding: V(hh), K(hh+1)
-      wait_groups(1 + (hh + 1 < n_half ? 1 : 0));
-      int start, len;
-      half_ref(hh, start, len);
-      const lds_byte* ks = lds + ((2 * hh) % kSlots) * kHalfBytes;
-      const lds_byte* vs = lds + ((2 * hh + 1) % kSlots) * kHalfBytes;
-
-      floatx16 s = half_tile_scores(ks, k_base, qf);
-      // the K slot is free (its LDS reads were consumed by the MFMAs above): it takes the group
-      // three places on, V(hh+1)
-      if (hh + 1 < n_half) issue_v(hh + 1);
-      ProbFrag pf;
-      half_tile_softmax(s, len, half, o, m_run, l_run, pf);
-      // V(hh) has landed once only K(hh+1) and V(hh+1) are outstanding
-      wait_groups(hh + 1 < n_half ? 2 : 0);
-      half_tile_weigh(vs, v_base, pf, o);
-      if (hh + 2 < n_half) issue_k(hh + 2);  // into the slot V(hh) just left
-    }
-
-    store_partial_state(p, col, half, o, m_run, l_run, 1.f);
+  for (int g = 0; g < T::kSlots; ++g) {
+    if (g >= n_groups) break;
+    if (g % 2) issue_v(g / 2);
+    else issue_k(g / 2);
   }
+  bf16x8 qf[kD / 16];
+  load_column<kD, ROPE>(col, prescale, qf);
+  floatx16 o[kD / 32];
+#pragma unroll
+  for (int ob = 0; ob < kD / 32; ++ob)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[ob][i] = 0.f;
+  float m_run = -1.0e30f, l_run = 0.f;
+
+  for (int hh = 0; hh < n_half; ++hh) {
+    wait_group(2 * hh);
+    int start, len;
+    half_ref(hh, start, len);
+    const lds_byte* ks = lds + ((2 * hh) % T::kSlots) * T::kBytes;
+    const lds_byte* vs = lds + ((2 * hh + 1) % T::kSlots) * T::kBytes;
+
+    floatx16 s = half_tile_scores<kD>(ks, k_base, qf);
+    refill_k(hh);  // the K slot is free: its LDS reads were consumed by the MFMAs above
+    ProbFrag pf;
+    half_tile_softmax<kD>(s, len, half, c2, o, m_run, l_run, pf);
+    wait_group(2 * hh + 1);
+    half_tile_weigh<kD>(vs, v_base, pf, o);
+    refill_v(hh);  // into the slot V(hh) just left
+  }
+
+  store_partial_state<kD>(p, col, half, o, m_run, l_run, 1.f);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -375,19 +427,20 @@ __global__ __launch_bounds__(64, 2) void decode_group_kernel(AttnParams p) {
 // tells that every wave is done with the tile before, whose slot takes the loads of the tile two
 // places on.  Ring of three (K, V) pairs of half tiles: two pairs in flight while one is used.
 constexpr int kPairs = 3;
-constexpr int kPairBytes = 2 * kHalfBytes;       // 16 KiB
-constexpr int kLdsShared = kPairs * kPairBytes;  // 48 KiB per workgroup: three workgroups per CU
+template <int kD>
+constexpr int kLdsShared = kPairs * 2 * HalfTile<kD>::kBytes;  // 48 KiB per workgroup: three workgroups per CU (64: 24 KiB)
 
-template <int W, bool ROPE>
+template <int kD, int W, bool ROPE>
 __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  using T = HalfTile<kD>;
   lds_byte* lds = (lds_byte*)smem;
-  constexpr int kPerWave = kLoadsPerGroup / W;  // load instructions per wave per K or V half tile
-  static_assert(kLoadsPerGroup % W == 0, "waves share the load instructions evenly");
+  constexpr int kPerWave = T::kLoads / W;  // load instructions per wave per K or V half tile
+  static_assert(T::kLoads % W == 0, "waves share the load instructions evenly");
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
   const int lane = threadIdx.x % 64, l32 = lane % 32, half = lane / 32;
-  const int r = p.n_q_heads / p.n_kv_heads;
-  const int qpw = 32 / r;  // queries per wave
+  const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
+  const int qpw = 32 / rp;  // queries per wave
   // a row's batch counts batches of W * qpw queries here
   DecodeItem it;
   if (!locate_decode_item(p, it)) return;
@@ -414,65 +467,61 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
     len = min(kHalf, n_keys - pos * kHalf);
   };
 
-  // this wave's load instructions of a half tile are the 1-KiB blocks b = wave + W * j (rows
-  // 4b .. 4b+3; lane -> row 4b + lane/16, 16-byte slot lane%16, swizzled as in decode_group_kernel)
+  // this wave's load instructions of a half tile are the 1-KiB blocks b = wave + W * j (rows kLoadRows * b ..;
+  // lane -> row + lane / kPieces, 16-byte piece lane % kPieces, swizzled as in decode_group_kernel)
+  const int lane_row = lane / T::kPieces, lane_piece = lane % T::kPieces;
   unsigned k_lane_off[kPerWave];
 #pragma unroll
   for (int j = 0; j < kPerWave; ++j)
-    k_lane_off[j] = static_cast<unsigned>((lane / 16) * k_stride +
-                                          (((lane % 16) ^ (4 * ((wave + W * j) % 4) + lane / 16)) * 8)) * 2u;
-  const unsigned v_lane_off =
-      static_cast<unsigned>((lane / 16) * v_stride + (((lane % 16) ^ (4 * ((lane / 16) % 4))) * 8)) * 2u;
+    k_lane_off[j] = static_cast<unsigned>(lane_row * k_stride +
+                                          ((lane_piece ^ T::k_swizzle(T::kLoadRows * (wave + W * j) + lane_row)) * 8)) * 2u;
+  const unsigned v_lane_off = static_cast<unsigned>(lane_row * v_stride + ((lane_piece ^ T::v_swizzle(lane_row)) * 8)) * 2u;
   auto issue_pair = [&](int hh) {
     int start, len;
     half_ref(hh, start, len);
-    lds_byte* k_stage = lds + (hh % kPairs) * kPairBytes;
-    lds_byte* v_stage = k_stage + kHalfBytes;
+    lds_byte* k_stage = lds + (hh % kPairs) * 2 * T::kBytes;
+    lds_byte* v_stage = k_stage + T::kBytes;
     const __bf16* kb = kbase + static_cast<int64_t>(start) * k_stride;
     const __bf16* vb = vbase + static_cast<int64_t>(start) * v_stride;
     if (len == kHalf) {
 #pragma unroll
       for (int j = 0; j < kPerWave; ++j) {
         const int b = wave + W * j;
-        dma16(kb + static_cast<int64_t>(4 * b) * k_stride, k_lane_off[j], k_stage + b * 1024);
+        dma16(kb + static_cast<int64_t>(T::kLoadRows * b) * k_stride, k_lane_off[j], k_stage + b * 1024);
       }
 #pragma unroll
       for (int j = 0; j < kPerWave; ++j) {
         const int b = wave + W * j;
-        dma16(vb + static_cast<int64_t>(4 * b) * v_stride, v_lane_off, v_stage + b * 1024);
+        dma16(vb + static_cast<int64_t>(T::kLoadRows * b) * v_stride, v_lane_off, v_stage + b * 1024);
       }
     } else {
 #pragma unroll
       for (int j = 0; j < kPerWave; ++j) {
         const int b = wave + W * j;
-        const int row_in = 4 * b + lane / 16;
+        const int row_in = T::kLoadRows * b + lane_row;
         const int row_k = min(row_in, len - 1);  // rows past the tail repeat the last key
-        dma16(kb, static_cast<unsigned>(row_k * k_stride + (((lane % 16) ^ (row_in % 16)) * 8)) * 2u,
-              k_stage + b * 1024);
+        dma16(kb, static_cast<unsigned>(row_k * k_stride + ((lane_piece ^ T::k_swizzle(row_in)) * 8)) * 2u, k_stage + b * 1024);
       }
 #pragma unroll
       for (int j = 0; j < kPerWave; ++j) {
         const int b = wave + W * j;
-        const int row_in = 4 * b + lane / 16;
+        const int row_in = T::kLoadRows * b + lane_row;
         const int row_v = min(row_in, len - 1);
-        dma16(vb, static_cast<unsigned>(row_v * v_stride + (((lane % 16) ^ (4 * (row_in % 4))) * 8)) * 2u,
-              v_stage + b * 1024);
+        dma16(vb, static_cast<unsigned>(row_v * v_stride + ((lane_piece ^ T::v_swizzle(row_in)) * 8)) * 2u, v_stage + b * 1024);
       }
     }
   };
 
-  const int k_base = l32 * kRowBytes + ((half ^ (l32 % 16)) * 16);
-  const int v_base = (4 * half + (lane % 16) / 4) * kRowBytes +
-                     (((2 * (l32 / 16) + (lane % 4) / 2) ^ (4 * ((lane % 16) / 4))) * 16) + (lane % 2) * 8;
-  const float c2 = p.scale_log2e;
+  const int k_base = T::k_base(l32, half), v_base = T::v_base(lane, l32, half);
+  const float prescale = ROPE ? p.scale_log2e : 1.f, c2 = ROPE ? 1.f : p.scale_log2e;
 
   // ---- this lane's column: query and head ----
-  const DecodeColumn col = decode_column<ROPE>(p, it, pass, active, r, l32, half);
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp, l32, half);
 
   issue_pair(0);
   if (1 < n_half) issue_pair(1);
   bf16x8 qf[kD / 16];
-  load_query_fragments<ROPE>(col.qp, col.rot, c2, qf);
+  load_column<kD, ROPE>(col, prescale, qf);
   floatx16 o[kD / 32];
 #pragma unroll
   for (int ob = 0; ob < kD / 32; ++ob)
@@ -491,13 +540,13 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
     if (!active) continue;
     int start, len;
     half_ref(hh, start, len);
-    const lds_byte* ks = lds + (hh % kPairs) * kPairBytes;
-    const lds_byte* vs = ks + kHalfBytes;
+    const lds_byte* ks = lds + (hh % kPairs) * 2 * T::kBytes;
+    const lds_byte* vs = ks + T::kBytes;
 
-    half_tile_attend(ks, vs, len, k_base, v_base, half, qf, o, m_run, l_run);
+    half_tile_attend<kD>(ks, vs, len, k_base, v_base, half, c2, qf, o, m_run, l_run);
   }
 
-  store_partial_state(p, col, half, o, m_run, l_run, 1.f);
+  store_partial_state<kD>(p, col, half, o, m_run, l_run, 1.f);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -507,8 +556,10 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
 // K(h+1), V(h+1)).  K fragments are read from the staged bytes directly and widened to bf16 in
 // registers; V is widened into one bf16 working tile (the transposed fragment reads need 16-bit
 // elements), same swizzle as the bf16 kernel.  24 KiB of LDS per wave keeps six waves per CU.
-// The per-head scales ride on Q (keys) and on the partial accumulators (values), so no key or
+// The per-head scales ride on the scores (keys) and on the partial accumulators (values), so no key or
 // value is ever multiplied.
+constexpr int kD = 128;
+constexpr int kPairBytes = 2 * kHalfBytes;      // 16 KiB
 constexpr int kSlot8 = 4096;
 constexpr int kLds8 = 4 * kSlot8 + kHalfBytes;  // 24 KiB per wave
 constexpr int kLoads8 = 4;                      // load instructions per group (the K or the V bytes of a half tile)
@@ -531,8 +582,8 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
   lds_byte* lds = (lds_byte*)smem;
   lds_byte* work_v = lds + 4 * kSlot8;
   const int lane = threadIdx.x, l32 = lane % 32, half = lane / 32;
-  const int r = p.n_q_heads / p.n_kv_heads;
-  const int qpw = 32 / r;
+  const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
+  const int qpw = 32 / rp;
   // this launch covers the rows of pool items only
   DecodeItem it;
   if (!locate_decode_item(p, it) || it.self_item) return;
@@ -584,21 +635,20 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
   // K fragment c of key row l32: channels 16c + 8*half .. +7 = 8 bytes of slot c ^ (l32 % 8)
   const int k8_base = l32 * 128 + 8 * half;
   const int k8_swz = l32 % 8;
-  const int v_base = (4 * half + (lane % 16) / 4) * kRowBytes +
-                     (((2 * (l32 / 16) + (lane % 4) / 2) ^ (4 * ((lane % 16) / 4))) * 16) + (lane % 2) * 8;
+  const int v_base = HalfTile<kD>::v_base(lane, l32, half);
 
   // ---- this lane's column (ROPE as in decode_group_kernel: the stored keys keep their encoding-time rotation) ----
-  const DecodeColumn col = decode_column<ROPE>(p, it, pass, true, r, l32, half);
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp, l32, half);
   issue_k(0);
   issue_v(0);
   if (1 < n_half) {
     issue_k(1);
     issue_v(1);
   }
-  const float c2 = p.scale_log2e * p.k_scale8[hk];
+  const float c8 = p.scale_log2e * p.k_scale8[hk], prescale = ROPE ? c8 : 1.f, c2 = ROPE ? 1.f : c8;
   const float v_scale = p.v_scale8[hk];
   bf16x8 qf[kD / 16];
-  load_query_fragments<ROPE>(col.qp, col.rot, c2, qf);
+  load_column<kD, ROPE>(col, prescale, qf);
   floatx16 o[kD / 32];
 #pragma unroll
   for (int ob = 0; ob < kD / 32; ++ob)
@@ -632,7 +682,7 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (hh + 2 < n_half) issue_k(hh + 2);
     ProbFrag pf;
-    half_tile_softmax(s, len, half, o, m_run, l_run, pf);
+    half_tile_softmax<kD>(s, len, half, c2, o, m_run, l_run, pf);
     // V(hh) has landed once only K(hh+1), V(hh+1) and K(hh+2) are outstanding
     wait_groups((more ? 2 : 0) + (hh + 2 < n_half ? 1 : 0));
     // staged V bytes -> the swizzled bf16 working tile
@@ -648,12 +698,12 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
     // the V slot is free: it takes the V bytes two half tiles on
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (hh + 2 < n_half) issue_v(hh + 2);
-    half_tile_weigh(work_v, v_base, pf, o);
+    half_tile_weigh<kD>(work_v, v_base, pf, o);
     // the working tile is rewritten in the next round: its reads must have returned
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   }
 
-  store_partial_state(p, col, half, o, m_run, l_run, v_scale);
+  store_partial_state<kD>(p, col, half, o, m_run, l_run, v_scale);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -677,8 +727,8 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
   constexpr int kPerWave = kLoads8 / W;  // load instructions per wave per K or V half tile (8 rows each)
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
   const int lane = threadIdx.x % 64, l32 = lane % 32, half = lane / 32;
-  const int r = p.n_q_heads / p.n_kv_heads;
-  const int qpw = 32 / r;
+  const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
+  const int qpw = 32 / rp;
   // this launch covers the rows of pool items only; a row's batch counts batches of W * qpw queries
   DecodeItem it;
   if (!locate_decode_item(p, it) || it.self_item) return;
@@ -742,18 +792,16 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
     }
   };
 
-  const int k_base = l32 * kRowBytes + ((half ^ (l32 % 16)) * 16);
-  const int v_base = (4 * half + (lane % 16) / 4) * kRowBytes +
-                     (((2 * (l32 / 16) + (lane % 4) / 2) ^ (4 * ((lane % 16) / 4))) * 16) + (lane % 2) * 8;
+  const int k_base = HalfTile<kD>::k_base(l32, half), v_base = HalfTile<kD>::v_base(lane, l32, half);
 
   // ---- this lane's column ----
-  const DecodeColumn col = decode_column<ROPE>(p, it, pass, active, r, l32, half);
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp, l32, half);
   issue_pair(0);
   if (1 < n_half) issue_pair(1);
-  const float c2 = p.scale_log2e * p.k_scale8[hk];
+  const float c8 = p.scale_log2e * p.k_scale8[hk], prescale = ROPE ? c8 : 1.f, c2 = ROPE ? 1.f : c8;
   const float v_scale = p.v_scale8[hk];
   bf16x8 qf[kD / 16];
-  load_query_fragments<ROPE>(col.qp, col.rot, c2, qf);
+  load_column<kD, ROPE>(col, prescale, qf);
   floatx16 o[kD / 32];
 #pragma unroll
   for (int ob = 0; ob < kD / 32; ++ob)
@@ -774,19 +822,20 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
     if (!active) continue;
     int start, len;
     half_ref(hh, start, len);
-    half_tile_attend(work_k, work_v, len, k_base, v_base, half, qf, o, m_run, l_run);
+    half_tile_attend<kD>(work_k, work_v, len, k_base, v_base, half, c2, qf, o, m_run, l_run);
   }
 
-  store_partial_state(p, col, half, o, m_run, l_run, v_scale);
+  store_partial_state<kD>(p, col, half, o, m_run, l_run, v_scale);
 }
 
 // Merge the partial states of one (query, head): slots [slot_ptr[u], slot_ptr[u+1]).
-// 2 x 128 threads: thread (part, d) owns output channel d for the slots of its parity.  The
+// 2 x D threads: thread (part, d) owns output channel d for the slots of its parity.  The
 // per-slot maxima and sums are read with one slot per thread (not one after the other by
 // everyone), the weights 2^(m_s - m*) go through LDS, and the weighted sum of the accumulators
 // runs with eight independent loads in flight per thread; the two parities meet in LDS.
-constexpr int kMergeThreads = 2 * kD;
-__global__ __launch_bounds__(kMergeThreads) void decode_group_merge_kernel(AttnParams p) {
+template <int kD>
+__global__ __launch_bounds__(2 * kD) void decode_group_merge_kernel(AttnParams p) {
+  constexpr int kMergeThreads = 2 * kD;
   constexpr int kRow = kD + kPartialPad, kCap = 256, kWaves = kMergeThreads / 64;
   __shared__ float w_sh[kCap];
   __shared__ float red[2][kWaves];
@@ -872,22 +921,32 @@ hipError_t launch_shared8(const AttnParams& p, hipStream_t stream) {
 }
 }  // namespace
 
+namespace {
+template <int kD>
+hipError_t launch_merge(const AttnParams& p, hipStream_t stream) {
+  decode_group_merge_kernel<kD><<<dim3(p.n_queries * p.n_q_heads), dim3(2 * kD), 0, stream>>>(p);
+  return hipGetLastError();
+}
+
+template <int kD, int W, bool ROPE>
+hipError_t launch_rows(const AttnParams& p, hipStream_t stream) {
+  if constexpr (W == 1) {
+    decode_group_kernel<kD, ROPE><<<decode_grid(p), dim3(64), HalfTile<kD>::kRingBytes, stream>>>(p);
+  } else {
+    decode_group_shared_kernel<kD, W, ROPE><<<decode_grid(p), dim3(64 * W), kLdsShared<kD>, stream>>>(p);
+  }
+  return hipGetLastError();
+}
+// the launch rows of p with W waves per workgroup
+template <int W>
+hipError_t launch_waves(const AttnParams& p, int head_dim, hipStream_t stream) {
+  if (head_dim == 64) return p.rope_table ? hipErrorInvalidValue : launch_rows<64, W, false>(p, stream);
+  return p.rope_table ? launch_rows<128, W, true>(p, stream) : launch_rows<128, W, false>(p, stream);
+}
+}  // namespace
+
 // p.decode_waves as for launch_decode_group (pool rows; the self rows below are single batches)
 hipError_t launch_decode_group_kv8(const AttnParams& p_in, hipStream_t stream) {
-  static std::atomic<bool> attr_set{false};  // setting it twice from two threads is harmless
-  if (!attr_set) {
-    for (const void* f : {reinterpret_cast<const void*>(decode_group_kv8_kernel<false>),
-                          reinterpret_cast<const void*>(decode_group_kv8_kernel<true>)}) {
-      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLds8);
-      if (e != hipSuccess) return e;
-    }
-    for (const void* f : {reinterpret_cast<const void*>(decode_group_kernel<false>),
-                          reinterpret_cast<const void*>(decode_group_kernel<true>)}) {
-      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-      if (e != hipSuccess) return e;
-    }
-    attr_set = true;
-  }
   AttnParams p = p_in;
   if (p.n_gm_items > 0) {
     p.row_offset = 0;
@@ -909,52 +968,14 @@ hipError_t launch_decode_group_kv8(const AttnParams& p_in, hipStream_t stream) {
   // every query's own (bf16) cache: the self items of the ordinary kernel
   p.row_offset = p.gm_pool_rows;
   p.launch_rows = p.gm_n_rows - p.gm_pool_rows;
-  if (p.rope_table)
-    decode_group_kernel<true><<<decode_grid(p), dim3(64), kLdsBytes, stream>>>(p);
-  else
-    decode_group_kernel<false><<<decode_grid(p), dim3(64), kLdsBytes, stream>>>(p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  decode_group_merge_kernel<<<dim3(p.n_queries * p.n_q_heads), dim3(kMergeThreads), 0, stream>>>(p);
-  return hipGetLastError();
+  const hipError_t e = launch_waves<1>(p, 128, stream);
+  return e == hipSuccess ? launch_merge<128>(p, stream) : e;
 }
-
-namespace {
-template <int W>
-hipError_t launch_shared(const AttnParams& p, hipStream_t stream) {
-  static std::atomic<bool> attr_set{false};  // setting it twice from two threads is harmless
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_group_shared_kernel<W, false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLdsShared);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_group_shared_kernel<W, true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsShared);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  const dim3 grid = decode_grid(p), block(64 * W);
-  if (p.rope_table)
-    decode_group_shared_kernel<W, true><<<grid, block, kLdsShared, stream>>>(p);
-  else
-    decode_group_shared_kernel<W, false><<<grid, block, kLdsShared, stream>>>(p);
-  return hipGetLastError();
-}
-}  // namespace
 
 // p.decode_waves = waves per workgroup (1, 2 or 4; the launch rows in p are those of batches of
-// decode_waves * 32 / r queries)
-hipError_t launch_decode_group(const AttnParams& p_in, hipStream_t stream) {
+// decode_waves * 32 / column_heads queries)
+hipError_t launch_decode_group(const AttnParams& p_in, int head_dim, hipStream_t stream) {
   AttnParams p = p_in;
-  static std::atomic<bool> attr_set{false};  // setting it twice from two threads is harmless
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_group_kernel<false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_group_kernel<true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
   hipError_t e;
   if (p.decode_matrix) {
     // Many queries per group: the pool items as a contraction (64 query rows per wave, four query heads
@@ -975,30 +996,14 @@ hipError_t launch_decode_group(const AttnParams& p_in, hipStream_t stream) {
     if (e != hipSuccess) return e;
     p.row_offset = p.gm_pool_rows;
     p.launch_rows = p.gm_n_rows - p.gm_pool_rows;
-    if (p.rope_table)
-      decode_group_kernel<true><<<decode_grid(p), dim3(64), kLdsBytes, stream>>>(p);
-    else
-      decode_group_kernel<false><<<decode_grid(p), dim3(64), kLdsBytes, stream>>>(p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    decode_group_merge_kernel<<<dim3(p.n_queries * p.n_q_heads), dim3(kMergeThreads), 0, stream>>>(p);
-    return hipGetLastError();
-  }
-  p.row_offset = 0;
-  p.launch_rows = p.gm_n_rows;
-  if (p.decode_waves == 4) {
-    e = launch_shared<4>(p, stream);
-  } else if (p.decode_waves == 2) {
-    e = launch_shared<2>(p, stream);
+    e = launch_waves<1>(p, head_dim, stream);
   } else {
-    const dim3 grid = decode_grid(p), block(64);
-    if (p.rope_table)
-      decode_group_kernel<true><<<grid, block, kLdsBytes, stream>>>(p);
-    else
-      decode_group_kernel<false><<<grid, block, kLdsBytes, stream>>>(p);
-    e = hipGetLastError();
+    p.row_offset = 0;
+    p.launch_rows = p.gm_n_rows;
+    e = p.decode_waves == 4 ? launch_waves<4>(p, head_dim, stream)
+        : p.decode_waves == 2 ? launch_waves<2>(p, head_dim, stream)
+                              : launch_waves<1>(p, head_dim, stream);
   }
   if (e != hipSuccess) return e;
-  decode_group_merge_kernel<<<dim3(p.n_queries * p.n_q_heads), dim3(kMergeThreads), 0, stream>>>(p);
-  return hipGetLastError();
+  return head_dim == 64 ? launch_merge<64>(p, stream) : launch_merge<128>(p, stream);
 }

@@ -52,6 +52,7 @@ struct AttnParams {
   const float* v_scale8;
   int32_t decode_reverse;     // decode: walk every run of keys from its last half tile to its first
   int32_t decode_waves;       // decode: waves per workgroup that share an item's tiles (1, 2 or 4)
+  int32_t column_heads;       // group-major decode: columns per query, n_q_heads / n_kv_heads rounded up to a power of two
   int32_t q_split;            // prefill: runs each Q tile's list is cut into (1 = no split, no merge pass)
   int32_t n_rows;             // prefill: rows of q / o
   // shapes
@@ -104,8 +105,8 @@ hipError_t launch_prefill64(const AttnParams& p, int head_dim, hipStream_t strea
 // the same kernel over rows gathered through references, leaving partial softmax states: the pool
 // items of a decode step with many queries per group (attn_prefill64.hip)
 hipError_t launch_decode_matrix_items(const AttnParams& p, hipStream_t stream);
-// group-major split-KV decode + merge for head_dim 128 (attn_decode.hip)
-hipError_t launch_decode_group(const AttnParams& p, hipStream_t stream);
+// group-major split-KV decode + merge (attn_decode.hip); head_dim 64 without re-positioning
+hipError_t launch_decode_group(const AttnParams& p, int head_dim, hipStream_t stream);
 // the same with pool K/V stored as fp8 (e4m3) bytes and per-KV-head scales
 hipError_t launch_decode_group_kv8(const AttnParams& p, hipStream_t stream);
 hipError_t launch_decode_mfma(const AttnParams& p, int head_dim, hipStream_t stream);

@@ -76,3 +76,28 @@ def test_scores_that_jump_at_head_dim_64(hq, hkv, block_m, jump):
     o = B.dbsa_preencode_attn(lay, q, k, to_dev(pc.v), pc.scale)
     assert_close(to_f64(o), orc.preencode_attn(to_f64(q), to_f64(k), synth.as_f64(pc.v), p.sink_len, p.demo_offsets,
                                                p.group_demo_offsets, pc.scale), f"d64 jump {jump}")
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_queries,n_split", [
+    (8, 2, 64, 4, 0), (4, 4, 64, 40, 0), (16, 2, 64, 70, 0),     # one, two and four waves per workgroup
+    (6, 2, 64, 5, 3), (6, 2, 128, 5, 0), (10, 2, 128, 45, 0), (7, 1, 128, 33, 0), (24, 1, 128, 3, 0),   # head ratios 3, 5, 7, 24
+    (12, 1, 128, 40, 0),                                          # 12: a multiple of four that is no power of two
+])
+def test_group_major_decode_at_head_dim_64_and_odd_head_ratios(hq, hkv, d, n_queries, n_split):
+    pc = small_pool_case("gmd", 7500 + hq + d, hq=hq, hkv=hkv, d=d, sink=70, pool_tokens=5000, groups=5, lens=(30, 200), sigma=0.5)
+    sels = ([[3, 0], [], [4, 1, 2, 0, 3]] + [[1, 4]] * n_queries)[:n_queries]
+    qc = synth.make_query_case("gmdq", 7501, pc, n_queries=n_queries, q_len=([64, 37, 100] + [9] * n_queries)[:n_queries],
+                               selections=sels, n_decode=2)
+    p = pc.pool
+    lay = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, cu_qlens=qc.cu_qlens, sel_ptr=qc.sel_ptr,
+                              sel_idx=qc.sel_idx, n_split=n_split, block_m=32, block_n=64)
+    shp = qc.k_cache.shape
+    kc, vc = to_dev(qc.k_cache.reshape(-1, hkv, d)).view(shp), to_dev(qc.v_cache.reshape(-1, hkv, d)).view(shp)
+    for s in range(2):   # (the second step walks the runs backwards)
+        self_len = (np.diff(qc.cu_qlens) + s + 1).astype(np.int32)
+        od = B.dbsa_decode_attn(lay, to_dev(qc.dec_q[s]), kc, vc, torch.from_numpy(self_len).cuda(), to_dev(pc.k), to_dev(pc.v),
+                                pc.scale)
+        ref = orc.decode_attn(synth.as_f64(qc.dec_q[s]), synth.as_f64(qc.k_cache), synth.as_f64(qc.v_cache), self_len,
+                              synth.as_f64(pc.k), synth.as_f64(pc.v), p.sink_len, p.demo_offsets, p.group_demo_offsets,
+                              qc.sel_ptr, qc.sel_idx, pc.scale)
+        assert_close(to_f64(od), ref, f"decode {hq}/{hkv}x{d} {n_queries} queries step {s}")
