@@ -486,16 +486,29 @@ int check_shapes(int32_t dtype, int32_t hq, int32_t hkv, int32_t d, float scale)
   return DBSA_OK;
 }
 
-// Largest number of query heads one workgroup can take so that heads * (block_m/32)
-// wavefronts <= 8 and the heads share one KV head.
-int pick_heads_per_block(int r, int block_m) {
-  const int subs = block_m / 32;
+// the shapes of launch_prefill64, which walks a schedule
+bool schedulable(int row_blocks, int head_dim) { return row_blocks == 4 || row_blocks == 8 || (row_blocks == 2 && head_dim == 64); }
+
+// Query heads of one KV head a workgroup takes: heads * (block_m / 32) row blocks of 32 rows, 1, 2, 4 or 8 of them.
+// More row blocks share a fetched K/V pair; what divides the head ratio wastes nothing.  Rates of the workgroup sizes
+// relative to eight row blocks, measured where the ratio is a power of two: four 0.92 (multi-head encoding 1040 against
+// 1170 TFLOP/s), two 0.5 (multi-head questions of 64 tokens 600; 0.75 at head_dim 64, whose one-wave workgroups
+// share a compute unit in fours), one 0.3.  Head ratio 3 thus runs as 4 with an idle wave (0.75) and 5 as 3 x 2
+// (0.83 x 0.92) instead of one head at a time.  Only the kernel with 64 rows per wave knows idle heads (idle_heads:
+// the call's strides are in its reach).
+int pick_heads_per_block(int r, int block_m, int head_dim, bool idle_heads) {
   int best = 1;
-  for (int h = 1; h <= r; ++h)
-    if (r % h == 0 && h * subs <= 8) {
-      const int nw = h * subs;
-      if (nw == 1 || nw == 2 || nw == 4 || nw == 8) best = h;
+  double most = 0.0;
+  for (int h = 8; h >= 1; h /= 2) {
+    const int row_blocks = h * (block_m / 32);
+    if (row_blocks > 8 || (r % h != 0 && !(idle_heads && schedulable(row_blocks, head_dim)))) continue;
+    const double rate = row_blocks == 8 ? 1.0 : row_blocks == 4 ? 0.92 : row_blocks == 2 ? (head_dim == 64 ? 0.75 : 0.5) : 0.3;
+    const double value = rate * r / (static_cast<double>((r + h - 1) / h) * h);
+    if (value > most) {
+      most = value;
+      best = h;
     }
+  }
   return best;
 }
 
@@ -523,8 +536,6 @@ int64_t prefill_places(const dbsa_layout* L, int row_blocks, int head_dim) {
   if (row_blocks == 8) return workgroup_slots(L) / 2;
   return workgroup_slots(L) * (head_dim == 64 && row_blocks == 2 ? 2 : 1);
 }
-// the shapes of launch_prefill64, which walks a schedule
-bool schedulable(int row_blocks, int head_dim) { return row_blocks == 4 || row_blocks == 8 || (row_blocks == 2 && head_dim == 64); }
 
 // what a list entry costs with all workers busy over what it costs with few (dbsa_cut_schedule)
 // (a K/V pair serves 32 rows per row block; 256 rows keep the matrix pipes busy at the rate the pairs arrive)
@@ -558,8 +569,8 @@ size_t query_prefill_states(const dbsa_layout* L, int32_t n_q_heads, int32_t hea
   size_t most = 0;
   for (int hpb = 1; hpb <= 8; hpb *= 2) {
     const int row_blocks = hpb * (L->block_m / 32);
-    if (n_q_heads % hpb != 0 || row_blocks < 1 || row_blocks > 8) continue;
-    const int64_t head_blocks = n_q_heads / hpb, places = prefill_places(L, row_blocks, head_dim), states = int64_t{1} * L->n_query_tokens * n_q_heads;
+    if (row_blocks < 1 || row_blocks > 8) continue;
+    const int64_t head_blocks = (n_q_heads + hpb - 1) / hpb, places = prefill_places(L, row_blocks, head_dim), states = int64_t{1} * L->n_query_tokens * n_q_heads;
     if (schedulable(row_blocks, head_dim)) {
       const int64_t classes = std::min<int64_t>(places / head_blocks, kMaxSchedClasses);
       const int64_t cuts = std::max<int64_t>(0, dbsa_cut_workers(L, classes) - 1);
@@ -684,12 +695,13 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
       return e == hipSuccess ? DBSA_OK : DBSA_ERR_HIP;
     }
     if (!mfma_tile_sizes_ok(L)) return DBSA_ERR_UNSUPPORTED;
-    p.heads_per_block = pick_heads_per_block(hq / hkv, L->block_m);
+    p.heads_per_block = pick_heads_per_block(hq / hkv, L->block_m, d, max_stride < (int64_t{1} << 24));
     p.n_rows = L->n_query_tokens;
     p.q_split = 1;
     const int row_blocks = p.heads_per_block * (L->block_m / 32);
     const bool pipelined = max_stride < (int64_t{1} << 24) && (d == 128 || schedulable(row_blocks, d));
-    const int64_t head_blocks = hq / p.heads_per_block, places = prefill_places(L, row_blocks, d);
+    const int64_t head_blocks = hkv * ((hq / hkv + p.heads_per_block - 1) / p.heads_per_block), places = prefill_places(L, row_blocks, d);
+    p.n_head_blocks = static_cast<int32_t>(head_blocks);
     const size_t state_bytes = (d + kPartialPad) * sizeof(float);
     const size_t room = workspace && reinterpret_cast<uintptr_t>(workspace) % 16 == 0 ? workspace_bytes / state_bytes : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -699,7 +711,6 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
     // which is one Q tile) cuts the lists to measure if the caller gave a workspace for the pieces' partial states.
     if (pipelined && schedulable(row_blocks, d)) {
       const int32_t classes = static_cast<int32_t>(std::min<int64_t>(places / head_blocks, kMaxSchedClasses));
-      p.n_head_blocks = static_cast<int32_t>(head_blocks);
       p.sched_classes = classes;
       if (want_query_stage && L->n_qtiles() < kCutTiles * classes && room > 0 &&
           ensure_cut_schedule(L, classes, cut_crowding(row_blocks), s) &&

@@ -24,8 +24,9 @@
 // for some rows) and is then left alone: it only has to keep the probabilities inside what bf16
 // and fp32 hold.  No row maxima are computed in the tile loop; the sum of a step's probabilities,
 // which the row sum needs anyway, shows when a row has outgrown its maximum, and that step's
-// probabilities are then made again around the true maximum before the product uses them
-// (shifts are whole log2 units).
+// probabilities are then made again around the true maximum before the product uses them.
+// (The maximum is taken as it is, not rounded up to a power of two: the largest probability of a row whose
+// first keys hold its maximum is then exactly 1, without a rounding error where few keys are visible.)
 #include <atomic>
 #include <cstdint>
 
@@ -93,8 +94,10 @@ struct StepCfg {
 };
 
 // NW wavefronts per workgroup, each owning row blocks 2*wave and 2*wave+1 of the workgroup's
-// 2*NW blocks of 32 rows; row block g covers query head hb * heads_per_block + g / spb (hb = the
-// workgroup's head block) and tokens q_start + (g % spb) * 32 .. + 31, spb = block_m / 32.  SL:
+// 2*NW blocks of 32 rows; head block hb of the workgroup = heads (hb / n_kv_heads) * heads_per_block ..
+// of KV head hb % n_kv_heads (so that the workgroups of one KV head are on one XCD where there are 8 KV heads);
+// row block g covers head g / spb of those (idle where the KV head has no such head: head ratios that
+// heads_per_block does not divide) and tokens q_start + (g % spb) * 32 .. + 31, spb = block_m / 32.  SL:
 // tiles between the issue of a tile's loads and the barrier that publishes them.  SELF: lists may
 // name tiles of the call's own K/V (query prefill).
 //
@@ -192,7 +195,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   const const_words sched = (const_words)(reinterpret_cast<uintptr_t>(p.sched_rec));
   const const_words all_ent = (const_words)(reinterpret_cast<uintptr_t>(p.list_ent));
   const const_words all_shift = (const_words)(reinterpret_cast<uintptr_t>(p.list_shift));
-  const int hk = (hb * p.heads_per_block) / r;
+  const int hk = hb % p.n_kv_heads, first_head = (hb / p.n_kv_heads) * p.heads_per_block;  // (of the KV head's r)
+  bool head_ok[2];
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) head_ok[rb] = first_head + (2 * wave + rb) / spb < r;
 
   const uint64_t kpool = uniform64(reinterpret_cast<uint64_t>(static_cast<const __bf16*>(p.k_pool.ptr) + hk * p.k_pool.stride_head));
   const uint64_t vpool = uniform64(reinterpret_cast<uint64_t>(static_cast<const __bf16*>(p.v_pool.ptr) + hk * p.v_pool.stride_head));
@@ -370,9 +376,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   const float c2 = p.scale_log2e;
   const float score_unit = kRawQ ? 1.f / c2 : 1.f;  // one log2 unit in units of the scores
   auto log2_units = [&](float s) DBSA_INLINE { return kRawQ ? s * c2 : s; };
-  // a running maximum moves by whole log2 units, which rescales exactly; raw scores are scaled in fp32 anyway, and the
-  // exact maximum leaves the largest probability without a rounding error
-  auto whole_units = [&](float x) DBSA_INLINE { return kRawQ ? x : __builtin_ceilf(x); };
   int head[2], row_local[2], row_tok[2], q_pos[2];
   int row_slot[2] = {0, 0};  // GATHER: where the row's partial state goes
   int row_rot[2] = {0, 0};   // GATHER with ROPE: the row's rotation id
@@ -381,9 +384,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       const int g = 2 * wave + rb;
-      head[rb] = hb * p.heads_per_block + g / spb;
+      head[rb] = hk * r + min(first_head + g / spb, r - 1);
       row_local[rb] = (g % spb) * 32 + l32;
-      row_valid[rb] = row_local[rb] < q_len;
+      row_valid[rb] = head_ok[rb] && row_local[rb] < q_len;
       row_tok[rb] = q_start + min(row_local[rb], q_len - 1);
       q_pos[rb] = q_start + row_local[rb];
       if constexpr (GATHER) {
@@ -524,7 +527,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         matrix_result_fence();
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
-          const float delta = whole_units(fmaxf(log2_units(row_max(S_w[rb])), 0.f));
+          const float delta = fmaxf(log2_units(row_max(S_w[rb])), 0.f);
           const float alpha = __builtin_amdgcn_exp2f(-delta);
           m_run[rb] += delta;
           l_run[rb] *= alpha;
@@ -566,7 +569,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         for (int rb = 0; rb < 2; ++rb) {
           const float m_true = row_max(S_r[rb]);
           const bool first = !seen[rb] & (m_true > kNoKey);
-          const float delta = first ? whole_units(log2_units(m_true)) : 0.f;
+          const float delta = first ? log2_units(m_true) : 0.f;
           seen[rb] = seen[rb] | first;
           m_run[rb] += delta;
 #pragma unroll
@@ -905,7 +908,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
             const floatx4 piece = *(lds_f128)(static_cast<uintptr_t>(stag + row * 256 + (((ln % 16) ^ (row % 16)) * 16)));
             // (GATHER: the slot of that row is held by the lane that owns the row)
             const int slot = GATHER ? __builtin_amdgcn_ds_bpermute(4 * row, o_slot[rb]) : first_row + row_base + row;
-            if (row_base + row < o_len) {
+            if (head_ok[rb] && row_base + row < o_len) {
               if constexpr (GATHER)
                 *reinterpret_cast<floatx4*>(p.partial + static_cast<int64_t>(o_head[rb]) * (kD + kPartialPad) + (ln % 16) * 4 +
                                             static_cast<int64_t>(slot) * p.n_q_heads * (kD + kPartialPad) + 64 * h2) = piece;
@@ -957,7 +960,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         for (int i = 0; i < 32 / kLoadRows; ++i) {
           const int row = kLoadRows * i + ln / kPieces16;
           const intx4 piece = *(lds_b128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((ln % kPieces16) ^ k_swizzle(row)) * 16)));
-          if (row_base + row < o_len)
+          if (head_ok[rb] && row_base + row < o_len)
             *reinterpret_cast<intx4*>(op + static_cast<int64_t>(o_start + row_base + row) * p.o.stride_tok) = piece;
         }
         if (p.lse && ehalf == 0 && o_valid[rb])
@@ -981,7 +984,7 @@ hipError_t launch_cfg64(const AttnParams& p, hipStream_t stream) {
   }
   const int n_split = p.q_split > 1 ? p.q_split : 1;
   const dim3 grid = PERSIST ? dim3(p.sched_classes * p.n_head_blocks)
-                            : dim3(p.n_q_heads / p.heads_per_block, p.n_qtiles, n_split);
+                            : dim3(p.n_head_blocks, p.n_qtiles, n_split);
   attn_prefill64_kernel<kD, NW, SL, SELF, PERSIST, GATHER, ROPE><<<grid, dim3(NW * 64), lds_bytes, stream>>>(p);
   return hipGetLastError();
 }

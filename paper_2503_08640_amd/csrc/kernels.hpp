@@ -58,7 +58,7 @@ struct AttnParams {
   // shapes
   int32_t n_q_heads, n_kv_heads, block_m, block_n;
   int32_t largest_tile;       // prefill: most rows any Q tile has
-  int32_t heads_per_block;    // query heads handled by one workgroup (divides Hq/Hkv)
+  int32_t heads_per_block;    // query heads of one KV head handled by one workgroup; n_head_blocks = Hkv * ceil(r / that)
   // persistent prefill-shaped launch (null: one workgroup per Q tile): workgroup w serves head block
   // w % n_head_blocks and records sched_ptr[c] .. sched_ptr[c+1]-1, c = w / n_head_blocks, of
   // sched_rec = [n_qtiles][4] (q_start, q_len, first list entry, entries)

@@ -101,3 +101,33 @@ def test_group_major_decode_at_head_dim_64_and_odd_head_ratios(hq, hkv, d, n_que
                               synth.as_f64(pc.k), synth.as_f64(pc.v), p.sink_len, p.demo_offsets, p.group_demo_offsets,
                               qc.sel_ptr, qc.sel_idx, pc.scale)
         assert_close(to_f64(od), ref, f"decode {hq}/{hkv}x{d} {n_queries} queries step {s}")
+
+
+@pytest.mark.parametrize("hq,hkv,d,block_m,pool", [
+    (6, 2, 128, 64, 1500), (10, 2, 128, 64, 1500), (7, 1, 128, 32, 1500), (3, 1, 128, 128, 1500),   # one workgroup per Q tile
+    (6, 2, 64, 64, 1500), (5, 1, 64, 32, 1500),
+    (24, 8, 128, 64, 6200), (40, 8, 128, 64, 4000),                                                # persistent
+])
+def test_prefill_at_head_ratios_that_leave_waves_idle(hq, hkv, d, block_m, pool):
+    pc = small_pool_case("odd", 7600 + hq + d + block_m, hq=hq, hkv=hkv, d=d, sink=70, pool_tokens=pool, groups=3 if pool < 2000 else 20,
+                         lens=(20, 110), sigma=0.5)
+    p = pc.pool
+    n = p.n_tokens
+    lay = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, block_m=block_m, block_n=64)
+    lse = torch.zeros((hq, n), device="cuda")
+    guard = torch.full((n, hq + 1, d), 7.0, dtype=torch.bfloat16, device="cuda")   # one head more than the call may write
+    o = B.dbsa_preencode_attn(lay, to_dev(pc.q), to_dev(pc.k), to_dev(pc.v), pc.scale, out=guard[:, :hq], lse=lse)
+    rows = np.arange(n) if n < 2000 else np.unique(np.concatenate([np.arange(140), np.arange(n - 140, n),
+                                                                   np.random.default_rng(2).integers(0, n, 300)]))
+    want, want_lse = orc.preencode_attn(synth.as_f64(pc.q), synth.as_f64(pc.k), synth.as_f64(pc.v), p.sink_len, p.demo_offsets,
+                                        p.group_demo_offsets, pc.scale, rows=rows, return_lse=True)
+    # (up to 10^7 values: the far tail of the rounding of the scaled row, where few keys are visible)
+    assert_close(to_f64(o)[rows], want, f"pre-encode {hq}/{hkv}x{d} bm={block_m}", max_tol=3e-2)
+    assert_close(to_f64(lse)[:, rows], want_lse, "lse", max_tol=3e-2)
+    assert (guard[:, hq] == 7.0).all()
+    qc = synth.make_query_case("oddq", 7601, pc, n_queries=3, q_len=[64, 100, 9], n_select=2)
+    layq, kp, vp = _query_setup(pc, qc, block_m, 0)
+    qs, ks, vs = to_dev(qc.q), to_dev(qc.k), to_dev(qc.v)
+    for ws in (False, None):
+        oq = B.dbsa_query_attn(layq, qs, ks, vs, kp, vp, pc.scale, workspace=ws)
+        assert_close(to_f64(oq), _oracle_query(pc, qc), f"query prefill {hq}/{hkv}x{d} bm={block_m} ws={ws}")
