@@ -187,3 +187,27 @@ def test_repositioned_config3_full_size():
     qc = synth.config3_query(pc)
     _repositioned_case(pc, qc, B.BENCH_BLOCK_M_QUERY, 500000.0, queries=(0, 5, 10, 15), decode_steps=(0, 31),
                        what="cfg3")
+
+
+@pytest.mark.parametrize("dtype,n,heads,d,lead", [("bf16", 3000, 32, 128, 0), ("bf16", 700, 7, 64, 0), ("bf16", 5, 1, 16, 0),
+                                                  ("f32", 900, 5, 48, 0), ("bf16", 40, 70, 128, 0), ("bf16", 300, 3, 128, 4),
+                                                  ("f32", 300, 3, 64, 1)])
+def test_rope_apply_on_rows_of_every_width_and_alignment(dtype, n, heads, d, lead):
+    """Several heads of a token per thread, tokens with more parts than a workgroup, tensors that are not on 16-byte
+    addresses (`lead` elements in front), strided outputs, and in place: against the oracle and each other bit for bit."""
+    rng = np.random.default_rng(7)
+    x = rng.standard_normal((n, heads, d)).astype(np.float32)
+    x = synth.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    tab = B.dbsa_rope_table(ro.inv_freq(10000.0, d), n + 50)
+    src = to_dev(x)
+    buf = torch.zeros(lead + src.numel(), dtype=src.dtype, device="cuda")
+    t = buf[lead:].view(n, heads, d)
+    t.copy_(src)
+    want = ro.rope(synth.as_f64(x), 20 + np.arange(n), ro.inv_freq(10000.0, d))
+    got = B.dbsa_rope_apply(t, tab, first_id=20)
+    # the table is rounded to fp32, the result to bf16 / fp32
+    assert np.abs(to_f64(got) - want).max() <= (2.0 ** -8 if dtype == "bf16" else 2e-6) * np.abs(want).max()
+    wide = torch.full((n, heads + 1, d), 9.0, dtype=src.dtype, device="cuda")
+    assert torch.equal(B.dbsa_rope_apply(t, tab, first_id=20, out=wide[:, :heads]), got) and (wide[:, heads] == 9.0).all()
+    ids = torch.arange(20, 20 + n, dtype=torch.int32, device="cuda")
+    assert torch.equal(B.dbsa_rope_apply(t, tab, positions=ids, out=t), got) and torch.equal(t, got)
