@@ -68,7 +68,8 @@ struct DecodeItem {
 // is (block, query batch); the rows of one block follow each other, so the workgroups that walk
 // one item's keys for different query batches have ids 8 apart: they start together AND on the
 // same XCD (ids are dealt to the 8 XCDs in turn), and all but the first find the keys in that
-// XCD's L2.  Rows exist only for batches some item of the block has.  False: the id names no item.
+// XCD's L2.  (The KV head slowest: with the heads of an item side by side, whose rows are neighbours in memory, a step
+// of 16 queries takes 92 us instead of 85, over an fp8 pool 61 instead of 55.)  Rows exist only for batches some item of the block has.  False: the id names no item.
 // Everything the first loads need (the run, the query references) is one load away from the item
 // index: all workgroups of a step start together, and every further dependent load at their start
 // is a microsecond or two in which no tile data moves.  (The schedule lists are read-only while a
@@ -157,6 +158,10 @@ __device__ DBSA_INLINE void load_column(const DecodeColumn& c, float prescale, b
 #pragma unroll
     for (int i = 0; i < kD / 16; ++i) qf[i] = *reinterpret_cast<const bf16x8*>(c.qp + 16 * i);
   }
+  // The rows arrive here, in front of the tile loop: at their first use inside it the compiler, which does not count
+  // the LDS-DMA loads, would wait for every load in flight, once per half tile.
+#pragma unroll
+  for (int i = 0; i < kD / 16; ++i) asm volatile("" : "+v"(qf[i]));
 }
 
 // The pieces of one half tile (32 keys) against the 32 columns of a wave.  The kernels differ in
@@ -264,19 +269,20 @@ __device__ DBSA_INLINE void store_partial_state(const AttnParams& p, const Decod
   }
 }
 
+// One wave over one item: a run of pool tiles for several queries, or one query's own cache.  lds: kRingBytes of the
+// wave's own.  LOCATE: the item is looked up here, behind the division by the head count (in front of it the same code
+// takes a step of 16 queries 0.7 us longer).
 // ROPE: the query row is un-rotated and is rotated here at the id that stands for the new
 // in-order position of the item's keys (Sec. 2.2), see AttnParams::gm_ref_pad.
-template <int kD, bool ROPE>
-__global__ __launch_bounds__(64, 2) void decode_group_kernel(AttnParams p) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+template <int kD, bool ROPE, bool LOCATE>
+__device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it, lds_byte* lds) {
   using T = HalfTile<kD>;
-  lds_byte* lds = (lds_byte*)smem;
-  const int lane = threadIdx.x, l32 = lane % 32, half = lane / 32;
+  const int lane = threadIdx.x % 64, l32 = lane % 32, half = lane / 32;
   const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
   const int qpw = 32 / rp;  // queries per wave
-  // ---- the item: a run of pool tiles for several queries, or one query's own cache ----
-  DecodeItem it;
-  if (!locate_decode_item(p, it)) return;
+  if constexpr (LOCATE) {
+    if (!locate_decode_item(p, it)) return;
+  }
   const int hk = it.hk, pass = it.batch, n_q = it.n_q, first_key = it.first_key, n_keys = it.n_keys, self_u = it.self_u;
   const bool self_item = it.self_item;
   // One workgroup per batch of 32 / rp queries of the item: an item that serves more queries than
@@ -416,6 +422,12 @@ __global__ __launch_bounds__(64, 2) void decode_group_kernel(AttnParams p) {
   }
 
   store_partial_state<kD>(p, col, half, o, m_run, l_run, 1.f);
+}
+
+template <int kD, bool ROPE>
+__global__ __launch_bounds__(64, 2) void decode_group_kernel(AttnParams p) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  walk_decode_item<kD, ROPE, true>(p, DecodeItem{}, (lds_byte*)smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -564,15 +576,16 @@ constexpr int kSlot8 = 4096;
 constexpr int kLds8 = 4 * kSlot8 + kHalfBytes;  // 24 KiB per wave
 constexpr int kLoads8 = 4;                      // load instructions per group (the K or the V bytes of a half tile)
 
+// (every e4m3 value is a bf16 value: the conversion is exact, one instruction per pair)
 __device__ inline bf16x8 widen8(unsigned w0, unsigned w1) {
   union {
     bf16x8 v;
     bf16x2 p2[4];
   } out;
-  out.p2[0] = __builtin_convertvector(__builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(w0), false), bf16x2);
-  out.p2[1] = __builtin_convertvector(__builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(w0), true), bf16x2);
-  out.p2[2] = __builtin_convertvector(__builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(w1), false), bf16x2);
-  out.p2[3] = __builtin_convertvector(__builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(w1), true), bf16x2);
+  out.p2[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.f, false);
+  out.p2[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.f, true);
+  out.p2[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.f, false);
+  out.p2[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.f, true);
   return out.v;
 }
 
@@ -584,9 +597,12 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
   const int lane = threadIdx.x, l32 = lane % 32, half = lane / 32;
   const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
   const int qpw = 32 / rp;
-  // this launch covers the rows of pool items only
   DecodeItem it;
-  if (!locate_decode_item(p, it) || it.self_item) return;
+  if (!locate_decode_item(p, it)) return;
+  if (it.self_item) {  // the query's own cache is bf16
+    walk_decode_item<kD, ROPE, false>(p, it, lds);
+    return;
+  }
   const int hk = it.hk, pass = it.batch, n_q = it.n_q, first_key = it.first_key, n_keys = it.n_keys;
   const int n_half = (n_keys + kHalf - 1) / kHalf;
   if (pass >= (n_q + qpw - 1) / qpw) return;
@@ -729,9 +745,13 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
   const int lane = threadIdx.x % 64, l32 = lane % 32, half = lane / 32;
   const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
   const int qpw = 32 / rp;
-  // this launch covers the rows of pool items only; a row's batch counts batches of W * qpw queries
+  // a row's batch counts batches of W * qpw queries
   DecodeItem it;
-  if (!locate_decode_item(p, it) || it.self_item) return;
+  if (!locate_decode_item(p, it)) return;
+  if (it.self_item) {  // the query's own cache is bf16: one wave walks it (and the workgroup leaves without a barrier)
+    if (wave == 0) walk_decode_item<kD, ROPE, false>(p, it, lds);
+    return;
+  }
   const int hk = it.hk, wg_batch = it.batch, n_q = it.n_q, first_key = it.first_key, n_keys = it.n_keys;
   const int n_half = (n_keys + kHalf - 1) / kHalf;
   const int n_pass = (n_q + qpw - 1) / qpw;
@@ -829,17 +849,18 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
 }
 
 // Merge the partial states of one (query, head): slots [slot_ptr[u], slot_ptr[u+1]).
-// 2 x D threads: thread (part, d) owns output channel d for the slots of its parity.  The
+// kParts x D threads: thread (part, d) owns output channel d for every kParts-th slot.  The
 // per-slot maxima and sums are read with one slot per thread (not one after the other by
 // everyone), the weights 2^(m_s - m*) go through LDS, and the weighted sum of the accumulators
-// runs with eight independent loads in flight per thread; the two parities meet in LDS.
-template <int kD>
-__global__ __launch_bounds__(2 * kD) void decode_group_merge_kernel(AttnParams p) {
-  constexpr int kMergeThreads = 2 * kD;
+// runs with eight independent loads in flight per thread; the parts meet in LDS.  Two parts fill the chip once
+// there are many (query, head) pairs; with few, eight shorten the chain (one question, 113 slots: 6.1 -> 4.4 us).
+template <int kD, int kParts>
+__global__ __launch_bounds__(kParts * kD) void decode_group_merge_kernel(AttnParams p) {
+  constexpr int kMergeThreads = kParts * kD;
   constexpr int kRow = kD + kPartialPad, kCap = 256, kWaves = kMergeThreads / 64;
   __shared__ float w_sh[kCap];
   __shared__ float red[2][kWaves];
-  __shared__ float acc_sh[kD];
+  __shared__ float acc_sh[kParts - 1][kD];
   const int u = blockIdx.x / p.n_q_heads, head = blockIdx.x % p.n_q_heads;
   const int t = threadIdx.x, d = t % kD, part = t / kD;
   const int s0 = static_cast<int>(p.gm_slot_ptr[u]), s1 = static_cast<int>(p.gm_slot_ptr[u + 1]);
@@ -874,22 +895,34 @@ __global__ __launch_bounds__(2 * kD) void decode_group_merge_kernel(AttnParams p
     __syncthreads();
     const float* col = partial + static_cast<int64_t>(base) * slot_stride + d;
     int i = part;
-    for (; i + 14 < n; i += 16) {
+    for (; i + 7 * kParts < n; i += 8 * kParts) {
       float v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = col[(i + 2 * j) * slot_stride];
+      for (int j = 0; j < 8; ++j) v[j] = col[(i + kParts * j) * slot_stride];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc = fmaf(v[j], w_sh[i + 2 * j], acc);
+      for (int j = 0; j < 8; ++j) acc = fmaf(v[j], w_sh[i + kParts * j], acc);
     }
-    for (; i < n; i += 2) acc = fmaf(col[i * slot_stride], w_sh[i], acc);
+    if constexpr (kParts > 2) {  // the rest, at once too (slots past the last repeat it and weigh nothing)
+      float v[7];
+#pragma unroll
+      for (int j = 0; j < 7; ++j) v[j] = col[min(i + kParts * j, n - 1) * slot_stride];
+#pragma unroll
+      for (int j = 0; j < 7; ++j) {
+        if (i + kParts * j < n) acc = fmaf(v[j], w_sh[i + kParts * j], acc);
+      }
+    } else {
+      for (; i < n; i += kParts) acc = fmaf(col[i * slot_stride], w_sh[i], acc);
+    }
   }
   const float l_star = block_reduce(l, false, 1);
-  if (part == 1) acc_sh[d] = acc;
+  if (part > 0) acc_sh[part - 1][d] = acc;
   __syncthreads();
   if (part == 0) {
+#pragma unroll
+    for (int j = 0; j < kParts - 1; ++j) acc += acc_sh[j][d];
     __bf16* o = static_cast<__bf16*>(const_cast<void*>(p.o.ptr));
     o[static_cast<int64_t>(u) * p.o.stride_tok + static_cast<int64_t>(head) * p.o.stride_head + d] =
-        static_cast<__bf16>((acc + acc_sh[d]) / l_star);
+        static_cast<__bf16>(acc / l_star);
   }
 }
 
@@ -924,7 +957,12 @@ hipError_t launch_shared8(const AttnParams& p, hipStream_t stream) {
 namespace {
 template <int kD>
 hipError_t launch_merge(const AttnParams& p, hipStream_t stream) {
-  decode_group_merge_kernel<kD><<<dim3(p.n_queries * p.n_q_heads), dim3(2 * kD), 0, stream>>>(p);
+  // (a workgroup of eight parts per pair: 128 pairs leave half the compute units idle; at 512 it is 5 % slower)
+  const int pairs = p.n_queries * p.n_q_heads;
+  if (pairs <= 128)
+    decode_group_merge_kernel<kD, 8><<<dim3(pairs), dim3(8 * kD), 0, stream>>>(p);
+  else
+    decode_group_merge_kernel<kD, 2><<<dim3(pairs), dim3(2 * kD), 0, stream>>>(p);
   return hipGetLastError();
 }
 
@@ -945,30 +983,24 @@ hipError_t launch_waves(const AttnParams& p, int head_dim, hipStream_t stream) {
 }
 }  // namespace
 
-// p.decode_waves as for launch_decode_group (pool rows; the self rows below are single batches)
+// p.decode_waves as for launch_decode_group.  Pool items and the queries' own caches go in one launch (in two, the own
+// caches of 16 queries cost 8 us after pool items of 47).
 hipError_t launch_decode_group_kv8(const AttnParams& p_in, hipStream_t stream) {
   AttnParams p = p_in;
-  if (p.n_gm_items > 0) {
-    p.row_offset = 0;
-    p.launch_rows = p.gm_pool_rows;
-    hipError_t e;
-    if (p.decode_waves == 4)
-      e = launch_shared8<4>(p, stream);
-    else if (p.decode_waves == 2)
-      e = launch_shared8<2>(p, stream);
-    else {
-      if (p.rope_table)
-        decode_group_kv8_kernel<true><<<decode_grid(p), dim3(64), kLds8, stream>>>(p);
-      else
-        decode_group_kv8_kernel<false><<<decode_grid(p), dim3(64), kLds8, stream>>>(p);
-      e = hipGetLastError();
-    }
-    if (e != hipSuccess) return e;
+  p.row_offset = 0;
+  p.launch_rows = p.gm_n_rows;
+  hipError_t e;
+  if (p.decode_waves == 4) {
+    e = launch_shared8<4>(p, stream);
+  } else if (p.decode_waves == 2) {
+    e = launch_shared8<2>(p, stream);
+  } else {
+    if (p.rope_table)
+      decode_group_kv8_kernel<true><<<decode_grid(p), dim3(64), kLds8, stream>>>(p);
+    else
+      decode_group_kv8_kernel<false><<<decode_grid(p), dim3(64), kLds8, stream>>>(p);
+    e = hipGetLastError();
   }
-  // every query's own (bf16) cache: the self items of the ordinary kernel
-  p.row_offset = p.gm_pool_rows;
-  p.launch_rows = p.gm_n_rows - p.gm_pool_rows;
-  const hipError_t e = launch_waves<1>(p, 128, stream);
   return e == hipSuccess ? launch_merge<128>(p, stream) : e;
 }
 

@@ -1008,7 +1008,9 @@ hipError_t launch_stage64(const AttnParams& p, hipStream_t stream) {
 
 // Eight row blocks per workgroup: four waves alone on a compute unit (112 KiB of LDS, two tiles
 // of load slack); four row blocks: two waves, two workgroups per compute unit (80 KiB each); two row blocks (head
-// dimension 64 only, whose tiles are half as large): one wave, four workgroups per compute unit (40 KiB each).
+// dimension 64 only, whose tiles are half as large): one wave, four workgroups per compute unit (40 KiB each).  At head
+// dimension 128 only two such workgroups fit a compute unit and half of its SIMDs stay idle: 10-20 % slower than the
+// two waves of 32 rows each of attn_prefill.hip (multi-head, 16 questions of 64 tokens: 253 against 228 us).
 // With a schedule in p (sched_rec) the launch is persistent and p.q_split must be 1.  The caller
 // runs the merge pass of a split launch.
 hipError_t launch_prefill64(const AttnParams& p, int head_dim, hipStream_t stream) {
