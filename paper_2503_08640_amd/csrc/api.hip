@@ -1015,7 +1015,8 @@ int decode_kv8_common(const dbsa_layout* L, dbsa_tensor q_step, dbsa_tensor k_se
   p.rope_n_pos = rope_n_pos;
   p.partial = static_cast<float*>(workspace);
   p.decode_waves = pick_decode_waves(L, r);
-  p.column_heads = r;
+  p.head_ratio = r;
+  while ((1 << p.column_heads_log2) < r) ++p.column_heads_log2;
   fill_decode_rows(p, L, r / p.decode_waves);
   if (order_behind_upload(L, static_cast<hipStream_t>(stream)) != hipSuccess) return DBSA_ERR_HIP;
   p.decode_reverse = next_walk_direction(L);  // nothing rejects the call from here on
@@ -1152,7 +1153,8 @@ int decode_common(const dbsa_layout* L, dbsa_tensor q_step, dbsa_tensor k_selfca
       // to outweigh the barrier per half tile (measured over 16-256 queries at 10-100 % retrieval: 2
       // waves pay from ~1.5 walks per key on, 4 from ~2.3).
       p.decode_waves = pick_decode_waves(L, columns);
-      p.column_heads = columns;
+      p.head_ratio = r;
+      while ((1 << p.column_heads_log2) < columns) ++p.column_heads_log2;
       // With query heads in fours per KV head and groups that serve many queries, the pool items run
       // as a contraction: 64 queries per wave, four heads of a KV head as the four waves of a
       // workgroup, one workgroup per compute unit walking a balanced share of the records

@@ -113,11 +113,12 @@ struct DecodeColumn {
 // (The addresses are formed here, before the tile loads go out: they wait for the query reference
 // just loaded, and that wait must not include the tile loads.)
 template <int kD, bool ROPE>
-__device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const DecodeItem& it, int pass, bool active, int r, int rp,
+__device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const DecodeItem& it, int pass, bool active, int r, int rp_log2,
                                                   int l32, int half) {
   DecodeColumn c;
-  const int q_local = pass * (32 / rp) + l32 / rp;  // index into the item's query list (< 32 also without a batch)
-  c.valid = active && q_local < it.n_q && l32 % rp < r;
+  const int rp = 1 << rp_log2;
+  const int q_local = pass * (32 >> rp_log2) + (l32 >> rp_log2);  // index into the item's query list (< 32 also without a batch)
+  c.valid = active && q_local < it.n_q && (l32 & (rp - 1)) < r;
   int u = it.self_u, rot_id = 0;
   if (it.self_item) {
     c.slot = static_cast<int>(p.gm_slot_ptr[it.self_u + 1]) - 1;
@@ -129,7 +130,7 @@ __device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const Dec
     c.slot = ref[1];
     if (ROPE) rot_id = ref[2];
   }
-  c.head = it.hk * r + min(l32 % rp, r - 1);
+  c.head = it.hk * r + min(l32 & (rp - 1), r - 1);
   c.rot = nullptr;
   if (ROPE) {
     rot_id = min(max(rot_id + p.self_len[u] - 1, 0), p.rope_n_pos - 1);
@@ -278,8 +279,8 @@ template <int kD, bool ROPE, bool LOCATE>
 __device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it, lds_byte* lds) {
   using T = HalfTile<kD>;
   const int lane = threadIdx.x % 64, l32 = lane % 32, half = lane / 32;
-  const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
-  const int qpw = 32 / rp;  // queries per wave
+  const int r = p.head_ratio, rp_log2 = p.column_heads_log2;
+  const int qpw = 32 >> rp_log2;  // queries per wave
   if constexpr (LOCATE) {
     if (!locate_decode_item(p, it)) return;
   }
@@ -386,7 +387,7 @@ __device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it,
   const bool scale_rows = ROPE || p.decode_matrix;
   const float prescale = scale_rows ? p.scale_log2e : 1.f, c2 = scale_rows ? 1.f : p.scale_log2e;
   // ---- this lane's column: query and head ----
-  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp, l32, half);
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp_log2, l32, half);
 
   // ---- wave-private ring: group g + kSlots goes out as soon as the product that reads group g is issued.  The first
   // groups are requested before the query row, so that both latencies run together. ----
@@ -451,8 +452,8 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
   static_assert(T::kLoads % W == 0, "waves share the load instructions evenly");
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
   const int lane = threadIdx.x % 64, l32 = lane % 32, half = lane / 32;
-  const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
-  const int qpw = 32 / rp;  // queries per wave
+  const int r = p.head_ratio, rp_log2 = p.column_heads_log2;
+  const int qpw = 32 >> rp_log2;  // queries per wave
   // a row's batch counts batches of W * qpw queries here
   DecodeItem it;
   if (!locate_decode_item(p, it)) return;
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
   const float prescale = ROPE ? p.scale_log2e : 1.f, c2 = ROPE ? 1.f : p.scale_log2e;
 
   // ---- this lane's column: query and head ----
-  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp, l32, half);
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp_log2, l32, half);
 
   issue_pair(0);
   if (1 < n_half) issue_pair(1);
@@ -595,8 +596,8 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
   lds_byte* lds = (lds_byte*)smem;
   lds_byte* work_v = lds + 4 * kSlot8;
   const int lane = threadIdx.x, l32 = lane % 32, half = lane / 32;
-  const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
-  const int qpw = 32 / rp;
+  const int r = p.head_ratio, rp_log2 = p.column_heads_log2;
+  const int qpw = 32 >> rp_log2;
   DecodeItem it;
   if (!locate_decode_item(p, it)) return;
   if (it.self_item) {  // the query's own cache is bf16
@@ -654,7 +655,7 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
   const int v_base = HalfTile<kD>::v_base(lane, l32, half);
 
   // ---- this lane's column (ROPE as in decode_group_kernel: the stored keys keep their encoding-time rotation) ----
-  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp, l32, half);
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp_log2, l32, half);
   issue_k(0);
   issue_v(0);
   if (1 < n_half) {
@@ -743,15 +744,11 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
   constexpr int kPerWave = kLoads8 / W;  // load instructions per wave per K or V half tile (8 rows each)
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
   const int lane = threadIdx.x % 64, l32 = lane % 32, half = lane / 32;
-  const int r = p.n_q_heads / p.n_kv_heads, rp = p.column_heads;
-  const int qpw = 32 / rp;
-  // a row's batch counts batches of W * qpw queries
+  const int r = p.head_ratio, rp_log2 = p.column_heads_log2;
+  const int qpw = 32 >> rp_log2;
+  // this launch covers the rows of pool items only; a row's batch counts batches of W * qpw queries
   DecodeItem it;
-  if (!locate_decode_item(p, it)) return;
-  if (it.self_item) {  // the query's own cache is bf16: one wave walks it (and the workgroup leaves without a barrier)
-    if (wave == 0) walk_decode_item<kD, ROPE, false>(p, it, lds);
-    return;
-  }
+  if (!locate_decode_item(p, it) || it.self_item) return;
   const int hk = it.hk, wg_batch = it.batch, n_q = it.n_q, first_key = it.first_key, n_keys = it.n_keys;
   const int n_half = (n_keys + kHalf - 1) / kHalf;
   const int n_pass = (n_q + qpw - 1) / qpw;
@@ -815,7 +812,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
   const int k_base = HalfTile<kD>::k_base(l32, half), v_base = HalfTile<kD>::v_base(lane, l32, half);
 
   // ---- this lane's column ----
-  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp, l32, half);
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp_log2, l32, half);
   issue_pair(0);
   if (1 < n_half) issue_pair(1);
   const float c8 = p.scale_log2e * p.k_scale8[hk], prescale = ROPE ? c8 : 1.f, c2 = ROPE ? 1.f : c8;
@@ -983,29 +980,37 @@ hipError_t launch_waves(const AttnParams& p, int head_dim, hipStream_t stream) {
 }
 }  // namespace
 
-// p.decode_waves as for launch_decode_group.  Pool items and the queries' own caches go in one launch (in two, the own
-// caches of 16 queries cost 8 us after pool items of 47).
+// p.decode_waves as for launch_decode_group.  With single waves the pool items and the queries' own caches go in one
+// launch (in two, the own caches of 16 queries cost 8 us after pool items of 47).  The shared kernel keeps to the pool
+// items: with the bf16 code for the own caches it needs 309 registers instead of 256, one wave per SIMD instead of two
+// (80 queries: 80 us in one launch, 69 in two).
 hipError_t launch_decode_group_kv8(const AttnParams& p_in, hipStream_t stream) {
   AttnParams p = p_in;
-  p.row_offset = 0;
-  p.launch_rows = p.gm_n_rows;
   hipError_t e;
-  if (p.decode_waves == 4) {
-    e = launch_shared8<4>(p, stream);
-  } else if (p.decode_waves == 2) {
-    e = launch_shared8<2>(p, stream);
-  } else {
+  p.row_offset = 0;
+  if (p.decode_waves == 1) {
+    p.launch_rows = p.gm_n_rows;
     if (p.rope_table)
       decode_group_kv8_kernel<true><<<decode_grid(p), dim3(64), kLds8, stream>>>(p);
     else
       decode_group_kv8_kernel<false><<<decode_grid(p), dim3(64), kLds8, stream>>>(p);
     e = hipGetLastError();
+  } else {
+    e = hipSuccess;
+    if (p.n_gm_items > 0) {
+      p.launch_rows = p.gm_pool_rows;
+      e = p.decode_waves == 4 ? launch_shared8<4>(p, stream) : launch_shared8<2>(p, stream);
+    }
+    if (e != hipSuccess) return e;
+    p.row_offset = p.gm_pool_rows;
+    p.launch_rows = p.gm_n_rows - p.gm_pool_rows;
+    e = launch_waves<1>(p, 128, stream);
   }
   return e == hipSuccess ? launch_merge<128>(p, stream) : e;
 }
 
 // p.decode_waves = waves per workgroup (1, 2 or 4; the launch rows in p are those of batches of
-// decode_waves * 32 / column_heads queries)
+// decode_waves * (32 >> column_heads_log2) queries)
 hipError_t launch_decode_group(const AttnParams& p_in, int head_dim, hipStream_t stream) {
   AttnParams p = p_in;
   hipError_t e;

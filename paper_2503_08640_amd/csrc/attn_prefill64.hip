@@ -386,7 +386,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       const int g = 2 * wave + rb;
       head[rb] = hk * r + min(first_head + g / spb, r - 1);
       row_local[rb] = (g % spb) * 32 + l32;
-      row_valid[rb] = head_ok[rb] && row_local[rb] < q_len;
+      row_valid[rb] = row_local[rb] < (head_ok[rb] ? q_len : 0);
       row_tok[rb] = q_start + min(row_local[rb], q_len - 1);
       q_pos[rb] = q_start + row_local[rb];
       if constexpr (GATHER) {
@@ -827,7 +827,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     period_barrier();
     // the rows this Q tile writes; then the next Q tile's rows of Q are requested along the drain steps,
     // and arrive during the epilogue
-    const int o_start = q_start, o_len = q_len, o_part = part_row;
+    const int o_start = q_start, o_part = part_row;
+    const int o_rows[2] = {head_ok[0] ? q_len : 0, head_ok[1] ? q_len : 0};
     int o_head[2], o_tok[2], o_slot[2];
     bool o_valid[2];
 #pragma unroll
@@ -908,7 +909,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
             const floatx4 piece = *(lds_f128)(static_cast<uintptr_t>(stag + row * 256 + (((ln % 16) ^ (row % 16)) * 16)));
             // (GATHER: the slot of that row is held by the lane that owns the row)
             const int slot = GATHER ? __builtin_amdgcn_ds_bpermute(4 * row, o_slot[rb]) : first_row + row_base + row;
-            if (head_ok[rb] && row_base + row < o_len) {
+            if (row_base + row < o_rows[rb]) {
               if constexpr (GATHER)
                 *reinterpret_cast<floatx4*>(p.partial + static_cast<int64_t>(o_head[rb]) * (kD + kPartialPad) + (ln % 16) * 4 +
                                             static_cast<int64_t>(slot) * p.n_q_heads * (kD + kPartialPad) + 64 * h2) = piece;
@@ -960,7 +961,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         for (int i = 0; i < 32 / kLoadRows; ++i) {
           const int row = kLoadRows * i + ln / kPieces16;
           const intx4 piece = *(lds_b128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((ln % kPieces16) ^ k_swizzle(row)) * 16)));
-          if (head_ok[rb] && row_base + row < o_len)
+          if (row_base + row < o_rows[rb])
             *reinterpret_cast<intx4*>(op + static_cast<int64_t>(o_start + row_base + row) * p.o.stride_tok) = piece;
         }
         if (p.lse && ehalf == 0 && o_valid[rb])

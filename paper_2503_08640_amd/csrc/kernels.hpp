@@ -52,7 +52,7 @@ struct AttnParams {
   const float* v_scale8;
   int32_t decode_reverse;     // decode: walk every run of keys from its last half tile to its first
   int32_t decode_waves;       // decode: waves per workgroup that share an item's tiles (1, 2 or 4)
-  int32_t column_heads;       // group-major decode: columns per query, n_q_heads / n_kv_heads rounded up to a power of two
+  int32_t head_ratio, column_heads_log2;  // group-major decode: n_q_heads / n_kv_heads; columns per query (the ratio rounded up to 2^log2)
   int32_t q_split;            // prefill: runs each Q tile's list is cut into (1 = no split, no merge pass)
   int32_t n_rows;             // prefill: rows of q / o
   // shapes
