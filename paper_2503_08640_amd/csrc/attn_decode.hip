@@ -569,8 +569,8 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
 // K(h+1), V(h+1)).  K fragments are read from the staged bytes directly and widened to bf16 in
 // registers; V is widened into one bf16 working tile (the transposed fragment reads need 16-bit
 // elements), same swizzle as the bf16 kernel.  24 KiB of LDS per wave keeps six waves per CU.
-// The per-head scales ride on the scores (keys) and on the partial accumulators (values), so no key or
-// value is ever multiplied.
+// The per-head scales ride on the scores (keys, see split_key_factor) and on the partial accumulators (values), so no key
+// or value is ever multiplied.
 constexpr int kD = 128;
 constexpr int kPairBytes = 2 * kHalfBytes;      // 16 KiB
 constexpr int kSlot8 = 4096;
@@ -588,6 +588,30 @@ __device__ inline bf16x8 widen8(unsigned w0, unsigned w1) {
   out.p2[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.f, false);
   out.p2[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.f, true);
   return out.v;
+}
+
+// Where the factor of a KV head's scores, scale * log2 e * k_scale, goes: on the scores, whose softmax takes a positive one
+// (its mask of the keys past a run's end is -inf, and the largest score must stay the largest), the sign and a factor of
+// zero (a head of zeros quantises to that) on the rows, both exact.  A rotated row is rounded anyway and takes it whole.
+struct KeyFactor {
+  float rows, scores;
+};
+template <bool ROPE>
+__device__ DBSA_INLINE KeyFactor split_key_factor(float c) {
+  if (ROPE) return {c, 1.f};
+  return {c > 0.f ? 1.f : c < 0.f ? -1.f : 0.f, c == 0.f ? 1.f : fabsf(c)};
+}
+// (The rows are requested without a look at the factor, which is itself on its way from memory: with the branch in front
+// of them a step of 16 queries takes 0.7 us longer.)
+template <bool ROPE>
+__device__ DBSA_INLINE void load_column_kv8(const DecodeColumn& c, const KeyFactor& factor, bf16x8 (&qf)[kD / 16]) {
+  load_column<kD, ROPE>(c, ROPE ? factor.rows : 1.f, qf);
+  if (!ROPE && factor.rows != 1.f) {
+#pragma unroll
+    for (int i = 0; i < kD / 16; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qf[i][e] = static_cast<__bf16>(static_cast<float>(qf[i][e]) * factor.rows);
+  }
 }
 
 template <bool ROPE>
@@ -662,10 +686,10 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
     issue_k(1);
     issue_v(1);
   }
-  const float c8 = p.scale_log2e * p.k_scale8[hk], prescale = ROPE ? c8 : 1.f, c2 = ROPE ? 1.f : c8;
+  const KeyFactor c8 = split_key_factor<ROPE>(p.scale_log2e * p.k_scale8[hk]);
   const float v_scale = p.v_scale8[hk];
   bf16x8 qf[kD / 16];
-  load_column<kD, ROPE>(col, prescale, qf);
+  load_column_kv8<ROPE>(col, c8, qf);
   floatx16 o[kD / 32];
 #pragma unroll
   for (int ob = 0; ob < kD / 32; ++ob)
@@ -699,7 +723,7 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (hh + 2 < n_half) issue_k(hh + 2);
     ProbFrag pf;
-    half_tile_softmax<kD>(s, len, half, c2, o, m_run, l_run, pf);
+    half_tile_softmax<kD>(s, len, half, c8.scores, o, m_run, l_run, pf);
     // V(hh) has landed once only K(hh+1), V(hh+1) and K(hh+2) are outstanding
     wait_groups((more ? 2 : 0) + (hh + 2 < n_half ? 1 : 0));
     // staged V bytes -> the swizzled bf16 working tile
@@ -815,10 +839,10 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
   const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp_log2, l32, half);
   issue_pair(0);
   if (1 < n_half) issue_pair(1);
-  const float c8 = p.scale_log2e * p.k_scale8[hk], prescale = ROPE ? c8 : 1.f, c2 = ROPE ? 1.f : c8;
+  const KeyFactor c8 = split_key_factor<ROPE>(p.scale_log2e * p.k_scale8[hk]);
   const float v_scale = p.v_scale8[hk];
   bf16x8 qf[kD / 16];
-  load_column<kD, ROPE>(col, prescale, qf);
+  load_column_kv8<ROPE>(col, c8, qf);
   floatx16 o[kD / 32];
 #pragma unroll
   for (int ob = 0; ob < kD / 32; ++ob)
@@ -839,7 +863,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
     if (!active) continue;
     int start, len;
     half_ref(hh, start, len);
-    half_tile_attend<kD>(work_k, work_v, len, k_base, v_base, half, c2, qf, o, m_run, l_run);
+    half_tile_attend<kD>(work_k, work_v, len, k_base, v_base, half, c8.scores, qf, o, m_run, l_run);
   }
 
   store_partial_state<kD>(p, col, half, o, m_run, l_run, v_scale);

@@ -57,6 +57,39 @@ def test_decode_over_an_fp8_pool_small(hq, hkv):
     _decode_case(pc, qc, range(3), what=f"Hq={hq} Hkv={hkv}")
 
 
+@pytest.mark.parametrize("n_queries", [4, 40])     # one wave per item, and four waves that share its keys
+def test_fp8_decode_takes_every_key_scale(n_queries):
+    """An element is byte * scale of its KV head, whatever the scale: a head of zeros quantises to scale 0, and a negative
+    scale is the positive one over negated bytes, bit for bit up to the rounding of the scaled query row.  The groups end
+    inside half tiles, so that keys past a run's end are masked under every scale."""
+    pc = synth.make_pool_case("kv8s", 6040, dtype="bf16", n_q_heads=16, n_kv_heads=4, head_dim=128, sink_len=70,
+                              pool_tokens=5000, demo_len_range=(30, 200), n_groups=5, k_channel_sigma=0.5)
+    sels = ([[3, 0], [], [4, 1, 2, 0, 3], [2]] + [[1, 4]] * 36)[:n_queries]
+    qc = synth.make_query_case("kv8sq", 6041, pc, n_queries=n_queries, q_len=([64, 37, 100, 1] + [9] * 36)[:n_queries],
+                               selections=sels, n_decode=2)
+    p = pc.pool
+    lens = np.diff(p.group_token_bounds())
+    assert p.sink_len % 32 and (lens % 32 != 0).any()
+    lay = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, cu_qlens=qc.cu_qlens, sel_ptr=qc.sel_ptr,
+                              sel_idx=qc.sel_idx, n_split=0, block_m=32, block_n=64)
+    k8, ks = quantise_per_head(to_dev(pc.k))
+    v8, vs = quantise_per_head(to_dev(pc.v))
+    # head 0: scale 0; head 1: negative over negated bytes; head 2: negative over the bytes as they are; head 3: ordinary
+    ks = ks * torch.tensor([0.0, -1.0, -1.0, 1.0], device="cuda")
+    k8[:, 1] = (-k8[:, 1].float()).to(torch.float8_e4m3fn)
+    kq, vq = dequantise(k8, ks), dequantise(v8, vs)
+    assert not kq[:, 0].any() and np.abs(kq[:, 2]).max() > 1
+    shp = qc.k_cache.shape
+    kc = to_dev(qc.k_cache.reshape(-1, shp[2], shp[3])).view(shp)
+    vc = to_dev(qc.v_cache.reshape(-1, shp[2], shp[3])).view(shp)
+    for s in range(2):
+        self_len = (np.diff(qc.cu_qlens) + s + 1).astype(np.int32)
+        od = B.dbsa_decode_attn_kv8(lay, to_dev(qc.dec_q[s]), kc, vc, torch.from_numpy(self_len).cuda(), k8, v8, ks, vs, pc.scale)
+        ref = orc.decode_attn(synth.as_f64(qc.dec_q[s]), synth.as_f64(qc.k_cache), synth.as_f64(qc.v_cache), self_len, kq, vq,
+                              p.sink_len, p.demo_offsets, p.group_demo_offsets, qc.sel_ptr, qc.sel_idx, pc.scale)
+        assert_close(to_f64(od), ref, f"{n_queries} queries, scales of zero and below, step {s}")
+
+
 def test_fp8_decode_rejects_what_it_does_not_implement():
     pc = synth.make_pool_case("kv8r", 6010, dtype="bf16", n_q_heads=6, n_kv_heads=2, head_dim=128, sink_len=8,
                               pool_tokens=600, demo_len_range=(30, 100), n_groups=2)      # 3 query heads per KV head
