@@ -556,10 +556,20 @@ __global__ __launch_bounds__(kMergeThreads) void prefill_cut_merge_kernel(AttnPa
       const float w_mine = lane < n ? __builtin_amdgcn_exp2f(mine[0] - m_star) : 0.f;
       l = fmaf(w_mine, mine[1], l);
       const float* state = part + z0 * stride + 4 * lane;
-      for (int z1 = 0; z1 < n; z1 += 8)  // (pieces past the last repeat it with weight zero)
+      int z1 = 0;
+      for (; z1 + 8 <= n; z1 += 8)
 #pragma unroll
-        for (int z = z1; z < z1 + 8; ++z)
-          acc += *reinterpret_cast<const floatx4*>(state + min(z, n - 1) * stride) * __shfl(w_mine, z, kLanes);
+        for (int z = z1; z < z1 + 8; ++z) acc += *reinterpret_cast<const floatx4*>(state + z * stride) * __shfl(w_mine, z, kLanes);
+      if (z1 < n) {  // the rest at once too: pieces past the last repeat it and are left out (an infinity times zero is none)
+        floatx4 x[7];
+#pragma unroll
+        for (int z = 0; z < 7; ++z) x[z] = *reinterpret_cast<const floatx4*>(state + min(z1 + z, n - 1) * stride);
+#pragma unroll
+        for (int z = 0; z < 7; ++z) {
+          const float w = __shfl(w_mine, z1 + z, kLanes);
+          if (z1 + z < n) acc += x[z] * w;
+        }
+      }
     }
 #pragma unroll
     for (int s = kLanes / 2; s > 0; s >>= 1) l += __shfl_xor(l, s, kLanes);

@@ -361,3 +361,20 @@ def test_query_prefill_with_lists_cut_to_measure(hq, hkv, block_m, q_len, rope):
         want = oracle_query_lse(pc, qc)
         for lse in lses:
             assert_close(to_f64(lse), want, f"lse bm={block_m}")
+
+
+@pytest.mark.parametrize("pool,groups", [(2500, 2), (9000, 3)])
+def test_an_infinite_value_survives_the_merge_of_a_cut_list(pool, groups):
+    """The first token of the question's own, which every row sees, has an infinite value in one channel: the rows have it
+    too, also where the list was cut into a number of pieces the merge does not read evenly (the token is in the last one)."""
+    pc = small_pool_case("infpool", 3500 + pool, hq=8, hkv=2, pool_tokens=pool, groups=groups, lens=(32, 200), sigma=0.5)
+    qc = synth.make_query_case("infq", 3501, pc, n_queries=1, q_len=[64], selections=[list(range(groups))])
+    lay, kp, vp = _query_setup(pc, qc, 64, 0)
+    qs, ks, vs = to_dev(qc.q), to_dev(qc.k), to_dev(qc.v)
+    vs[0, 1, 5] = float("inf")          # KV head 1: query heads 4 .. 7
+    ref = _oracle_query(pc, qc)
+    for what, ws in (("whole", False), ("cut", None)):
+        o = to_f64(B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, workspace=ws))
+        assert np.all(o[:, 4:, 5] == np.inf), f"{what}: {o[0, 4:, 5]}"
+        o[:, 4:, 5] = ref[:, 4:, 5]
+        assert_close(o, ref, f"{what} list beside an infinite channel")
