@@ -209,15 +209,13 @@ hipError_t upload_lists(dbsa_layout* L, hipStream_t stream) {
   put(o_mqs, L->mx_qshift.data(), b_mqs);
   put(o_msp, L->mx_slot_ptr.data(), b_msp);
   L->dev.cut_room = static_cast<unsigned char*>(blk.dev) + o_cut;
-  size_t lists_end = o_cut;
-  if (L->cut_worth) lists_end += place_cut_lists(L, h + o_cut);
   // the staging twin stays with the block, so nothing has to wait for the copy here; calls on
   // other streams are ordered behind it through the event
   hipEvent_t uploaded = nullptr;
   e = hipEventCreateWithFlags(&uploaded, hipEventDisableTiming);
   if (e == hipSuccess) {
-    // (the room behind lists_end is filled by the first calls that use another schedule)
-    e = hipMemcpyAsync(blk.dev, blk.pinned, lists_end, hipMemcpyHostToDevice, stream);
+    // (the room behind o_cut is filled by the first calls that use a schedule)
+    e = hipMemcpyAsync(blk.dev, blk.pinned, o_cut, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipEventRecord(uploaded, stream);
     if (e != hipSuccess) {
       (void)hipStreamSynchronize(stream);  // the copy may have been queued: the block must not be reused under it
@@ -257,10 +255,6 @@ hipError_t upload_lists(dbsa_layout* L, hipStream_t stream) {
   L->dev.sched_ptr = reinterpret_cast<int32_t*>(b + o_sptr);
   L->dev.mx_sched_rec = reinterpret_cast<int32_t*>(b + o_mrec);
   L->dev.mx_sched_ptr = reinterpret_cast<int32_t*>(b + o_mptr);
-  if (L->cut_worth) {  // the upload's own event orders other streams behind these lists
-    L->dev.cut_stream = stream;
-    L->cut_on_device = true;
-  }
   return hipSuccess;
 }
 
@@ -424,13 +418,7 @@ bool ensure_matrix_schedule(const dbsa_layout* L, int32_t n_classes, bool planne
 bool ensure_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd, hipStream_t stream) {
   if (n_classes < 1 || n_classes > kMaxSchedClasses || !L->dev.cut_room) return false;
   std::lock_guard<std::mutex> lock(L->sched_mutex);
-  if (L->cut_classes != 0 && L->cut_classes != n_classes) {
-    if (!L->cut_guessed) return false;
-    // the schedule that came with the lists is for another model and nothing has read it: a new one takes its place
-    // (its copy is ordered behind the lists', and overwrites whatever that one picks up of it)
-    L->cut_classes = 0;
-    L->cut_on_device = L->cut_worth = false;
-  }
+  if (L->cut_classes != 0 && L->cut_classes != n_classes) return false;
   if (!L->cut_on_device) {
     if (L->cut_classes != 0 && !L->cut_worth) return false;
     // (under capture nothing can be copied; the call then takes its other launch form)
@@ -447,7 +435,6 @@ bool ensure_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd, 
         return false;
       }
     }
-    L->cut_guessed = false;
     if (!L->cut_worth) return false;
     const size_t first = static_cast<size_t>(L->dev.cut_room - static_cast<unsigned char*>(L->dev.base));
     unsigned char* const staging = static_cast<unsigned char*>(L->dev.staging) + first;
@@ -463,10 +450,9 @@ bool ensure_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd, 
     L->dev.cut_uploaded = done;
     L->dev.cut_stream = stream;
     L->cut_on_device = true;
-  } else if (stream != L->dev.cut_stream && L->dev.cut_uploaded) {
+  } else if (stream != L->dev.cut_stream) {
     if (hipStreamWaitEvent(stream, static_cast<hipEvent_t>(L->dev.cut_uploaded), 0) != hipSuccess) return false;
   }
-  L->cut_guessed = false;
   return true;
 }
 
@@ -784,20 +770,6 @@ int build_layout(const dbsa_pool_desc* pool, const dbsa_select_desc* sel, int32_
     return rc;
   }
   if (!(flags & DBSA_LAYOUT_HOST_ONLY)) {
-    // The schedule of the query prefill for 8 KV heads and workgroups of four query heads travels with the lists; for
-    // other models the first call makes its own (host work and a copy of some 20 us).
-    if (L->query_stage && (block_m == 32 || block_m == 64)) {
-      const int32_t classes = static_cast<int32_t>(std::min<int64_t>(prefill_places(L, block_m / 8, 128) / 8, kMaxSchedClasses));
-      try {
-        if (classes >= 1 && L->n_qtiles() < kCutTiles * classes) {
-          dbsa_cut_schedule(L, classes, cut_crowding(block_m / 8));
-          L->cut_guessed = true;
-        }
-      } catch (...) {
-        delete L;
-        return DBSA_ERR_INVALID_ARG;
-      }
-    }
     const hipError_t e = upload_lists(L, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) {
       delete L;

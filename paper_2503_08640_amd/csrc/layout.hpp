@@ -146,7 +146,6 @@ struct dbsa_layout {
   mutable std::vector<int32_t> cut_ptr, cut_rec, cut_part, cut_tab;
   mutable int64_t cut_rows = 0;
   mutable bool cut_worth = false, cut_on_device = false;
-  mutable bool cut_guessed = false;  // made with the lists for a likely model, not used by a call yet
   // the same for the records of mx_rec (a second, independent schedule)
   mutable int32_t mx_classes = 0;
   mutable std::vector<int32_t> mx_sched_ptr, mx_sched_rec;
