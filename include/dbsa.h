@@ -230,6 +230,28 @@ int dbsa_layout_export_schedule(const dbsa_layout* layout, int32_t n_classes, co
                                 const int32_t** records);
 
 /*
+ * Schedule of a query prefill with few Q tiles (plumbing; query-stage layouts): the concatenated lists of the tiles, in
+ * launch order, are dealt to n_workers workers per block of query heads (fewer when a worker's share would hold under
+ * 6 entries; the others get no records), each taking entries until its cost (entries + 5 per record) reaches a share, and
+ * cut there; no piece of a cut list is shorter than 5 entries.  The share is the smallest that leaves the last worker no
+ * more than the others.
+ *   worker_ptr : int32 [n_workers + 1]: worker c takes records worker_ptr[c] .. worker_ptr[c+1]-1.
+ *   records    : int32 [n_records][4] = (q_start, q_len, first list entry, list entries).
+ *   part_rows  : int32 [n_records]: first row of the record's partial states in the workspace, -1 for a whole list.
+ *   cut_tiles  : int32 [n_cut_tiles][4] = (q_start, q_len, first partial row, pieces), the pieces of a tile q_len rows
+ *                apart.
+ *   worth      : 1 if a launch whose workgroups take row_blocks (2, 4 or 8) blocks of 32 rows runs the schedule, 0 if it
+ *                takes whole lists or runs of one length.
+ * A layout keeps ONE such schedule, fixed by the first call that needs one (this call, or dbsa_query_attn with a
+ * workspace): a model with another number of workers on the same layout then runs whole lists or runs of one length.
+ * INVALID_ARG for another n_workers later, for n_workers outside [1, 512] or other row_blocks.  The arrays belong to the
+ * layout; any output pointer may be NULL.
+ */
+int dbsa_layout_export_cut_schedule(const dbsa_layout* layout, int32_t n_workers, int32_t row_blocks, int32_t* worth,
+                                    const int32_t** worker_ptr, const int32_t** records, const int32_t** part_rows,
+                                    const int32_t** cut_tiles, int32_t* n_cut_tiles);
+
+/*
  * The records of a decode step that runs as a contraction (plumbing; query-stage layouts): record i =
  * four int32 (first reference, references, first tile, tiles): at most 64 queries over the tiles
  * seg_ent[first tile .. + tiles) of one run of one segment.  row_fill = share of the 64 rows of a

@@ -44,7 +44,7 @@ EXPORTED_SYMBOLS = (
     "dbsa_query_attn", "dbsa_decode_attn", "dbsa_rope_table", "dbsa_rope_apply", "dbsa_query_attn_rope",
     "dbsa_decode_attn_rope", "dbsa_decode_attn_kv8", "dbsa_decode_attn_kv8_rope", "dbsa_decode_attn_static", "dbsa_pooled_list_blocks", "dbsa_layout_export_matrix_records",
     "dbsa_layout_export_matrix_plan",
-    "dbsa_layout_export_schedule",
+    "dbsa_layout_export_schedule", "dbsa_layout_export_cut_schedule",
 )
 DBSA_STATIC_SCRATCH_BYTES = 32 << 20
 
@@ -108,6 +108,9 @@ def lib() -> C.CDLL:
     L.dbsa_layout_export_schedule.restype = C.c_int
     L.dbsa_layout_export_schedule.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.POINTER(C.c_int32)),
                                               C.POINTER(C.POINTER(C.c_int32))]
+    L.dbsa_layout_export_cut_schedule.restype = C.c_int
+    L.dbsa_layout_export_cut_schedule.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(C.c_int32)] + \
+        [C.POINTER(C.POINTER(C.c_int32))] * 4 + [C.POINTER(C.c_int32)]
     L.dbsa_layout_export_matrix_records.restype = C.c_int
     L.dbsa_layout_export_matrix_records.argtypes = [C.c_void_p, C.POINTER(C.POINTER(C.c_int32)), C.POINTER(C.c_int64),
                                                     C.POINTER(C.c_float)]
@@ -281,6 +284,20 @@ class Layout:
         n = int(ptr[-1])
         rec = np.ctypeslib.as_array(rc, shape=(n, 4)).copy() if n else np.zeros((0, 4), np.int32)
         return ptr, rec
+
+    def export_cut_schedule(self, n_workers: int, row_blocks: int):
+        """-> (worth, worker_ptr [n_workers+1], records [n, 4], part_rows [n], cut_tiles [m, 4]) int32 copies."""
+        worth, n_cut = C.c_int32(), C.c_int32()
+        wp, rc, pr, ct = (C.POINTER(C.c_int32)() for _ in range(4))
+        _check(lib().dbsa_layout_export_cut_schedule(self.handle, int(n_workers), int(row_blocks), C.byref(worth), C.byref(wp),
+                                                     C.byref(rc), C.byref(pr), C.byref(ct), C.byref(n_cut)),
+               "dbsa_layout_export_cut_schedule")
+
+        def arr(p, *shape):
+            return np.ctypeslib.as_array(p, shape=shape).copy() if shape[0] else np.zeros(shape, np.int32)
+        ptr = arr(wp, n_workers + 1)
+        n = int(ptr[-1])
+        return bool(worth.value), ptr, arr(rc, n, 4), arr(pr, n), arr(ct, n_cut.value, 4)
 
     def workspace_bytes(self, n_q_heads: int, head_dim: int) -> int:
         return int(lib().dbsa_workspace_bytes(self.handle, n_q_heads, head_dim))

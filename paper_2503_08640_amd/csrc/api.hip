@@ -412,30 +412,33 @@ bool ensure_matrix_schedule(const dbsa_layout* L, int32_t n_classes, bool planne
   });
 }
 
+// The cut lists of the layout for n_classes workers, made on first use (L->sched_mutex held by the caller).  False if
+// it holds those for another number, or if they cannot be made.
+bool plan_cut_schedule(const dbsa_layout* L, int32_t n_classes) {
+  if (L->cut_classes == 0) {
+    try {
+      dbsa_cut_schedule(L, n_classes);
+    } catch (...) {
+      return false;
+    }
+  }
+  return L->cut_classes == n_classes;
+}
+
 // The schedule of a query prefill with lists cut to measure for n_classes workers per head block, on the device and
 // ordered before `stream`'s next work.  Like ensure_slot's schedules a layout keeps ONE: false if it holds one for
 // another number of workers, if the launch gains nothing from it, or if it would have to be copied under capture.
-bool ensure_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd, hipStream_t stream) {
+bool ensure_cut_schedule(const dbsa_layout* L, int32_t n_classes, int row_blocks, hipStream_t stream) {
   if (n_classes < 1 || n_classes > kMaxSchedClasses || !L->dev.cut_room) return false;
   std::lock_guard<std::mutex> lock(L->sched_mutex);
-  if (L->cut_classes != 0 && L->cut_classes != n_classes) return false;
+  if (!plan_cut_schedule(L, n_classes) || !dbsa_cut_worth(L, row_blocks)) return false;
   if (!L->cut_on_device) {
-    if (L->cut_classes != 0 && !L->cut_worth) return false;
     // (under capture nothing can be copied; the call then takes its other launch form)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
       (void)hipGetLastError();
       return false;
     }
-    if (L->cut_classes == 0) {
-      try {
-        dbsa_cut_schedule(L, n_classes, crowd);
-      } catch (...) {
-        L->cut_classes = 0;
-        return false;
-      }
-    }
-    if (!L->cut_worth) return false;
     const size_t first = static_cast<size_t>(L->dev.cut_room - static_cast<unsigned char*>(L->dev.base));
     unsigned char* const staging = static_cast<unsigned char*>(L->dev.staging) + first;
     const size_t bytes = place_cut_lists(L, staging);
@@ -522,10 +525,6 @@ int64_t prefill_places(const dbsa_layout* L, int row_blocks, int head_dim) {
   if (row_blocks == 8) return workgroup_slots(L) / 2;
   return workgroup_slots(L) * (head_dim == 64 && row_blocks == 2 ? 2 : 1);
 }
-
-// what a list entry costs with all workers busy over what it costs with few (dbsa_cut_schedule)
-// (a K/V pair serves 32 rows per row block; 256 rows keep the matrix pipes busy at the rate the pairs arrive)
-double cut_crowding(int row_blocks) { return row_blocks == 8 ? 1.0 : row_blocks == 4 ? 1.5 : 3.0; }
 
 // Runs per list of a launch of `wgs` workgroups (one run each) on `places`: the number that makes rounds * length
 // shortest.  A run costs kPieceCost entries to start and finish; every further run of a row is one more partial state,
@@ -699,7 +698,7 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
       const int32_t classes = static_cast<int32_t>(std::min<int64_t>(places / head_blocks, kMaxSchedClasses));
       p.sched_classes = classes;
       if (want_query_stage && L->n_qtiles() < kCutTiles * classes && room > 0 &&
-          ensure_cut_schedule(L, classes, cut_crowding(row_blocks), s) &&
+          ensure_cut_schedule(L, classes, row_blocks, s) &&
           static_cast<size_t>(L->cut_rows) * hq <= room) {
         p.sched_rec = L->dev.cut_rec;
         p.sched_ptr = L->dev.cut_ptr;
@@ -863,6 +862,22 @@ int dbsa_layout_export_schedule(const dbsa_layout* L, int32_t n_classes, const i
   }
   if (class_ptr) *class_ptr = L->sched_ptr.data();
   if (records) *records = L->sched_rec.data();
+  return DBSA_OK;
+}
+
+int dbsa_layout_export_cut_schedule(const dbsa_layout* L, int32_t n_workers, int32_t row_blocks, int32_t* worth,
+                                    const int32_t** worker_ptr, const int32_t** records, const int32_t** part_rows,
+                                    const int32_t** cut_tiles, int32_t* n_cut_tiles) {
+  if (!L || !L->query_stage || n_workers < 1 || n_workers > kMaxSchedClasses) return DBSA_ERR_INVALID_ARG;
+  if (row_blocks != 2 && row_blocks != 4 && row_blocks != 8) return DBSA_ERR_INVALID_ARG;
+  std::lock_guard<std::mutex> lock(L->sched_mutex);
+  if (!plan_cut_schedule(L, n_workers)) return DBSA_ERR_INVALID_ARG;
+  if (worth) *worth = dbsa_cut_worth(L, row_blocks) ? 1 : 0;
+  if (worker_ptr) *worker_ptr = L->cut_ptr.data();
+  if (records) *records = L->cut_rec.data();
+  if (part_rows) *part_rows = L->cut_part.data();
+  if (cut_tiles) *cut_tiles = L->cut_tab.data();
+  if (n_cut_tiles) *n_cut_tiles = static_cast<int32_t>(L->cut_tab.size() / 4);
   return DBSA_OK;
 }
 

@@ -502,6 +502,7 @@ int dbsa_build_host_lists(const dbsa_pool_desc* pool, const dbsa_select_desc* se
   L->shortest_list = INT64_MAX;
   for (int64_t t = 0; t < L->n_qtiles(); ++t) {
     L->shortest_list = std::min(L->shortest_list, L->list_ptr[t + 1] - L->list_ptr[t]);
+    L->longest_list = std::max(L->longest_list, L->list_ptr[t + 1] - L->list_ptr[t]);
     L->largest_tile = std::max(L->largest_tile, L->qtile_tab[4 * t + 1]);
     if (!L->list_shift.empty())
       for (int64_t e = L->list_ptr[t]; e < L->list_ptr[t + 1]; ++e)
@@ -592,7 +593,7 @@ int64_t dbsa_cut_workers(const dbsa_layout* L, int64_t n_classes) {
   return std::max<int64_t>(1, std::min<int64_t>(n_classes, L->n_ent() / kMinShare));
 }
 
-void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd) {
+void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes) {
   const int64_t nt = L->n_qtiles();
   auto entries = [&](int32_t t) { return L->list_ptr[t + 1] - L->list_ptr[t]; };
   const int64_t total = L->n_ent(), workers = dbsa_cut_workers(L, n_classes);
@@ -660,35 +661,43 @@ void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd) {
     const int64_t mid = (lo + hi) / 2;
     (deal(mid, false) <= mid ? hi : lo) = mid;
   }
-  deal(hi, false);
-  // Against whole Q tiles dealt to the same workers, and against runs of one length, one per workgroup: where these
-  // come out even (16 Q tiles over 32 workers in two runs each: 412 us against 421) every worker has one record to
-  // start and finish, and workers walk in step.  The merge pass costs about as much as two entries.  `crowd` is what
-  // an entry costs with every place taken over what it costs with few: two small workgroups per compute unit fetch a
-  // K/V pair per 128 rows each and are then bound by that traffic (512 of them move 7.4 TB/s; 50 questions of 20
-  // tokens on 400 of 512 places: whole lists 771 us, all places with cut lists 803).
-  auto per_entry = [&](int64_t busy) { return std::max(1.0, crowd * std::min(1.0, static_cast<double>(busy) / static_cast<double>(n_classes))); };
-  int64_t longest_list = 0;
-  for (int64_t t = 0; t < nt; ++t) longest_list = std::max(longest_list, entries(static_cast<int32_t>(t)));
-  const double list = static_cast<double>(longest_list), cost = static_cast<double>(kPieceCost);
-  const double cut = 1.03 * static_cast<double>(longest) * per_entry(workers) + 2.0;
-  double other = 1e30;
+  deal(hi, true);
+  L->cut_longest = longest;
+  // the same workers with whole Q tiles, for dbsa_cut_worth
+  L->cut_whole = 0;
   if (nt >= 2 * n_classes) {
     std::vector<int32_t> ptr, rec;
     dbsa_balance_schedule(L, n_classes, &ptr, &rec);
-    int64_t whole = 0;
     for (int32_t c = 0; c < n_classes; ++c) {
       int64_t load = 0;
       for (int32_t k = ptr[static_cast<size_t>(c)]; k < ptr[static_cast<size_t>(c) + 1]; ++k) load += rec[4 * static_cast<size_t>(k) + 3] + kTileCost;
-      whole = std::max(whole, load);
+      L->cut_whole = std::max(L->cut_whole, load);
     }
-    other = static_cast<double>(whole) * per_entry(nt);
+  }
+  L->cut_classes = n_classes;
+}
+
+// Against whole Q tiles dealt to the same workers, and against runs of one length, one per workgroup: where these
+// come out even (16 Q tiles over 32 workers in two runs each: 412 us against 421) every worker has one record to
+// start and finish, and workers walk in step.  The merge pass costs about as much as two entries.  An entry costs
+// `crowd` times as much with every place taken as with few: a K/V pair serves 32 rows per row block, and 256 rows keep
+// the matrix pipes busy at the rate the pairs arrive.  Two small workgroups per compute unit fetch a pair per 128 rows
+// each and are bound by that traffic (512 of them move 7.4 TB/s; 50 questions of 20 tokens on 400 of 512 places: whole
+// lists 771 us, all places with cut lists 803).
+bool dbsa_cut_worth(const dbsa_layout* L, int row_blocks) {
+  const int64_t nt = L->n_qtiles();
+  const double crowd = row_blocks == 8 ? 1.0 : row_blocks == 4 ? 1.5 : 3.0;
+  const double classes = static_cast<double>(L->cut_classes), cost = static_cast<double>(kPieceCost);
+  auto per_entry = [&](int64_t busy) { return std::max(1.0, crowd * std::min(1.0, static_cast<double>(busy) / classes)); };
+  const double cut = 1.03 * static_cast<double>(L->cut_longest) * per_entry(dbsa_cut_workers(L, L->cut_classes)) + 2.0;
+  double other = 1e30;
+  if (nt >= 2 * L->cut_classes) {
+    other = static_cast<double>(L->cut_whole) * per_entry(nt);
   } else {
+    const double list = static_cast<double>(L->longest_list);
     for (int64_t runs = 1; runs <= std::max<int64_t>(1, std::min(kMaxQuerySplit, L->shortest_list / kMinRun)); ++runs)
-      other = std::min(other, static_cast<double>((nt * runs + n_classes - 1) / n_classes) *
+      other = std::min(other, static_cast<double>((nt * runs + L->cut_classes - 1) / L->cut_classes) *
                                       (list / static_cast<double>(runs) * per_entry(nt * runs) + cost) + (runs > 1 ? 2.0 : 0.0));
   }
-  L->cut_worth = cut < other;
-  if (L->cut_worth) deal(hi, true);
-  L->cut_classes = n_classes;
+  return cut < other;
 }

@@ -123,6 +123,7 @@ struct dbsa_layout {
   // figures the attention calls need on every launch, taken once at build time
   int32_t gm_max_queries = 1;       // most queries any schedule item serves
   int64_t shortest_list = 0;        // fewest entries any Q tile lists
+  int64_t longest_list = 0;         // most
   int32_t largest_tile = 0;         // most rows any Q tile has (at most block_m)
   int64_t max_rotation_id = -1;     // largest id a prefill row looks up: max(list_shift[e] + rows of the tile) - 1
   int64_t max_decode_shift = 0;     // largest gm_qshift: a decode row of self_len n looks up id shift + n - 1
@@ -141,11 +142,12 @@ struct dbsa_layout {
   // Schedule of a query prefill whose lists are cut to measure for cut_classes workers (dbsa_cut_schedule): class c
   // walks records cut_ptr[c] .. cut_ptr[c+1]-1 of cut_rec (words as in sched_rec, a record being a run of a Q
   // tile's list); cut_part: first partial row of a record, -1 = the record is a whole Q tile; cut_tab: the cut Q
-  // tiles (q_start, q_len, first partial row, pieces).  cut_worth: the launch gains from it.
+  // tiles (q_start, q_len, first partial row, pieces).  cut_longest: cost of the busiest worker; cut_whole: that of the
+  // same workers with whole Q tiles (0: too few tiles for that).
   mutable int32_t cut_classes = 0;
   mutable std::vector<int32_t> cut_ptr, cut_rec, cut_part, cut_tab;
-  mutable int64_t cut_rows = 0;
-  mutable bool cut_worth = false, cut_on_device = false;
+  mutable int64_t cut_rows = 0, cut_longest = 0, cut_whole = 0;
+  mutable bool cut_on_device = false;
   // the same for the records of mx_rec (a second, independent schedule)
   mutable int32_t mx_classes = 0;
   mutable std::vector<int32_t> mx_sched_ptr, mx_sched_rec;
@@ -190,11 +192,13 @@ void dbsa_balance_records(const std::vector<int32_t>& rec_in, int32_t n_classes,
 // Cuts the lists of the Q tiles to measure for n_classes workers: the tiles are walked in launch order and dealt to
 // the workers one after the other, each taking list entries until its cost (entries + kPieceCost per record) reaches
 // the share; what does not fit is cut there, no piece is shorter than kMinPiece entries.  The share is the smallest
-// that leaves the last worker no more than the others.  Fills cut_classes and cut_worth of L and, if it is worth it,
-// the cut_* lists.  crowd: what an entry costs with all workers busy over what it costs with few.
+// that leaves the last worker no more than the others.  Fills the cut_* members of L.
 constexpr int64_t kMinPiece = 5;
 int64_t dbsa_cut_workers(const dbsa_layout* L, int64_t n_classes);  // workers that get records (the first ones)
-void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes, double crowd);
+void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes);
+// Whether a launch of workgroups of `row_blocks` blocks of 32 rows gains from the schedule L holds.  Not part of it: models
+// with the same number of workers may differ in this.
+bool dbsa_cut_worth(const dbsa_layout* L, int row_blocks);
 
 // Pure host integer work; returns a DBSA_* code and fills `L` on success.
 // first_group < 0: every segment; >= 0 (pre-encode only): Q tiles of groups first_group.. alone

@@ -580,6 +580,105 @@ def test_persistent_schedule_deals_every_tile_once_and_balances(n_classes):
     assert B.lib().dbsa_layout_export_schedule(None, 4, None, None) == B.DBSA_ERR_INVALID_ARG
 
 
+def _random_query_layout(rng, block_m):
+    """A pool of 1 .. 20 groups, 1 .. 30 questions with any number of them selected."""
+    sink, groups, nq = int(rng.integers(0, 200)), int(rng.integers(1, 21)), int(rng.integers(1, 31))
+    demos, starts = [sink], [0]
+    for _ in range(groups):
+        n = int(rng.integers(1, 5))
+        demos += list(demos[-1] + np.cumsum(rng.integers(1, 900, n)))
+        starts.append(starts[-1] + n)
+    cu = np.concatenate([[0], np.cumsum(rng.integers(1, rng.choice([40, 100, 700]), nq))])
+    sels = [rng.permutation(groups)[:int(rng.integers(0, groups + 1))] for _ in range(nq)]
+    return B.dbsa_layout_build(sink, demos, starts, cu_qlens=cu, sel_ptr=np.concatenate([[0], np.cumsum([len(x) for x in sels])]),
+                               sel_idx=np.concatenate(sels), block_m=block_m, block_n=64, host_only=True)
+
+
+def _cut_is_worth_it(tab, ptr, worker_ptr, rec, n_workers, row_blocks):
+    """Cost of the busiest worker against whole Q tiles on the same workers, or runs of one length, one per workgroup: an
+    entry costs 1, with all workers busy 1.5 (four row blocks) or 3 (two); a record 5 more, a whole tile among several 3; a
+    merge 2; cut lists must win by 3 %."""
+    entries = np.diff(ptr)
+    crowd = {8: 1.0, 4: 1.5, 2: 3.0}[row_blocks]
+    per = lambda busy: max(1.0, crowd * min(1.0, busy / n_workers))
+    load = max(rec[a:b, 3].sum() + 5 * (b - a) for a, b in zip(worker_ptr[:-1], worker_ptr[1:]))
+    cut = 1.03 * load * per(max(1, min(n_workers, int(ptr[-1]) // 6))) + 2
+    nt = len(entries)
+    if nt >= 2 * n_workers:
+        return None, cut                       # needs the schedule of whole tiles
+    top = max(1, min(16, int(entries.min()) // 8))
+    return cut < min(-(-nt * r // n_workers) * (entries.max() / r * per(nt * r) + 5) + (2 if r > 1 else 0)
+                     for r in range(1, top + 1)), cut
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_lists_cut_to_measure_cover_every_entry_once_and_balance(seed):
+    rng = np.random.default_rng(4100 + seed)
+    seen = set()
+    for _ in range(25):
+        n_workers = int(rng.choice([1, 2, 7, 16, 32, 64, 512]))
+        lay = _random_query_layout(rng, int(rng.choice([32, 64, 128, 256])))
+        tab, ptr, _ = lay.export()
+        order = lay.export_order()
+        worth, wptr, rec, part, cut = lay.export_cut_schedule(n_workers, 8)
+        nt, total = len(tab), int(ptr[-1])
+        workers = max(1, min(n_workers, total // 6))
+        assert wptr[0] == 0 and wptr[-1] == len(rec) == len(part) and np.all(np.diff(wptr) >= 0)
+        assert wptr[workers] == len(rec) and len(rec) <= nt + workers - 1
+        # the records, one worker after the other, are the lists in launch order, each in consecutive pieces
+        k, rows, cuts = 0, 0, []
+        for t in order:
+            pos, first = int(ptr[t]), k
+            while pos < ptr[t + 1]:
+                assert list(rec[k, :3]) == [tab[t, 0], tab[t, 1], pos] and rec[k, 3] >= 1
+                pos += int(rec[k, 3])
+                k += 1
+            assert pos == ptr[t + 1]
+            if k - first == 1:
+                assert part[first] == -1
+            else:
+                assert rec[first:k, 3].min() >= 5
+                assert np.array_equal(part[first:k], rows + tab[t, 1] * np.arange(k - first))
+                cuts.append([tab[t, 0], tab[t, 1], rows, k - first])
+                rows += int(tab[t, 1]) * (k - first)
+        assert k == len(rec) and cut.tolist() == cuts
+        # every cut adds a record, a tile's pieces are one more than its cuts: what the workspace is sized by
+        assert sum(c[3] for c in cuts) <= min(2 * (workers - 1), workers - 1 + nt)
+        load = np.array([rec[a:b, 3].sum() + 5 * (b - a) for a, b in zip(wptr[:-1], wptr[1:])])
+        assert load.max() <= (total + 5 * (nt + workers)) // workers + 16
+        want, cost = _cut_is_worth_it(tab, ptr, wptr, rec, n_workers, 8)
+        if want is None:
+            cp, whole = lay.export_schedule(n_workers)
+            want = cost < max(whole[a:b, 3].sum() + 3 * (b - a) for a, b in zip(cp[:-1], cp[1:]))
+        assert worth == want
+        seen.add(worth)
+        # a layout keeps one schedule
+        args = [None] * 6
+        assert B.lib().dbsa_layout_export_cut_schedule(lay.handle, n_workers % 512 + 1, 8, *args) == B.DBSA_ERR_INVALID_ARG
+        assert B.lib().dbsa_layout_export_cut_schedule(lay.handle, n_workers, 3, *args) == B.DBSA_ERR_INVALID_ARG
+    assert seen == {True, False}
+
+
+def test_models_with_as_many_workers_decide_for_themselves_whether_to_cut():
+    """64 workers are those of workgroups of four row blocks over 8 head blocks and of eight over 4: the same lists, but a
+    launch of the small workgroups is bound by its traffic earlier.  Neither's answer depends on who asked first."""
+    differ = 0
+    for seed in range(400):
+        answers = []
+        for first, second in ((4, 8), (8, 4)):
+            lay = _random_query_layout(np.random.default_rng(5200 + seed), 32)
+            tab, ptr, _ = lay.export()
+            if len(tab) >= 128:
+                break
+            got = {rb: lay.export_cut_schedule(64, rb) for rb in (first, second)}
+            assert all(np.array_equal(a, b) for a, b in zip(got[4][1:], got[8][1:]))
+            for rb in (4, 8):
+                assert got[rb][0] == _cut_is_worth_it(tab, ptr, got[rb][1], got[rb][2], 64, rb)[0]
+            answers.append((got[4][0], got[8][0]))
+        differ += len(answers) == 2 and answers[0][0] != answers[0][1]
+    assert differ >= 3, "no layout on which the two decide differently"
+
+
 def _check_plan_covers_segments(rec, refs, slots, seg_ptr, sel_ptr, sel_idx, n_queries):
     assert rec[0, 0] == 0 and np.array_equal(rec[1:, 0], (rec[:, 0] + rec[:, 1])[:-1]) and rec[-1, 0] + rec[-1, 1] == len(refs)
     seen = {}                      # (segment, query) -> tiles covered so far
