@@ -330,6 +330,27 @@ int device_compute_units() {
   return cus[device];
 }
 
+// Orders `stream` behind a schedule's copy, whose event is `uploaded`.  Once the copy has been seen to have landed there
+// is nothing left to wait for, on any stream, and calls ask no more; until then only a call on another stream than the
+// copy's waits.  A stream under capture cannot wait for work outside the capture, and where the graph will run is not
+// known: false there while the copy is under way (the caller then takes its other launch form).  (The event is asked
+// in relaxed capture mode: asking changes nothing a capture could hold, but the stricter modes refuse it.)
+bool order_behind_copy(bool* landed, void* uploaded, void* copy_stream, hipStream_t stream) {
+  if (*landed) return true;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  *landed = hipEventQuery(static_cast<hipEvent_t>(uploaded)) == hipSuccess;
+  if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (*landed) return true;
+  (void)hipGetLastError();  // "not ready" is an answer
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+      (stream == copy_stream || hipStreamWaitEvent(stream, static_cast<hipEvent_t>(uploaded), 0) == hipSuccess))
+    return true;
+  (void)hipGetLastError();
+  return false;
+}
+
 // One persistent-launch schedule of a layout: its host copy, its room in the device block, the
 // event behind its copy.
 struct ScheduleSlot {
@@ -341,6 +362,7 @@ struct ScheduleSlot {
   int32_t* dev_ptr;
   void** uploaded;
   void** upload_stream;
+  bool* landed;
 };
 
 // The schedule in `slot` for n_classes workers per head block, on the device and ordered before
@@ -376,21 +398,21 @@ bool ensure_slot(const dbsa_layout* L, const ScheduleSlot& slot, int32_t n_class
         hipEventRecord(done, stream) != hipSuccess) {
       (void)hipStreamSynchronize(stream);
       (void)hipEventDestroy(done);
+      (void)hipGetLastError();
       return false;
     }
     *slot.uploaded = done;
     *slot.upload_stream = stream;
     *slot.on_device = true;
-  } else if (stream != *slot.upload_stream) {
-    if (hipStreamWaitEvent(stream, static_cast<hipEvent_t>(*slot.uploaded), 0) != hipSuccess) return false;
+    return true;
   }
-  return true;
+  return order_behind_copy(slot.landed, *slot.uploaded, *slot.upload_stream, stream);
 }
 
 // the schedule of the prefill-shaped launches over the layout's Q tiles
 bool ensure_schedule(const dbsa_layout* L, int32_t n_classes, hipStream_t stream) {
   const ScheduleSlot slot{&L->sched_classes, &L->sched_ptr, &L->sched_rec, &L->sched_on_device, L->dev.sched_rec,
-                          L->dev.sched_ptr, &L->dev.sched_uploaded, &L->dev.sched_stream};
+                          L->dev.sched_ptr, &L->dev.sched_uploaded, &L->dev.sched_stream, &L->dev.sched_landed};
   return ensure_slot(L, slot, n_classes, stream, [&](int32_t n, std::vector<int32_t>* ptr, std::vector<int32_t>* rec) {
     dbsa_balance_schedule(L, n, ptr, rec);
   });
@@ -401,7 +423,7 @@ bool ensure_schedule(const dbsa_layout* L, int32_t n_classes, hipStream_t stream
 bool ensure_matrix_schedule(const dbsa_layout* L, int32_t n_classes, bool planned, hipStream_t stream) {
   if (L->mx_rec.empty()) return false;
   const ScheduleSlot slot{&L->mx_classes, &L->mx_sched_ptr, &L->mx_sched_rec, &L->mx_on_device, L->dev.mx_sched_rec,
-                          L->dev.mx_sched_ptr, &L->dev.mx_uploaded, &L->dev.mx_stream};
+                          L->dev.mx_sched_ptr, &L->dev.mx_uploaded, &L->dev.mx_stream, &L->dev.mx_landed};
   return ensure_slot(L, slot, n_classes, stream, [&](int32_t n, std::vector<int32_t>* ptr, std::vector<int32_t>* rec) {
     if (planned) {
       *ptr = L->mx_plan_ptr;
@@ -448,15 +470,15 @@ bool ensure_cut_schedule(const dbsa_layout* L, int32_t n_classes, int row_blocks
         hipEventRecord(done, stream) != hipSuccess) {
       (void)hipStreamSynchronize(stream);
       (void)hipEventDestroy(done);
+      (void)hipGetLastError();
       return false;
     }
     L->dev.cut_uploaded = done;
     L->dev.cut_stream = stream;
     L->cut_on_device = true;
-  } else if (stream != L->dev.cut_stream) {
-    if (hipStreamWaitEvent(stream, static_cast<hipEvent_t>(L->dev.cut_uploaded), 0) != hipSuccess) return false;
+    return true;
   }
-  return true;
+  return order_behind_copy(&L->dev.cut_landed, L->dev.cut_uploaded, L->dev.cut_stream, stream);
 }
 
 bool tensor_ok(const dbsa_tensor& t, int dtype) {

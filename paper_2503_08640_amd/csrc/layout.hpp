@@ -36,6 +36,7 @@ struct dbsa_device_lists {
   int32_t* sched_ptr = nullptr;   // [kMaxSchedClasses + 1]
   void* sched_uploaded = nullptr; // event recorded behind the schedule's copy
   void* sched_stream = nullptr;   // stream of that copy
+  bool sched_landed = false;      // a call has seen the copy done
   // room for ONE schedule with lists cut to measure (dbsa_layout::cut_*), filled by the first query prefill that uses one
   unsigned char* cut_room = nullptr;
   int32_t* cut_rec = nullptr;     // [n_records][4]
@@ -44,6 +45,7 @@ struct dbsa_device_lists {
   int32_t* cut_tab = nullptr;     // [n_cut_tiles][4]
   void* cut_uploaded = nullptr;
   void* cut_stream = nullptr;
+  bool cut_landed = false;
   // decode steps that run their pool items as a contraction (dbsa_layout::mx_rec): the segments'
   // tile entries, the flat references, and room for that launch's schedule, filled by the first
   // decode call that uses it
@@ -53,6 +55,7 @@ struct dbsa_device_lists {
   int32_t* mx_sched_ptr = nullptr; // [kMaxSchedClasses + 1]
   void* mx_uploaded = nullptr;
   void* mx_stream = nullptr;
+  bool mx_landed = false;
   // ordering of the asynchronous upload against the calls that read the lists (HIP handles kept
   // as plain pointers so that host-only code can include this header)
   void* upload_stream = nullptr;  // stream the lists were copied on

@@ -378,3 +378,79 @@ def test_an_infinite_value_survives_the_merge_of_a_cut_list(pool, groups):
         assert np.all(o[:, 4:, 5] == np.inf), f"{what}: {o[0, 4:, 5]}"
         o[:, 4:, 5] = ref[:, 4:, 5]
         assert_close(o, ref, f"{what} list beside an infinite channel")
+
+
+def test_cut_query_prefill_on_other_streams_and_in_a_graph():
+    """The schedule of the cut lists is copied on the stream of the first call that uses it.  Calls on another stream are
+    ordered behind that copy, also the very next one, and a graph captured on a third stream holds the same launches:
+    every result equals the first stream's bit for bit.  The same for the whole lists of a persistent launch."""
+    pc = small_pool_case("cutstream", 3600, hq=8, hkv=2, pool_tokens=9000, groups=3, lens=(32, 200), sigma=0.5)
+    qc = synth.make_query_case("cutstreamq", 3601, pc, n_queries=2, q_len=[64, 20], selections=[[0, 1, 2], [1]])
+    lay, kp, vp = _query_setup(pc, qc, 64, 0)
+    qs, ks, vs = to_dev(qc.q), to_dev(qc.k), to_dev(qc.v)
+    ws = torch.empty(lay.workspace_bytes(8, 128), dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(qs)
+
+    def run():
+        return B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, out=out, workspace=ws)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    want = run().clone()
+    assert_close(to_f64(want), _oracle_query(pc, qc), "cut lists")
+    whole = B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, workspace=False)
+    assert not torch.equal(whole, want), "the workspace did not switch the cut lists on"
+    side.wait_stream(torch.cuda.current_stream())
+    for _ in range(3):
+        with torch.cuda.stream(side):
+            out.fill_(float("nan"))
+            run()
+        side.synchronize()
+        assert torch.equal(out, want)
+    # a fresh layout, whose schedule is copied by the first of two calls on two streams
+    for _ in range(4):
+        lay, _, _ = _query_setup(pc, qc, 64, 0)
+        out2, ws2 = torch.empty_like(out), torch.empty_like(ws)
+        side.wait_stream(torch.cuda.current_stream())
+        run()
+        with torch.cuda.stream(side):
+            B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, out=out2, workspace=ws2)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(out2, want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for rep in range(4):
+        out.fill_(float("nan"))
+        ws.random_(0, 255)              # eager work between the replays
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), f"replay {rep}"
+    # captured before any call has made the schedule: nothing is copied, the lists run in another form
+    fresh, _, _ = _query_setup(pc, qc, 64, 0)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.dbsa_query_attn(fresh, qs, ks, vs, kp, vp, pc.scale, out=out, workspace=ws)
+    for rep in range(2):
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_close(to_f64(out), _oracle_query(pc, qc), f"captured before the schedule was made, replay {rep}")
+    # the schedule of a persistent launch: many Q tiles, captured on a stream that has not used it
+    many = synth.make_query_case("cutstreamm", 3602, pc, n_queries=600, q_len=[1 + (7 * i) % 64 for i in range(600)], n_select=1)
+    lay, _, _ = _query_setup(pc, many, 64, 0)
+    qs, ks, vs = to_dev(many.q), to_dev(many.k), to_dev(many.v)
+    got = B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, workspace=False)
+    want = got.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, out=got, workspace=False)
+    for rep in range(3):
+        got.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), f"persistent launch, replay {rep}"
