@@ -374,7 +374,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
   // ---- per Q tile: rows, Q^T fragments, softmax state ----
   const float c2 = p.scale_log2e;
-  const float score_unit = kRawQ ? 1.f / c2 : 1.f;  // one log2 unit in units of the scores
+  // one log2 unit in units of the scores (finite: below a c2 of 2^-128 every score is zero log2 units, and so is a shift)
+  const float score_unit = kRawQ ? fminf(1.f / c2, 1.7e38f) : 1.f;
   auto log2_units = [&](float s) DBSA_INLINE { return kRawQ ? s * c2 : s; };
   int head[2], row_local[2], row_tok[2], q_pos[2];
   int row_slot[2] = {0, 0};  // GATHER: where the row's partial state goes

@@ -131,3 +131,15 @@ def test_prefill_at_head_ratios_that_leave_waves_idle(hq, hkv, d, block_m, pool)
     for ws in (False, None):
         oq = B.dbsa_query_attn(layq, qs, ks, vs, kp, vp, pc.scale, workspace=ws)
         assert_close(to_f64(oq), _oracle_query(pc, qc), f"query prefill {hq}/{hkv}x{d} bm={block_m} ws={ws}")
+
+
+def test_a_scale_whose_reciprocal_is_infinite_at_head_dim_64():
+    """Any positive scale is taken: with one below 2^-128 all scores are zero to every digit, and a row is the mean of the
+    values it sees."""
+    pc = small_pool_case("d64t", 7700, hq=4, hkv=2, d=64, pool_tokens=700, groups=2, lens=(32, 128))
+    p = pc.pool
+    lay = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, block_m=64, block_n=64)
+    o = B.dbsa_preencode_attn(lay, to_dev(pc.q), to_dev(pc.k), to_dev(pc.v), 1e-39)
+    want = orc.preencode_attn(synth.as_f64(pc.q), synth.as_f64(pc.k), synth.as_f64(pc.v), p.sink_len, p.demo_offsets,
+                              p.group_demo_offsets, 1e-39)
+    assert_close(to_f64(o), want, "d64 with a scale of 1e-39")
