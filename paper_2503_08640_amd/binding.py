@@ -369,8 +369,11 @@ def _cache(t) -> Tensor:
 
 
 def _stream() -> int:
+    """Handle of the current stream.  (current_device() is what sets torch's device state up, and what refuses in a process
+    forked from one that has it; the raw handle is a private call of torch, so builds without it take the public one.)"""
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
 
 
 def dbsa_preencode_attn(layout: Layout, q, k, v, scale: float, out=None, lse=None):

@@ -757,3 +757,17 @@ def test_query_stage_launch_order_groups_queries_by_their_selections():
     assert firsts == sorted(range(n_q), key=lambda u: (sels[u], u))
     same = owners[:-1] == owners[1:]
     assert np.all(lens[:-1][same] >= lens[1:][same])
+
+
+def test_the_current_stream_is_asked_for_with_torchs_checks(monkeypatch):
+    """A call in a process forked from one that used the device is refused by torch before the library sees it, and a torch
+    without the private raw handle is asked the public way."""
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "_initialized", False)
+    monkeypatch.setattr(torch.cuda, "_is_in_bad_fork", lambda: True)
+    with pytest.raises(RuntimeError, match="forked subprocess"):
+        B._stream()
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *_: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert B._stream() == 77
