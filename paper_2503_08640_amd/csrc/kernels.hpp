@@ -95,9 +95,10 @@ struct AttnParams {
   float scale_log2e;          // scale * log2(e)
 };
 
-// bf16 MFMA kernels (attn_mfma.hip)
+// bf16 MFMA kernels (attn_mfma.hip): token strides of 2^24 elements and more
 hipError_t launch_prefill_mfma(const AttnParams& p, int head_dim, hipStream_t stream);
-// software-pipelined variants (attn_prefill.hip): head_dim 128, or 64 with more than one row block per workgroup
+// software-pipelined variants (attn_prefill.hip): head_dim 128, or 64 with two, four or eight row blocks per workgroup
+// (every workgroup size that is chosen at head_dim 64)
 hipError_t launch_prefill_pipelined(const AttnParams& p, int head_dim, hipStream_t stream);
 // the same mathematics with 64 query rows per wave, one wave per SIMD (attn_prefill64.hip); kernel
 // only: launch_prefill_pipelined runs the merge pass of a split launch

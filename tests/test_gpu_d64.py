@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
     (4, 1, 64, 1100, 3, 5, 1),       # four waves of 64 rows, one workgroup per Q tile
     (4, 2, 64, 900, 2, 64, 0),       # two waves
     (4, 4, 64, 1100, 3, 130, 2),     # one wave
-    (4, 4, 32, 500, 2, 0, 0),        # one row block: the kernel that is not pipelined
+    (4, 4, 32, 500, 2, 0, 0),        # one wave whose second row block has no head
     (32, 8, 64, 6200, 23, 64, 0),    # the same persistently: Q tiles of many short groups in one stream
     (16, 16, 128, 9000, 20, 4, 0),
     (16, 16, 64, 9000, 20, 4, 0),
