@@ -204,8 +204,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   const uint64_t vpool = uniform64(reinterpret_cast<uint64_t>(static_cast<const __bf16*>(p.v_pool.ptr) + hk * p.v_pool.stride_head));
   const uint64_t kself = uniform64(reinterpret_cast<uint64_t>(static_cast<const __bf16*>(p.k_self.ptr) + hk * p.k_self.stride_head));
   const uint64_t vself = uniform64(reinterpret_cast<uint64_t>(static_cast<const __bf16*>(p.v_self.ptr) + hk * p.v_self.stride_head));
-  const int kp_stride = static_cast<int>(p.k_pool.stride_tok), vp_stride = static_cast<int>(p.v_pool.stride_tok);
-  const int ks_stride = static_cast<int>(p.k_self.stride_tok), vs_stride = static_cast<int>(p.v_self.stride_tok);
+  // (Arguments that the loops read go into registers of their own where registers run short.  They arrive in blocks of 16,
+  // and a block of which one is read is spilled and brought back whole: 32 lane reads per tile for the two strides, and as
+  // many per row piece stored.  Persistent query prefill of 64 questions of 64 tokens 1588 -> 1527 us; the other instances
+  // do not spill them.)
+  auto own_register = [](auto x) DBSA_INLINE {
+    if constexpr (kPieces && kD == 128 && NW == 4) asm volatile("" : "+s"(x));
+    return x;
+  };
+  const int kp_stride = own_register(static_cast<int>(p.k_pool.stride_tok)), vp_stride = own_register(static_cast<int>(p.v_pool.stride_tok));
+  const int ks_stride = own_register(static_cast<int>(p.k_self.stride_tok)), vs_stride = own_register(static_cast<int>(p.v_self.stride_tok));
 
   auto decode_ref = [&](int w0, int w1) DBSA_INLINE {
     return TileRef{w0, w1 & 0xFFFF, ((w1 >> 16) & 1) != 0, SELF && ((w1 >> 17) & 1) != 0};
@@ -958,12 +966,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         const int row_base = ((2 * wave + rb) % spb) * 32;
         __bf16* op = static_cast<__bf16*>(const_cast<void*>(p.o.ptr)) + static_cast<int64_t>(o_head[rb]) * p.o.stride_head +
                      (ln % kPieces16) * 8;
+        const int64_t o_stride = own_register(p.o.stride_tok);
 #pragma unroll
         for (int i = 0; i < 32 / kLoadRows; ++i) {
           const int row = kLoadRows * i + ln / kPieces16;
           const intx4 piece = *(lds_b128)(static_cast<uintptr_t>(stag + row * kRowBytes + (((ln % kPieces16) ^ k_swizzle(row)) * 16)));
           if (row_base + row < o_rows[rb])
-            *reinterpret_cast<intx4*>(op + static_cast<int64_t>(o_start + row_base + row) * p.o.stride_tok) = piece;
+            *reinterpret_cast<intx4*>(op + static_cast<int64_t>(o_start + row_base + row) * o_stride) = piece;
         }
         if (p.lse && ehalf == 0 && o_valid[rb])
           p.lse[static_cast<int64_t>(o_head[rb]) * p.lse_stride + o_tok[rb]] = (m_run[rb] + __log2f(l_tot)) * 0.69314718055994531f;
