@@ -230,11 +230,13 @@ int dbsa_layout_export_schedule(const dbsa_layout* layout, int32_t n_classes, co
                                 const int32_t** records);
 
 /*
- * Schedule of a query prefill with few Q tiles (plumbing; query-stage layouts): the concatenated lists of the tiles, in
- * launch order, are dealt to n_workers workers per block of query heads (fewer when a worker's share would hold under
- * 6 entries; the others get no records), each taking entries until its cost (entries + 5 per record) reaches a share, and
- * cut there; no piece of a cut list is shorter than 5 entries.  The share is the smallest that leaves the last worker no
- * more than the others.
+ * Schedule of a query prefill with few Q tiles (plumbing; query-stage layouts), for n_workers workers per block of
+ * query heads (fewer when a worker's share would hold under 6 list entries; the others get no records).  As many rounds
+ * of whole tiles as every worker gets one in go first, dealt as in dbsa_layout_export_schedule; the lists of the other
+ * tiles, in launch order, are dealt to the workers one after the other, each taking entries until its cost (entries + 5
+ * per record, + 3 per whole tile before) reaches a share, and cut there; no piece of a cut list is shorter than 5
+ * entries.  The share is the smallest that leaves the last worker no more than the others.  (Where the lists are so
+ * unequal that the rounds leave workers idle, all of them are dealt that way.)
  *   worker_ptr : int32 [n_workers + 1]: worker c takes records worker_ptr[c] .. worker_ptr[c+1]-1.
  *   records    : int32 [n_records][4] = (q_start, q_len, first list entry, list entries).
  *   part_rows  : int32 [n_records]: first row of the record's partial states in the workspace, -1 for a whole list.

@@ -549,13 +549,13 @@ int64_t prefill_places(const dbsa_layout* L, int row_blocks, int head_dim) {
 }
 
 // Runs per list of a launch of `wgs` workgroups (one run each) on `places`: the number that makes rounds * length
-// shortest.  A run costs kPieceCost entries to start and finish; every further run of a row is one more partial state,
-// 2 * 528 bytes for each of rows * heads / places states per place at the 20 KB a place gets in the time of a tile.
+// shortest.  A run costs kPieceCost entries to start and finish; every further run of a row is one more partial state
+// (kStateCost), of which a place leaves rows * heads / places.
 int64_t query_runs(const dbsa_layout* L, int64_t wgs, int64_t places, int64_t states) {
   if (wgs <= 0 || wgs >= places) return 1;
   const int64_t most = std::min(std::min(kMaxQuerySplit, L->shortest_list / kMinRun), 2 * places / wgs);
   const double entries = static_cast<double>(L->n_ent()) / static_cast<double>(std::max<int64_t>(1, L->n_qtiles()));
-  const double merge = static_cast<double>(states) * 1056.0 / static_cast<double>(places) / 20000.0;
+  const double merge = static_cast<double>(states) * kStateCost / static_cast<double>(places);
   int64_t best = 1;
   double least = entries + kPieceCost;
   for (int64_t s = 2; s <= most; ++s) {

@@ -572,19 +572,25 @@ void dbsa_balance_records(const std::vector<int32_t>& rec_in, int32_t n_classes,
   }
 }
 
+namespace {
+// the first n Q tiles in launch order as records
+std::vector<int32_t> tile_records(const dbsa_layout* L, int64_t n) {
+  std::vector<int32_t> rec;
+  rec.reserve(static_cast<size_t>(n) * 4);
+  for (int64_t i = 0; i < n; ++i) {
+    const int32_t t = L->order[static_cast<size_t>(i)];
+    rec.push_back(L->qtile_tab[4 * t + 0]);
+    rec.push_back(L->qtile_tab[4 * t + 1]);
+    rec.push_back(static_cast<int32_t>(L->list_ptr[t]));
+    rec.push_back(static_cast<int32_t>(L->list_ptr[t + 1] - L->list_ptr[t]));
+  }
+  return rec;
+}
+}  // namespace
+
 void dbsa_balance_schedule(const dbsa_layout* L, int32_t n_classes, std::vector<int32_t>* class_ptr,
                            std::vector<int32_t>* rec) {
-  const int64_t nt = L->n_qtiles();
-  std::vector<int32_t> in_order;
-  in_order.reserve(static_cast<size_t>(nt) * 4);
-  for (int64_t i = 0; i < nt; ++i) {
-    const int32_t t = L->order[static_cast<size_t>(i)];
-    in_order.push_back(L->qtile_tab[4 * t + 0]);
-    in_order.push_back(L->qtile_tab[4 * t + 1]);
-    in_order.push_back(static_cast<int32_t>(L->list_ptr[t]));
-    in_order.push_back(static_cast<int32_t>(L->list_ptr[t + 1] - L->list_ptr[t]));
-  }
-  dbsa_balance_records(in_order, n_classes, class_ptr, rec);
+  dbsa_balance_records(tile_records(L, L->n_qtiles()), n_classes, class_ptr, rec);
 }
 
 int64_t dbsa_cut_workers(const dbsa_layout* L, int64_t n_classes) {
@@ -593,31 +599,39 @@ int64_t dbsa_cut_workers(const dbsa_layout* L, int64_t n_classes) {
   return std::max<int64_t>(1, std::min<int64_t>(n_classes, L->n_ent() / kMinShare));
 }
 
-void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes) {
-  const int64_t nt = L->n_qtiles();
-  auto entries = [&](int32_t t) { return L->list_ptr[t + 1] - L->list_ptr[t]; };
-  const int64_t total = L->n_ent(), workers = dbsa_cut_workers(L, n_classes);
-  // One walk for a given share.  Returns the cost of the last worker, who takes the rest, or with `emit` fills the lists.
-  int64_t longest = 0;  // cost of the busiest worker of the last walk
-  auto deal = [&](int64_t share, bool emit) {
-    if (emit) {
-      L->cut_ptr.assign(1, 0);
-      L->cut_rec.clear();
-      L->cut_part.clear();
-      L->cut_tab.clear();
-      L->cut_rows = 0;
-    }
-    int64_t w = 0, acc = 0, n_rec = 0;
-    longest = 0;
-    auto next_worker = [&]() {
-      ++w;
-      acc = 0;
-      if (emit) L->cut_ptr.push_back(static_cast<int32_t>(n_rec));
-    };
-    for (int64_t i = 0; i < nt; ++i) {
-      const int32_t t = L->order[static_cast<size_t>(i)];
-      const int32_t* tile = &L->qtile_tab[4 * static_cast<size_t>(t)];
-      const int64_t n = entries(t), first_rec = n_rec;
+namespace {
+// Lists dealt to workers: the first n_whole tiles of `tiles` whole, in rounds, the others cut to measure.
+struct CutPlan {
+  struct Piece {
+    int64_t tile, first, take, worker;  // tile: index in `tiles`
+  };
+  std::vector<int32_t> whole_ptr, whole_rec;
+  std::vector<Piece> pieces;
+  double cost = 0.0;  // of the busiest worker
+};
+
+// stray: cost of an entry of a piece over that of a whole tile's
+CutPlan plan_cuts(const std::vector<int32_t>& tiles, int64_t n_whole, int64_t workers, double stray) {
+  CutPlan plan;
+  const int64_t nt = static_cast<int64_t>(tiles.size() / 4);
+  plan.whole_ptr.assign(static_cast<size_t>(workers) + 1, 0);
+  if (n_whole > 0)
+    dbsa_balance_records(std::vector<int32_t>(tiles.begin(), tiles.begin() + 4 * n_whole), static_cast<int32_t>(workers),
+                         &plan.whole_ptr, &plan.whole_rec);
+  std::vector<int64_t> load(static_cast<size_t>(workers), 0);
+  int64_t total = 0, rest = 0;
+  for (size_t c = 0; c < load.size(); ++c) {
+    for (int32_t k = plan.whole_ptr[c]; k < plan.whole_ptr[c + 1]; ++k) load[c] += plan.whole_rec[4 * static_cast<size_t>(k) + 3] + kTileCost;
+    total += load[c];
+  }
+  const int64_t heaviest = *std::max_element(load.begin(), load.end());
+  for (int64_t i = n_whole; i < nt; ++i) rest += tiles[4 * static_cast<size_t>(i) + 3];
+  // One walk over the rest for a given share; returns the load of the last worker, who takes what is left.
+  auto deal = [&](int64_t share) {
+    plan.pieces.clear();
+    int64_t w = 0, acc = load[0];
+    for (int64_t i = n_whole; i < nt; ++i) {
+      const int64_t first = tiles[4 * static_cast<size_t>(i) + 2], n = tiles[4 * static_cast<size_t>(i) + 3];
       for (int64_t pos = 0; pos < n;) {
         const int64_t room = share - acc - kPieceCost, rem = n - pos;
         int64_t take = rem;
@@ -626,43 +640,80 @@ void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes) {
           // that has nothing yet always takes something
           take = std::min(room, rem - kMinPiece);
           if (take < kMinPiece && acc > 0) {
-            next_worker();
+            acc = load[static_cast<size_t>(++w)];
             continue;
           }
           if (take < kMinPiece) take = rem < 2 * kMinPiece ? rem : kMinPiece;
         }
         acc += kPieceCost + take;
-        longest = std::max(longest, acc);
-        ++n_rec;
-        if (emit) {
-          L->cut_rec.insert(L->cut_rec.end(), {tile[0], tile[1], static_cast<int32_t>(L->list_ptr[t] + pos), static_cast<int32_t>(take)});
-          L->cut_part.push_back(-1);
-        }
+        plan.pieces.push_back({i, first + pos, take, w});
         pos += take;
-        if (w + 1 < workers && acc + kPieceCost + kMinPiece > share) next_worker();
+        if (w + 1 < workers && acc + kPieceCost + kMinPiece > share) acc = load[static_cast<size_t>(++w)];
       }
-      if (emit && n_rec - first_rec > 1) {
-        L->cut_tab.insert(L->cut_tab.end(), {tile[0], tile[1], static_cast<int32_t>(L->cut_rows), static_cast<int32_t>(n_rec - first_rec)});
-        for (int64_t k = first_rec; k < n_rec; ++k) {
-          L->cut_part[static_cast<size_t>(k)] = static_cast<int32_t>(L->cut_rows);
-          L->cut_rows += tile[1];
-        }
-      }
-    }
-    if (emit) {
-      while (static_cast<int64_t>(L->cut_ptr.size()) <= n_classes) L->cut_ptr.push_back(static_cast<int32_t>(n_rec));
     }
     return w + 1 < workers ? int64_t{0} : acc;
   };
   // The smallest share with which the last worker is left no more than the others.  (With `hi` it surely is: a
   // worker stops less than kPieceCost + 2 kMinPiece short of its share, and there are at most nt + workers records.)
-  int64_t lo = total / workers, hi = (total + kPieceCost * (nt + workers)) / workers + kPieceCost + 2 * kMinPiece + 1;
+  int64_t lo = (total + rest) / workers - 1;
+  int64_t hi = heaviest + (rest + kPieceCost * (nt + workers)) / workers + kPieceCost + 2 * kMinPiece + 1;
   while (lo + 1 < hi) {
     const int64_t mid = (lo + hi) / 2;
-    (deal(mid, false) <= mid ? hi : lo) = mid;
+    (deal(mid) <= mid ? hi : lo) = mid;
   }
-  deal(hi, true);
-  L->cut_longest = longest;
+  deal(hi);
+  std::vector<double> cost(load.begin(), load.end());
+  for (const CutPlan::Piece& x : plan.pieces) cost[static_cast<size_t>(x.worker)] += stray * static_cast<double>(x.take) + kPieceCost;
+  plan.cost = *std::max_element(cost.begin(), cost.end());
+  return plan;
+}
+}  // namespace
+
+// With several Q tiles per worker, whole tiles go round first and only what does not fill a round is cut.  Tiles next to
+// each other in launch order selected the same groups, and in a round the workers walk them side by side: a group is
+// fetched once for all of them.  Cutting the whole order to measure instead, a stretch of it to each worker, sends
+// every worker through other groups: 300 questions of 32 tokens over 64 workers 1443 us against 1182 with whole tiles
+// (4.7 rounds) and 1190 in rounds, 140 questions 707 / 659 / 574, 70 questions 362 / 433 / 311.  An entry of a piece
+// costs about 1.13 times what it costs in step, 1.4 times where everything is cut over several tiles per worker, which
+// only lists of very different lengths are worth.
+void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes) {
+  const int64_t nt = L->n_qtiles(), workers = dbsa_cut_workers(L, n_classes);
+  const std::vector<int32_t> tiles = tile_records(L, nt);
+  CutPlan plan = plan_cuts(tiles, nt / workers * workers, workers, 1.13);
+  if (nt >= workers && plan.cost > 1.4 * static_cast<double>(L->n_ent() / workers + kPieceCost)) {
+    CutPlan all = plan_cuts(tiles, 0, workers, 1.4);
+    if (all.cost < plan.cost) plan = std::move(all);
+  }
+  // ---- a worker's whole tiles, then its pieces; the pieces of a cut tile get partial rows ----
+  L->cut_rec.clear();
+  L->cut_part.clear();
+  L->cut_tab.clear();
+  L->cut_rows = 0;
+  std::vector<int64_t> part(plan.pieces.size(), -1);
+  for (size_t a = 0, b; a < part.size(); a = b) {
+    for (b = a + 1; b < part.size() && plan.pieces[b].tile == plan.pieces[a].tile;) ++b;
+    if (b - a == 1) continue;
+    const int32_t* tile = &tiles[4 * static_cast<size_t>(plan.pieces[a].tile)];
+    L->cut_tab.insert(L->cut_tab.end(), {tile[0], tile[1], static_cast<int32_t>(L->cut_rows), static_cast<int32_t>(b - a)});
+    for (size_t k = a; k < b; ++k, L->cut_rows += tile[1]) part[k] = L->cut_rows;
+  }
+  L->cut_ptr.assign(static_cast<size_t>(n_classes) + 1, 0);
+  size_t k = 0;
+  for (int64_t c = 0; c < n_classes; ++c) {
+    if (c < workers) {
+      L->cut_rec.insert(L->cut_rec.end(), plan.whole_rec.begin() + 4 * plan.whole_ptr[static_cast<size_t>(c)],
+                        plan.whole_rec.begin() + 4 * plan.whole_ptr[static_cast<size_t>(c) + 1]);
+      L->cut_part.resize(L->cut_rec.size() / 4, -1);
+      for (; k < part.size() && plan.pieces[k].worker == c; ++k) {
+        const int32_t* tile = &tiles[4 * static_cast<size_t>(plan.pieces[k].tile)];
+        L->cut_rec.insert(L->cut_rec.end(), {tile[0], tile[1], static_cast<int32_t>(plan.pieces[k].first),
+                                             static_cast<int32_t>(plan.pieces[k].take)});
+        L->cut_part.push_back(static_cast<int32_t>(part[k]));
+      }
+    }
+    L->cut_ptr[static_cast<size_t>(c) + 1] = static_cast<int32_t>(L->cut_part.size());
+  }
+  L->cut_cost = plan.cost;
   // the same workers with whole Q tiles, for dbsa_cut_worth
   L->cut_whole = 0;
   if (nt >= 2 * n_classes) {
@@ -677,27 +728,27 @@ void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes) {
   L->cut_classes = n_classes;
 }
 
-// Against whole Q tiles dealt to the same workers, and against runs of one length, one per workgroup: where these
-// come out even (16 Q tiles over 32 workers in two runs each: 412 us against 421) every worker has one record to
-// start and finish, and workers walk in step.  The merge pass costs about as much as two entries.  An entry costs
-// `crowd` times as much with every place taken as with few: a K/V pair serves 32 rows per row block, and 256 rows keep
-// the matrix pipes busy at the rate the pairs arrive.  Two small workgroups per compute unit fetch a pair per 128 rows
-// each and are bound by that traffic (512 of them move 7.4 TB/s; 50 questions of 20 tokens on 400 of 512 places: whole
-// lists 771 us, all places with cut lists 803).
+// Against whole Q tiles dealt to the same workers, and while there are fewer tiles than workers against runs of one length,
+// one per workgroup, which walk in step and have one record each to start and finish: 29 questions of 64 tokens over 32
+// workers take 713 us whole and 779 cut to measure, 14 take 378 in two runs each and 390 cut, one takes 58 in 32 pieces.
+// The partial states of either are priced by their bytes.  An entry costs `crowd` times as much with every place taken as
+// with few: a K/V pair serves 32 rows per row block, and 256 rows keep the matrix pipes busy at the rate the pairs
+// arrive.  Two small workgroups per compute unit fetch a pair per 128 rows each and are bound by that traffic (512 of them
+// move 7.4 TB/s; 50 questions of 20 tokens on 400 of 512 places: whole lists 771 us, all places with cut lists 803).
 bool dbsa_cut_worth(const dbsa_layout* L, int row_blocks) {
   const int64_t nt = L->n_qtiles();
   const double crowd = row_blocks == 8 ? 1.0 : row_blocks == 4 ? 1.5 : 3.0;
-  const double classes = static_cast<double>(L->cut_classes), cost = static_cast<double>(kPieceCost);
+  const double classes = static_cast<double>(L->cut_classes), heads = std::max(1, row_blocks * 32 / std::max(1, L->block_m));
   auto per_entry = [&](int64_t busy) { return std::max(1.0, crowd * std::min(1.0, static_cast<double>(busy) / classes)); };
-  const double cut = 1.03 * static_cast<double>(L->cut_longest) * per_entry(dbsa_cut_workers(L, L->cut_classes)) + 2.0;
+  auto merge = [&](int64_t rows) { return rows > 0 ? static_cast<double>(rows) * heads / classes * kStateCost + 2.0 : 0.0; };
+  const double cut = 1.03 * (L->cut_cost * per_entry(dbsa_cut_workers(L, L->cut_classes)) + merge(L->cut_rows));
+  if (nt >= 2 * L->cut_classes) return cut < static_cast<double>(L->cut_whole) * per_entry(nt);
+  // (query_runs() splits lists only while whole ones leave places free)
+  const int64_t top = nt < L->cut_classes ? std::max<int64_t>(1, std::min(kMaxQuerySplit, L->shortest_list / kMinRun)) : 1;
   double other = 1e30;
-  if (nt >= 2 * L->cut_classes) {
-    other = static_cast<double>(L->cut_whole) * per_entry(nt);
-  } else {
-    const double list = static_cast<double>(L->longest_list);
-    for (int64_t runs = 1; runs <= std::max<int64_t>(1, std::min(kMaxQuerySplit, L->shortest_list / kMinRun)); ++runs)
-      other = std::min(other, static_cast<double>((nt * runs + L->cut_classes - 1) / L->cut_classes) *
-                                      (list / static_cast<double>(runs) * per_entry(nt * runs) + cost) + (runs > 1 ? 2.0 : 0.0));
-  }
+  for (int64_t runs = 1; runs <= top; ++runs)
+    other = std::min(other, static_cast<double>((nt * runs + L->cut_classes - 1) / L->cut_classes) *
+                                    (static_cast<double>(L->longest_list) / static_cast<double>(runs) * per_entry(nt * runs) + kPieceCost) +
+                                merge(runs > 1 ? runs * L->n_query_tokens : 0));
   return cut < other;
 }

@@ -145,11 +145,12 @@ struct dbsa_layout {
   // Schedule of a query prefill whose lists are cut to measure for cut_classes workers (dbsa_cut_schedule): class c
   // walks records cut_ptr[c] .. cut_ptr[c+1]-1 of cut_rec (words as in sched_rec, a record being a run of a Q
   // tile's list); cut_part: first partial row of a record, -1 = the record is a whole Q tile; cut_tab: the cut Q
-  // tiles (q_start, q_len, first partial row, pieces).  cut_longest: cost of the busiest worker; cut_whole: that of the
+  // tiles (q_start, q_len, first partial row, pieces).  cut_cost: cost of the busiest worker; cut_whole: that of the
   // same workers with whole Q tiles (0: too few tiles for that).
   mutable int32_t cut_classes = 0;
   mutable std::vector<int32_t> cut_ptr, cut_rec, cut_part, cut_tab;
-  mutable int64_t cut_rows = 0, cut_longest = 0, cut_whole = 0;
+  mutable int64_t cut_rows = 0, cut_whole = 0;
+  mutable double cut_cost = 0.0;
   mutable bool cut_on_device = false;
   // the same for the records of mx_rec (a second, independent schedule)
   mutable int32_t mx_classes = 0;
@@ -173,6 +174,8 @@ constexpr int32_t kMaxSchedClasses = 512;
 // what a record of a persistent prefill costs beyond its list, in list entries (whole Q tiles; a piece also leaves
 // partial states: 64-token pieces of 4 heads run at 3.0 k cycles an entry and 14 k around the list)
 constexpr int64_t kTileCost = 3, kPieceCost = 5;
+// what a partial state (528 bytes, written and read) costs the place that leaves it, in list entries of 20 KB
+constexpr double kStateCost = 1056.0 / 20000.0;
 // runs of one length a query prefill's lists may be cut into instead: most runs per list, fewest entries per run
 constexpr int64_t kMaxQuerySplit = 16, kMinRun = 8;
 // share of a wave's 64 rows that must carry a query before a decode step runs its pool items as a
@@ -192,10 +195,12 @@ void dbsa_balance_schedule(const dbsa_layout* L, int32_t n_classes, std::vector<
 void dbsa_balance_records(const std::vector<int32_t>& rec_in, int32_t n_classes, std::vector<int32_t>* class_ptr,
                           std::vector<int32_t>* rec);
 
-// Cuts the lists of the Q tiles to measure for n_classes workers: the tiles are walked in launch order and dealt to
-// the workers one after the other, each taking list entries until its cost (entries + kPieceCost per record) reaches
-// the share; what does not fit is cut there, no piece is shorter than kMinPiece entries.  The share is the smallest
-// that leaves the last worker no more than the others.  Fills the cut_* members of L.
+// Cuts the lists of the Q tiles to measure for n_classes workers: as many rounds of whole tiles as every worker gets one
+// in, in launch order (dbsa_balance_records); the rest is walked in that order and dealt to the workers one after the
+// other, each taking list entries until its cost (entries + kPieceCost per record, on top of its whole tiles) reaches
+// the share; what does not fit is cut there, no piece is shorter than kMinPiece entries.  The share is the smallest that
+// leaves the last worker no more than the others.  Where lists are so unequal that the rounds leave workers idle,
+// everything is dealt by that walk.  Fills the cut_* members of L.
 constexpr int64_t kMinPiece = 5;
 int64_t dbsa_cut_workers(const dbsa_layout* L, int64_t n_classes);  // workers that get records (the first ones)
 void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes);

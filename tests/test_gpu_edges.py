@@ -316,18 +316,20 @@ def test_persistent_query_prefill_with_hundreds_of_ragged_queries():
     assert_close(to_f64(oq)[rows], ref[rows], "persistent query prefill, 700 ragged queries")
 
 
-@pytest.mark.parametrize("hq,hkv,block_m,q_len,rope", [
-    (8, 2, 64, [64], False),            # one question: one Q tile in as many pieces as there are workers
-    (8, 2, 64, [64], True),
-    (8, 2, 64, [1, 130, 64, 20, 77], True),   # pieces of several Q tiles per worker, rows of very unequal tiles
-    (16, 4, 32, [31, 5, 32], False),    # two-wave workgroups
-    (4, 4, 256, [700, 90], False),      # four-wave workgroups of one head
+@pytest.mark.parametrize("hq,hkv,block_m,q_len,rope,n_workers,row_blocks", [
+    (8, 2, 64, [64], False, 128, 8),            # one question: one Q tile in many pieces
+    (8, 2, 64, [64], True, 128, 8),
+    (8, 2, 64, [1, 130, 64, 20, 77], True, 128, 8),   # pieces of several Q tiles per worker, rows of very unequal tiles
+    (16, 4, 32, [31, 5, 32], False, 128, 4),    # two-wave workgroups
+    (4, 4, 256, [700, 90], False, 64, 8),       # four-wave workgroups of one head
+    (32, 8, 64, [60] * 40, False, 32, 8),       # more tiles than workers: a round of whole tiles, then pieces
+    (32, 8, 32, [20, 32, 9] * 25, True, 64, 4),
 ])
-def test_query_prefill_with_lists_cut_to_measure(hq, hkv, block_m, q_len, rope):
+def test_query_prefill_with_lists_cut_to_measure(hq, hkv, block_m, q_len, rope, n_workers, row_blocks):
     """Few Q tiles on many compute units: lists cut into unequal pieces, whose partial states a merge pass combines.
     A workspace too small for them leaves the lists in fewer pieces or whole; every form must match the oracle."""
     pc = small_pool_case("cutpool", 3400 + block_m + len(q_len), hq=hq, hkv=hkv, pool_tokens=9000, groups=3, lens=(32, 200), sigma=0.5)
-    sels = [[2, 0], [0, 1, 2], [1], [], [2, 1, 0]][:len(q_len)]
+    sels = ([[2, 0, 1] if len(q_len) == 1 else [2, 0], [0, 1, 2], [1], [], [2, 1, 0]] + [[1, 0]] * 80)[:len(q_len)]
     qc = synth.make_query_case("cutq", 3401, pc, n_queries=len(q_len), q_len=q_len, selections=sels)
     p = pc.pool
     lay, kp, vp = _query_setup(pc, qc, block_m, 0)
@@ -355,6 +357,10 @@ def test_query_prefill_with_lists_cut_to_measure(hq, hkv, block_m, q_len, rope):
     outs = [run(False)] + [run(torch.empty(n, dtype=torch.uint8, device="cuda")) for n in (need, need // 3, 16)]
     for o, what in zip(outs, ("whole lists", "cut lists", "a third of the workspace", "no room")):
         assert_close(to_f64(o), ref, f"{what} bm={block_m} T={q_len}")
+    # (256 compute units; a schedule for other workers would be refused here)
+    worth, _, rec, part, cut = lay.export_cut_schedule(n_workers, row_blocks)
+    assert worth and len(cut), "the lists were not cut"
+    assert (len(q_len) < n_workers) or (part[:] == -1).any()
     assert not torch.equal(outs[0], outs[1]), "the workspace did not switch the cut lists on"
     assert torch.equal(outs[0], outs[3])
     if not rope:
