@@ -8,6 +8,7 @@ built (``python -m paper_2503_08640_amd.build``); there is no fallback.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Optional, Sequence
 
@@ -368,12 +369,18 @@ def _cache(t) -> Tensor:
     return Tensor(t.data_ptr(), s[1], s[2])
 
 
+@functools.lru_cache(maxsize=None)
+def _stream_calls():
+    """torch's calls behind _stream, looked up once (they are what a launch waits for)."""
+    import torch
+    return torch.cuda.current_device, getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_stream
+
+
 def _stream() -> int:
     """Handle of the current stream.  (current_device() is what sets torch's device state up, and what refuses in a process
     forked from one that has it; the raw handle is a private call of torch, so builds without it take the public one.)"""
-    import torch
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
+    device, raw, stream = _stream_calls()
+    return stream().cuda_stream if raw is None else raw(device())
 
 
 def dbsa_preencode_attn(layout: Layout, q, k, v, scale: float, out=None, lse=None):

@@ -803,10 +803,13 @@ def test_the_current_stream_is_asked_for_with_torchs_checks(monkeypatch):
     without the private raw handle is asked the public way."""
     import types
     import torch
+    B._stream_calls.cache_clear()
     monkeypatch.setattr(torch.cuda, "_initialized", False)
     monkeypatch.setattr(torch.cuda, "_is_in_bad_fork", lambda: True)
     with pytest.raises(RuntimeError, match="forked subprocess"):
         B._stream()
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *_: types.SimpleNamespace(cuda_stream=77))
     monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    B._stream_calls.cache_clear()
     assert B._stream() == 77
+    B._stream_calls.cache_clear()
