@@ -53,8 +53,9 @@ def test_fp32_attention_at_the_edges_of_its_blocks(hq, hkv, d, sink, pool, group
 
 
 def test_a_value_beyond_a_short_block_does_not_reach_the_result():
-    """Keys past a segment's end share their block's operands with the segment's last key: an infinite value there
-    must reach the rows that see it and no others."""
+    """Keys past a segment's end share their block's operands with the segment's last key: an infinite value there must
+    reach the row that sees it and no row of another Q tile, those of its own group among them.  (The 16 rows of one
+    workgroup share the value as an operand, and where causality hides it from a row it meets a weight of zero.)"""
     pc = synth.make_pool_case("f32inf", 7100, dtype="f32", n_q_heads=2, n_kv_heads=1, head_dim=64, sink_len=5, pool_tokens=60,
                               demo_len_range=(8, 12), n_groups=2)
     p = pc.pool
@@ -62,5 +63,9 @@ def test_a_value_beyond_a_short_block_does_not_reach_the_result():
     v[p.n_tokens - 1] = float("inf")   # seen by the last row only
     lay = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, block_m=16, block_n=64)
     o = B.dbsa_preencode_attn(lay, to_dev(pc.q), to_dev(pc.k), v, pc.scale)
-    last_group = int(p.group_token_bounds()[-2])
-    assert torch.isfinite(o[:last_group]).all() and torch.isinf(o[-1]).all()
+    q64, k64, v64 = pool_f64(pc)
+    tile, last_group = int(lay.export()[0][:, 0].max()), int(p.group_token_bounds()[-2])
+    assert last_group < tile < p.n_tokens - 1 and (p.n_tokens - last_group) % 16   # rows of the group in front of the last tile
+    want = orc.preencode_attn(q64, k64, v64, p.sink_len, p.demo_offsets, p.group_demo_offsets, pc.scale)
+    assert_close(to_f64(o)[:tile], want[:tile], "rows of the other tiles", MAX_TOL, MEAN_TOL)
+    assert torch.isinf(o[-1]).all()
