@@ -308,10 +308,12 @@ void dbsa_layout_destroy(dbsa_layout* layout);
  * of its two schedules (B * n_split slots, or slot_ptr[B] slots), and at least 4 slots per query
  * token while the layout has few Q tiles.  dbsa_query_attn uses it when the layout has so few Q
  * tiles that whole lists would leave compute units idle or unevenly loaded; it then cuts KV lists
- * into pieces and merges their partial states (at most two pieces more than there are compute
- * units per head block: 69 MB on 256 compute units at head_dim 128, much less for short queries;
+ * into pieces and merges their partial states (at most twice as many pieces as there are workers per
+ * block of query heads: 69 MB on 256 compute units at head_dim 128, much less for short queries;
  * without a workspace, or with a smaller one, it cuts less or not at all: same result up to
- * summation order).
+ * summation order).  A layout keeps the pieces of ONE number of workers, that of its first such
+ * call (dbsa_layout_export_cut_schedule): models that differ in it should have layouts of their
+ * own, or the later ones run whole lists or runs of one length.
  * The pre-encode call needs none.  Returns 0 for a pre-encode layout.
  */
 size_t dbsa_workspace_bytes(const dbsa_layout* layout, int32_t n_q_heads, int32_t head_dim);
