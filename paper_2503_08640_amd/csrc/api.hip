@@ -626,8 +626,8 @@ void fill_decode_rows(AttnParams& p, const dbsa_layout* L, int r) {
   int k = 0;
   while ((32 >> k) > 32 / r) ++k;  // a wave takes 32 / r queries
   p.gm_rows = L->dev.gm_rows + L->gm_rows_off[k];
-  p.gm_n_rows = L->gm_rows_off[k + 1] - L->gm_rows_off[k];
-  p.gm_pool_rows = L->gm_pool_rows[k];
+  p.gm_direct = L->gm_direct[k];
+  p.gm_pool_rows = p.gm_direct + L->gm_rows_off[k + 1] - L->gm_rows_off[k];
 }
 
 // waves per decode workgroup for r columns per query (a power of two), see decode_common
@@ -654,7 +654,7 @@ void fill_lists(AttnParams& p, const dbsa_layout* L) {
   p.gm_ref_pad = L->dev.gm_ref_pad;
   p.n_gm_items = static_cast<int32_t>(L->gm_items.size() / 4);
   p.gm_max_queries = L->gm_max_queries;
-  p.n_pool_blocks = (p.n_gm_items + 7) / 8;
+  p.n_self_blocks = (L->n_queries + 7) / 8;
   p.n_qtiles = static_cast<int32_t>(L->n_qtiles());
   p.n_split = L->n_split;
   p.n_queries = L->n_queries;

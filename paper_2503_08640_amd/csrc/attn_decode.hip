@@ -78,11 +78,17 @@ __device__ DBSA_INLINE bool locate_decode_item(const AttnParams& p, DecodeItem& 
   const int in_block = blockIdx.x % 8;
   const int row_id = (blockIdx.x / 8) % p.launch_rows;
   it.hk = (blockIdx.x / 8) / p.launch_rows;
-  const int row = ((const_words)(reinterpret_cast<uintptr_t>(p.gm_rows)))[p.row_offset + row_id];
-  it.batch = row & 0xFF;
-  const int block = row >> 8;
-  it.self_item = block >= p.n_pool_blocks;
-  it.item = it.self_item ? p.n_gm_items + 8 * (block - p.n_pool_blocks) + in_block : 8 * block + in_block;
+  // (rows: the own caches' blocks, the first batches of gm_direct blocks of pool items, then those that take a look)
+  const int row = p.row_offset + row_id, pool_row = row - p.n_self_blocks;
+  it.self_item = pool_row < 0;
+  int block = pool_row;
+  it.batch = 0;
+  if (pool_row >= p.gm_direct) {
+    const int word = ((const_words)(reinterpret_cast<uintptr_t>(p.gm_rows)))[pool_row - p.gm_direct];
+    block = word >> 8;
+    it.batch = word & 0xFF;
+  }
+  it.item = it.self_item ? p.n_gm_items + 8 * row + in_block : 8 * block + in_block;
   if (it.item >= (it.self_item ? p.n_gm_items + p.n_queries : p.n_gm_items)) return false;
   const const_words runs = (const_words)(reinterpret_cast<uintptr_t>(p.gm_item_run));
   it.n_q = 1, it.first_key = 0, it.n_keys = 0, it.self_u = 0;
@@ -92,7 +98,7 @@ __device__ DBSA_INLINE bool locate_decode_item(const AttnParams& p, DecodeItem& 
     it.n_q = runs[4 * it.item + 2];
   } else {
     it.self_u = it.item - p.n_gm_items;
-    it.n_keys = __builtin_amdgcn_readfirstlane(p.self_len[it.self_u]);
+    it.n_keys = ((const_words)(reinterpret_cast<uintptr_t>(p.self_len)))[it.self_u];
   }
   return true;
 }
@@ -106,15 +112,30 @@ struct DecodeColumn {
   const float* rot;  // ROPE: table row of the column, 16 floats (cos, sin of 8 channel pairs) per (chunk c < 4, half)
 };
 
+// The references of a pool item's queries, (query, slot, shift, 0) each, go to LDS like a tile, in front of the first tiles:
+// requested into registers they would have to arrive before the tiles are requested, because the compiler waits for a load
+// of its own by waiting for everything in flight.  With one look-up less in front of the work item the first tiles of a
+// step of 16 queries are requested 4.5 us after its start instead of 5.6: 85.4 -> 84.8 us, over an fp8 pool 53.3 -> 50.9,
+// one re-positioned question 30.5 -> 29.9.  kRefBytes: the 32 references and, because a load fills 1 KiB, the same again.
+constexpr int kRefBytes = 1024;
+__device__ DBSA_INLINE void request_references(const AttnParams& p, const DecodeItem& it, lds_byte* refs) {
+  if (!it.self_item)
+    dma16(p.gm_ref_pad + static_cast<int64_t>(it.item) * 128, static_cast<unsigned>(threadIdx.x % 32) * 16u, refs);
+}
+// ROPE: the lengths of the first 64 queries' own caches, one per lane, requested with the first look-ups.
+template <bool ROPE>
+__device__ DBSA_INLINE int request_lengths(const AttnParams& p) {
+  return ROPE ? p.self_len[min(static_cast<int>(threadIdx.x % 64), p.n_queries - 1)] : 0;
+}
+
 // rp: columns per query, r rounded up to a power of two.
 // pass: the wave's query batch (of 32 / rp queries) inside the item; active: the wave has a batch.
+// refs: the item's references in LDS, arrived.
 // ROPE: the row is rotated at the id that stands for the new in-order position of the item's keys
 // (Sec. 2.2): shift of the reference + the query's own length - 1.
-// (The addresses are formed here, before the tile loads go out: they wait for the query reference
-// just loaded, and that wait must not include the tile loads.)
 template <int kD, bool ROPE>
 __device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const DecodeItem& it, int pass, bool active, int r, int rp_log2,
-                                                  int l32, int half) {
+                                                  int l32, int half, const lds_byte* refs, int lengths) {
   DecodeColumn c;
   const int rp = 1 << rp_log2;
   const int q_local = pass * (32 >> rp_log2) + (l32 >> rp_log2);  // index into the item's query list (< 32 also without a batch)
@@ -123,9 +144,9 @@ __device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const Dec
   if (it.self_item) {
     c.slot = static_cast<int>(p.gm_slot_ptr[it.self_u + 1]) - 1;
   } else {
-    // (query, slot, shift, 0); references past the item's last one repeat it
+    // (references past the item's last one repeat it)
     typedef int intx4 __attribute__((ext_vector_type(4)));
-    const intx4 ref = *reinterpret_cast<const intx4*>(p.gm_ref_pad + (static_cast<int64_t>(it.item) * 32 + q_local) * 4);
+    const intx4 ref = *(reinterpret_cast<const __attribute__((address_space(3))) intx4*>(refs) + q_local);
     u = ref[0];
     c.slot = ref[1];
     if (ROPE) rot_id = ref[2];
@@ -133,13 +154,12 @@ __device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const Dec
   c.head = it.hk * r + min(l32 & (rp - 1), r - 1);
   c.rot = nullptr;
   if (ROPE) {
-    rot_id = min(max(rot_id + p.self_len[u] - 1, 0), p.rope_n_pos - 1);
+    const int length = p.n_queries <= 64 ? __shfl(lengths, u, 64) : p.self_len[u];
+    rot_id = min(max(rot_id + length - 1, 0), p.rope_n_pos - 1);
     c.rot = p.rope_table + static_cast<int64_t>(rot_id) * kD + 16 * half;
-    asm volatile("" : "+v"(c.rot));
   }
   c.qp = static_cast<const __bf16*>(p.q.ptr) + static_cast<int64_t>(u) * p.q.stride_tok +
          static_cast<int64_t>(c.head) * p.q.stride_head + 8 * half;
-  asm volatile("" : "+v"(c.qp));
   return c;
 }
 
@@ -270,13 +290,13 @@ __device__ DBSA_INLINE void store_partial_state(const AttnParams& p, const Decod
   }
 }
 
-// One wave over one item: a run of pool tiles for several queries, or one query's own cache.  lds: kRingBytes of the
-// wave's own.  LOCATE: the item is looked up here, behind the division by the head count (in front of it the same code
+// One wave over one item: a run of pool tiles for several queries, or one query's own cache.  lds: ring_bytes (kRingBytes at
+// least) and kRefBytes of the wave's own.  LOCATE: the item is looked up here, behind the division by the head count (in front of it the same code
 // takes a step of 16 queries 0.7 us longer).
 // ROPE: the query row is un-rotated and is rotated here at the id that stands for the new
 // in-order position of the item's keys (Sec. 2.2), see AttnParams::gm_ref_pad.
 template <int kD, bool ROPE, bool LOCATE>
-__device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it, lds_byte* lds) {
+__device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it, lds_byte* lds, int ring_bytes) {
   using T = HalfTile<kD>;
   const int lane = threadIdx.x % 64, l32 = lane % 32, half = lane / 32;
   const int r = p.head_ratio, rp_log2 = p.column_heads_log2;
@@ -286,6 +306,7 @@ __device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it,
   }
   const int hk = it.hk, pass = it.batch, n_q = it.n_q, first_key = it.first_key, n_keys = it.n_keys, self_u = it.self_u;
   const bool self_item = it.self_item;
+  const int lengths = request_lengths<ROPE>(p);
   // One workgroup per batch of 32 / rp queries of the item: an item that serves more queries than
   // one wave has columns is walked by several workgroups side by side instead of by one workgroup
   // several times, which would make it the last to finish.
@@ -386,17 +407,24 @@ __device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it,
   const int k_base = T::k_base(l32, half), v_base = T::v_base(lane, l32, half);
   const bool scale_rows = ROPE || p.decode_matrix;
   const float prescale = scale_rows ? p.scale_log2e : 1.f, c2 = scale_rows ? 1.f : p.scale_log2e;
-  // ---- this lane's column: query and head ----
-  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp_log2, l32, half);
-
   // ---- wave-private ring: group g + kSlots goes out as soon as the product that reads group g is issued.  The first
   // groups are requested before the query row, so that both latencies run together. ----
+  lds_byte* const refs = lds + ring_bytes;
+  if (ROPE) asm volatile("" : : "v"(lengths));  // (they arrive here, in front of the tiles: see request_references)
+  request_references(p, it, refs);
 #pragma unroll
   for (int g = 0; g < T::kSlots; ++g) {
     if (g >= n_groups) break;
     if (g % 2) issue_v(g / 2);
     else issue_k(g / 2);
   }
+  // the references have landed once only the tiles' groups are outstanding
+  static_for<T::kSlots>([&](auto I) DBSA_INLINE {
+    if (n_groups == decltype(I)::value) wait_vmcnt<decltype(I)::value * T::kLoads>();
+  });
+  if (n_groups >= T::kSlots) wait_vmcnt<T::kSlots * T::kLoads>();
+  // ---- this lane's column: query and head ----
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp_log2, l32, half, refs, lengths);
   bf16x8 qf[kD / 16];
   load_column<kD, ROPE>(col, prescale, qf);
   floatx16 o[kD / 32];
@@ -428,7 +456,7 @@ __device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it,
 template <int kD, bool ROPE>
 __global__ __launch_bounds__(64, 2) void decode_group_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  walk_decode_item<kD, ROPE, true>(p, DecodeItem{}, (lds_byte*)smem);
+  walk_decode_item<kD, ROPE, true>(p, DecodeItem{}, (lds_byte*)smem, HalfTile<kD>::kRingBytes);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -440,8 +468,8 @@ __global__ __launch_bounds__(64, 2) void decode_group_kernel(AttnParams p) {
 // tells that every wave is done with the tile before, whose slot takes the loads of the tile two
 // places on.  Ring of three (K, V) pairs of half tiles: two pairs in flight while one is used.
 constexpr int kPairs = 3;
-template <int kD>
-constexpr int kLdsShared = kPairs * 2 * HalfTile<kD>::kBytes;  // 48 KiB per workgroup: three workgroups per CU (64: 24 KiB)
+template <int kD, int W>
+constexpr int kLdsShared = kPairs * 2 * HalfTile<kD>::kBytes + W * kRefBytes;  // 50 or 52 KiB per workgroup: three workgroups per CU (64: 26 or 28 KiB)
 
 template <int kD, int W, bool ROPE>
 __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams p) {
@@ -465,6 +493,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
   if (wg_batch * W >= n_pass) return;
   const int pass = wg_batch * W + wave;
   const bool active = pass < n_pass;  // a wave without a batch still loads its share and keeps the barriers
+  const int lengths = request_lengths<ROPE>(p);
 
   const __bf16* kbase = self_item ? static_cast<const __bf16*>(p.k_self.ptr) + self_u * p.stride_query +
                                         hk * p.k_self.stride_head
@@ -528,11 +557,15 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
   const int k_base = T::k_base(l32, half), v_base = T::v_base(lane, l32, half);
   const float prescale = ROPE ? p.scale_log2e : 1.f, c2 = ROPE ? 1.f : p.scale_log2e;
 
-  // ---- this lane's column: query and head ----
-  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp_log2, l32, half);
-
+  lds_byte* const refs = lds + kPairs * 2 * T::kBytes + wave * kRefBytes;
+  if (ROPE) asm volatile("" : : "v"(lengths));
+  request_references(p, it, refs);
   issue_pair(0);
   if (1 < n_half) issue_pair(1);
+  if (1 < n_half) wait_vmcnt<4 * kPerWave>();
+  else wait_vmcnt<2 * kPerWave>();
+  // ---- this lane's column: query and head ----
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp_log2, l32, half, refs, lengths);
   bf16x8 qf[kD / 16];
   load_column<kD, ROPE>(col, prescale, qf);
   floatx16 o[kD / 32];
@@ -625,11 +658,12 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
   DecodeItem it;
   if (!locate_decode_item(p, it)) return;
   if (it.self_item) {  // the query's own cache is bf16
-    walk_decode_item<kD, ROPE, false>(p, it, lds);
+    walk_decode_item<kD, ROPE, false>(p, it, lds, kLds8);
     return;
   }
   const int hk = it.hk, pass = it.batch, n_q = it.n_q, first_key = it.first_key, n_keys = it.n_keys;
   const int n_half = (n_keys + kHalf - 1) / kHalf;
+  const int lengths = request_lengths<ROPE>(p);
   if (pass >= (n_q + qpw - 1) / qpw) return;
 
   const unsigned char* kbase = static_cast<const unsigned char*>(p.k_pool.ptr) + hk * p.k_pool.stride_head;
@@ -678,14 +712,20 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
   const int k8_swz = l32 % 8;
   const int v_base = HalfTile<kD>::v_base(lane, l32, half);
 
-  // ---- this lane's column (ROPE as in decode_group_kernel: the stored keys keep their encoding-time rotation) ----
-  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp_log2, l32, half);
+  lds_byte* const refs = lds + kLds8;
+  if (ROPE) asm volatile("" : : "v"(lengths));
+  request_references(p, it, refs);
   issue_k(0);
   issue_v(0);
   if (1 < n_half) {
     issue_k(1);
     issue_v(1);
+    wait_vmcnt<4 * kLoads8>();
+  } else {
+    wait_vmcnt<2 * kLoads8>();
   }
+  // ---- this lane's column (ROPE as in decode_group_kernel: the stored keys keep their encoding-time rotation) ----
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, true, r, rp_log2, l32, half, refs, lengths);
   const KeyFactor c8 = split_key_factor<ROPE>(p.scale_log2e * p.k_scale8[hk]);
   const float v_scale = p.v_scale8[hk];
   bf16x8 qf[kD / 16];
@@ -756,7 +796,8 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
 // arithmetic on that pair.  Two barriers per half tile: before the widening (every wave is done
 // with the working pair of the half tile before) and after it (the working pair is complete).
 constexpr int kStagePair8 = 2 * kSlot8;                               // 8 KiB of bytes per (K, V) half tile
-constexpr int kLdsShared8 = kPairs * kStagePair8 + kPairBytes;        // 24 KiB staging + 16 KiB working pair
+template <int W>
+constexpr int kLdsShared8 = kPairs * kStagePair8 + kPairBytes + W * kRefBytes;  // 24 KiB staging + 16 KiB working pair + references
 
 template <int W, bool ROPE>
 __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnParams p) {
@@ -779,6 +820,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
   if (wg_batch * W >= n_pass) return;  // (the same for all waves: the workgroup leaves as one)
   const int pass = wg_batch * W + wave;
   const bool active = pass < n_pass;
+  const int lengths = request_lengths<ROPE>(p);
 
   const unsigned char* kbase = static_cast<const unsigned char*>(p.k_pool.ptr) + hk * p.k_pool.stride_head;
   const unsigned char* vbase = static_cast<const unsigned char*>(p.v_pool.ptr) + hk * p.v_pool.stride_head;
@@ -835,10 +877,15 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
 
   const int k_base = HalfTile<kD>::k_base(l32, half), v_base = HalfTile<kD>::v_base(lane, l32, half);
 
-  // ---- this lane's column ----
-  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp_log2, l32, half);
+  lds_byte* const refs = lds + kPairs * kStagePair8 + kPairBytes + wave * kRefBytes;
+  if (ROPE) asm volatile("" : : "v"(lengths));
+  request_references(p, it, refs);
   issue_pair(0);
   if (1 < n_half) issue_pair(1);
+  if (1 < n_half) wait_vmcnt<4 * kPerWave>();
+  else wait_vmcnt<2 * kPerWave>();
+  // ---- this lane's column ----
+  const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp_log2, l32, half, refs, lengths);
   const KeyFactor c8 = split_key_factor<ROPE>(p.scale_log2e * p.k_scale8[hk]);
   const float v_scale = p.v_scale8[hk];
   bf16x8 qf[kD / 16];
@@ -961,16 +1008,16 @@ hipError_t launch_shared8(const AttnParams& p, hipStream_t stream) {
   if (!attr_set) {
     for (const void* f : {reinterpret_cast<const void*>(decode_group_kv8_shared_kernel<W, false>),
                           reinterpret_cast<const void*>(decode_group_kv8_shared_kernel<W, true>)}) {
-      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsShared8);
+      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsShared8<W>);
       if (e != hipSuccess) return e;
     }
     attr_set = true;
   }
   const dim3 grid = decode_grid(p), block(64 * W);
   if (p.rope_table)
-    decode_group_kv8_shared_kernel<W, true><<<grid, block, kLdsShared8, stream>>>(p);
+    decode_group_kv8_shared_kernel<W, true><<<grid, block, kLdsShared8<W>, stream>>>(p);
   else
-    decode_group_kv8_shared_kernel<W, false><<<grid, block, kLdsShared8, stream>>>(p);
+    decode_group_kv8_shared_kernel<W, false><<<grid, block, kLdsShared8<W>, stream>>>(p);
   return hipGetLastError();
 }
 }  // namespace
@@ -990,9 +1037,9 @@ hipError_t launch_merge(const AttnParams& p, hipStream_t stream) {
 template <int kD, int W, bool ROPE>
 hipError_t launch_rows(const AttnParams& p, hipStream_t stream) {
   if constexpr (W == 1) {
-    decode_group_kernel<kD, ROPE><<<decode_grid(p), dim3(64), HalfTile<kD>::kRingBytes, stream>>>(p);
+    decode_group_kernel<kD, ROPE><<<decode_grid(p), dim3(64), HalfTile<kD>::kRingBytes + kRefBytes, stream>>>(p);
   } else {
-    decode_group_shared_kernel<kD, W, ROPE><<<decode_grid(p), dim3(64 * W), kLdsShared<kD>, stream>>>(p);
+    decode_group_shared_kernel<kD, W, ROPE><<<decode_grid(p), dim3(64 * W), kLdsShared<kD, W>, stream>>>(p);
   }
   return hipGetLastError();
 }
@@ -1013,21 +1060,22 @@ hipError_t launch_decode_group_kv8(const AttnParams& p_in, hipStream_t stream) {
   hipError_t e;
   p.row_offset = 0;
   if (p.decode_waves == 1) {
-    p.launch_rows = p.gm_n_rows;
+    p.launch_rows = p.n_self_blocks + p.gm_pool_rows;
     if (p.rope_table)
-      decode_group_kv8_kernel<true><<<decode_grid(p), dim3(64), kLds8, stream>>>(p);
+      decode_group_kv8_kernel<true><<<decode_grid(p), dim3(64), kLds8 + kRefBytes, stream>>>(p);
     else
-      decode_group_kv8_kernel<false><<<decode_grid(p), dim3(64), kLds8, stream>>>(p);
+      decode_group_kv8_kernel<false><<<decode_grid(p), dim3(64), kLds8 + kRefBytes, stream>>>(p);
     e = hipGetLastError();
   } else {
     e = hipSuccess;
     if (p.n_gm_items > 0) {
+      p.row_offset = p.n_self_blocks;
       p.launch_rows = p.gm_pool_rows;
       e = p.decode_waves == 4 ? launch_shared8<4>(p, stream) : launch_shared8<2>(p, stream);
     }
     if (e != hipSuccess) return e;
-    p.row_offset = p.gm_pool_rows;
-    p.launch_rows = p.gm_n_rows - p.gm_pool_rows;
+    p.row_offset = 0;
+    p.launch_rows = p.n_self_blocks;
     e = launch_waves<1>(p, 128, stream);
   }
   return e == hipSuccess ? launch_merge<128>(p, stream) : e;
@@ -1055,12 +1103,12 @@ hipError_t launch_decode_group(const AttnParams& p_in, int head_dim, hipStream_t
     g.lse = nullptr;
     e = launch_decode_matrix_items(g, stream);
     if (e != hipSuccess) return e;
-    p.row_offset = p.gm_pool_rows;
-    p.launch_rows = p.gm_n_rows - p.gm_pool_rows;
+    p.row_offset = 0;
+    p.launch_rows = p.n_self_blocks;
     e = launch_waves<1>(p, head_dim, stream);
   } else {
     p.row_offset = 0;
-    p.launch_rows = p.gm_n_rows;
+    p.launch_rows = p.n_self_blocks + p.gm_pool_rows;
     e = p.decode_waves == 4 ? launch_waves<4>(p, head_dim, stream)
         : p.decode_waves == 2 ? launch_waves<2>(p, head_dim, stream)
                               : launch_waves<1>(p, head_dim, stream);

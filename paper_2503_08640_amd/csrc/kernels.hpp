@@ -41,12 +41,12 @@ struct AttnParams {
   float* partial;             // decode: [slot][Hq][D + kPartialPad]; per-query splits use slot = u*n_split + s;
                               // split prefill: [row][Hq][q_split][D + kPartialPad];
                               // prefill with cut lists: [partial row][Hq][D + kPartialPad], see sched_part
-  // group-major decode launch: workgroup id -> row (id / 8) % launch_rows of gm_rows + row_offset,
-  // KV head (id / 8) / launch_rows, item 8 * block + id % 8 of the row's block; blocks below
-  // n_pool_blocks hold pool items, the others self items (one per query)
-  const int32_t* gm_rows;     // (block << 8 | query batch), pool rows first
-  int32_t gm_n_rows, gm_pool_rows;
-  int32_t n_pool_blocks;
+  // group-major decode launch: workgroup id -> row row_offset + (id / 8) % launch_rows, KV head (id / 8) / launch_rows, item
+  // 8 * block + id % 8 of the row's block.  Rows: n_self_blocks blocks of self items (one per query), then gm_pool_rows
+  // of pool items: batch 0 of blocks 0 .. gm_direct-1, and those in gm_rows
+  const int32_t* gm_rows;     // (block << 8 | query batch)
+  int32_t gm_pool_rows, gm_direct;
+  int32_t n_self_blocks;
   int32_t row_offset, launch_rows;
   const float* k_scale8;      // decode over an fp8 pool: k = k8 * k_scale8[kv head], v = v8 * v_scale8[kv head]
   const float* v_scale8;

@@ -477,16 +477,23 @@ int dbsa_build_host_lists(const dbsa_pool_desc* pool, const dbsa_select_desc* se
   }
   if (L->query_stage) {
     const int32_t n_items = static_cast<int32_t>(L->gm_items.size() / 4);
-    const int32_t pool_blocks = (n_items + 7) / 8, self_blocks = (L->n_queries + 7) / 8;
+    const int32_t pool_blocks = (n_items + 7) / 8;
     for (int k = 0; k < 6; ++k) {
       const int32_t per_wave = 32 >> k;
-      L->gm_rows_off[k] = static_cast<int32_t>(L->gm_rows.size());
+      std::vector<int32_t> batches(static_cast<size_t>(pool_blocks), 0);
+      int64_t more = 0;
       for (int32_t b = 0; b < pool_blocks; ++b) {
         int32_t most = 0;
         for (int32_t it = 8 * b; it < std::min(n_items, 8 * b + 8); ++it) most = std::max(most, L->gm_items[4 * it + 3]);
-        for (int32_t z = 0; z * per_wave < most; ++z) L->gm_rows.push_back((b << 8) | z);
+        batches[static_cast<size_t>(b)] = (most + per_wave - 1) / per_wave;
+        more += batches[static_cast<size_t>(b)] - 1;
       }
-      L->gm_pool_rows[k] = static_cast<int32_t>(L->gm_rows.size()) - L->gm_rows_off[k];
+      // While few blocks have a second batch the first batches need no table (one look-up less in front of the first
+      // tiles); otherwise the batches of a block stay next to each other, all in the table.
+      L->gm_direct[k] = 4 * more <= pool_blocks ? pool_blocks : 0;
+      L->gm_rows_off[k] = static_cast<int32_t>(L->gm_rows.size());
+      for (int32_t b = 0; b < pool_blocks; ++b)
+        for (int32_t z = L->gm_direct[k] ? 1 : 0; z < batches[static_cast<size_t>(b)]; ++z) L->gm_rows.push_back((b << 8) | z);
       // how often a key of the pool items is walked when a wave takes per_wave queries
       double keys = 0.0, walked = 0.0;
       for (int32_t it = 0; it < n_items; ++it) {
@@ -495,7 +502,6 @@ int dbsa_build_host_lists(const dbsa_pool_desc* pool, const dbsa_select_desc* se
         walked += n * ((L->gm_item_run[4 * it + 2] + per_wave - 1) / per_wave);
       }
       L->gm_walks_per_key[k] = keys > 0.0 ? static_cast<float>(walked / keys) : 1.f;
-      for (int32_t b = 0; b < self_blocks; ++b) L->gm_rows.push_back((pool_blocks + b) << 8);
     }
     L->gm_rows_off[6] = static_cast<int32_t>(L->gm_rows.size());
   }

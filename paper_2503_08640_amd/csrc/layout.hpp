@@ -101,12 +101,12 @@ struct dbsa_layout {
   // tail repeating the last real reference
   std::vector<int32_t> gm_item_run; // [n_items][4]
   std::vector<int32_t> gm_ref_pad;  // [n_items][32][4]
-  // launch rows of the decode kernel, one table per number of queries a wave takes (32 >> k,
+  // launch rows of the decode kernel's pool items, one table per number of queries a wave takes (32 >> k,
   // k = 0..5): a row is (block of 8 work items) << 8 | query batch, listed only where some item of
-  // the block has that many queries; blocks of pool items first, then blocks of self items
+  // the block has that many queries; batch 0 of the first gm_direct[k] blocks is not listed
   std::vector<int32_t> gm_rows;
   int32_t gm_rows_off[7] = {0, 0, 0, 0, 0, 0, 0};   // table k is gm_rows[off[k] .. off[k+1])
-  int32_t gm_pool_rows[6] = {0, 0, 0, 0, 0, 0};     // rows of table k that belong to pool items
+  int32_t gm_direct[6] = {0, 0, 0, 0, 0, 0};
   float gm_walks_per_key[6] = {1, 1, 1, 1, 1, 1};   // batches per pool item at 32 >> k queries per wave, weighted by keys
   // Records for steps that run as a contraction (64 query rows per wave): [n_mx][4] = (first reference,
   // references (at most 64), first tile entry in gm_seg_ent, entries).  mx_row_fill: share of the 64 rows
