@@ -134,6 +134,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   // rotated once per record, each at its own id
   constexpr bool kEntryIds = ROPE && !GATHER;
   constexpr bool kPieces = PERSIST && SELF;  // records may be pieces of a Q tile's list
+  // The table rows of the positions a Q tile is rotated at lie in LDS, behind the stages (four waves, at most 64 tokens):
+  // read from memory, lanes 512 bytes apart, every load costs the address unit 64 lines, and each of the four heads
+  // repeats them: a rotation took 6.5 us of a lone question's 50.  The rows of the next segment come as whole lines, once
+  // per workgroup, a period before they are needed; what is left is the rows of Q (2-3 us).  One question of 64 tokens
+  // 60.1 -> 53.7 us, six of 100 tokens over 25 groups 167 -> 152, 16 of 64 tokens 450 -> 438; same bits.  (Two waves have
+  // no LDS left: 80 KiB each, two to a compute unit.)
+  constexpr bool kStagedTable = kEntryIds && NW == 4;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   constexpr int kRowBytes = kD * 2;            // 256 or 128
   constexpr int kTileBytes = kBN * kRowBytes;  // 16 or 8 KiB per K or V tile
@@ -332,6 +339,24 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       nx_n = sched[4 * (f_k + 1) + 3];
     }
   }
+  // kStagedTable: rows shift .. shift + block_m - 1 of the table into LDS, 16-byte piece s of row i in place s ^ (i % 32)
+  // (whoever reads the rows that lie there has met the others since)
+  const bool staged = kStagedTable && p.block_m <= 64;
+  const unsigned table_at = lds0 + (KS + VS) * kTileBytes;
+  int table_shift = 0;
+  auto stage_table = [&](int shift) DBSA_INLINE {
+    table_shift = shift;
+    const int first = min(max(shift, 0), p.rope_n_pos - 1), rows_per_wave = p.block_m / NW;
+    const uint64_t base = uniform64(reinterpret_cast<uint64_t>(p.rope_table + static_cast<int64_t>(first) * kD));
+#pragma unroll
+    for (int b = 0; b < 8; ++b)
+      if (2 * b < rows_per_wave) {
+        const int row = wave * rows_per_wave + 2 * b + lane / 32;
+        const int id = min(max(shift + row, 0), p.rope_n_pos - 1);
+        dma16(base, static_cast<unsigned>((id - first) * kD * 4 + ((lane % 32) ^ (row % 32)) * 16), table_at + (wave * rows_per_wave + 2 * b) * (kD * 4));
+      }
+  };
+
   int in_w0 = 0, in_w1 = 0, in_w2 = 0;  // the entry requested last (ROPE: and its rotation id)
   auto request_entry = [&]() DBSA_INLINE {
     if (__builtin_expect(f_left == 0, 0)) {
@@ -359,26 +384,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     }
     f_left -= 1;
   };
-
-  // (rw0, rw1)[i] = words of the entry i tiles ahead of the one whose scores the current period computes
-  int rw0[2 + SL], rw1[2 + SL], rw2[2 + SL];
-#pragma unroll
-  for (int i = 0; i < 2 + SL; ++i) {
-    request_entry();
-    rw0[i] = in_w0;
-    rw1[i] = in_w1;
-    rw2[i] = in_w2;
-  }
-  // K(0 .. SL) and V(0 .. SL-2) of the stream go out now, in the order later periods keep
-  // (K(i), V(i-2)); the period of tile j issues K(j+1+SL) and V(j-1+SL)
-  issue_k(decode_ref(rw0[0], rw1[0]), 0);
-  issue_k(decode_ref(rw0[1], rw1[1]), 1);
-#pragma unroll
-  for (int i = 2; i <= SL; ++i) {
-    issue_k(decode_ref(rw0[i], rw1[i]), i);
-    issue_v(decode_ref(rw0[i - 2], rw1[i - 2]), i - 2);
-  }
-  int k_wr = (1 + SL) % KS, v_wr = (SL - 1) % VS;  // stages the next period's loads fill
 
   // ---- per Q tile: rows, Q^T fragments, softmax state ----
   const float c2 = p.scale_log2e;
@@ -427,6 +432,35 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll
       for (int c = 0; c < kD / 16; ++c) q_raw[rb][c] = *reinterpret_cast<const bf16x8*>(q_next[rb] + 16 * c);
   };
+  // (kStagedTable: requested in front of the first tiles, so that they arrive with the table's rows)
+  if constexpr (kStagedTable) {
+    place_rows();
+    load_q();
+  }
+
+  // (rw0, rw1)[i] = words of the entry i tiles ahead of the one whose scores the current period computes
+  int rw0[2 + SL], rw1[2 + SL], rw2[2 + SL];
+#pragma unroll
+  for (int i = 0; i < 2 + SL; ++i) {
+    request_entry();
+    rw0[i] = in_w0;
+    rw1[i] = in_w1;
+    rw2[i] = in_w2;
+  }
+  if constexpr (kStagedTable) {
+    if (staged) stage_table(rw2[0]);
+  }
+  // K(0 .. SL) and V(0 .. SL-2) of the stream go out now, in the order later periods keep
+  // (K(i), V(i-2)); the period of tile j issues K(j+1+SL) and V(j-1+SL)
+  issue_k(decode_ref(rw0[0], rw1[0]), 0);
+  issue_k(decode_ref(rw0[1], rw1[1]), 1);
+#pragma unroll
+  for (int i = 2; i <= SL; ++i) {
+    issue_k(decode_ref(rw0[i], rw1[i]), i);
+    issue_v(decode_ref(rw0[i - 2], rw1[i - 2]), i - 2);
+  }
+  int k_wr = (1 + SL) % KS, v_wr = (SL - 1) % VS;  // stages the next period's loads fill
+
   intx4 qf[2][kD / 16];  // Q^T fragments (pre-multiplied by scale*log2(e) unless kRawQ), in accumulation registers
   auto scale_q = [&]() DBSA_INLINE {
 #pragma unroll
@@ -452,16 +486,31 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   // ROPE: the fragments of both row blocks from the rows in memory, rotated at shift + row index and
   // pre-multiplied like scale_q's (rare: once per segment of a list)
   int cur_shift = 0;
-  auto rotate_q = [&](int shift) DBSA_INLINE {
+  auto rotate_q = [&](int shift, auto FROM_RAW) DBSA_INLINE {
+    constexpr bool kFromRaw = decltype(FROM_RAW)::value;  // the rows are in q_raw
     cur_shift = shift;
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       const __bf16* qp = static_cast<const __bf16*>(p.q.ptr) + static_cast<int64_t>(row_tok[rb]) * p.q.stride_tok +
                          static_cast<int64_t>(head[rb]) * p.q.stride_head + 8 * half;
       const int id = min(max(GATHER ? row_rot[rb] : shift + row_local[rb], 0), p.rope_n_pos - 1);
-      const float* rot = p.rope_table + static_cast<int64_t>(id) * kD + 16 * half;
       bf16x8 frag[8];
-      load_query_fragments<true>(qp, rot, c2, frag);
+      if (kStagedTable && staged) {
+        const unsigned row_at = table_at + static_cast<unsigned>(row_local[rb]) * (kD * 4);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const bf16x8 lo = kFromRaw ? q_raw[rb][c] : *reinterpret_cast<const bf16x8*>(qp + 16 * c);
+          const bf16x8 hi = kFromRaw ? q_raw[rb][c + 4] : *reinterpret_cast<const bf16x8*>(qp + 16 * (c + 4));
+          floatx4 cs[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            cs[j] = *(reinterpret_cast<const __attribute__((address_space(3))) floatx4*>(
+                static_cast<uintptr_t>(row_at + static_cast<unsigned>(((4 * half + 8 * c + j) ^ l32) * 16))));
+          rotate_pair(lo, hi, cs, c2, frag[c], frag[c + 4]);
+        }
+      } else {
+        load_query_fragments<true>(qp, p.rope_table + static_cast<int64_t>(id) * kD + 16 * half, c2, frag);
+      }
 #pragma unroll
       for (int c = 0; c < kD / 16; ++c) {
         qf[rb][c] = __builtin_bit_cast(intx4, frag[c]);
@@ -470,8 +519,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     }
     valu_result_fence();
   };
-  place_rows();
-  if constexpr (!ROPE) load_q();
+  if constexpr (kStagedTable) {
+    if (staged) {  // the table's rows have landed once only the tiles' loads are outstanding
+      wait_vmcnt<2 * SL * kBlocksPerWave>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
+    rotate_q(rw2[0], std::true_type{});
+  } else {
+    place_rows();
+    if constexpr (!ROPE) load_q();
+  }
 
   floatx16 o[2][kD / 32];
   floatx16 neg_m[2];                     // minus the running maximum (in units of the scores) in every element: C operand of a score block's first product
@@ -769,10 +827,23 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     __builtin_amdgcn_s_barrier();
   };
 
+  // kStagedTable: if the next entry is rotated at other positions than the table rows in LDS stand for, theirs are
+  // requested, in front of this period's tile loads: the barrier at the next period's start covers them.  read_now: this
+  // wave has read the rows since the last barrier, and so may others still be doing.
+  auto stage_next = [&](bool read_now) DBSA_INLINE {
+    if constexpr (kStagedTable) {
+      if (__builtin_expect(staged && rw2[1] != table_shift, 0)) {
+        if (read_now) __builtin_amdgcn_s_barrier();
+        stage_table(rw2[1]);
+      }
+    }
+  };
+
   for (;;) {
     // ---- a Q tile: its rows of Q are in q_raw (requested before the previous tile's epilogue) ----
-    if constexpr (ROPE)
-      rotate_q(kEntryIds ? rw2[0] : 0);
+    if constexpr (kStagedTable) {
+    } else if constexpr (ROPE)
+      rotate_q(kEntryIds ? rw2[0] : 0, std::false_type{});
     else
       scale_q();
     int nq_start = 0, nq_len = 0, nq_e0 = 0, nq_n = 0, nq_part = -1;  // PERSIST: the record after this one
@@ -808,6 +879,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     request_entry();
     {
       const TileRef t0 = decode_ref(rw0[0], rw1[0]);
+      stage_next(false);
       aim_k();
       step(StepCfg<true, false, false, 0, 0, false, false, 1, true>{}, s_e, s_o, p_o, p_e, t0);
       aim_v();
@@ -823,7 +895,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       if constexpr (kEntryIds) {
         // this period computes the scores of an entry of another segment: rebuild Q for it (every matrix
         // instruction that read the old fragments was issued a period ago)
-        if (__builtin_expect(rw2[0] != cur_shift, 0)) rotate_q(rw2[0]);
+        const bool rotated = rw2[0] != cur_shift;
+        if (__builtin_expect(rotated, 0)) rotate_q(rw2[0], std::false_type{});
+        stage_next(rotated);
       }
       aim_k();
       step(StepCfg<true, true, true, 0, 0, true, true, 1, true>{}, s_e, s_o, p_o, p_e, tq);
@@ -979,13 +1053,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       }
     }
     if (!more) break;
+    if constexpr (kStagedTable) rotate_q(rw2[0], std::false_type{});
   }
 }
 
 template <int kD, int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false>
 hipError_t launch_cfg64(const AttnParams& p, hipStream_t stream) {
   // (four waves over tiles of 8 KiB: two more for the epilogue)
-  constexpr int lds_bytes = (3 + 2 * SL + (NW == 4 && kD == 64 ? 2 : 0)) * kBN * kD * 2;
+  // (re-positioned query prefill of four waves: the rotation table's rows of 64 tokens)
+  constexpr int lds_bytes = (3 + 2 * SL + (NW == 4 && kD == 64 ? 2 : 0)) * kBN * kD * 2 + (ROPE && !GATHER && NW == 4 ? 64 * kD * 4 : 0);
   static std::atomic<bool> attr_set{false};  // setting it twice from two threads is harmless
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill64_kernel<kD, NW, SL, SELF, PERSIST, GATHER, ROPE>),

@@ -101,6 +101,24 @@ __device__ inline void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
+// Channels lo (d ..) and hi (d + 64 ..) of a row rotated by the (cos, sin) pairs cs and multiplied by c2, rounded to bf16.
+__device__ DBSA_INLINE void rotate_pair(const bf16x8& lo, const bf16x8& hi, const floatx4* cs, float c2, bf16x8& out_lo, bf16x8& out_hi) {
+  union {
+    bf16x8 v;
+    bf16x2 p2[4];
+  } a, b;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float x0 = static_cast<float>(lo[2 * e]), y0 = static_cast<float>(hi[2 * e]);
+    const float x1 = static_cast<float>(lo[2 * e + 1]), y1 = static_cast<float>(hi[2 * e + 1]);
+    const float c0 = cs[e][0] * c2, s0 = cs[e][1] * c2, c1 = cs[e][2] * c2, s1 = cs[e][3] * c2;
+    a.p2[e] = __builtin_convertvector(floatx2{x0 * c0 - y0 * s0, x1 * c1 - y1 * s1}, bf16x2);
+    b.p2[e] = __builtin_convertvector(floatx2{y0 * c0 + x0 * s0, y1 * c1 + x1 * s1}, bf16x2);
+  }
+  out_lo = a.v;
+  out_hi = b.v;
+}
+
 // The 8 B-operand fragments of one score column for head_dim 128: the query row (qp points at this
 // lane's first channel, 8 * half), pre-multiplied by c2 = scale * log2 e and rounded to bf16 again.
 // ROPE: the row is stored un-rotated and is rotated here with the table row `rot` (16 floats = cos,
@@ -117,20 +135,7 @@ __device__ DBSA_INLINE void load_query_fragments(const __bf16* qp, const float* 
       floatx4 cs[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) cs[j] = *reinterpret_cast<const floatx4*>(rot + 32 * c + 4 * j);
-      union {
-        bf16x8 v;
-        bf16x2 p2[4];
-      } a, b;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float x0 = static_cast<float>(lo[2 * e]), y0 = static_cast<float>(hi[2 * e]);
-        const float x1 = static_cast<float>(lo[2 * e + 1]), y1 = static_cast<float>(hi[2 * e + 1]);
-        const float c0 = cs[e][0] * c2, s0 = cs[e][1] * c2, c1 = cs[e][2] * c2, s1 = cs[e][3] * c2;
-        a.p2[e] = __builtin_convertvector(floatx2{x0 * c0 - y0 * s0, x1 * c1 - y1 * s1}, bf16x2);
-        b.p2[e] = __builtin_convertvector(floatx2{y0 * c0 + x0 * s0, y1 * c1 + x1 * s1}, bf16x2);
-      }
-      qf[c] = a.v;
-      qf[c + kQD / 32] = b.v;
+      rotate_pair(lo, hi, cs, c2, qf[c], qf[c + kQD / 32]);
     }
   } else {
 #pragma unroll

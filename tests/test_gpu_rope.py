@@ -94,6 +94,20 @@ def test_repositioned_query_and_decode_small(hq, hkv, block_m, base):
     _repositioned_case(pc, qc, block_m, base, decode_steps=range(3), what=f"Hq={hq} Hkv={hkv}")
 
 
+@pytest.mark.parametrize("hq,hkv,block_m,n_queries", [(8, 2, 64, 6), (8, 1, 32, 6), (4, 4, 32, 3), (64, 16, 64, 40)])
+def test_repositioned_prefill_over_groups_of_one_tile(hq, hkv, block_m, n_queries):
+    """Every list entry is a segment of its own, so the rows are rotated anew in every period while the next entry's
+    table rows are on their way (workgroups of four waves); 40 queries over 16 KV heads walk whole lists one after the
+    other, few cut them into pieces."""
+    pc = synth.make_pool_case("ropeshort", 4040 + hq, dtype="bf16", n_q_heads=hq, n_kv_heads=hkv, head_dim=128,
+                              sink_len=40, pool_tokens=1200, demo_len_range=(40, 60), n_groups=22, k_channel_sigma=0.35)
+    rng = np.random.default_rng(17)
+    sels = [[int(g) for g in rng.permutation(22)[:rng.integers(0, 23)]] for _ in range(n_queries)]
+    q_len = [64, 37, 130, 1, 33, 70] if n_queries == 6 else [int(x) for x in rng.integers(1, 80, size=n_queries)]
+    qc = synth.make_query_case("ropeshortq", 4041, pc, n_queries=n_queries, q_len=q_len, selections=sels, n_decode=0)
+    _repositioned_case(pc, qc, block_m, 10000.0, what=f"one-tile groups Hq={hq} Hkv={hkv}")
+
+
 @pytest.mark.parametrize("hq,hkv", [(8, 2), (4, 2), (16, 2)])
 def test_repositioned_decode_with_many_queries_per_group(hq, hkv):
     """40 queries on 3 groups: every group serves several batches of 32 / r queries, so the decode step runs the
