@@ -543,9 +543,22 @@ size_t decode_workspace_need(const dbsa_layout* L, int32_t n_q_heads, int32_t he
 
 // Workgroups of a prefill-shaped launch that the chip holds at once: those of eight row blocks (four waves of 64 rows)
 // sit alone on a compute unit, smaller ones in pairs, and at head_dim 64 those of two row blocks (one wave) in fours.
-int64_t prefill_places(const dbsa_layout* L, int row_blocks, int head_dim) {
-  if (row_blocks == 8) return workgroup_slots(L) / 2;
-  return workgroup_slots(L) * (head_dim == 64 && row_blocks == 2 ? 2 : 1);
+// crowded: at head_dim 64 those of four and eight row blocks twice as many, two waves to a SIMD (crowd_launch).
+int64_t prefill_places(const dbsa_layout* L, int row_blocks, int head_dim, bool crowded) {
+  const int64_t single = row_blocks == 8 ? workgroup_slots(L) / 2 : workgroup_slots(L) * (head_dim == 64 && row_blocks == 2 ? 2 : 1);
+  return crowded ? 2 * single : single;
+}
+
+// Whether a launch runs two waves to a SIMD, whose exponentials fill each other's gaps: at head_dim 64 the registers allow
+// it (256 each; not the one-wave workgroups, which LDS holds to four).  It takes workgroups for most of the places: a list
+// runs at little more than half its speed beside another, so that a launch whose longest list decides only loses.  Query
+// prefill (lists of about one length) from three quarters of the places on: 100 questions of 20 tokens, 0.78, 273 -> 255 us;
+// 12 of 400, 1.3, 412 -> 370; encoding from nine tenths on: 63 lists x 8 head blocks, 0.98, 501 -> 431 us, 6000 tokens of
+// 16 heads, 0.75, 55 -> 64.
+bool crowd_launch(const dbsa_layout* L, int row_blocks, int head_dim, int64_t head_blocks) {
+  if (head_dim != 64 || (row_blocks != 4 && row_blocks != 8)) return false;
+  const int64_t wgs = L->n_qtiles() * head_blocks, places = prefill_places(L, row_blocks, head_dim, true);
+  return L->query_stage ? 4 * wgs >= 3 * places : 10 * wgs >= 9 * places;
 }
 
 // Runs per list of a launch of `wgs` workgroups (one run each) on `places`: the number that makes rounds * length
@@ -577,15 +590,20 @@ size_t query_prefill_states(const dbsa_layout* L, int32_t n_q_heads, int32_t hea
   for (int hpb = 1; hpb <= 8; hpb *= 2) {
     const int row_blocks = hpb * (L->block_m / 32);
     if (row_blocks < 1 || row_blocks > 8) continue;
-    const int64_t head_blocks = (n_q_heads + hpb - 1) / hpb, places = prefill_places(L, row_blocks, head_dim), states = int64_t{1} * L->n_query_tokens * n_q_heads;
-    if (schedulable(row_blocks, head_dim)) {
-      const int64_t classes = std::min<int64_t>(places / head_blocks, kMaxSchedClasses);
-      const int64_t cuts = std::max<int64_t>(0, dbsa_cut_workers(L, classes) - 1);
-      const int64_t pieces = std::min(2 * cuts, cuts + L->n_qtiles());
-      if (L->n_qtiles() < kCutTiles * classes) most = std::max(most, static_cast<size_t>(pieces * L->largest_tile * n_q_heads));
+    const int64_t head_blocks = (n_q_heads + hpb - 1) / hpb, states = int64_t{1} * L->n_query_tokens * n_q_heads;
+    // (head ratios hpb does not divide have more head blocks: either number of places)
+    for (const bool crowded : {false, true}) {
+      const int64_t places = prefill_places(L, row_blocks, head_dim, crowded);
+      if (crowded && (head_dim != 64 || row_blocks < 4)) continue;
+      if (schedulable(row_blocks, head_dim)) {
+        const int64_t classes = std::min<int64_t>(places / head_blocks, kMaxSchedClasses);
+        const int64_t cuts = std::max<int64_t>(0, dbsa_cut_workers(L, classes) - 1);
+        const int64_t pieces = std::min(2 * cuts, cuts + L->n_qtiles());
+        if (L->n_qtiles() < kCutTiles * classes) most = std::max(most, static_cast<size_t>(pieces * L->largest_tile * n_q_heads));
+      }
+      const int64_t runs = query_runs(L, L->n_qtiles() * head_blocks, places, states);
+      if (runs > 1) most = std::max(most, static_cast<size_t>(runs * states));
     }
-    const int64_t runs = query_runs(L, L->n_qtiles() * head_blocks, places, states);
-    if (runs > 1) most = std::max(most, static_cast<size_t>(runs * states));
   }
   return most;
 }
@@ -707,7 +725,9 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
     p.q_split = 1;
     const int row_blocks = p.heads_per_block * (L->block_m / 32);
     const bool pipelined = max_stride < (int64_t{1} << 24) && (d == 128 || schedulable(row_blocks, d));
-    const int64_t head_blocks = hkv * ((hq / hkv + p.heads_per_block - 1) / p.heads_per_block), places = prefill_places(L, row_blocks, d);
+    const int64_t head_blocks = hkv * ((hq / hkv + p.heads_per_block - 1) / p.heads_per_block);
+    p.crowded = crowd_launch(L, row_blocks, d, head_blocks) ? 1 : 0;
+    const int64_t places = prefill_places(L, row_blocks, d, p.crowded != 0);
     p.n_head_blocks = static_cast<int32_t>(head_blocks);
     const size_t state_bytes = (d + kPartialPad) * sizeof(float);
     const size_t room = workspace && reinterpret_cast<uintptr_t>(workspace) % 16 == 0 ? workspace_bytes / state_bytes : 0;

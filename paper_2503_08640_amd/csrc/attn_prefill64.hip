@@ -63,6 +63,9 @@ typedef int intx4 __attribute__((ext_vector_type(4)));
 __device__ DBSA_INLINE void mfma_scores_first(floatx16& d, const bf16x8& k, const intx4& q, const floatx16& c) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(__builtin_bit_cast(intx4, k)), "a"(q), "v"(c));
 }
+__device__ DBSA_INLINE void mfma_scores_first(floatx16& d, const bf16x8& k, const intx4& q) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(__builtin_bit_cast(intx4, k)), "a"(q));
+}
 __device__ DBSA_INLINE void mfma_scores_acc(floatx16& d, const bf16x8& k, const intx4& q) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(__builtin_bit_cast(intx4, k)), "a"(q));
 }
@@ -126,8 +129,14 @@ struct StepCfg {
 // the shift, so the fragments are rebuilt only where it changes, from the rows in memory.
 // With GATHER (decode step) a record lies inside one segment, so its rows are rotated once, at the record's
 // start, each at its own id gather_shift[reference] + self_len[query] - 1.
-template <int kD, int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_prefill64_kernel(AttnParams p) {
+//
+// CROWD (head_dim 64, where 256 registers hold a wave): two waves to a SIMD instead of one.  A step there is 16 matrix
+// instructions (512 cycles) beside 112 vector ones, 32 of them exponentials; alone, an in-order wave takes 1200 cycles for
+// it, two waves fill each other's gaps: 0.87 us per 64-key tile and wave against 1.21.  32k tokens, 32/8 heads, encode
+// 650 -> 575 us, 16/16 heads 400 -> 340, 5000 tokens 61 -> 52, one group appended 504 -> 431, 12 questions of 400 tokens
+// 425 -> 378, 100 of 20 tokens 275 -> 254.  (Wave priorities in turn, so that the older wave does not run ahead: +-2 %.)
+template <int kD, int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false, bool CROWD = false>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(CROWD ? 2 : 1, CROWD ? 2 : 1))) void attn_prefill64_kernel(AttnParams p) {
   static_assert(!GATHER || (PERSIST && !SELF), "gathered rows come with a schedule and pool tiles only");
   static_assert(!ROPE || (SELF != GATHER), "rows are re-positioned at the query prefill and at the decode step");
   // the query prefill rotates a Q tile per list entry (the ids ride with the entries); gathered rows are
@@ -156,10 +165,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   // as they are, scores are raw dot products and a probability costs a multiplication more (the rounding of the
   // scaled row weighs twice as much over half the channels; the matrix pipe waits for the exponentials either way).
   constexpr bool kRawQ = kD == 64;
+  // CROWD: scores start at zero and the multiplication that scales them takes the running maximum off as well, which saves
+  // the 32 registers the maxima fill as the first product's C operand (alone on a SIMD that form is 1 % slower).
+  constexpr bool kFromZero = CROWD;
   constexpr int kBlocksPerWave = kTileBytes / 1024 / NW;  // 1-KiB load blocks of one operand per wave
   constexpr int KS = 2 + SL, VS = 1 + SL;  // LDS stages of K and of V
   static_assert(kD == 128 || kD == 64, "head dimension");
   static_assert(NW == 2 || NW == 4 || (NW == 1 && kD == 64), "wave count");
+  static_assert(!CROWD || (kD == 64 && NW > 1), "two waves to a SIMD");
   static_assert(!ROPE || kD == 128, "rows of 64 channels are not re-positioned here");
   static_assert(SL == 1 || SL == 2 || SL == 3, "load slack");
   const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_byte*)smem));
@@ -387,9 +400,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
   // ---- per Q tile: rows, Q^T fragments, softmax state ----
   const float c2 = p.scale_log2e;
-  // one log2 unit in units of the scores (finite: below a c2 of 2^-128 every score is zero log2 units, and so is a shift)
-  const float score_unit = kRawQ ? fminf(1.f / c2, 1.7e38f) : 1.f;
-  auto log2_units = [&](float s) DBSA_INLINE { return kRawQ ? s * c2 : s; };
   int head[2], row_local[2], row_tok[2], q_pos[2];
   int row_slot[2] = {0, 0};  // GATHER: where the row's partial state goes
   int row_rot[2] = {0, 0};   // GATHER with ROPE: the row's rotation id
@@ -532,8 +542,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   }
 
   floatx16 o[2][kD / 32];
-  floatx16 neg_m[2];                     // minus the running maximum (in units of the scores) in every element: C operand of a score block's first product
+  // minus the running maximum (in units of the scores) in every element: C operand of a score block's first product
+  floatx16 neg_m[kFromZero ? 1 : 2];
   float m_run[2], l_run[2];              // running max (log2 domain, meaningful once seen); this lane's share of the row sum
+  // one log2 unit in units of the scores (finite: below a c2 of 2^-128 every score is zero log2 units, and so is a shift)
+  const float score_unit = kRawQ && !kFromZero ? fminf(1.f / c2, 1.7e38f) : 1.f;
+  // what a score block's element is in log2 units above the running maximum
+  auto above_max = [&](float score, int rb) DBSA_INLINE { return kFromZero ? fmaf(score, c2, -m_run[rb]) : kRawQ ? score * c2 : score; };
   bool seen[2];                          // the row has met a visible key
 
   // masks of a causal or short tile, applied to the scores of its key half kb
@@ -594,9 +609,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         matrix_result_fence();
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
-          const float delta = fmaxf(log2_units(row_max(S_w[rb])), 0.f);
+          const float delta = fmaxf(above_max(row_max(S_w[rb]), rb), 0.f);
           const float alpha = __builtin_amdgcn_exp2f(-delta);
           m_run[rb] += delta;
+          const float less = kFromZero ? 0.f : delta;
           l_run[rb] *= alpha;
           // the accumulators live in accumulation registers; the opaque statements pin the copies to
           // and from ordinary registers inside this rare block (the compiler otherwise hoists them
@@ -610,15 +626,18 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
           float sum = 0.f;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            const float x0 = __builtin_amdgcn_exp2f(log2_units(S_w[rb][2 * e]) - delta), x1 = __builtin_amdgcn_exp2f(log2_units(S_w[rb][2 * e + 1]) - delta);
+            const float x0 = __builtin_amdgcn_exp2f(above_max(S_w[rb][2 * e], rb) - less);
+            const float x1 = __builtin_amdgcn_exp2f(above_max(S_w[rb][2 * e + 1], rb) - less);
             P_r[rb][e] = __builtin_convertvector(floatx2{x0, x1}, bf16x2);
             sum += x0 + x1;
           }
           ls[rb] = sum;
+          if constexpr (!kFromZero) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) S_r[rb][i] -= delta * score_unit;
+            for (int i = 0; i < 16; ++i) S_r[rb][i] -= delta * score_unit;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) neg_m[rb][i] -= delta * score_unit;
+            for (int i = 0; i < 16; ++i) neg_m[rb][i] -= delta * score_unit;
+          }
         }
         valu_result_fence();
       }
@@ -636,13 +655,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         for (int rb = 0; rb < 2; ++rb) {
           const float m_true = row_max(S_r[rb]);
           const bool first = !seen[rb] & (m_true > kNoKey);
-          const float delta = first ? log2_units(m_true) : 0.f;
+          const float delta = first ? above_max(m_true, rb) : 0.f;  // (m_run is zero until then)
           seen[rb] = seen[rb] | first;
           m_run[rb] += delta;
+          if constexpr (!kFromZero) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i) S_r[rb][i] -= delta * score_unit;
+            for (int i = 0; i < 16; ++i) S_r[rb][i] -= delta * score_unit;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) neg_m[rb][i] -= delta * score_unit;
+            for (int i = 0; i < 16; ++i) neg_m[rb][i] -= delta * score_unit;
+          }
         }
         all_seen = __builtin_amdgcn_ballot_w64(!seen[0] | !seen[1]) == 0;
         valu_result_fence();
@@ -674,7 +695,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       constexpr int t = decltype(T)::value, f = t / 2, rb = t % 2;
       // ---- matrix instruction of this slot ----
       if constexpr (f < nK) {
-        if constexpr (f == 0)
+        if constexpr (f == 0 && kFromZero)
+          mfma_scores_first(S_w[rb], ring[f % kRing], qf[rb][f]);
+        else if constexpr (f == 0)
           mfma_scores_first(S_w[rb], ring[f % kRing], qf[rb][f], neg_m[rb]);
         else
           mfma_scores_acc(S_w[rb], ring[f % kRing], qf[rb][f]);
@@ -723,7 +746,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         // two whole units per slot.
         if constexpr (nSlots >= 32) {
           constexpr int u = t / 2, w = t % 2;
-          ee[u % 2][w] = __builtin_amdgcn_exp2f(log2_units(S_r[u / 8][2 * (u % 8) + w]));
+          ee[u % 2][w] = __builtin_amdgcn_exp2f(above_max(S_r[u / 8][2 * (u % 8) + w], u / 8));
           asm volatile("" : "+v"(ee[u % 2][w]));
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (u > 0) {
@@ -740,8 +763,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
         } else {
           static_for<16 / nSlots>([&](auto K) DBSA_INLINE {
             constexpr int u = t * (16 / nSlots) + decltype(K)::value;
-            ee[u % 2][0] = __builtin_amdgcn_exp2f(log2_units(S_r[u / 8][2 * (u % 8)]));
-            ee[u % 2][1] = __builtin_amdgcn_exp2f(log2_units(S_r[u / 8][2 * (u % 8) + 1]));
+            ee[u % 2][0] = __builtin_amdgcn_exp2f(above_max(S_r[u / 8][2 * (u % 8)], u / 8));
+            ee[u % 2][1] = __builtin_amdgcn_exp2f(above_max(S_r[u / 8][2 * (u % 8) + 1], u / 8));
             asm volatile("" : "+v"(ee[u % 2][0]), "+v"(ee[u % 2][1]));
             // the previous unit is packed behind these exponentials
             __builtin_amdgcn_sched_barrier(0);
@@ -863,8 +886,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
       for (int ob = 0; ob < kD / 32; ++ob)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[rb][ob][i] = 0.f;
+      if constexpr (!kFromZero) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) neg_m[rb][i] = 0.f;
+        for (int i = 0; i < 16; ++i) neg_m[rb][i] = 0.f;
+      }
       m_run[rb] = 0.f;
       l_run[rb] = 0.f;
       ls[rb] = 0.f;
@@ -1057,14 +1082,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   }
 }
 
-template <int kD, int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false>
+template <int kD, int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false, bool CROWD = false>
 hipError_t launch_cfg64(const AttnParams& p, hipStream_t stream) {
-  // (four waves over tiles of 8 KiB: two more for the epilogue)
-  // (re-positioned query prefill of four waves: the rotation table's rows of 64 tokens)
+  // (four waves over tiles of 8 KiB: two more for the epilogue; re-positioned query prefill of four waves: the rotation
+  // table's rows of 64 tokens)
   constexpr int lds_bytes = (3 + 2 * SL + (NW == 4 && kD == 64 ? 2 : 0)) * kBN * kD * 2 + (ROPE && !GATHER && NW == 4 ? 64 * kD * 4 : 0);
   static std::atomic<bool> attr_set{false};  // setting it twice from two threads is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill64_kernel<kD, NW, SL, SELF, PERSIST, GATHER, ROPE>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill64_kernel<kD, NW, SL, SELF, PERSIST, GATHER, ROPE, CROWD>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (e != hipSuccess) return e;
     attr_set = true;
@@ -1072,7 +1097,7 @@ hipError_t launch_cfg64(const AttnParams& p, hipStream_t stream) {
   const int n_split = p.q_split > 1 ? p.q_split : 1;
   const dim3 grid = PERSIST ? dim3(p.sched_classes * p.n_head_blocks)
                             : dim3(p.n_head_blocks, p.n_qtiles, n_split);
-  attn_prefill64_kernel<kD, NW, SL, SELF, PERSIST, GATHER, ROPE><<<grid, dim3(NW * 64), lds_bytes, stream>>>(p);
+  attn_prefill64_kernel<kD, NW, SL, SELF, PERSIST, GATHER, ROPE, CROWD><<<grid, dim3(NW * 64), lds_bytes, stream>>>(p);
   return hipGetLastError();
 }
 
@@ -1086,6 +1111,15 @@ hipError_t launch_stage64(const AttnParams& p, hipStream_t stream) {
     }
   }
   if (p.rope_table) return hipErrorInvalidValue;
+  if constexpr (kD == 64 && NW > 1) {
+    if (p.crowded) {
+      if (p.sched_rec)
+        return p.query_stage ? launch_cfg64<kD, NW, SL, true, true, false, false, true>(p, stream)
+                             : launch_cfg64<kD, NW, SL, false, true, false, false, true>(p, stream);
+      return p.query_stage ? launch_cfg64<kD, NW, SL, true, false, false, false, true>(p, stream)
+                           : launch_cfg64<kD, NW, SL, false, false, false, false, true>(p, stream);
+    }
+  }
   if (p.sched_rec)
     return p.query_stage ? launch_cfg64<kD, NW, SL, true, true>(p, stream) : launch_cfg64<kD, NW, SL, false, true>(p, stream);
   return p.query_stage ? launch_cfg64<kD, NW, SL, true, false>(p, stream) : launch_cfg64<kD, NW, SL, false, false>(p, stream);
@@ -1098,6 +1132,7 @@ hipError_t launch_stage64(const AttnParams& p, hipStream_t stream) {
 // dimension 64 only, whose tiles are half as large): one wave, four workgroups per compute unit (40 KiB each).  At head
 // dimension 128 only two such workgroups fit a compute unit and half of its SIMDs stay idle: 10-20 % slower than the
 // two waves of 32 rows each of attn_prefill.hip (multi-head, 16 questions of 64 tokens: 253 against 228 us).
+// p.crowded: at head_dim 64 the four- and two-wave workgroups twice as many to a compute unit (72 and 40 KiB), see CROWD.
 // With a schedule in p (sched_rec) the launch is persistent and p.q_split must be 1.  The caller
 // runs the merge pass of a split launch.
 hipError_t launch_prefill64(const AttnParams& p, int head_dim, hipStream_t stream) {

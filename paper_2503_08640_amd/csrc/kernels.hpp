@@ -65,6 +65,7 @@ struct AttnParams {
   const int32_t* sched_rec;
   const int32_t* sched_ptr;
   int32_t sched_classes, n_head_blocks;
+  int32_t crowded;            // head_dim 64: two waves to a SIMD (twice the workgroups of the other launches)
   // query prefill whose schedule cuts lists to measure (null: every record is a whole Q tile): record k leaves
   // the partial states of its rows in partial rows sched_part[k] .., or the finished rows if that is -1.
   // cut_tab: [n_cut_tiles][4] = (q_start, q_len, first partial row, pieces), the pieces q_len rows apart

@@ -142,3 +142,48 @@ def test_a_scale_whose_reciprocal_is_infinite_at_head_dim_64():
     want = orc.preencode_attn(synth.as_f64(pc.q), synth.as_f64(pc.k), synth.as_f64(pc.v), p.sink_len, p.demo_offsets,
                               p.group_demo_offsets, 1e-39)
     assert_close(to_f64(o), want, "d64 with a scale of 1e-39")
+
+
+@pytest.mark.parametrize("hq,hkv,block_m,pool,groups,jump", [
+    (32, 8, 64, 4200, 3, 0.0), (32, 8, 64, 4200, 3, 300.0), (32, 8, 64, 8800, 20, 0.0),     # four waves: one Q tile each, several
+    (16, 16, 128, 7700, 4, 0.0), (16, 16, 128, 7700, 4, 40.0), (16, 16, 128, 16900, 20, 0.0),   # two waves
+])
+def test_encoding_with_two_waves_to_a_simd(hq, hkv, block_m, pool, groups, jump):
+    """Launches with workgroups for nine tenths of two per SIMD; jump: as in the test of scores that jump."""
+    pc = small_pool_case("d64crowd", 7800 + pool, hq=hq, hkv=hkv, d=64, sink=70, pool_tokens=pool, groups=groups, lens=(20, 120),
+                         sigma=0.5)
+    p = pc.pool
+    n = p.n_tokens
+    q, k, v = to_dev(pc.q).float(), to_dev(pc.k).float(), to_dev(pc.v)
+    if jump:
+        b = p.group_token_bounds()
+        pos = np.concatenate([np.arange(p.sink_len)] + [np.arange(b[g + 1] - b[g]) for g in range(p.n_groups)])
+        q[..., 0] = 4.0
+        k[..., 0] = torch.from_numpy((pos // 97).astype(np.float32)).cuda()[:, None] * (jump / (pc.scale * 4.0))
+    q, k = q.bfloat16(), k.bfloat16()
+    lay = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, block_m=block_m, block_n=64)
+    lse = torch.zeros((hq, n), device="cuda")
+    o = B.dbsa_preencode_attn(lay, q, k, v, pc.scale, lse=lse)
+    rows = np.unique(np.concatenate([np.arange(140), np.arange(n - 140, n), np.random.default_rng(3).integers(0, n, 200)]))
+    want, want_lse = orc.preencode_attn(to_f64(q), to_f64(k), to_f64(v), p.sink_len, p.demo_offsets, p.group_demo_offsets, pc.scale,
+                                        rows=rows, return_lse=True)
+    assert_close(to_f64(o)[rows], want, f"d64 crowded {hq}/{hkv} jump={jump}")
+    if not jump:
+        assert_close(to_f64(lse)[:, rows], want_lse, "d64 crowded lse")
+    one = B.dbsa_preencode_attn(lay, q, k, torch.ones_like(v), pc.scale)
+    assert (one.float() - 1).abs().max().item() <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("block_m,n_queries,top", [(64, 52, 64), (64, 30, 150), (32, 100, 20)])
+def test_query_prefill_with_two_waves_to_a_simd(block_m, n_queries, top):
+    """Questions for three quarters of two workgroups per SIMD and more, whole lists and lists cut to measure."""
+    pc = small_pool_case("d64crowdq", 7900 + block_m, hq=32, hkv=8, d=64, sink=70, pool_tokens=2600, groups=3, lens=(32, 120), sigma=0.5)
+    rng = np.random.default_rng(5)
+    q_len = [int(x) for x in rng.integers(max(1, top // 2), top + 1, size=n_queries)]
+    sels = [[int(g) for g in rng.permutation(3)[:rng.integers(0, 4)]] for _ in range(n_queries)]
+    qc = synth.make_query_case("d64crowdqq", 7901, pc, n_queries=n_queries, q_len=q_len, selections=sels)
+    lay, kp, vp = _query_setup(pc, qc, block_m, 0)
+    qs, ks, vs = to_dev(qc.q), to_dev(qc.k), to_dev(qc.v)
+    ref = _oracle_query(pc, qc)
+    for ws in (False, None):
+        assert_close(to_f64(B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, workspace=ws)), ref, f"crowded queries ws={ws}")
