@@ -2,9 +2,17 @@
 // query prefill, Sec. 2.2) at head_dim 128 on gfx950.  Same mathematics and register
 // plan as attn_mfma.hip (transposed scores S^T = K Q^T, per-lane softmax statistics,
 // O^T = V^T P^T).  The kernel is organised so that a wavefront never waits on a latency
-// inside a KV tile: between two workgroup barriers it runs 32 matrix instructions, each
+// inside a KV tile: between two workgroup barriers it runs 16 matrix instructions, each
 // followed by the few vector instructions that fit in its shadow.
 //
+//   * workgroups here have one or two blocks of 32 rows (multi-head models, tiles of 32 and 64 tokens).  LDS holds two
+//     of them per compute unit, which with one wave per row block is one wave per SIMD or less: an in-order wave alone
+//     takes 3900 cycles for a tile that is 1024 of matrix work.  So two waves share a row block: each takes half of
+//     every tile's keys, with a running maximum, sum and outputs of its own, and they meet in LDS at the end of the
+//     list (no state leaves the chip).  Multi-head, 16 questions of 64 tokens over 8256 keys each: 228 -> 204 us;
+//     without any load in the loop 122, with all loads aimed at one tile 148: what is left is the traffic behind L2
+//     (864 MB of the 2.26 GB requested miss it; 537 MB are unique).  Loads requested two tiles ahead instead of one
+//     make it 231 us: workgroups that walk the same keys drift further apart and 1174 MB miss L2.
 //   * K and V tiles go from global memory straight into LDS with
 //     global_load_lds_dwordx4 (no staging registers, no ds_write).  A wave-level load
 //     fills 1 KiB of LDS in lane order, so the layout is unpadded and bank conflicts are
@@ -47,7 +55,7 @@ constexpr int kD = 128;
 constexpr int kBN = 64;                       // keys per KV tile
 constexpr int kRowBytes = kD * 2;             // 256
 constexpr int kTileBytes = kBN * kRowBytes;   // 16 KiB per K or V tile
-constexpr int kRing = 4;                      // operand fragments in flight per wave (divides 32)
+constexpr int kRing = 4;                      // operand fragments in flight per wave (divides 16)
 constexpr int kDist = kRing - 1;              // a fragment is read this many matrix instructions early
 constexpr float kRescaleSlack = 8.f;          // log2 units
 
@@ -56,27 +64,29 @@ struct TileRef {
   bool causal, self;
 };
 
-// NW wavefronts per workgroup, each owning one 32-row block; SL: steps between the issue of a
+// NW row blocks of 32 rows per workgroup, two wavefronts each: one takes keys 0-31 of every tile, the other keys 32-63
+// (`part`), and their states meet in LDS at the end.  SL: steps between the issue of a
 // tile's loads and the barrier that publishes them; SELF: the lists may name tiles of the
 // call's own K/V (query prefill) besides pool tiles (pre-encode lists name pool tiles only).
-// Row block g = wave covers query head (blockIdx.x * heads_per_block + g / spb) and tokens
+// Row block g covers query head (blockIdx.x * heads_per_block + g / spb) and tokens
 // q_start + (g % spb)*32 .. +31, spb = block_m / 32.
 // ROPE (query prefill only): Q is un-rotated; the keys carry the rotation of the id they were
 // encoded with, and every list entry names the id at which its rows must be rotated instead
 // (AttnParams::list_shift: the new in-order positions of Sec. 2.2 as a rotation of the query).
 // Entries of one segment share that id, so the Q fragments are rebuilt at segment changes only.
 template <int NW, int SL, bool SELF, bool ROPE = false>
-__global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) {
+__global__ __launch_bounds__(NW * 128, 2) void attn_prefill_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  constexpr int kBlocksPerWave = 16 / NW;  // 1-KiB load blocks of one operand per wave (NW <= 8 < 16)
+  constexpr int kBlocksPerWave = 8 / NW;  // 1-KiB load blocks of one operand per wave
   constexpr int KS = 2 + SL, VS = 1 + SL;  // LDS stages of K and of V
-  static_assert(NW == 1 || NW == 2 || NW == 4 || NW == 8, "wave count");
+  static_assert(NW == 1 || NW == 2, "row blocks");
   static_assert(SL == 1 || SL == 2, "load slack");
-  static_assert(32 % kRing == 0 && kDist >= 1 && kDist <= 8, "ring size");
+  static_assert(16 % kRing == 0 && kDist >= 1 && kDist <= 8, "ring size");
   const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_byte*)smem));
 
   const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, half = lane / 32;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int row_block = wave % NW, part = wave / NW;
   const int r = p.n_q_heads / p.n_kv_heads;
 
   // ---- rows of this wave, tiles of this workgroup ----
@@ -87,8 +97,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
   const int q_start = __builtin_amdgcn_readfirstlane(p.qtile_tab[tile * 4 + 0]);
   const int q_len = __builtin_amdgcn_readfirstlane(p.qtile_tab[tile * 4 + 1]);
   const int spb = p.block_m / 32;
-  const int head = blockIdx.x * p.heads_per_block + wave / spb;
-  const int row_local = (wave % spb) * 32 + l32;
+  const int head = blockIdx.x * p.heads_per_block + row_block / spb;
+  const int row_local = (row_block % spb) * 32 + l32;
   const bool row_valid = row_local < q_len;
   const int row_tok = q_start + min(row_local, q_len - 1);
   const int q_pos = q_start + row_local;
@@ -172,56 +182,90 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
   };
 
   // ---- per-lane LDS read addresses (absolute LDS byte addresses, stage included) ----
-  // K fragment (kb, c): row kb*32 + l32, slot (2c + half) ^ (l32 % 16)
+  // K fragment c: row part*32 + l32, slot (2c + half) ^ (l32 % 16)
   // = k_base ^ (32*c): the chunk index only flips bits 5..7 of the swizzled slot offset
-  const int k_base = l32 * kRowBytes + ((half ^ (l32 % 16)) * 16);
-  // V transpose-read fragment (ob, keys k0..): row k0 + 4*half + j, j = (lane%16)/4; channel
+  const int k_base = (part * 32 + l32) * kRowBytes + ((half ^ (l32 % 16)) * 16);
+  // V transpose-read fragment (ob, keys k0..): row part*32 + k0 + 4*half + j, j = (lane%16)/4; channel
   // slot 4*ob + 2*(l32/16) + (lane%4)/2, swizzled by 4*j; 8-byte half (lane%2)
   // = v_base ^ (64*ob): the channel block only flips bits 6..7 of the swizzled slot offset
-  const int v_base = (4 * half + (lane % 16) / 4) * kRowBytes +
+  const int v_base = (part * 32 + 4 * half + (lane % 16) / 4) * kRowBytes +
                      (((2 * (l32 / 16) + (lane % 4) / 2) ^ (4 * ((lane % 16) / 4))) * 16) + (lane % 2) * 8;
   int kaddr[8], vaddr[4];  // of the K stage / V stage the fragment reads currently walk
 #pragma unroll
   for (int c = 0; c < 8; ++c) kaddr[c] = static_cast<int>(lds0) + (k_base ^ (32 * c));
 #pragma unroll
   for (int ob = 0; ob < 4; ++ob) vaddr[ob] = static_cast<int>(lds0) + KS * kTileBytes + (v_base ^ (64 * ob));
-  // K fragment t (t = kb*8 + c); V fragment t (t = kb*8 + ch*4 + ob)
+  // K fragment t = c; V fragment t = ch*4 + ob
   auto ld_k = [&](auto T) DBSA_INLINE {
-    constexpr int t = decltype(T)::value;
-    return *(reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(static_cast<uintptr_t>(kaddr[t % 8])) +
-             (t / 8) * 32 * kRowBytes / 16);
+    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(static_cast<uintptr_t>(kaddr[decltype(T)::value]));
   };
   auto ld_v = [&](auto T) DBSA_INLINE {
     constexpr int t = decltype(T)::value;
-    const lds_byte* vp = reinterpret_cast<const lds_byte*>(static_cast<uintptr_t>(vaddr[t % 4])) +
-                         ((t / 8) * 32 + ((t / 4) % 2) * 16) * kRowBytes;
+    const lds_byte* vp = reinterpret_cast<const lds_byte*>(static_cast<uintptr_t>(vaddr[t % 4])) + (t / 4) * 16 * kRowBytes;
     const bf16x4 lo = lds_read_tr(vp);
     const bf16x4 hi = lds_read_tr(vp + 8 * kRowBytes);
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
   // ---- Q^T fragments, pre-multiplied by scale*log2(e) ----
+  // The two waves of a row block use the same fragments: each makes the four of chunks 2*part, 2*part + 1 and those
+  // rotated with them (+ 4), and they pass through a free V stage (a lane's pieces of a row lie in its own lines: loading
+  // all of them in both waves keeps the address unit busy twice as long; one re-positioned question 52.5 us that way).
   const float c2 = p.scale_log2e;
   bf16x8 qf[kD / 16];
+  const __bf16* const qp = static_cast<const __bf16*>(p.q.ptr) + static_cast<int64_t>(row_tok) * p.q.stride_tok +
+                           static_cast<int64_t>(head) * p.q.stride_head + 8 * half + 32 * part;
   const const_words lshift = (const_words)(reinterpret_cast<uintptr_t>(p.list_shift + (ROPE ? e0 : 0)));
-  // rebuilds qf rotated at id shift + (row inside the tile)
-  auto load_q_rotated = [&](int shift) DBSA_INLINE {
-    const __bf16* qp = static_cast<const __bf16*>(p.q.ptr) + static_cast<int64_t>(row_tok) * p.q.stride_tok +
-                       static_cast<int64_t>(head) * p.q.stride_head + 8 * half;
-    const int id = min(max(shift + row_local, 0), p.rope_n_pos - 1);
-    const float* rot = p.rope_table + static_cast<int64_t>(id) * kD + 16 * half;
-    load_query_fragments<true>(qp, rot, c2, qf);
+  struct RawQ {
+    bf16x8 lo[2], hi[2];
+    floatx4 cs[ROPE ? 2 : 1][4];
+  };
+  // the row's channels, and the table row of id shift + (row inside the tile)
+  auto request_q = [&](int shift) DBSA_INLINE {
+    RawQ raw;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      raw.lo[j] = *reinterpret_cast<const bf16x8*>(qp + 16 * j);
+      raw.hi[j] = *reinterpret_cast<const bf16x8*>(qp + 16 * j + kD / 2);
+    }
+    if constexpr (ROPE) {
+      const int id = min(max(shift + row_local, 0), p.rope_n_pos - 1);
+      const float* rot = p.rope_table + static_cast<int64_t>(id) * kD + 16 * half + 64 * part;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) raw.cs[j][i] = *reinterpret_cast<const floatx4*>(rot + 32 * j + 4 * i);
+    }
+    return raw;
+  };
+  auto q_area = [&](int stage) DBSA_INLINE {  // [row block][chunk][lane]
+    return reinterpret_cast<bf16x8*>(smem + (KS + stage) * kTileBytes) + row_block * (kD / 16 * 64) + lane;
+  };
+  auto place_q = [&](const RawQ& raw, int stage) DBSA_INLINE {
+    bf16x8* const at = q_area(stage) + 2 * part * 64;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      bf16x8 lo, hi;
+      if constexpr (ROPE) {
+        rotate_pair(raw.lo[j], raw.hi[j], raw.cs[j], c2, lo, hi);
+      } else {
+        lo = scale_row(raw.lo[j], c2);
+        hi = scale_row(raw.hi[j], c2);
+      }
+      at[j * 64] = lo;
+      at[(j + 4) * 64] = hi;
+    }
+  };
+  auto fetch_q = [&](int stage) DBSA_INLINE {
+#pragma unroll
+    for (int c = 0; c < kD / 16; ++c) qf[c] = q_area(stage)[c * 64];
   };
   int cur_shift = 0, nxt_shift = 0;  // rotation ids of the entry whose scores are computed next / after that
   if constexpr (ROPE) {
     cur_shift = lshift[0];
     nxt_shift = n_tiles > 1 ? lshift[1] : cur_shift;
-    load_q_rotated(cur_shift);
-  } else {
-    const __bf16* qp = static_cast<const __bf16*>(p.q.ptr) + static_cast<int64_t>(row_tok) * p.q.stride_tok +
-                       static_cast<int64_t>(head) * p.q.stride_head + 8 * half;
-    load_query_fragments<false>(qp, nullptr, c2, qf);
   }
+  const RawQ first_q = request_q(cur_shift);
 
   floatx16 o[kD / 32];
   float m_run = 0.f, l_run = 0.f;  // running max (log2 domain), this lane's share of the row sum
@@ -231,18 +275,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
     for (int i = 0; i < 16; ++i) o[ob][i] = 0.f;
 
   // masks of a causal or short tile, applied to the scores
-  auto apply_mask = [&](floatx16 (&s)[2], const TileRef& t) DBSA_INLINE {
+  auto apply_mask = [&](floatx16& s, const TileRef& t) DBSA_INLINE {
     const int limit = t.causal ? (q_pos - t.start) : kBN;  // visible iff key_local <= limit
-    int key0 = 4 * half;
-    asm volatile("" : "+v"(key0));  // keeps 32 loop-invariant key indices out of registers: this path is rare
+    int key0 = part * 32 + 4 * half;
+    asm volatile("" : "+v"(key0));  // keeps 16 loop-invariant key indices out of registers: this path is rare
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int key_local = key0 + (kb * 32 + 8 * (i / 4) + (i % 4));
-        const bool vis = key_local < t.len && key_local <= limit;
-        s[kb][i] = vis ? s[kb][i] : -INFINITY;
-      }
+    for (int i = 0; i < 16; ++i) {
+      const int key_local = key0 + (8 * (i / 4) + (i % 4));
+      const bool vis = key_local < t.len && key_local <= limit;
+      s[i] = vis ? s[i] : -INFINITY;
+    }
   };
 
   // ---- prologue: K(0 .. 1+SL), V(0 .. SL-1) in flight; scores of tile 0 fix the first running max ----
@@ -255,35 +297,35 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
   for (int i = 0; i < 1 + SL; ++i)
     if (i + 1 < n_tiles) issue_k(refs[i], i + 1);
   issue_v(cur, 0);
-  if (SL == 2 && n_tiles > 1) issue_v(refs[0], 1);
+  static_assert(SL == 1 && KS == 3 && VS == 2, "V stage 1 is free until step 0, then the one that step's loads fill");
+  place_q(first_q, 1);
   wait_vmcnt<0>();
   __syncthreads();
+  fetch_q(1);
 
-  floatx16 s_a[2], s_b[2];  // scores (minus running max) of the tile being consumed / of the next tile
-  float mx_cur;             // row maximum of the tile being consumed, relative to the running max
+  floatx16 s_a, s_b;  // scores (minus running max) of the tile being consumed / of the next tile
+  float mx_cur;       // row maximum of the tile being consumed, relative to the running max
+  // mx_cur above this: the running maximum moves.  A row takes it from its first visible key in this wave's half of the
+  // tiles (a short or causal tile may show it none), so until then anything finite is above.
+  constexpr float kUnseen = -3.0e38f;
+  float move_above;
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s_a[kb][i] = 0.f;
-  static_for<16>([&](auto T) DBSA_INLINE {
-    constexpr int t = decltype(T)::value;
+  for (int i = 0; i < 16; ++i) s_a[i] = 0.f;
+  static_for<8>([&](auto T) DBSA_INLINE {
     const bf16x8 kf = ld_k(T);
-    s_a[t / 8] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[t % 8], s_a[t / 8], 0, 0, 0);
+    s_a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[decltype(T)::value], s_a, 0, 0, 0);
   });
   if (cur.causal || cur.len < kBN) apply_mask(s_a, cur);
   {
-    float m = s_a[0][0];
+    float m = s_a[0];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int i = 0; i < 16; ++i) m = fmaxf(m, s_a[i]);
+    m = half_swap_max(m);
+    move_above = m > kUnseen ? kRescaleSlack : kUnseen;
+    m_run = m > kUnseen ? m : 0.f;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) m = fmaxf(m, s_a[kb][i]);
-    // every row sees at least one key of its first listed tile, so the maximum is finite
-    m_run = fmaxf(half_swap_max(m), -1.0e30f);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s_a[kb][i] -= m_run;
-    mx_cur = 0.f;
+    for (int i = 0; i < 16; ++i) s_a[i] -= m_run;
+    mx_cur = m > kUnseen ? 0.f : m;
   }
   // minus the running maximum in every element: the C operand of the first matrix instruction of
   // each score block, so that accumulators need no per-step initialisation
@@ -305,7 +347,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
   // fragments of K(it+1).  K(it+1) is visible since the previous barrier; V(it) becomes
   // visible with this one.  The last tile computes an s_nxt nobody uses (stale LDS contents)
   // so that every tile runs the same straight-line code.
-  auto tile_step = [&](int it, floatx16 (&s_cur)[2], floatx16 (&s_nxt)[2]) DBSA_INLINE {
+  auto tile_step = [&](int it, floatx16& s_cur, floatx16& s_nxt) DBSA_INLINE {
     // what this step needs was issued SL steps ago; with SL == 2 the K and V loads of the
     // previous step (2*kBlocksPerWave instructions, if that step issued both sets) may stay in flight
     if (SL == 2 && it + 1 + SL < n_tiles)
@@ -314,27 +356,31 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
       wait_vmcnt<0>();
     __syncthreads();
 
-    // rare: some row's maximum outgrew the lagging running maximum
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx_cur > kRescaleSlack) != 0, 0)) {
-      const float delta = fmaxf(mx_cur, 0.f);
-      const float alpha = __builtin_amdgcn_exp2f(-delta);
+    // rare: some row's maximum outgrew the lagging running maximum, or a row sees its first key
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx_cur > move_above) != 0, 0)) {
+      const bool first = move_above < 0.f && mx_cur > move_above;
+      const float delta = first ? mx_cur : fmaxf(mx_cur, 0.f);
+      const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-delta);  // (nothing to rescale at the first key)
+      move_above = first ? kRescaleSlack : move_above;
       m_run += delta;
       l_run *= alpha;
 #pragma unroll
       for (int ob = 0; ob < kD / 32; ++ob) o[ob] *= alpha;
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s_cur[kb][i] -= delta;
+      for (int i = 0; i < 16; ++i) s_cur[i] -= delta;
 #pragma unroll
       for (int i = 0; i < 16; ++i) neg_m[i] -= delta;
     }
 
     if constexpr (ROPE) {
       // this step computes the scores of entry it+1: rebuild Q when that entry starts a new segment
+      // (through the V stage this step's loads fill; all waves of the workgroup walk the same list)
       if (__builtin_expect(nxt_shift != cur_shift, 0)) {
         cur_shift = nxt_shift;
-        load_q_rotated(cur_shift);
+        place_q(request_q(cur_shift), v_wr);
+        __syncthreads();
+        fetch_q(v_wr);
+        __syncthreads();
       }
     }
     const bool has_next = it + 1 < n_tiles;
@@ -351,19 +397,18 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
     if constexpr (ROPE) {
       if (it + 2 < n_tiles) nxt_shift = lshift[it + 2];
     }
-    bf16x2 pk[2][8];
+    bf16x2 pk[8];
     float p0 = 0.f, p1 = 0.f;  // exponentials of one matrix step, packed during the next
 
     // -- S(it+1) = K(it+1) Q^T (matrix pipe) || probabilities of tile it (vector ALU) --
     __builtin_amdgcn_sched_barrier(0);
-    static_for<16>([&](auto T) DBSA_INLINE {
+    static_for<8>([&](auto T) DBSA_INLINE {
       constexpr int t = decltype(T)::value;
-      s_nxt[t / 8] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[t % kRing], qf[t % 8], t % 8 == 0 ? neg_m : s_nxt[t / 8],
-                                                             0, 0, 0);
-      if constexpr (t + kDist < 16)
-        ring[(t + kDist) % kRing] = ld_k(std::integral_constant<int, (t + kDist) % 16>{});
+      s_nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[t % kRing], qf[t], t == 0 ? neg_m : s_nxt, 0, 0, 0);
+      if constexpr (t + kDist < 8)
+        ring[(t + kDist) % kRing] = ld_k(std::integral_constant<int, t + kDist>{});
       else
-        ring[(t + kDist) % kRing] = ld_v(std::integral_constant<int, (t + kDist) % 16>{});
+        ring[(t + kDist) % kRing] = ld_v(std::integral_constant<int, t + kDist - 8>{});
       if constexpr (t == 0) {
         // this step's loads go out behind the first matrix instruction: K(it+2+SL), V(it+SL).
         // (Spreading them over the phase, one per few matrix instructions, measured slower: every
@@ -373,17 +418,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
       }
       if constexpr (t > 0) {
         constexpr int u = t - 1;
-        pk[u / 8][u % 8] = __builtin_convertvector(floatx2{p0, p1}, bf16x2);
+        pk[u] = __builtin_convertvector(floatx2{p0, p1}, bf16x2);
         l_run += p0 + p1;
-        asm volatile("" : "+v"(pk[u / 8][u % 8]));
+        asm volatile("" : "+v"(pk[u]));
       }
-      p0 = __builtin_amdgcn_exp2f(s_cur[t / 8][2 * (t % 8)]);
-      p1 = __builtin_amdgcn_exp2f(s_cur[t / 8][2 * (t % 8) + 1]);
+      p0 = __builtin_amdgcn_exp2f(s_cur[2 * t]);
+      p1 = __builtin_amdgcn_exp2f(s_cur[2 * t + 1]);
       // keep the vector work in this step, next to the MFMA it overlaps with
       asm volatile("" : "+v"(p0), "+v"(p1), "+v"(l_run));
       __builtin_amdgcn_sched_barrier(0);
     });
-    pk[1][7] = __builtin_convertvector(floatx2{p0, p1}, bf16x2);
+    pk[7] = __builtin_convertvector(floatx2{p0, p1}, bf16x2);
     l_run += p0 + p1;
     if (__builtin_expect(has_next && (nxt.causal || nxt.len < kBN), 0)) apply_mask(s_nxt, nxt);
     {
@@ -396,22 +441,22 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
     }
 
     // -- O^T += V(it)^T P^T (matrix pipe) || row maximum of tile it+1, next accumulator init (vector ALU) --
-    float mt = s_nxt[0][0];
+    float mt = s_nxt[0];
     __builtin_amdgcn_sched_barrier(0);
-    static_for<16>([&](auto T) DBSA_INLINE {
+    static_for<8>([&](auto T) DBSA_INLINE {
       constexpr int t = decltype(T)::value;
       union {
         bf16x8 v;
         bf16x2 p2[4];
       } pf;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) pf.p2[e] = pk[t / 8][4 * ((t / 4) % 2) + e];
-      o[t % 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[(16 + t) % kRing], pf.v, o[t % 4], 0, 0, 0);
-      if constexpr (t + kDist < 16)
-        ring[(16 + t + kDist) % kRing] = ld_v(std::integral_constant<int, (t + kDist) % 16>{});
+      for (int e = 0; e < 4; ++e) pf.p2[e] = pk[4 * (t / 4) + e];
+      o[t % 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[(8 + t) % kRing], pf.v, o[t % 4], 0, 0, 0);
+      if constexpr (t + kDist < 8)
+        ring[(8 + t + kDist) % kRing] = ld_v(std::integral_constant<int, t + kDist>{});
       else
-        ring[(16 + t + kDist) % kRing] = ld_k(std::integral_constant<int, (t + kDist) % 16>{});
-      mt = fmaxf(mt, fmaxf(s_nxt[t / 8][2 * (t % 8)], s_nxt[t / 8][2 * (t % 8) + 1]));
+        ring[(8 + t + kDist) % kRing] = ld_k(std::integral_constant<int, t + kDist - 8>{});
+      mt = fmaxf(mt, fmaxf(s_nxt[2 * t], s_nxt[2 * t + 1]));
       asm volatile("" : "+v"(mt));
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -440,39 +485,79 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_kernel(AttnParams p) 
 
   // ---- epilogue ----
   {
-    const float l_tot = half_swap_sum(l_run);
+    float l_tot = half_swap_sum(l_run);
+    // the two halves of a row block meet: each wave finishes channels 64*part .. and gives the others away, 8 pieces of 16
+    // bytes per lane, and its running maximum, sum and whether it saw a key
+    floatx4* const meet = reinterpret_cast<floatx4*>(smem) + row_block * (18 * 64) + lane;
+    floatx4* const mine = meet + part * (9 * 64);
+    const floatx4* const theirs = meet + (1 - part) * (9 * 64);
+    floatx16 fin[2];
+    __syncthreads();  // the last tile's fragment reads are through
+    auto give = [&](const floatx16& x, int j) DBSA_INLINE {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) mine[(4 * j + g) * 64] = floatx4{x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
+    };
+    if (part == 0) {
+      give(o[2], 0);
+      give(o[3], 1);
+      fin[0] = o[0];
+      fin[1] = o[1];
+    } else {
+      give(o[0], 0);
+      give(o[1], 1);
+      fin[0] = o[2];
+      fin[1] = o[3];
+    }
+    mine[8 * 64] = floatx4{m_run, l_tot, move_above, 0.f};
+    __syncthreads();
+    {
+      const floatx4 other = theirs[8 * 64];
+      const float m_0 = move_above > 0.f ? m_run : -1.0e38f, m_1 = other[2] > 0.f ? other[0] : -1.0e38f;
+      m_run = fmaxf(m_0, m_1);
+      const float w_0 = __builtin_amdgcn_exp2f(m_0 - m_run), w_1 = __builtin_amdgcn_exp2f(m_1 - m_run);
+      l_tot = l_tot * w_0 + other[1] * w_1;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const floatx4 x = theirs[(4 * j + g) * 64];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) fin[j][4 * g + i] = fin[j][4 * g + i] * w_0 + x[i] * w_1;
+        }
+    }
+    const int ch0 = 64 * part + 4 * half;  // this lane's first channel
     if (!row_valid) return;
     if (gridDim.z > 1) {
-      float* part = p.partial + ((static_cast<int64_t>(row_tok) * p.n_q_heads + head) * gridDim.z + blockIdx.z) *
-                                    (kD + kPartialPad);
+      float* state = p.partial + ((static_cast<int64_t>(row_tok) * p.n_q_heads + head) * gridDim.z + blockIdx.z) *
+                                     (kD + kPartialPad);
 #pragma unroll
-      for (int ob = 0; ob < kD / 32; ++ob)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<floatx4*>(part + 32 * ob + 8 * g + 4 * half) =
-              floatx4{o[ob][4 * g], o[ob][4 * g + 1], o[ob][4 * g + 2], o[ob][4 * g + 3]};
-      if (half == 0) {
-        part[kD] = m_run;
-        part[kD + 1] = l_tot;
+          *reinterpret_cast<floatx4*>(state + ch0 + 32 * j + 8 * g) =
+              floatx4{fin[j][4 * g], fin[j][4 * g + 1], fin[j][4 * g + 2], fin[j][4 * g + 3]};
+      if (part == 0 && half == 0) {
+        state[kD] = m_run;
+        state[kD + 1] = l_tot;
       }
       return;
     }
     const float inv = 1.f / l_tot;
     __bf16* op = static_cast<__bf16*>(const_cast<void*>(p.o.ptr)) + static_cast<int64_t>(row_tok) * p.o.stride_tok +
-                 static_cast<int64_t>(head) * p.o.stride_head + 4 * half;
+                 static_cast<int64_t>(head) * p.o.stride_head + ch0;
 #pragma unroll
-    for (int ob = 0; ob < kD / 32; ++ob)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         union {
           bf16x4 v;
           bf16x2 p2[2];
         } w;
-        w.p2[0] = __builtin_convertvector(floatx2{o[ob][4 * g] * inv, o[ob][4 * g + 1] * inv}, bf16x2);
-        w.p2[1] = __builtin_convertvector(floatx2{o[ob][4 * g + 2] * inv, o[ob][4 * g + 3] * inv}, bf16x2);
-        *reinterpret_cast<bf16x4*>(op + 32 * ob + 8 * g) = w.v;
+        w.p2[0] = __builtin_convertvector(floatx2{fin[j][4 * g] * inv, fin[j][4 * g + 1] * inv}, bf16x2);
+        w.p2[1] = __builtin_convertvector(floatx2{fin[j][4 * g + 2] * inv, fin[j][4 * g + 3] * inv}, bf16x2);
+        *reinterpret_cast<bf16x4*>(op + 32 * j + 8 * g) = w.v;
       }
-    if (p.lse && half == 0)
+    if (p.lse && part == 0 && half == 0)
       p.lse[static_cast<int64_t>(head) * p.lse_stride + row_tok] = (m_run + __log2f(l_tot)) * 0.69314718055994531f;
   }
 }
@@ -614,7 +699,7 @@ hipError_t launch_cfg(const AttnParams& p, hipStream_t stream) {
     attr_set = true;
   }
   const int n_split = p.q_split > 1 ? p.q_split : 1;
-  dim3 grid(p.n_q_heads / p.heads_per_block, p.n_qtiles, n_split), block(NW * 64);
+  dim3 grid(p.n_q_heads / p.heads_per_block, p.n_qtiles, n_split), block(NW * 128);
   attn_prefill_kernel<NW, SL, SELF, ROPE><<<grid, block, lds_bytes, stream>>>(p);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? launch_merge<kD>(p, stream) : e;
@@ -628,9 +713,8 @@ hipError_t launch_stage(const AttnParams& p, hipStream_t stream) {
 
 }  // namespace
 
-// One workgroup takes heads_per_block * (block_m / 32) row blocks of 32 rows, one per wave.  Eight
-// waves fill a compute unit on their own (one workgroup per CU: 112 KiB of LDS buy two steps of
-// load slack); smaller workgroups share a CU in pairs and take 80 KiB each.
+// One workgroup takes heads_per_block * (block_m / 32) row blocks of 32 rows.  Those of one or two share a compute unit in
+// pairs, 80 KiB of LDS each, with two waves per row block.
 hipError_t launch_prefill_pipelined(const AttnParams& p, int head_dim, hipStream_t stream) {
   if (p.n_qtiles == 0) return hipSuccess;
   const int row_blocks = p.heads_per_block * (p.block_m / 32);

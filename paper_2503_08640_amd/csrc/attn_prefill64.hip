@@ -1131,7 +1131,7 @@ hipError_t launch_stage64(const AttnParams& p, hipStream_t stream) {
 // of load slack); four row blocks: two waves, two workgroups per compute unit (80 KiB each); two row blocks (head
 // dimension 64 only, whose tiles are half as large): one wave, four workgroups per compute unit (40 KiB each).  At head
 // dimension 128 only two such workgroups fit a compute unit and half of its SIMDs stay idle: 10-20 % slower than the
-// two waves of 32 rows each of attn_prefill.hip (multi-head, 16 questions of 64 tokens: 253 against 228 us).
+// waves of 32 rows each of attn_prefill.hip (multi-head, 16 questions of 64 tokens: 253 against 204 us).
 // p.crowded: at head_dim 64 the four- and two-wave workgroups twice as many to a compute unit (72 and 40 KiB), see CROWD.
 // With a schedule in p (sched_rec) the launch is persistent and p.q_split must be 1.  The caller
 // runs the merge pass of a split launch.

@@ -119,6 +119,18 @@ __device__ DBSA_INLINE void rotate_pair(const bf16x8& lo, const bf16x8& hi, cons
   out_hi = b.v;
 }
 
+// Eight channels of a row multiplied by c2, rounded to bf16.
+__device__ DBSA_INLINE bf16x8 scale_row(const bf16x8& raw, float c2) {
+  union {
+    bf16x8 v;
+    bf16x2 p2[4];
+  } sc;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    sc.p2[e] = __builtin_convertvector(floatx2{static_cast<float>(raw[2 * e]) * c2, static_cast<float>(raw[2 * e + 1]) * c2}, bf16x2);
+  return sc.v;
+}
+
 // The 8 B-operand fragments of one score column for head_dim 128: the query row (qp points at this
 // lane's first channel, 8 * half), pre-multiplied by c2 = scale * log2 e and rounded to bf16 again.
 // ROPE: the row is stored un-rotated and is rotated here with the table row `rot` (16 floats = cos,
@@ -139,18 +151,7 @@ __device__ DBSA_INLINE void load_query_fragments(const __bf16* qp, const float* 
     }
   } else {
 #pragma unroll
-    for (int c = 0; c < kQD / 16; ++c) {
-      const bf16x8 raw = *reinterpret_cast<const bf16x8*>(qp + 16 * c);
-      union {
-        bf16x8 v;
-        bf16x2 p2[4];
-      } sc;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        sc.p2[e] = __builtin_convertvector(
-            floatx2{static_cast<float>(raw[2 * e]) * c2, static_cast<float>(raw[2 * e + 1]) * c2}, bf16x2);
-      qf[c] = sc.v;
-    }
+    for (int c = 0; c < kQD / 16; ++c) qf[c] = scale_row(*reinterpret_cast<const bf16x8*>(qp + 16 * c), c2);
   }
 }
 
