@@ -179,6 +179,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(CROWD ?
 
   const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, half = lane / 32;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  // The lane index for the rare blocks of the tile loop and for the epilogue.  CROWD: counted anew there, because the
+  // compiler otherwise keeps what they derive from it through the loop, 6-34 registers more than the 256 hold, and a
+  // reload from scratch waits for every tile load in flight: encoding 150 groups of 218 tokens, 16/16 heads, 333-token
+  // sink 178 us that way, 141 so (157 with one wave to a SIMD); 300 groups of 109 tokens, 32/8 heads 124 and 110 (130).
+  auto lane_here = [&]() DBSA_INLINE {
+    int x = lane;
+    if constexpr (CROWD) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
+    return x;
+  };
   const int r = p.n_q_heads / p.n_kv_heads;
   const int spb = p.block_m / 32;
 
@@ -553,13 +562,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(CROWD ?
 
   // masks of a causal or short tile, applied to the scores of its key half kb
   auto apply_mask = [&](floatx16 (&s)[2], const TileRef& t, int kb) DBSA_INLINE {
-    int key0 = 4 * half + 32 * kb;
+    const int ln = lane_here();
+    int key0 = 4 * (ln / 32) + 32 * kb;
     asm volatile("" : "+v"(key0));  // keeps loop-invariant key indices out of registers: this path is rare
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       // element i holds key key0 + 8 * (i / 4) + i % 4 of the tile; it is visible iff that index is below the
       // tile's length and (causal tiles) not beyond the row's own position: one bound per lane, relative to key0
-      const int last = min(t.causal ? (q_pos[rb] - t.start) : kBN, t.len - 1) - key0;
+      const int pos = CROWD ? q_start + ((2 * wave + rb) % spb) * 32 + ln % 32 : q_pos[rb];
+      const int last = min(t.causal ? (pos - t.start) : kBN, t.len - 1) - key0;
       // (a row block that sees all 32 keys of this half needs nothing: 27 is the largest element offset)
       if (__builtin_amdgcn_ballot_w64(last < 27) == 0) continue;
 #pragma unroll
@@ -793,12 +804,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(CROWD ?
   // a short tile or a tile of the call's own K/V gets its own for the period that loads it.
   bool k_special = false, v_special = false;
   auto lane_offsets = [&](unsigned (&off)[kBlocksPerWave], const TileRef& t, int stride, bool for_v) DBSA_INLINE {
+    const int ln = lane_here();
 #pragma unroll
     for (int i = 0; i < kBlocksPerWave; ++i) {
-      const int row_in = block_row(i);
+      const int row_in = kLoadRows * (wave * kBlocksPerWave + i) + ln / kPieces16;
       const int row = min(row_in, t.len - 1);  // rows past the tail repeat the last key
       const int sw = for_v ? v_swizzle(row_in) : k_swizzle(row_in);
-      off[i] = static_cast<unsigned>(row * stride + (((lane % kPieces16) ^ sw) * 8)) * 2u + lane_bias(i);
+      off[i] = static_cast<unsigned>(row * stride + (((ln % kPieces16) ^ sw) * 8)) * 2u + lane_bias(i);
     }
   };
   // the K tile (entry 1+SL ahead) / the V tile (entry SL-1 ahead) a period loads
@@ -972,8 +984,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(CROWD ?
     // ---- epilogue ----
     // (kPieces: an opaque copy of the lane index, because what the two ways out derive from it would otherwise be kept
     // in registers all through the tile loop, where none are free)
-    int ln = lane;
-    if constexpr (kPieces) asm volatile("" : "+v"(ln));
+    int ln = lane_here();
+    if constexpr (kPieces && !CROWD) asm volatile("" : "+v"(ln));
     const int el32 = ln % 32, ehalf = ln / 32;
     // 8 KiB of LDS per wave to turn its rows around in: in the stages of the last K and V tiles, and for the waves those
     // do not hold (four waves, tiles of 8 KiB) behind the ring
