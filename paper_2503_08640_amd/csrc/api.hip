@@ -550,15 +550,10 @@ int64_t prefill_places(const dbsa_layout* L, int row_blocks, int head_dim, bool 
 }
 
 // Whether a launch runs two waves to a SIMD, whose exponentials fill each other's gaps: at head_dim 64 the registers allow
-// it (256 each; not the one-wave workgroups, which LDS holds to four).  It takes workgroups for most of the places: a list
-// runs at little more than half its speed beside another, so that a launch whose longest list decides only loses.  Query
-// prefill (lists of about one length) from three quarters of the places on: 100 questions of 20 tokens, 0.78, 273 -> 255 us;
-// 12 of 400, 1.3, 412 -> 370; encoding from nine tenths on: 63 lists x 8 head blocks, 0.98, 501 -> 431 us, 6000 tokens of
-// 16 heads, 0.75, 55 -> 64.
-bool crowd_launch(const dbsa_layout* L, int row_blocks, int head_dim, int64_t head_blocks) {
+// it (256 each; not the one-wave workgroups, which LDS holds to four).
+bool crowd_launch(const dbsa_layout* L, int row_blocks, int head_dim, int64_t head_blocks, bool cuts) {
   if (head_dim != 64 || (row_blocks != 4 && row_blocks != 8)) return false;
-  const int64_t wgs = L->n_qtiles() * head_blocks, places = prefill_places(L, row_blocks, head_dim, true);
-  return L->query_stage ? 4 * wgs >= 3 * places : 10 * wgs >= 9 * places;
+  return dbsa_crowd_worth(L, prefill_places(L, row_blocks, head_dim, true) / head_blocks, cuts);
 }
 
 // Runs per list of a launch of `wgs` workgroups (one run each) on `places`: the number that makes rounds * length
@@ -726,11 +721,11 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
     const int row_blocks = p.heads_per_block * (L->block_m / 32);
     const bool pipelined = max_stride < (int64_t{1} << 24) && (d == 128 || schedulable(row_blocks, d));
     const int64_t head_blocks = hkv * ((hq / hkv + p.heads_per_block - 1) / p.heads_per_block);
-    p.crowded = crowd_launch(L, row_blocks, d, head_blocks) ? 1 : 0;
-    const int64_t places = prefill_places(L, row_blocks, d, p.crowded != 0);
     p.n_head_blocks = static_cast<int32_t>(head_blocks);
     const size_t state_bytes = (d + kPartialPad) * sizeof(float);
     const size_t room = workspace && reinterpret_cast<uintptr_t>(workspace) % 16 == 0 ? workspace_bytes / state_bytes : 0;
+    p.crowded = pipelined && crowd_launch(L, row_blocks, d, head_blocks, want_query_stage && room > 0) ? 1 : 0;
+    const int64_t places = prefill_places(L, row_blocks, d, p.crowded != 0);
     hipStream_t s = static_cast<hipStream_t>(stream);
     // The kernel with 64 rows per wave runs persistently: as many workgroups as the chip holds (one of four
     // waves or two of two per compute unit), each walking a balanced share of the Q tiles of its head block.  With
@@ -739,7 +734,12 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
     if (pipelined && schedulable(row_blocks, d)) {
       const int32_t classes = static_cast<int32_t>(std::min<int64_t>(places / head_blocks, kMaxSchedClasses));
       p.sched_classes = classes;
-      if (want_query_stage && L->n_qtiles() < kCutTiles * classes && room > 0 &&
+      const bool listed = places / head_blocks <= kMaxSchedClasses;
+      // Two waves to a SIMD: also few tiles are dealt, the longest first, so that a long list lies beside a short one and the
+      // last group's do not come last (encoding 11000 tokens of 16/16 heads in two groups 161 -> 155 us, 7000 tokens of 32/8 in
+      // four 79 -> 68; questions over one and up to two rounds start where a place is free: 66 of 64 tokens 375, dealt 402).
+      const bool dealt_early = p.crowded && (!want_query_stage || L->n_qtiles() <= classes);
+      if (want_query_stage && L->n_qtiles() < kCutTiles * classes && room > 0 && (listed || !p.crowded) &&
           ensure_cut_schedule(L, classes, row_blocks, s) &&
           static_cast<size_t>(L->cut_rows) * hq <= room) {
         p.sched_rec = L->dev.cut_rec;
@@ -748,7 +748,7 @@ int prefill_common(const dbsa_layout* L, bool want_query_stage, dbsa_tensor q, d
         p.cut_tab = L->dev.cut_tab;
         p.n_cut_tiles = static_cast<int32_t>(L->cut_tab.size() / 4);
         p.partial = static_cast<float*>(workspace);
-      } else if (classes >= 1 && places / head_blocks <= kMaxSchedClasses && L->n_qtiles() >= 2 * classes && ensure_schedule(L, classes, s)) {
+      } else if (classes >= 1 && listed && L->n_qtiles() >= (dealt_early ? 1 : 2 * classes) && ensure_schedule(L, classes, s)) {
         p.sched_rec = L->dev.sched_rec;
         p.sched_ptr = L->dev.sched_ptr;
       }

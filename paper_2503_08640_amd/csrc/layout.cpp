@@ -546,6 +546,8 @@ int dbsa_build_host_lists(const dbsa_pool_desc* pool, const dbsa_select_desc* se
     if (oa != ob) return oa < ob;
     return (L->list_ptr[a + 1] - L->list_ptr[a]) > (L->list_ptr[b + 1] - L->list_ptr[b]);
   });
+  for (int64_t i = nt; i > 0 && L->qtile_tab[4 * L->order[static_cast<size_t>(i - 1)] + 2] == L->qtile_tab[4 * L->order.back() + 2]; --i)
+    L->last_owner_tiles += 1;
   return DBSA_OK;
 }
 
@@ -732,6 +734,53 @@ void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes) {
     }
   }
   L->cut_classes = n_classes;
+}
+
+namespace {
+// what an entry costs with two waves to a SIMD (1.74 us beside another wave), in entries of a wave alone (1.21)
+constexpr double kBesideCost = 1.44;
+}  // namespace
+
+// Two waves fill each other's gaps, but a list beside another runs at 0.7 of its speed: it takes work for most of the places,
+// and a launch whose longest list decides only loses.  16/16 heads, 128-token tiles, encoding two groups of 3650 tokens 78 us
+// with one wave to a SIMD and 94 with two, of 4500 115 / 128, of 5500 169 / 155; twenty groups of 450 tokens 35 / 33;
+// 32/8 heads, one group of 4400 tokens 104 / 100, of 5200 139 / 129, of 3600 76 / 77; four groups of 900 38 / 29.  Questions
+// without a workspace: 48 of 64 tokens over 64 workers 289 / 245, 66 427 / 375, 100 of 20 tokens over 128 305 / 250 (nothing
+// below three quarters was measured); one that selects 16 times as many groups as the 55 others 158 / 165.  Lists that can
+// be cut to measure take four fifths: over 64 workers 40 questions 195 cut for one wave each, 48 231 / 245, 52 253 / 250,
+// 60 292 / 262.  More workers than a schedule can name leave the launch to the order of the lists, or their cuts to half
+// the places: 4/1 heads, 1200 questions of 30 tokens 114 / 167, encoding 60000 tokens 127 / 143; with one list per worker
+// they gain, 900 questions 88 / 80, 32000 tokens 63 / 53.
+bool dbsa_crowd_worth(const dbsa_layout* L, int64_t classes, bool cuts) {
+  const int64_t nt = L->n_qtiles(), alone = classes / 2;
+  if (nt == 0 || alone < 1) return false;
+  const bool encoding = !L->query_stage, listed = classes <= kMaxSchedClasses;
+  if (encoding ? 10 * nt < 9 * classes : cuts ? 5 * nt < 4 * classes : 4 * nt < 3 * classes) return false;
+  if (!listed && nt > classes && (encoding || cuts)) return false;
+  if (cuts) return true;
+  // entries of the busiest of n workers, by the longest list, by all entries, and by how many lists it takes
+  auto busiest = [&](int64_t n, int64_t per_tile) {
+    return std::max({static_cast<double>(L->longest_list + per_tile), static_cast<double>(L->n_ent() + per_tile * nt) / static_cast<double>(n),
+                     static_cast<double>((nt + n - 1) / n * (L->shortest_list + per_tile))});
+  };
+  // one wave to a SIMD; without a schedule the lists start in launch order, those of the last owner when the work of the
+  // others is nearly done
+  const bool dealt = nt >= 2 * alone;
+  double single = busiest(alone, dealt ? kTileCost : kPieceCost);
+  const int64_t before = nt - L->last_owner_tiles;
+  if (!dealt && encoding && before >= alone)
+    single = std::max(single, static_cast<double>(L->n_ent() + kPieceCost * nt) / static_cast<double>(alone) * static_cast<double>(before) /
+                                      static_cast<double>(nt) + static_cast<double>(L->longest_list));
+  // two: beside the longest list lies one of middling length (the lists are dealt longest first)
+  const double beside = static_cast<double>(L->n_ent() + kTileCost * nt) / static_cast<double>(classes);
+  double both = busiest(classes, kTileCost) + (kBesideCost - 1.0) * beside;
+  if (!encoding && nt > classes && (!listed || nt < 2 * classes)) {  // no schedule: rounds, the last one perhaps not full
+    const int64_t rounds = (nt + classes - 1) / classes;
+    const double fill = static_cast<double>(nt - (rounds - 1) * classes) / static_cast<double>(classes);
+    const double cost = kBesideCost * static_cast<double>(rounds - 1) + 1.0 + (kBesideCost - 1.0) * std::min(1.0, 4.0 * fill);
+    both = std::max(both, cost * static_cast<double>(L->shortest_list + kPieceCost));
+  }
+  return both < single;
 }
 
 // Against whole Q tiles dealt to the same workers, and while there are fewer tiles than workers against runs of one length,

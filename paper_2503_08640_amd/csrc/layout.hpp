@@ -127,6 +127,7 @@ struct dbsa_layout {
   int32_t gm_max_queries = 1;       // most queries any schedule item serves
   int64_t shortest_list = 0;        // fewest entries any Q tile lists
   int64_t longest_list = 0;         // most
+  int64_t last_owner_tiles = 0;     // Q tiles of the group (or question) that is last in launch order
   int32_t largest_tile = 0;         // most rows any Q tile has (at most block_m)
   int64_t max_rotation_id = -1;     // largest id a prefill row looks up: max(list_shift[e] + rows of the tile) - 1
   int64_t max_decode_shift = 0;     // largest gm_qshift: a decode row of self_len n looks up id shift + n - 1
@@ -207,6 +208,9 @@ void dbsa_cut_schedule(const dbsa_layout* L, int32_t n_classes);
 // Whether a launch of workgroups of `row_blocks` blocks of 32 rows gains from the schedule L holds.  Not part of it: models
 // with the same number of workers may differ in this.
 bool dbsa_cut_worth(const dbsa_layout* L, int row_blocks);
+// Whether a launch of L's Q tiles gains from two waves to a SIMD: `classes` workers per head block that way, half as many
+// otherwise.  cuts: its lists can be cut to measure.
+bool dbsa_crowd_worth(const dbsa_layout* L, int64_t classes, bool cuts);
 
 // Pure host integer work; returns a DBSA_* code and fills `L` on success.
 // first_group < 0: every segment; >= 0 (pre-encode only): Q tiles of groups first_group.. alone

@@ -1,8 +1,10 @@
 """Helpers for the GPU parity tests: numpy <-> device tensors and error metrics."""
+import ctypes
+
 import numpy as np
 import torch
 
-from paper_2503_08640_amd import synth
+from paper_2503_08640_amd import binding, synth
 
 MAX_ABS_TOL = 2e-2    # bf16 inputs vs the fp64 oracle
 MEAN_ABS_TOL = 2e-3
@@ -17,6 +19,14 @@ def to_dev(x: np.ndarray) -> torch.Tensor:
 
 def to_f64(t: torch.Tensor) -> np.ndarray:
     return t.detach().float().cpu().numpy().astype(np.float64)
+
+
+def two_waves(layout, classes, cuts=False):
+    """Whether a head_dim 64 launch over `layout` runs two waves to a SIMD with `classes` workers per head block
+    (the library's own C++ rule)."""
+    rule = binding.lib()._Z16dbsa_crowd_worthPK11dbsa_layoutlb
+    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.c_void_p, ctypes.c_int64, ctypes.c_bool]
+    return bool(rule(layout.handle, classes, cuts))
 
 
 def errors(got: np.ndarray, want: np.ndarray):

@@ -11,6 +11,7 @@ from oracle import dbsa_oracle as orc
 from oracle import layout_oracle as lo
 from paper_2503_08640_amd import binding as B
 from paper_2503_08640_amd import synth
+from gpu_util import two_waves
 
 
 def rand_pool(rng, sink_len, n_groups, demos_per_group=(1, 4), demo_len=(1, 9)):
@@ -813,3 +814,54 @@ def test_the_current_stream_is_asked_for_with_torchs_checks(monkeypatch):
     B._stream_calls.cache_clear()
     assert B._stream() == 77
     B._stream_calls.cache_clear()
+
+
+def _even_pool(groups, tokens, block_m, sink=64, **kw):
+    return B.dbsa_layout_build(sink, sink + tokens * np.arange(groups + 1), np.arange(groups + 1), block_m=block_m, block_n=64,
+                               host_only=True, **kw)
+
+
+@pytest.mark.parametrize("block_m,groups,tokens,classes,want", [
+    (64, 8, 4096, 64, True),      # 32k tokens of 32/8 heads: several Q tiles per worker
+    (64, 15, 240, 64, True),      # one each, short lists
+    (64, 1, 4400, 64, False),     # the longest list is most of what a worker gets
+    (64, 1, 6000, 64, True),
+    (128, 2, 3650, 64, False),    # 16/16 heads: two groups, their longest lists side by side
+    (128, 2, 4500, 64, False),
+    (128, 20, 450, 64, True),
+    (64, 4, 700, 64, False),      # too few workgroups
+    (64, 20, 1500, 512, True),    # 4/1 heads: a block of heads has all places
+    (32, 20, 1500, 1024, True),   # more workers than a schedule has: only while each takes one list
+    (32, 20, 3000, 1024, False),
+    (64, 20, 3000, 512, True),
+])
+def test_encoding_takes_two_waves_to_a_simd_unless_the_longest_list_decides(block_m, groups, tokens, classes, want):
+    """head_dim 64; every line was measured both ways (a worker's list beside another runs at 0.7 of its speed)."""
+    assert two_waves(_even_pool(groups, tokens, block_m), classes) is want
+
+
+@pytest.mark.parametrize("block_m,questions,q_len,per_list,classes,whole,cut", [
+    (64, 52, 64, 4096, 64, True, True),
+    (64, 48, 64, 4096, 64, True, False),     # one wave to a SIMD and lists cut to measure are faster
+    (64, 40, 64, 4096, 64, False, False),
+    (64, 66, 64, 4096, 64, True, True),
+    (32, 98, 20, 4096, 128, True, False),
+    (32, 180, 20, 4096, 128, True, True),
+    (32, 700, 30, 1024, 512, False, True),   # short lists, a second round that is a third full
+    (32, 900, 30, 1024, 1024, True, True),
+    (32, 1200, 30, 1024, 1024, True, False), # more workers than a schedule has
+])
+def test_questions_take_two_waves_to_a_simd_where_there_are_enough_of_them(block_m, questions, q_len, per_list, classes, whole, cut):
+    """head_dim 64, two groups of per_list tokens each; every line was measured both ways."""
+    lay = _even_pool(2, per_list, block_m, cu_qlens=q_len * np.arange(questions + 1), sel_ptr=2 * np.arange(questions + 1),
+                     sel_idx=np.tile([0, 1], questions))
+    assert two_waves(lay, classes) is whole and two_waves(lay, classes, cuts=True) is cut
+
+
+@pytest.mark.parametrize("groups", [4, 16, 64])
+def test_one_question_that_selects_far_more_keeps_one_wave_to_a_simd(groups):
+    """56 questions, all but one over a single group of 512 tokens: whole lists, and the longest decides."""
+    sels = [np.arange(groups)] + [np.array([i]) for i in range(55)]
+    lay = _even_pool(64, 512, 64, cu_qlens=64 * np.arange(57), sel_ptr=np.concatenate([[0], np.cumsum([len(x) for x in sels])]),
+                     sel_idx=np.concatenate(sels))
+    assert not two_waves(lay, 64)
