@@ -122,11 +122,29 @@ __device__ DBSA_INLINE void request_references(const AttnParams& p, const Decode
   if (!it.self_item)
     dma16(p.gm_ref_pad + static_cast<int64_t>(it.item) * 128, static_cast<unsigned>(threadIdx.x % 32) * 16u, refs);
 }
-// ROPE: the lengths of the first 64 queries' own caches, one per lane, requested with the first look-ups.
+// ROPE: the lengths of the queries' own caches, requested with the first look-ups: two queries per lane up to 128; beyond
+// that the one of the lane's column, behind a look-up of its reference.  Requested after the tiles, as it was beyond 64
+// queries, it waits for them: 70 / 100 / 128 queries of 16/8 heads 49.0 / 56.1 / 62.7 us that way and 48.6 / 55.5 / 61.9 so.
+struct OwnLengths {
+  int first, second;
+};
 template <bool ROPE>
-__device__ DBSA_INLINE int request_lengths(const AttnParams& p) {
-  return ROPE ? p.self_len[min(static_cast<int>(threadIdx.x % 64), p.n_queries - 1)] : 0;
+__device__ DBSA_INLINE OwnLengths request_lengths(const AttnParams& p, const DecodeItem& it, int pass, int rp_log2) {
+  OwnLengths n{0, 0};
+  if constexpr (ROPE) {
+    const int lane = threadIdx.x % 64;
+    if (p.n_queries <= 128) {
+      n.first = p.self_len[min(lane, p.n_queries - 1)];
+      if (p.n_queries > 64) n.second = p.self_len[min(lane + 64, p.n_queries - 1)];
+    } else if (!it.self_item) {
+      const int q_local = pass * (32 >> rp_log2) + ((lane % 32) >> rp_log2);
+      n.first = p.self_len[p.gm_ref_pad[(static_cast<int64_t>(it.item) * 32 + q_local) * 4]];
+    }
+  }
+  return n;
 }
+// (they arrive here, in front of the tiles: see request_references)
+__device__ DBSA_INLINE void await_lengths(const OwnLengths& n) { asm volatile("" : : "v"(n.first), "v"(n.second)); }
 
 // rp: columns per query, r rounded up to a power of two.
 // pass: the wave's query batch (of 32 / rp queries) inside the item; active: the wave has a batch.
@@ -135,7 +153,7 @@ __device__ DBSA_INLINE int request_lengths(const AttnParams& p) {
 // (Sec. 2.2): shift of the reference + the query's own length - 1.
 template <int kD, bool ROPE>
 __device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const DecodeItem& it, int pass, bool active, int r, int rp_log2,
-                                                  int l32, int half, const lds_byte* refs, int lengths) {
+                                                  int l32, int half, const lds_byte* refs, const OwnLengths& lengths) {
   DecodeColumn c;
   const int rp = 1 << rp_log2;
   const int q_local = pass * (32 >> rp_log2) + (l32 >> rp_log2);  // index into the item's query list (< 32 also without a batch)
@@ -154,7 +172,14 @@ __device__ DBSA_INLINE DecodeColumn decode_column(const AttnParams& p, const Dec
   c.head = it.hk * r + min(l32 & (rp - 1), r - 1);
   c.rot = nullptr;
   if (ROPE) {
-    const int length = p.n_queries <= 64 ? __shfl(lengths, u, 64) : p.self_len[u];
+    int length = it.self_item ? it.n_keys : lengths.first;
+    if (!it.self_item && p.n_queries <= 128) {
+      length = __shfl(lengths.first, u % 64, 64);
+      if (p.n_queries > 64) {
+        const int high = __shfl(lengths.second, u % 64, 64);
+        length = u < 64 ? length : high;
+      }
+    }
     rot_id = min(max(rot_id + length - 1, 0), p.rope_n_pos - 1);
     c.rot = p.rope_table + static_cast<int64_t>(rot_id) * kD + 16 * half;
   }
@@ -306,7 +331,7 @@ __device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it,
   }
   const int hk = it.hk, pass = it.batch, n_q = it.n_q, first_key = it.first_key, n_keys = it.n_keys, self_u = it.self_u;
   const bool self_item = it.self_item;
-  const int lengths = request_lengths<ROPE>(p);
+  const OwnLengths lengths = request_lengths<ROPE>(p, it, pass, rp_log2);
   // One workgroup per batch of 32 / rp queries of the item: an item that serves more queries than
   // one wave has columns is walked by several workgroups side by side instead of by one workgroup
   // several times, which would make it the last to finish.
@@ -410,7 +435,7 @@ __device__ DBSA_INLINE void walk_decode_item(const AttnParams& p, DecodeItem it,
   // ---- wave-private ring: group g + kSlots goes out as soon as the product that reads group g is issued.  The first
   // groups are requested before the query row, so that both latencies run together. ----
   lds_byte* const refs = lds + ring_bytes;
-  if (ROPE) asm volatile("" : : "v"(lengths));  // (they arrive here, in front of the tiles: see request_references)
+  if (ROPE) await_lengths(lengths);
   request_references(p, it, refs);
 #pragma unroll
   for (int g = 0; g < T::kSlots; ++g) {
@@ -493,7 +518,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
   if (wg_batch * W >= n_pass) return;
   const int pass = wg_batch * W + wave;
   const bool active = pass < n_pass;  // a wave without a batch still loads its share and keeps the barriers
-  const int lengths = request_lengths<ROPE>(p);
+  const OwnLengths lengths = request_lengths<ROPE>(p, it, pass, rp_log2);
 
   const __bf16* kbase = self_item ? static_cast<const __bf16*>(p.k_self.ptr) + self_u * p.stride_query +
                                         hk * p.k_self.stride_head
@@ -558,7 +583,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_shared_kernel(AttnParams 
   const float prescale = ROPE ? p.scale_log2e : 1.f, c2 = ROPE ? 1.f : p.scale_log2e;
 
   lds_byte* const refs = lds + kPairs * 2 * T::kBytes + wave * kRefBytes;
-  if (ROPE) asm volatile("" : : "v"(lengths));
+  if (ROPE) await_lengths(lengths);
   request_references(p, it, refs);
   issue_pair(0);
   if (1 < n_half) issue_pair(1);
@@ -663,7 +688,7 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
   }
   const int hk = it.hk, pass = it.batch, n_q = it.n_q, first_key = it.first_key, n_keys = it.n_keys;
   const int n_half = (n_keys + kHalf - 1) / kHalf;
-  const int lengths = request_lengths<ROPE>(p);
+  const OwnLengths lengths = request_lengths<ROPE>(p, it, pass, rp_log2);
   if (pass >= (n_q + qpw - 1) / qpw) return;
 
   const unsigned char* kbase = static_cast<const unsigned char*>(p.k_pool.ptr) + hk * p.k_pool.stride_head;
@@ -713,7 +738,7 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
   const int v_base = HalfTile<kD>::v_base(lane, l32, half);
 
   lds_byte* const refs = lds + kLds8;
-  if (ROPE) asm volatile("" : : "v"(lengths));
+  if (ROPE) await_lengths(lengths);
   request_references(p, it, refs);
   issue_k(0);
   issue_v(0);
@@ -820,7 +845,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
   if (wg_batch * W >= n_pass) return;  // (the same for all waves: the workgroup leaves as one)
   const int pass = wg_batch * W + wave;
   const bool active = pass < n_pass;
-  const int lengths = request_lengths<ROPE>(p);
+  const OwnLengths lengths = request_lengths<ROPE>(p, it, pass, rp_log2);
 
   const unsigned char* kbase = static_cast<const unsigned char*>(p.k_pool.ptr) + hk * p.k_pool.stride_head;
   const unsigned char* vbase = static_cast<const unsigned char*>(p.v_pool.ptr) + hk * p.v_pool.stride_head;
@@ -878,7 +903,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
   const int k_base = HalfTile<kD>::k_base(l32, half), v_base = HalfTile<kD>::v_base(lane, l32, half);
 
   lds_byte* const refs = lds + kPairs * kStagePair8 + kPairBytes + wave * kRefBytes;
-  if (ROPE) asm volatile("" : : "v"(lengths));
+  if (ROPE) await_lengths(lengths);
   request_references(p, it, refs);
   issue_pair(0);
   if (1 < n_half) issue_pair(1);

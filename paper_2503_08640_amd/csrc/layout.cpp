@@ -790,6 +790,8 @@ bool dbsa_crowd_worth(const dbsa_layout* L, int64_t classes, bool cuts) {
 // with few: a K/V pair serves 32 rows per row block, and 256 rows keep the matrix pipes busy at the rate the pairs
 // arrive.  Two small workgroups per compute unit fetch a pair per 128 rows each and are bound by that traffic (512 of them
 // move 7.4 TB/s; 50 questions of 20 tokens on 400 of 512 places: whole lists 771 us, all places with cut lists 803).
+// Eight row blocks with two waves to a SIMD are priced like one: with kBesideCost instead 41 prefills of 52 to 800 questions
+// took the same time to 1 % (200 of 20 tokens 456 us so and 468 with it, 220 of them 509 and 501).
 bool dbsa_cut_worth(const dbsa_layout* L, int row_blocks) {
   const int64_t nt = L->n_qtiles();
   const double crowd = row_blocks == 8 ? 1.0 : row_blocks == 4 ? 1.5 : 3.0;

@@ -118,13 +118,28 @@ def test_repositioned_decode_over_an_fp8_pool(hq, hkv):
     ids, THEN quantised.  The oracle gets the de-quantised keys rotated back in fp64 (a rotation
     is undone by the opposite angle), i.e. the un-rotated keys whose encoding-time rotation
     gives exactly the stored values, and rotates them at the new in-order ids itself."""
-    from oracle import rope_oracle as ro
     pc = synth.make_pool_case("kv8rope", 6020 + hq, dtype="bf16", n_q_heads=hq, n_kv_heads=hkv, head_dim=128,
                               sink_len=70, pool_tokens=4000, demo_len_range=(30, 200), n_groups=5,
                               k_channel_sigma=0.5)
     sels = [[3, 0], [], [4, 1, 2, 0, 3], [2]] + [[4, 1]] * 20
     qc = synth.make_query_case("kv8ropeq", 6021, pc, n_queries=24, q_len=[64, 37, 100, 1] + [9] * 20, selections=sels,
                                n_decode=2)
+    _repositioned_steps(pc, qc, 2, f"Hq={hq} Hkv={hkv}")
+
+
+@pytest.mark.parametrize("n_queries", [100, 150])
+@pytest.mark.parametrize("hq,hkv,n_select,groups", [(8, 2, 1, 40), (4, 2, 2, 6), (8, 2, 2, 6)])
+def test_repositioned_decode_over_an_fp8_pool_of_more_questions_than_a_wave_has_lanes(n_queries, hq, hkv, n_select, groups):
+    """Single waves, two and four that share an item's tiles; own caches of unequal lengths."""
+    pc = synth.make_pool_case("kv8lengths", 6040 + hq, dtype="bf16", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, sink_len=40,
+                              pool_tokens=200 * groups, demo_len_range=(30, 120), n_groups=groups, k_channel_sigma=0.35)
+    q_len = [int(x) for x in np.random.default_rng(29).integers(1, 60, size=n_queries)]
+    qc = synth.make_query_case("kv8lengthsq", 6041, pc, n_queries=n_queries, q_len=q_len, n_select=n_select, n_decode=1)
+    _repositioned_steps(pc, qc, 1, f"{n_queries} questions Hq={hq} Hkv={hkv}")
+
+
+def _repositioned_steps(pc, qc, steps, what):
+    from oracle import rope_oracle as ro
     p = pc.pool
     f = ro.inv_freq(500000.0, 128)
     lay = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, cu_qlens=qc.cu_qlens,
@@ -139,14 +154,14 @@ def test_repositioned_decode_over_an_fp8_pool(hq, hkv):
     kc = B.dbsa_rope_apply(to_dev(qc.k_cache.reshape(-1, shp[2], shp[3])), tab, positions=cache_pos).view(shp)
     vc = to_dev(qc.v_cache.reshape(-1, shp[2], shp[3])).view(shp)
     lens = np.diff(qc.cu_qlens)
-    for s in range(2):
+    for s in range(steps):
         self_len = (lens + s + 1).astype(np.int32)
         od = B.dbsa_decode_attn_kv8(lay, to_dev(qc.dec_q[s]), kc, vc, torch.from_numpy(self_len).cuda(), k8, v8, ks, vs,
                                     pc.scale, rope_table=tab)
         ref = ro.decode_attn_repositioned(synth.as_f64(qc.dec_q[s]), synth.as_f64(qc.k_cache), synth.as_f64(qc.v_cache),
                                           self_len, k_unrot, vq, p.sink_len, p.demo_offsets, p.group_demo_offsets,
                                           qc.sel_ptr, qc.sel_idx, f, pc.scale)
-        assert_close(to_f64(od), ref, f"Hq={hq} Hkv={hkv} re-positioned fp8-pool decode step {s}")
+        assert_close(to_f64(od), ref, f"{what} re-positioned fp8-pool decode step {s}")
 
 
 def test_fp8_decode_takes_the_rescale_path_when_row_maxima_keep_growing():

@@ -225,3 +225,29 @@ def test_rope_apply_on_rows_of_every_width_and_alignment(dtype, n, heads, d, lea
     assert torch.equal(B.dbsa_rope_apply(t, tab, first_id=20, out=wide[:, :heads]), got) and (wide[:, heads] == 9.0).all()
     ids = torch.arange(20, 20 + n, dtype=torch.int32, device="cuda")
     assert torch.equal(B.dbsa_rope_apply(t, tab, positions=ids, out=t), got) and torch.equal(t, got)
+
+
+def _many_questions(hq, hkv, n_queries, n_select, groups):
+    """Own caches of unequal lengths, so that a length taken from another question turns the row by another angle."""
+    pc = synth.make_pool_case("ropelengths", 4050 + hq, dtype="bf16", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, sink_len=40,
+                              pool_tokens=200 * groups, demo_len_range=(30, 120), n_groups=groups, k_channel_sigma=0.35)
+    rng = np.random.default_rng(23)
+    q_len = [int(x) for x in rng.integers(1, 60, size=n_queries)]
+    qc = synth.make_query_case("ropelengthsq", 4051, pc, n_queries=n_queries, q_len=q_len, n_select=n_select, n_decode=1)
+    p = pc.pool
+    host = B.dbsa_layout_build(p.sink_len, p.demo_offsets, p.group_demo_offsets, cu_qlens=qc.cu_qlens, sel_ptr=qc.sel_ptr,
+                               sel_idx=qc.sel_idx, n_split=0, block_m=32, block_n=64, host_only=True)
+    return pc, qc, host.export_matrix_records()[1] >= 0.22 and (hq // hkv) % 4 == 0
+
+
+@pytest.mark.parametrize("n_queries", [64, 65, 100, 128, 129, 150])
+@pytest.mark.parametrize("hq,hkv,n_select,groups,contraction", [
+    (4, 4, 1, 50, False),   # single waves
+    (4, 2, 2, 6, False),    # waves that share an item's tiles
+    (8, 2, 1, 40, False),
+    (8, 2, 2, 5, True),     # the contraction, the own caches in a launch of their own
+])
+def test_repositioned_decode_of_more_questions_than_a_wave_has_lanes(n_queries, hq, hkv, n_select, groups, contraction):
+    pc, qc, gathered = _many_questions(hq, hkv, n_queries, n_select, groups)
+    assert gathered == contraction
+    _repositioned_case(pc, qc, 32, 10000.0, what=f"{n_queries} questions Hq={hq} Hkv={hkv}")
