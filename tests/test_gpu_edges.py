@@ -462,24 +462,30 @@ def test_cut_query_prefill_on_other_streams_and_in_a_graph():
         assert torch.equal(got, want), f"persistent launch, replay {rep}"
 
 
+def _scores_in_runs(rng, pc, qc, jump):
+    """Keys and queries whose scores lie `jump` (natural-log units) apart in runs of 16 keys."""
+    unit = np.zeros(pc.head_dim, dtype=np.float32)
+    unit[0] = 1.0
+    for c in (pc, qc):
+        n, heads, d = c.k.shape
+        level = np.repeat(rng.integers(-1, 2, size=n // 16 + 1), 16)[:n].astype(np.float32)
+        c.k = synth.f32_to_bf16_bits(level[:, None, None] * (jump / (pc.scale * 32.0)) * unit + 0.3 * rng.standard_normal((n, heads, d)).astype(np.float32))
+        c.q = synth.f32_to_bf16_bits(32.0 * unit + rng.standard_normal(c.q.shape).astype(np.float32))
+
+
 @pytest.mark.parametrize("hq,hkv,block_m", [(4, 4, 64), (4, 4, 32), (4, 2, 32)])
 @pytest.mark.parametrize("sink,jump", [(4, 0.0), (31, 300.0), (33, 300.0), (64, 40.0)])
 def test_small_workgroups_whose_waves_share_the_keys_of_a_tile(hq, hkv, block_m, sink, jump):
     """Workgroups of one and two row blocks: one wave has keys 0-31 of every tile, the other keys 32-63.  Tiles too short for
     the second wave, lists in which it meets its first key late or never, and scores `jump` (natural-log units) apart in
-    runs of 16 keys, so that the two waves' maxima lie far from each other; encoding, whole and split lists, log-sum-exp."""
+    runs of 16 keys, so that the two waves' maxima lie far from each other; encoding, questions whose lists are too short to
+    be split, log-sum-exp."""
     rng = np.random.default_rng(93)
     pc = small_pool_case("halves", 3900 + sink, hq=hq, hkv=hkv, sink=sink, pool_tokens=2600, groups=40, lens=(9, 40), sigma=0.5)
     sels = [[0], list(range(0, 40, 2)), [39, 3], list(range(40)), []]
     qc = synth.make_query_case("halvesq", 3901, pc, n_queries=5, q_len=[5, 33, 64, 130, 20], selections=sels)
     if jump:
-        unit = np.zeros(pc.head_dim, dtype=np.float32)
-        unit[0] = 1.0
-        for c in (pc, qc):
-            n, heads, d = c.k.shape
-            level = np.repeat(rng.integers(-1, 2, size=n // 16 + 1), 16)[:n].astype(np.float32)
-            c.k = synth.f32_to_bf16_bits(level[:, None, None] * (jump / (pc.scale * 32.0)) * unit + 0.3 * rng.standard_normal((n, heads, d)).astype(np.float32))
-            c.q = synth.f32_to_bf16_bits(32.0 * unit + rng.standard_normal(c.q.shape).astype(np.float32))
+        _scores_in_runs(rng, pc, qc, jump)
     _, o, _ = run_preencode(pc, block_m)
     assert_close(to_f64(o), oracle_preencode(pc), f"halves, encoding, sink={sink} jump={jump}")
     lay, kp, vp = _query_setup(pc, qc, block_m, 0)
@@ -491,3 +497,30 @@ def test_small_workgroups_whose_waves_share_the_keys_of_a_tile(hq, hkv, block_m,
         assert_close(to_f64(got), ref, f"halves, query prefill, sink={sink} jump={jump} ws={ws}")
         if not jump:
             assert_close(to_f64(lse), want_lse, f"halves, log-sum-exp, ws={ws}")
+
+
+@pytest.mark.parametrize("hq,hkv,block_m", [(4, 4, 64), (4, 4, 32), (4, 2, 32)])
+@pytest.mark.parametrize("sink,group,jump", [(4, 65, 0.0), (31, 29, 0.0), (33, 65, 300.0), (31, 29, 300.0)])
+def test_small_workgroups_with_split_lists(hq, hkv, block_m, sink, group, jump):
+    """The same for lists in several runs, whose states both waves of a row block leave: groups of 29 tokens show the second
+    wave no key in a whole run, those of 65 one in every other tile."""
+    rng = np.random.default_rng(94)
+    groups = 60
+    pc = synth.make_pool_case("halfruns", 3950 + sink, dtype="bf16", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, sink_len=sink,
+                              pool_tokens=group * groups, uniform_demo_len=group, demos_per_group=1, k_channel_sigma=0.5)
+    sels = [list(range(0, 60, 2)), list(range(20)), list(range(60)), list(range(59, 20, -1))]
+    qc = synth.make_query_case("halfrunsq", 3951, pc, n_queries=4, q_len=[5, 33, 130, 20], selections=sels)
+    if jump:
+        _scores_in_runs(rng, pc, qc, jump)
+    lay, kp, vp = _query_setup(pc, qc, block_m, 0)
+    assert np.diff(lay.export()[1]).min() >= 16
+    qs, ks, vs = to_dev(qc.q), to_dev(qc.k), to_dev(qc.v)
+    ref, want_lse = _oracle_query(pc, qc), oracle_query_lse(pc, qc)
+    outs = []
+    for ws in (False, None):
+        lse = torch.zeros(hq, qs.shape[0], device="cuda")
+        outs.append(B.dbsa_query_attn(lay, qs, ks, vs, kp, vp, pc.scale, lse=lse, workspace=ws))
+        assert_close(to_f64(outs[-1]), ref, f"half runs, sink={sink} group={group} jump={jump} ws={ws}")
+        if not jump:
+            assert_close(to_f64(lse), want_lse, f"half runs, log-sum-exp, ws={ws}")
+    assert not torch.equal(outs[0], outs[1]), "the workspace did not split the lists"

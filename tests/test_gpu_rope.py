@@ -129,6 +129,24 @@ def test_repositioned_decode_with_many_queries_per_group(hq, hkv):
     _repositioned_case(pc, qc, 32, 10000.0, decode_steps=range(2), what=f"many queries Hq={hq} Hkv={hkv}")
 
 
+@pytest.mark.parametrize("hq,hkv,block_m", [(4, 4, 64), (4, 4, 32), (4, 2, 32)])
+@pytest.mark.parametrize("group", [29, 65])
+def test_repositioned_split_prefill_of_small_workgroups(hq, hkv, block_m, group):
+    """Two waves share the keys of a row block and its rotated rows; lists in several runs, a segment per entry or two."""
+    pc = synth.make_pool_case("ropehalf", 4060 + group, dtype="bf16", n_q_heads=hq, n_kv_heads=hkv, head_dim=128, sink_len=31,
+                              pool_tokens=60 * group, uniform_demo_len=group, demos_per_group=1, k_channel_sigma=0.35)
+    sels = [list(range(0, 60, 2)), list(range(20)), list(range(60)), list(range(59, 20, -1))]
+    qc = synth.make_query_case("ropehalfq", 4061, pc, n_queries=4, q_len=[5, 33, 130, 20], selections=sels, n_decode=0)
+    lay = B.dbsa_layout_build(pc.pool.sink_len, pc.pool.demo_offsets, pc.pool.group_demo_offsets, cu_qlens=qc.cu_qlens,
+                              sel_ptr=qc.sel_ptr, sel_idx=qc.sel_idx, block_m=block_m, block_n=64)
+    assert np.diff(lay.export()[1]).min() >= 16
+    tab = B.dbsa_rope_table(ro.inv_freq(10000.0, 128), 3 * pc.pool.n_tokens)
+    one, several = (B.dbsa_query_attn_rope(lay, *(to_dev(x) for x in (qc.q, qc.k, qc.v, pc.k, pc.v)), tab, pc.scale, workspace=ws)
+                    for ws in (False, None))
+    assert not torch.equal(one, several), "the workspace did not split the lists"
+    _repositioned_case(pc, qc, block_m, 10000.0, what=f"half runs, groups of {group} Hq={hq} Hkv={hkv}")
+
+
 @pytest.mark.parametrize("hq,hkv,block_m,q_len", [(4, 4, 128, [1500, 1283]), (4, 2, 256, [1700, 1201]), (2, 2, 256, [1999])])
 def test_repositioned_split_prefill_with_large_q_tiles(hq, hkv, block_m, q_len):
     """Few long queries under Q tiles of 128 / 256 rows: the lists are cut into runs (the workspace is given),
