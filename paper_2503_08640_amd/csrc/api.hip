@@ -525,11 +525,6 @@ int pick_heads_per_block(int r, int block_m, int head_dim, bool idle_heads) {
 
 // Q tiles per worker up to which a query prefill may cut its lists to measure (with more, whole Q tiles balance)
 constexpr int64_t kCutTiles = 8;
-// attn_prefill.hip starts a row's running maximum from the first
-// tile of its run, so that tile must hold a key the row sees.  Only the tiles on a Q tile's own
-// diagonal hide keys from some of its rows, they are the last block_m / 64 entries of a list and
-// every row sees the first of them: a run of more entries than that never starts behind it.
-static_assert(kMinRun > 256 / 64, "a run of a split list must reach back beyond the diagonal tiles of a Q tile");
 // workgroups the device the layout was built for holds at two per compute unit
 int64_t workgroup_slots(const dbsa_layout* L) { return 2 * static_cast<int64_t>(L->compute_units); }
 

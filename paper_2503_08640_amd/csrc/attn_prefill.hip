@@ -20,8 +20,8 @@
 //     whose 16-byte slots are XOR-swizzled, K by (row % 16) for the 128-bit fragment
 //     reads (16 consecutive rows, same slot -> 16 distinct bank groups) and V by
 //     4*(row % 4) for the 64-bit transpose reads (4 rows x 4 slots per half-wave).
-//   * tiles are fetched SL steps before the barrier that publishes them (2 + SL stages of
-//     K, 1 + SL of V) and K becomes visible one barrier before its scores are computed:
+//   * tiles are fetched one step before the barrier that publishes them (three stages of
+//     K, two of V) and K becomes visible one barrier before its scores are computed:
 //     a step is  [barrier]  S(j+1) = K(j+1) Q^T  |  O += V(j) P(j)  and the operand
 //     fragments of a step's first matrix instructions are already in registers when the
 //     barrier opens (they were read from LDS at the end of the previous step).
@@ -58,6 +58,7 @@ constexpr int kTileBytes = kBN * kRowBytes;   // 16 KiB per K or V tile
 constexpr int kRing = 4;                      // operand fragments in flight per wave (divides 16)
 constexpr int kDist = kRing - 1;              // a fragment is read this many matrix instructions early
 constexpr float kRescaleSlack = 8.f;          // log2 units
+constexpr int KS = 3, VS = 2;                 // LDS stages of K and of V
 
 struct TileRef {
   int start, len;
@@ -65,8 +66,7 @@ struct TileRef {
 };
 
 // NW row blocks of 32 rows per workgroup, two wavefronts each: one takes keys 0-31 of every tile, the other keys 32-63
-// (`part`), and their states meet in LDS at the end.  SL: steps between the issue of a
-// tile's loads and the barrier that publishes them; SELF: the lists may name tiles of the
+// (`part`), and their states meet in LDS at the end.  SELF: the lists may name tiles of the
 // call's own K/V (query prefill) besides pool tiles (pre-encode lists name pool tiles only).
 // Row block g covers query head (blockIdx.x * heads_per_block + g / spb) and tokens
 // q_start + (g % spb)*32 .. +31, spb = block_m / 32.
@@ -74,13 +74,11 @@ struct TileRef {
 // encoded with, and every list entry names the id at which its rows must be rotated instead
 // (AttnParams::list_shift: the new in-order positions of Sec. 2.2 as a rotation of the query).
 // Entries of one segment share that id, so the Q fragments are rebuilt at segment changes only.
-template <int NW, int SL, bool SELF, bool ROPE = false>
+template <int NW, bool SELF, bool ROPE = false>
 __global__ __launch_bounds__(NW * 128, 2) void attn_prefill_kernel(AttnParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   constexpr int kBlocksPerWave = 8 / NW;  // 1-KiB load blocks of one operand per wave
-  constexpr int KS = 2 + SL, VS = 1 + SL;  // LDS stages of K and of V
   static_assert(NW == 1 || NW == 2, "row blocks");
-  static_assert(SL == 1 || SL == 2, "load slack");
   static_assert(16 % kRing == 0 && kDist >= 1 && kDist <= 8, "ring size");
   const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>((lds_byte*)smem));
 
@@ -287,18 +285,17 @@ __global__ __launch_bounds__(NW * 128, 2) void attn_prefill_kernel(AttnParams p)
     }
   };
 
-  // ---- prologue: K(0 .. 1+SL), V(0 .. SL-1) in flight; scores of tile 0 fix the first running max ----
-  // refs[i] = list entry it+1+i at the top of step it (i = 0 .. SL+1; zero length past the end)
-  TileRef cur = tile_ref(0), refs[2 + SL];
+  // ---- prologue: K(0 .. 2), V(0) in flight; scores of tile 0 fix the first running max ----
+  // refs[i] = list entry it+1+i at the top of step it (zero length past the end)
+  TileRef cur = tile_ref(0), refs[3];
 #pragma unroll
-  for (int i = 0; i < 2 + SL; ++i) refs[i] = (i + 1 < n_tiles) ? tile_ref(i + 1) : TileRef{0, 0, false, false};
+  for (int i = 0; i < 3; ++i) refs[i] = (i + 1 < n_tiles) ? tile_ref(i + 1) : TileRef{0, 0, false, false};
   issue_k(cur, 0);
 #pragma unroll
-  for (int i = 0; i < 1 + SL; ++i)
+  for (int i = 0; i < 2; ++i)
     if (i + 1 < n_tiles) issue_k(refs[i], i + 1);
   issue_v(cur, 0);
-  static_assert(SL == 1 && KS == 3 && VS == 2, "V stage 1 is free until step 0, then the one that step's loads fill");
-  place_q(first_q, 1);
+  place_q(first_q, 1);  // (V stage 1 is free until step 0, then the one that step's loads fill)
   wait_vmcnt<0>();
   __syncthreads();
   fetch_q(1);
@@ -336,7 +333,7 @@ __global__ __launch_bounds__(NW * 128, 2) void attn_prefill_kernel(AttnParams p)
   // the fragment reads now walk K stage 1 (tile 1) and V stage 0 (tile 0); the first kDist
   // fragments of K(1) enter the ring (stale data if the list has one entry: never used)
   int k_rd = 1, v_rd = 0;    // stage the K / V fragment addresses point into
-  int k_wr = 0, v_wr = SL;   // stage the loads issued in step 0 fill: K(2+SL) -> (2+SL) % KS, V(SL)
+  int k_wr = 0, v_wr = 1;    // stage the loads issued in step 0 fill: K(3), V(1)
 #pragma unroll
   for (int c = 0; c < 8; ++c) kaddr[c] += kTileBytes;
   bf16x8 ring[kRing];
@@ -348,12 +345,7 @@ __global__ __launch_bounds__(NW * 128, 2) void attn_prefill_kernel(AttnParams p)
   // visible with this one.  The last tile computes an s_nxt nobody uses (stale LDS contents)
   // so that every tile runs the same straight-line code.
   auto tile_step = [&](int it, floatx16& s_cur, floatx16& s_nxt) DBSA_INLINE {
-    // what this step needs was issued SL steps ago; with SL == 2 the K and V loads of the
-    // previous step (2*kBlocksPerWave instructions, if that step issued both sets) may stay in flight
-    if (SL == 2 && it + 1 + SL < n_tiles)
-      wait_vmcnt<(SL == 2 ? 2 * kBlocksPerWave : 0)>();
-    else
-      wait_vmcnt<0>();
+    wait_vmcnt<0>();  // what this step needs was issued in the one before
     __syncthreads();
 
     // rare: some row's maximum outgrew the lagging running maximum, or a row sees its first key
@@ -385,14 +377,14 @@ __global__ __launch_bounds__(NW * 128, 2) void attn_prefill_kernel(AttnParams p)
     }
     const bool has_next = it + 1 < n_tiles;
     const TileRef nxt = refs[0];
-    // List entry it+3+SL (zero past the end), needed by the next step's K load.  Requested FIRST:
+    // List entry it+4 (zero past the end), needed by the next step's K load.  Requested FIRST:
     // a scalar load shares its counter with the LDS fragment reads and returns out of order with
     // them, so while it is in flight every fragment wait drains the whole queue; behind the
     // load instructions of this step it has returned before the first such wait.
     int in_w0 = 0, in_w1 = 0;
-    if (it + 3 + SL < n_tiles) {
-      in_w0 = ent[2 * (it + 3 + SL)];
-      in_w1 = ent[2 * (it + 3 + SL) + 1];
+    if (it + 4 < n_tiles) {
+      in_w0 = ent[2 * (it + 4)];
+      in_w1 = ent[2 * (it + 4) + 1];
     }
     if constexpr (ROPE) {
       if (it + 2 < n_tiles) nxt_shift = lshift[it + 2];
@@ -410,11 +402,11 @@ __global__ __launch_bounds__(NW * 128, 2) void attn_prefill_kernel(AttnParams p)
       else
         ring[(t + kDist) % kRing] = ld_v(std::integral_constant<int, t + kDist - 8>{});
       if constexpr (t == 0) {
-        // this step's loads go out behind the first matrix instruction: K(it+2+SL), V(it+SL).
+        // this step's loads go out behind the first matrix instruction: K(it+3), V(it+1).
         // (Spreading them over the phase, one per few matrix instructions, measured slower: every
         // load sits behind a branch on the list length, and each branch splits the straight-line code.)
-        if (it + 2 + SL < n_tiles) issue_k(refs[1 + SL], k_wr);
-        if (it + SL < n_tiles) issue_v(refs[SL - 1], v_wr);
+        if (it + 3 < n_tiles) issue_k(refs[2], k_wr);
+        if (it + 1 < n_tiles) issue_v(refs[0], v_wr);
       }
       if constexpr (t > 0) {
         constexpr int u = t - 1;
@@ -472,8 +464,8 @@ __global__ __launch_bounds__(NW * 128, 2) void attn_prefill_kernel(AttnParams p)
       k_wr = (k_wr + 1 == KS) ? 0 : k_wr + 1;
       v_wr = (v_wr + 1 == VS) ? 0 : v_wr + 1;
 #pragma unroll
-      for (int i = 0; i < 1 + SL; ++i) refs[i] = refs[i + 1];
-      refs[1 + SL] = TileRef{in_w0, in_w1 & 0xFFFF, ((in_w1 >> 16) & 1) != 0, SELF && ((in_w1 >> 17) & 1) != 0};
+      for (int i = 0; i < 2; ++i) refs[i] = refs[i + 1];
+      refs[2] = TileRef{in_w0, in_w1 & 0xFFFF, ((in_w1 >> 16) & 1) != 0, SELF && ((in_w1 >> 17) & 1) != 0};
     }
   };
 
@@ -688,27 +680,27 @@ hipError_t launch_merge(const AttnParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int NW, int SL, bool SELF, bool ROPE = false>
+template <int NW, bool SELF, bool ROPE = false>
 hipError_t launch_cfg(const AttnParams& p, hipStream_t stream) {
-  constexpr int lds_bytes = (3 + 2 * SL) * kTileBytes;
+  constexpr int lds_bytes = (KS + VS) * kTileBytes;
   static std::atomic<bool> attr_set{false};  // setting it twice from two threads is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_kernel<NW, SL, SELF, ROPE>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_kernel<NW, SELF, ROPE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   const int n_split = p.q_split > 1 ? p.q_split : 1;
   dim3 grid(p.n_q_heads / p.heads_per_block, p.n_qtiles, n_split), block(NW * 128);
-  attn_prefill_kernel<NW, SL, SELF, ROPE><<<grid, block, lds_bytes, stream>>>(p);
+  attn_prefill_kernel<NW, SELF, ROPE><<<grid, block, lds_bytes, stream>>>(p);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? launch_merge<kD>(p, stream) : e;
 }
 
-template <int NW, int SL>
+template <int NW>
 hipError_t launch_stage(const AttnParams& p, hipStream_t stream) {
-  if (p.rope_table) return p.query_stage ? launch_cfg<NW, SL, true, true>(p, stream) : hipErrorInvalidValue;
-  return p.query_stage ? launch_cfg<NW, SL, true>(p, stream) : launch_cfg<NW, SL, false>(p, stream);
+  if (p.rope_table) return p.query_stage ? launch_cfg<NW, true, true>(p, stream) : hipErrorInvalidValue;
+  return p.query_stage ? launch_cfg<NW, true>(p, stream) : launch_cfg<NW, false>(p, stream);
 }
 
 }  // namespace
@@ -726,8 +718,8 @@ hipError_t launch_prefill_pipelined(const AttnParams& p, int head_dim, hipStream
     return head_dim == 64 ? launch_merge<64>(p, stream) : launch_merge<128>(p, stream);
   }
   switch (row_blocks) {
-    case 1: return launch_stage<1, 1>(p, stream);
-    case 2: return launch_stage<2, 1>(p, stream);
+    case 1: return launch_stage<1>(p, stream);
+    case 2: return launch_stage<2>(p, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -58,8 +58,8 @@ def test_query_stage_log_sum_exp_matches_the_oracle(hq, hkv, block_m):
                                                   (2, 2, 256, [1999])])
 def test_split_query_prefill_with_large_q_tiles(hq, hkv, block_m, q_len):
     """Long queries under Q tiles of 128 and 256 rows: the last block_m / 64 list entries of a Q tile lie
-    on its diagonal and hide keys from its upper rows, and the lists are cut into runs.  Every run
-    must start at a tile all of its rows see; the result must not depend on the cut."""
+    on its diagonal and hide keys from its upper rows, and the lists are cut into runs.  The result must
+    not depend on the cut."""
     pc = small_pool_case("bigtile", 3200 + block_m + hq, hq=hq, hkv=hkv, pool_tokens=6000, groups=3, lens=(64, 300), sigma=0.5)
     sels = [[0, 1, 2], [1]][:len(q_len)]
     qc = synth.make_query_case("bigq", 3201, pc, n_queries=len(q_len), q_len=q_len, selections=sels)

@@ -150,8 +150,7 @@ def test_repositioned_split_prefill_of_small_workgroups(hq, hkv, block_m, group)
 @pytest.mark.parametrize("hq,hkv,block_m,q_len", [(4, 4, 128, [1500, 1283]), (4, 2, 256, [1700, 1201]), (2, 2, 256, [1999])])
 def test_repositioned_split_prefill_with_large_q_tiles(hq, hkv, block_m, q_len):
     """Few long queries under Q tiles of 128 / 256 rows: the lists are cut into runs (the workspace is given),
-    and the last block_m / 64 entries of every list hide keys from the Q tile's upper rows.  No run may start
-    among them behind the first: the kernel takes a row's first maximum from the first tile of its run."""
+    and the last block_m / 64 entries of every list hide keys from the Q tile's upper rows."""
     pc = synth.make_pool_case("ropebig", 4030 + block_m + hq, dtype="bf16", n_q_heads=hq, n_kv_heads=hkv, head_dim=128,
                               sink_len=70, pool_tokens=6000, demo_len_range=(64, 300), n_groups=3)
     sels = [[2, 0, 1], [1]][:len(q_len)]
