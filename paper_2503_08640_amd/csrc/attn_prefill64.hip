@@ -1,5 +1,7 @@
 // bf16 MFMA attention for prefill-shaped calls (pre-encode, Sec. 2.1; query prefill, Sec. 2.2)
-// at head_dim 128 on gfx950, with 64 query rows per wavefront and ONE wavefront per SIMD.
+// at head_dim 128 and 64 on gfx950, with 64 query rows per wavefront and one wavefront per SIMD
+// (head_dim 64: two where a launch fills them, see CROWD).  Figures in this header are those of
+// head_dim 128; at 64 a step has half as many matrix instructions behind the same exponentials.
 //
 // Same mathematics, operand layouts and LDS swizzles as attn_prefill.hip (transposed scores
 // S^T = K Q^T, per-lane softmax statistics, O^T = V^T P^T, tiles moved by
@@ -132,9 +134,9 @@ struct StepCfg {
 //
 // CROWD (head_dim 64, where 256 registers hold a wave): two waves to a SIMD instead of one.  A step there is 16 matrix
 // instructions (512 cycles) beside 112 vector ones, 32 of them exponentials; alone, an in-order wave takes 1200 cycles for
-// it, two waves fill each other's gaps: 0.87 us per 64-key tile and wave against 1.21.  32k tokens, 32/8 heads, encode
-// 650 -> 575 us, 16/16 heads 400 -> 340, 5000 tokens 61 -> 52, one group appended 504 -> 431, 12 questions of 400 tokens
-// 425 -> 378, 100 of 20 tokens 275 -> 254.  (Wave priorities in turn, so that the older wave does not run ahead: +-2 %.)
+// it, two waves fill each other's gaps: 1.74 us per 64-key tile of two waves against 1.21 of one.  32k tokens, 32/8 heads,
+// encode 666 -> 598 us, 16/16 heads 393 -> 341, 4400 tokens in four groups 43 -> 35, 12 questions of 400 tokens 423 -> 393,
+// 60 of 64 tokens 295 -> 260.  (Wave priorities in turn, so that the older wave does not run ahead: +-2 %.)
 template <int kD, int NW, int SL, bool SELF, bool PERSIST, bool GATHER = false, bool ROPE = false, bool CROWD = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(CROWD ? 2 : 1, CROWD ? 2 : 1))) void attn_prefill64_kernel(AttnParams p) {
   static_assert(!GATHER || (PERSIST && !SELF), "gathered rows come with a schedule and pool tiles only");

@@ -76,8 +76,7 @@ struct AttnParams {
   const int32_t* gather_refs;
   const int32_t* gather_shift;  // [n_refs]: with re-positioning, rotation id of reference i's row = gather_shift[i] + self_len - 1
   // decode step: 1 = the pool items run as a contraction through launch_decode_matrix_items with the
-  // schedule mx_sched_* over list entries mx_ent, the self items in the ordinary kernel (gm_rows then
-  // holds the table of single-wave workgroups)
+  // schedule mx_sched_* over list entries mx_ent, the self items in the ordinary kernel
   int32_t decode_matrix;
   const int32_t* mx_sched_rec;
   const int32_t* mx_sched_ptr;
@@ -101,7 +100,7 @@ hipError_t launch_prefill_mfma(const AttnParams& p, int head_dim, hipStream_t st
 // software-pipelined variants (attn_prefill.hip): head_dim 128, or 64 with two, four or eight row blocks per workgroup
 // (every workgroup size that is chosen at head_dim 64)
 hipError_t launch_prefill_pipelined(const AttnParams& p, int head_dim, hipStream_t stream);
-// the same mathematics with 64 query rows per wave, one wave per SIMD (attn_prefill64.hip); kernel
+// the same mathematics with 64 query rows per wave, one wave per SIMD or two (attn_prefill64.hip); kernel
 // only: launch_prefill_pipelined runs the merge pass of a split launch
 hipError_t launch_prefill64(const AttnParams& p, int head_dim, hipStream_t stream);
 // the same kernel over rows gathered through references, leaving partial softmax states: the pool

@@ -489,7 +489,9 @@ int dbsa_build_host_lists(const dbsa_pool_desc* pool, const dbsa_select_desc* se
         more += batches[static_cast<size_t>(b)] - 1;
       }
       // While few blocks have a second batch the first batches need no table (one look-up less in front of the first
-      // tiles); otherwise the batches of a block stay next to each other, all in the table.
+      // tiles); otherwise the batches of a block stay next to each other, all in the table.  us with the table / without:
+      // no second batches, 32/8 heads, one question 25.9 / 25.7, 8 questions 81.1 / 80.8; for 0.09 of the blocks, 24 of 100
+      // groups 83.2 / 80.8; 0.10, 16 questions 86.1 / 85.8; 0.20, 20 questions 87.4 / 87.9; 0.35, 22 questions 91.6 / 94.4.
       L->gm_direct[k] = 4 * more <= pool_blocks ? pool_blocks : 0;
       L->gm_rows_off[k] = static_cast<int32_t>(L->gm_rows.size());
       for (int32_t b = 0; b < pool_blocks; ++b)
