@@ -9,7 +9,8 @@
 //     of them per compute unit, which with one wave per row block is one wave per SIMD or less: an in-order wave alone
 //     takes 3900 cycles for a tile that is 1024 of matrix work.  So two waves share a row block: each takes half of
 //     every tile's keys, with a running maximum, sum and outputs of its own, and they meet in LDS at the end of the
-//     list (no state leaves the chip).  Multi-head, 16 questions of 64 tokens over 8256 keys each: 228 -> 204 us (launches
+//     list (no state leaves the chip): two waves per SIMD with two row blocks, one with one.  Multi-head, 16 questions of
+//     64 tokens over 8256 keys each: 228 -> 204 us (launches
 //     in a row once the clock has settled; the first hundred after a pause take 197 to 265);
 //     without any load in the loop 122, with all loads aimed at one tile 148: what is left is the traffic behind L2
 //     (861 MB of the 2.26 GB requested miss it; 537 MB are unique).  Loads requested two tiles ahead instead of one
