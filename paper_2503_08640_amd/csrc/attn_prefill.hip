@@ -13,7 +13,7 @@
 //     64 tokens over 8256 keys each: 228 -> 204 us (launches
 //     in a row once the clock has settled; the first hundred after a pause take 197 to 265);
 //     without any load in the loop 122, with all loads aimed at one tile 148: what is left is the traffic behind L2
-//     (861 MB of the 2.26 GB requested miss it; 537 MB are unique).  Loads requested two tiles ahead instead of one
+//     (861 and 906 MB of the 2.26 GB requested miss it in two runs; 537 MB are unique).  Loads requested two tiles ahead instead of one
 //     make it 231 us: workgroups that walk the same keys drift further apart and 1174 MB miss L2.
 //   * K and V tiles go from global memory straight into LDS with
 //     global_load_lds_dwordx4 (no staging registers, no ds_write).  A wave-level load

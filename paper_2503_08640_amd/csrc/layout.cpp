@@ -750,7 +750,8 @@ constexpr double kBesideCost = 1.44;
 // without a workspace: 48 of 64 tokens over 64 workers 289 / 245, 66 427 / 375, 100 of 20 tokens over 128 305 / 250 (nothing
 // below three quarters was measured); one that selects 16 times as many groups as the 55 others 158 / 165.  Lists that can
 // be cut to measure take four fifths: over 64 workers 40 questions 195 cut for one wave each, 48 231 / 245, 52 253 / 250,
-// 60 292 / 262.  More workers than a schedule can name leave the launch to the order of the lists, or their cuts to half
+// 60 292 / 262; fewer gain or lose and keep one wave (1 question of 64 tokens 30.6 / 22.3, 5 39.9 / 41.6, 20 118 / 108,
+// 30 149 / 154; 1 of 400 51.6 / 48.8, 4 153 / 139; 5 ragged ones 67 / 66).  More workers than a schedule can name leave the launch to the order of the lists, or their cuts to half
 // the places: 4/1 heads, 1200 questions of 30 tokens 114 / 167, encoding 60000 tokens 127 / 143; with one list per worker
 // they gain, 900 questions 88 / 80, 32000 tokens 63 / 53.
 bool dbsa_crowd_worth(const dbsa_layout* L, int64_t classes, bool cuts) {

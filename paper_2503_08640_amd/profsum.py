@@ -151,7 +151,7 @@ def cmd_traffic(args) -> int:
     w_fac, w_cal = calibration(write, "WRITE_SIZE")
     print(f"calibration copy: FETCH_SIZE raw {f_cal[1]:.1f} -> factor {f_fac:.3f}; WRITE_SIZE raw {w_cal[1]:.1f} -> factor {w_fac:.3f}")
 
-    # attn_prefill64_kernel<head dim, waves, slack, SELF, PERSIST, GATHER, ROPE>: SELF = false is the pre-encode launch
+    # attn_prefill64_kernel<head dim, waves, slack, SELF, PERSIST, GATHER, ROPE, CROWD>: SELF = false is the pre-encode launch
     groups = {
         "preencode": [("attn_prefill64_kernel<", "SELF=false")],
         "query_prefill": [("attn_prefill64_kernel<", "SELF=true"), ("prefill_merge_kernel",)],
