@@ -824,8 +824,11 @@ __global__ __launch_bounds__(64, 2) void decode_group_kv8_kernel(AttnParams p) {
 // arithmetic on that pair.  Two barriers per half tile: before the widening (every wave is done
 // with the working pair of the half tile before) and after it (the working pair is complete).
 constexpr int kStagePair8 = 2 * kSlot8;                               // 8 KiB of bytes per (K, V) half tile
-template <int W>
-constexpr int kLdsShared8 = kPairs * kStagePair8 + kPairBytes + W * kRefBytes;  // 24 KiB staging + 16 KiB working pair + references
+// 24 KiB staging + 16 KiB working pair.  The references lie where the working pair comes to lie: with 2 KiB of their own the
+// two-wave form fits a compute unit three times instead of four, and its registers allow four (128 questions, 10 % of a 90k
+// pool, 89.2 us with four and 96.2 with three; 128 of 32/16 heads over 32k 98.4 / 104.7).
+constexpr int kLdsShared8 = kPairs * kStagePair8 + kPairBytes;
+static_assert(4 * kLdsShared8 <= 160 * 1024, "four workgroups of two waves to a compute unit");
 
 template <int W, bool ROPE>
 __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnParams p) {
@@ -905,7 +908,8 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
 
   const int k_base = HalfTile<kD>::k_base(l32, half), v_base = HalfTile<kD>::v_base(lane, l32, half);
 
-  lds_byte* const refs = lds + kPairs * kStagePair8 + kPairBytes + wave * kRefBytes;
+  static_assert(W * kRefBytes <= kPairBytes, "references in the working pair");
+  lds_byte* const refs = work_k + wave * kRefBytes;
   if (ROPE) await_lengths(lengths);
   request_references(p, it, refs);
   issue_pair(0);
@@ -914,6 +918,7 @@ __global__ __launch_bounds__(64 * W) void decode_group_kv8_shared_kernel(AttnPar
   else wait_vmcnt<2 * kPerWave>();
   // ---- this lane's column ----
   const DecodeColumn col = decode_column<kD, ROPE>(p, it, pass, active, r, rp_log2, l32, half, refs, lengths);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // they are read: behind the first barrier the waves widen into their place
   const KeyFactor c8 = split_key_factor<ROPE>(p.scale_log2e * p.k_scale8[hk]);
   const float v_scale = p.v_scale8[hk];
   bf16x8 qf[kD / 16];
@@ -1036,16 +1041,16 @@ hipError_t launch_shared8(const AttnParams& p, hipStream_t stream) {
   if (!attr_set) {
     for (const void* f : {reinterpret_cast<const void*>(decode_group_kv8_shared_kernel<W, false>),
                           reinterpret_cast<const void*>(decode_group_kv8_shared_kernel<W, true>)}) {
-      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsShared8<W>);
+      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsShared8);
       if (e != hipSuccess) return e;
     }
     attr_set = true;
   }
   const dim3 grid = decode_grid(p), block(64 * W);
   if (p.rope_table)
-    decode_group_kv8_shared_kernel<W, true><<<grid, block, kLdsShared8<W>, stream>>>(p);
+    decode_group_kv8_shared_kernel<W, true><<<grid, block, kLdsShared8, stream>>>(p);
   else
-    decode_group_kv8_shared_kernel<W, false><<<grid, block, kLdsShared8<W>, stream>>>(p);
+    decode_group_kv8_shared_kernel<W, false><<<grid, block, kLdsShared8, stream>>>(p);
   return hipGetLastError();
 }
 }  // namespace
